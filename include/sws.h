@@ -350,6 +350,39 @@ sws_status sws_conv2d_grad_weight(const float *x, const float *gy, float *gw, in
                                   int32_t kw, int32_t sh, int32_t sw, int32_t ph, int32_t pw,
                                   sws_stream_t stream);
 
+/* sws_conv1d, sws_conv2d, their forms under boundary rules and their adjoints with respect to the input, with device memory lent by the caller for
+ * the duration of the call (`workspace`, 16-byte aligned, work on it is enqueued on `stream`; its contents
+ * before and after are meaningless).  With sws_conv_workspace() bytes of it, dense layers (groups = 1, up to
+ * 64 taps, strides 1 and 2) run on kernels that first write the weights there as bf16 pieces: a product is
+ * then six exact products of pieces as stated above (inputs must be finite).  A NULL or smaller workspace is no error: the
+ * call is then the one without it.
+ * sws_conv_workspace(Cin, Cout, taps, positions): bytes that suffice for a layer that reads Cin and writes Cout
+ * channels (an adjoint reads the forward layer's output channels) with `taps` taps (kh*kw, or k) and
+ * `positions` = N*Ho*Wo or B*Lo forward outputs per channel; 0 if no kernel uses one. */
+int64_t sws_conv_workspace(int64_t Cin, int64_t Cout, int64_t taps, int64_t positions);
+sws_status sws_conv1d_ws(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
+                         int64_t Cout, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
+                         int32_t groups, void *workspace, int64_t workspace_bytes, sws_stream_t stream);
+sws_status sws_conv1d_grad_input_ws(const float *gy, const float *wgt, float *gx, int64_t B,
+                                    int64_t Cin, int64_t L, int64_t Cout, int32_t k, int32_t stride,
+                                    int32_t pad, int32_t dilation, int32_t groups, void *workspace,
+                                    int64_t workspace_bytes, sws_stream_t stream);
+sws_status sws_conv2d_ws(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin,
+                         int64_t H, int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh,
+                         int32_t sw, int32_t ph, int32_t pw, void *workspace, int64_t workspace_bytes,
+                         sws_stream_t stream);
+sws_status sws_conv2d_grad_input_ws(const float *gy, const float *wgt, float *gx, int64_t N,
+                                    int64_t Cin, int64_t H, int64_t W, int64_t Cout, int32_t kh,
+                                    int32_t kw, int32_t sh, int32_t sw, int32_t ph, int32_t pw,
+                                    void *workspace, int64_t workspace_bytes, sws_stream_t stream);
+sws_status sws_conv1d_padded_ws(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
+                             int64_t Cout, int32_t k, int32_t stride, int32_t pad_left, int32_t pad_right,
+                             int32_t dilation, int32_t groups, sws_pad_mode mode, void *workspace, int64_t workspace_bytes, sws_stream_t stream);
+sws_status sws_conv2d_padded_ws(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,
+                             int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh, int32_t sw,
+                             int32_t pad_top, int32_t pad_left, int32_t pad_bottom, int32_t pad_right,
+                             sws_pad_mode mode, void *workspace, int64_t workspace_bytes, sws_stream_t stream);
+
 /* Plain device-to-device copy of n floats with the same 128-bit access pattern the
  * sliding kernels use.  Not part of the method: it measures the HBM ceiling a
  * one-read-one-write kernel can reach on this device, and calibrates byte counters. */

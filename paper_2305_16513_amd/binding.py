@@ -6,6 +6,8 @@ dtype / device / contiguity, and passes raw device pointers plus the current HIP
 to the C ABI.  There is no fallback: a missing library or a non-zero status raises.
 """
 import ctypes
+import functools
+import math
 import os
 
 import torch
@@ -19,7 +21,7 @@ _lib = None
 
 _i64, _i32, _f32, _vp = ctypes.c_int64, ctypes.c_int32, ctypes.c_float, ctypes.c_void_p
 
-EXPORTS = ("sws_slide1d", "sws_slide1d_16", "sws_slide1d_padded", "sws_slide1d_pair", "sws_pool2d", "sws_maxpool2d_grad", "sws_avgpool2d_grad", "sws_pool2d_16", "sws_pool2d_ex", "sws_pool2d_padded", "sws_conv1d", "sws_conv1d_padded", "sws_conv1d_16", "sws_conv1d_grad_input", "sws_conv1d_grad_weight", "sws_conv2d", "sws_conv2d_padded", "sws_conv2d_grad_input", "sws_conv2d_grad_weight", "sws_copy", "sws_out_len",
+EXPORTS = ("sws_slide1d", "sws_slide1d_16", "sws_slide1d_padded", "sws_slide1d_pair", "sws_pool2d", "sws_maxpool2d_grad", "sws_avgpool2d_grad", "sws_pool2d_16", "sws_pool2d_ex", "sws_pool2d_padded", "sws_conv1d", "sws_conv1d_padded", "sws_conv1d_16", "sws_conv1d_grad_input", "sws_conv1d_grad_weight", "sws_conv2d", "sws_conv2d_padded", "sws_conv2d_grad_input", "sws_conv2d_grad_weight", "sws_conv_workspace", "sws_conv1d_ws", "sws_conv1d_grad_input_ws", "sws_conv2d_ws", "sws_conv2d_grad_input_ws", "sws_conv1d_padded_ws", "sws_conv2d_padded_ws", "sws_copy", "sws_out_len",
            "sws_status_string", "sws_set_option", "sws_version")
 
 
@@ -81,6 +83,13 @@ def lib():
         for f in (L.sws_conv2d_grad_input, L.sws_conv2d_grad_weight):
             f.restype = ctypes.c_int
             f.argtypes = [_vp, _vp, _vp, _i64, _i64, _i64, _i64, _i64, _i32, _i32, _i32, _i32, _i32, _i32, _vp]
+        L.sws_conv_workspace.restype = _i64
+        L.sws_conv_workspace.argtypes = [_i64, _i64, _i64, _i64]
+        for f, plain in ((L.sws_conv1d_ws, L.sws_conv1d), (L.sws_conv1d_grad_input_ws, L.sws_conv1d_grad_input),
+                         (L.sws_conv2d_ws, L.sws_conv2d), (L.sws_conv2d_grad_input_ws, L.sws_conv2d_grad_input),
+                         (L.sws_conv1d_padded_ws, L.sws_conv1d_padded), (L.sws_conv2d_padded_ws, L.sws_conv2d_padded)):
+            f.restype = ctypes.c_int
+            f.argtypes = plain.argtypes[:-1] + [_vp, _i64, _vp]
         L.sws_copy.restype = ctypes.c_int
         L.sws_copy.argtypes = [_vp, _vp, _i64, _vp]
         L.sws_out_len.restype = _i64
@@ -124,6 +133,25 @@ def _stream(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream)
+
+
+@functools.lru_cache(maxsize=1024)
+def _workspace_bytes(cin, cout, taps, positions):
+    return lib().sws_conv_workspace(cin, cout, taps, positions)
+
+
+def _workspace(wgt, cin, cout, taps, positions, stream):
+    """Device memory for the split weights of a dense layer that reads cin and writes cout channels, allocated on
+    the stream that the call runs on: (tensor, address, bytes), or (None, None, 0) where no kernel uses one."""
+    n = _workspace_bytes(cin, cout, taps, positions)
+    if n == 0:
+        return None, None, 0
+    if stream is None:
+        t = torch.empty(n, dtype=torch.uint8, device=wgt.device)
+    else:
+        with torch.cuda.stream(stream):
+            t = torch.empty(n, dtype=torch.uint8, device=wgt.device)
+    return t, t.data_ptr(), n
 
 
 def _out(y, shape, like, name="y"):
@@ -318,8 +346,9 @@ def sws_conv1d_padded(x, wgt, stride=1, pad_left=0, pad_right=0, dilation=1, gro
     if lo < 1 or cig * groups != cin or pad_left < 0 or pad_right < 0:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d_padded")
     y = _out(y, (b, cout, lo), x)
-    _check(lib().sws_conv1d_padded(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), b, cin, length, cout, k, stride, pad_left,
-                                   pad_right, dilation, groups, mode, _stream(stream)), "sws_conv1d_padded")
+    keep, ws, ws_bytes = _workspace(wgt, cig, cout, k, b * lo, stream) if groups == 1 else (None, None, 0)
+    _check(lib().sws_conv1d_padded_ws(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), b, cin, length, cout, k, stride, pad_left,
+                                   pad_right, dilation, groups, mode, ws, ws_bytes, _stream(stream)), "sws_conv1d_padded")
     return y
 
 
@@ -335,8 +364,9 @@ def sws_conv1d(x, wgt, stride=1, pad=0, dilation=1, groups=1, y=None, stream=Non
     if lo < 1:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d")
     y = _out(y, (b, cout, lo), x)
-    _check(lib().sws_conv1d(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), b, cin, length, cout, k, stride,
-                            pad, dilation, groups, _stream(stream)), "sws_conv1d")
+    keep, ws, ws_bytes = _workspace(wgt, cig, cout, k, b * lo, stream) if groups == 1 else (None, None, 0)
+    _check(lib().sws_conv1d_ws(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), b, cin, length, cout, k, stride,
+                            pad, dilation, groups, ws, ws_bytes, _stream(stream)), "sws_conv1d")
     return y
 
 
@@ -375,8 +405,9 @@ def sws_conv1d_grad_input(gy, wgt, length, stride=1, pad=0, dilation=1, groups=1
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d_grad_input")
     cin = cig * groups
     gx = _out(gx, (b, cin, length), gy, "gx")
-    _check(lib().sws_conv1d_grad_input(gy.data_ptr(), wgt.data_ptr(), gx.data_ptr(), b, cin, length, cout, k, stride,
-                                       pad, dilation, groups, _stream(stream)), "sws_conv1d_grad_input")
+    keep, ws, ws_bytes = _workspace(wgt, cout, cig, k, b * lo, stream) if groups == 1 else (None, None, 0)
+    _check(lib().sws_conv1d_grad_input_ws(gy.data_ptr(), wgt.data_ptr(), gx.data_ptr(), b, cin, length, cout, k, stride,
+                                       pad, dilation, groups, ws, ws_bytes, _stream(stream)), "sws_conv1d_grad_input")
     return gx
 
 
@@ -406,8 +437,9 @@ def sws_conv2d_padded(x, wgt, sh=1, sw=1, pads=(0, 0, 0, 0), mode=0, y=None, str
     if cin2 != cin or ho < 1 or wo < 1 or min(pads) < 0:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d_padded")
     y = _out(y, (n, cout, ho, wo), x)
-    _check(lib().sws_conv2d_padded(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), n, cin, h, wd, cout, kh, kw, sh, sw,
-                                   pt, pl, pb, pr, mode, _stream(stream)), "sws_conv2d_padded")
+    keep, ws, ws_bytes = _workspace(wgt, cin, cout, kh * kw, n * ho * wo, stream)
+    _check(lib().sws_conv2d_padded_ws(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), n, cin, h, wd, cout, kh, kw, sh, sw,
+                                   pt, pl, pb, pr, mode, ws, ws_bytes, _stream(stream)), "sws_conv2d_padded")
     return y
 
 
@@ -423,8 +455,9 @@ def sws_conv2d(x, wgt, sh=1, sw=1, ph=0, pw=0, y=None, stream=None):
     if ho < 1 or wo < 1:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d")
     y = _out(y, (n, cout, ho, wo), x)
-    _check(lib().sws_conv2d(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), n, cin, h, wd, cout, kh, kw,
-                            sh, sw, ph, pw, _stream(stream)), "sws_conv2d")
+    keep, ws, ws_bytes = _workspace(wgt, cin, cout, kh * kw, n * ho * wo, stream)
+    _check(lib().sws_conv2d_ws(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), n, cin, h, wd, cout, kh, kw,
+                            sh, sw, ph, pw, ws, ws_bytes, _stream(stream)), "sws_conv2d")
     return y
 
 
@@ -437,8 +470,9 @@ def sws_conv2d_grad_input(gy, wgt, h, wd, sh=1, sw=1, ph=0, pw=0, gx=None, strea
     if cout2 != cout or ho != sws_out_len(h, kh, sh, ph) or wo != sws_out_len(wd, kw, sw, pw):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d_grad_input")
     gx = _out(gx, (n, cin, h, wd), gy, "gx")
-    _check(lib().sws_conv2d_grad_input(gy.data_ptr(), wgt.data_ptr(), gx.data_ptr(), n, cin, h, wd, cout, kh, kw,
-                                       sh, sw, ph, pw, _stream(stream)), "sws_conv2d_grad_input")
+    keep, ws, ws_bytes = _workspace(wgt, cout, cin, kh * kw, n * ho * wo, stream)
+    _check(lib().sws_conv2d_grad_input_ws(gy.data_ptr(), wgt.data_ptr(), gx.data_ptr(), n, cin, h, wd, cout, kh, kw,
+                                       sh, sw, ph, pw, ws, ws_bytes, _stream(stream)), "sws_conv2d_grad_input")
     return gx
 
 

@@ -542,8 +542,16 @@ constexpr int kThinMaxK = 64;
 // the matrix rate on how much of its 64-channel tile the output channels fill.
 // With stride 2 the vector-ALU kernel has half the taps per staged phase: k = 51: 36-44, k = 31:
 // 29-38, k = 9: 6-8, k = 3: 2-3, against 10 / 24 / 52 / 80 on the matrix cores for C = 8 / 16 / 32 / 64.
-bool prefer_few(int64_t Cin, int64_t Cout, int k, bool strided)
+// With a workspace the matrix side is the split-operand kernel (conv_split.hip): any channel counts in steps of 16
+// and 32, 100 TFLOP/s and more where they are filled ([16,60,3474] -> 32, k = 3: 45 us on the vector ALU, 20 us there).
+bool prefer_few(int64_t Cin, int64_t Cout, int k, bool strided, bool split)
 {
+    if (split) {
+        const double fill = (double)(Cin * Cout) / (double)(((Cin + 15) / 16 * 16) * ((Cout + 31) / 32 * 32));
+        const double valu = strided ? (k >= 40 ? 38.0 : (k >= 24 ? 31.0 : (k >= 12 ? 14.0 : (k >= 6 ? 7.0 : 2.5))))
+                                    : (k >= 24 ? 55.0 : (k >= 12 ? 35.0 : (k >= 6 ? 22.0 : 11.0)));
+        return valu > 100.0 * fill;
+    }
     if (Cin % 8 != 0) return true;                   // the matrix kernel stages 8 input channels at a time
     const double cm = (double)(Cout < 64 ? Cout : 64);
     if (strided) {
@@ -558,7 +566,7 @@ bool prefer_few(int64_t Cin, int64_t Cout, int k, bool strided)
 
 hipError_t launch_conv1d(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
                          int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
-                         int32_t groups, hipStream_t s, int wadj, bool *taken)
+                         int32_t groups, hipStream_t s, int wadj, bool *taken, Workspace ws)
 {
     // wadj: wgt is the [Cin, Cout/groups, k] array of the convolution whose adjoint this call
     // evaluates (x holds output gradients); the kernels read it transposed inside each group, taps
@@ -586,18 +594,26 @@ hipError_t launch_conv1d(const float *x, const float *wgt, float *y, int64_t B, 
     if (variant == 3 && !dense_ok) variant = 0;
     if (variant == 6 && !few_ok) variant = 0;
     if (variant == 7 && !strided_ok) variant = 0;
+    const bool split_ok = ws.p && k <= 64 && stride <= 2 && g_opt.conv1d_variant == 0 && g_opt.conv2d_variant == 0;
     const bool valu_ok = few_ok || (strided_ok && cig > 1);
     if (variant == 0) {
         if (thin_ok) variant = 2;
         else if (thin_dil_ok) variant = 4;
-        else if (dense_ok && !(valu_ok && prefer_few(Cin, Cout, k, stride > 1))) variant = 3;
+        else if (dense_ok && !(valu_ok && prefer_few(Cin, Cout, k, stride > 1, split_ok))) variant = 3;
         else variant = few_ok ? 6 : (strided_ok ? 7 : 1);
     }
-    if (variant == 3 && g_opt.conv1d_variant == 0 && !wadj && stride == 1 && dilation == 1) {
-        // a few dozen channels: the split-operand kernel that streams the input straight from memory
+    if (variant == 3 && g_opt.conv1d_variant == 0) {
         bool taken_s = false;
-        const hipError_t e = launch_conv1d_split(x, wgt, y, B, Cin, L, Cout, Lo, k, pad, s, &taken_s);
-        if (taken_s || e != hipSuccess) return e;
+        if (ws.p) {                                   // the caller lends memory for split weights
+            const hipError_t e = launch_conv2d_split(x, wgt, y, B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad, 1, dilation, s,
+                                                     &taken_s, wadj, ws);
+            if (taken_s || e != hipSuccess) return e;
+        }
+        if (!wadj && stride == 1 && dilation == 1) {
+            // a few dozen channels: the split-operand kernel that streams the input straight from memory
+            const hipError_t e = launch_conv1d_split(x, wgt, y, B, Cin, L, Cout, Lo, k, pad, s, &taken_s);
+            if (taken_s || e != hipSuccess) return e;
+        }
     }
     if (variant == 3) {
         // the dense contraction is the 2-D kernel on images of height 1
@@ -675,10 +691,10 @@ hipError_t launch_conv1d(const float *x, const float *wgt, float *y, int64_t B, 
 // point's case; every other geometry is evaluated directly.
 hipError_t launch_conv1d_padded(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
                                 int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad_left, int32_t pad_right,
-                                int32_t dilation, int32_t groups, int mode, hipStream_t s)
+                                int32_t dilation, int32_t groups, int mode, hipStream_t s, Workspace ws)
 {
     if (mode == SWS_PAD_IDENTITY && pad_left == pad_right)
-        return launch_conv1d(x, wgt, y, B, Cin, L, Cout, Lo, k, stride, pad_left, dilation, groups, s);
+        return launch_conv1d(x, wgt, y, B, Cin, L, Cout, Lo, k, stride, pad_left, dilation, groups, s, 0, nullptr, ws);
     const int cig = (int)(Cin / groups), cog = (int)(Cout / groups);
     if (cig == 1 && stride == 1 && dilation == 1 && k <= kThinMaxK && g_opt.conv1d_variant != 1) {
         hipError_t e = kNotTaken;

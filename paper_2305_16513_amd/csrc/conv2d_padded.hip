@@ -235,14 +235,14 @@ void interior(int len, int k, int s, int pad, int lo, int *i0, int *i1)
 
 hipError_t launch_conv2d_padded(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H, int64_t W,
                                 int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh, int32_t sw,
-                                int32_t pt, int32_t pl, int32_t pb, int32_t pr, int mode, hipStream_t s)
+                                int32_t pt, int32_t pl, int32_t pb, int32_t pr, int mode, hipStream_t s, Workspace ws)
 {
     const bool even = pt == pb && pl == pr;
-    if (mode == SWS_PAD_IDENTITY && even) return launch_conv2d(x, wgt, y, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, pt, pl, s);
+    if (mode == SWS_PAD_IDENTITY && even) return launch_conv2d(x, wgt, y, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, pt, pl, s, ws);
     const int64_t cgroups = (Cout + kCoPer - 1) / kCoPer;
     // the tap set of a workgroup is a 64-bit mask
     if (mode != SWS_PAD_IDENTITY && even && g_opt.conv2d_variant != 1 && N * cgroups <= 65535 && kh * (int64_t)kw <= 64) {
-        const hipError_t e = launch_conv2d(x, wgt, y, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, pt, pl, s);
+        const hipError_t e = launch_conv2d(x, wgt, y, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, pt, pl, s, ws);
         if (e != hipSuccess) return e;
         Frame f;
         interior((int)H, kh, sh, pt, (int)Ho, &f.r0, &f.r1);

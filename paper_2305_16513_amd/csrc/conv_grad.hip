@@ -604,12 +604,12 @@ __global__ __launch_bounds__(kThreads) void conv2d_grad_weight_naive_kernel(
 // stride 1: the dense kernel above, one kernel row per tap group.
 hipError_t launch_conv2d_grad_input(const float *gy, const float *wgt, float *gx, int64_t N, int64_t Cin, int64_t H,
                                     int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
-                                    int32_t sw, int32_t ph, int32_t pw, hipStream_t s)
+                                    int32_t sw, int32_t ph, int32_t pw, hipStream_t s, Workspace ws)
 {
     if (sh == 1 && sw == 1 && ph <= kh - 1 && pw <= kw - 1 && g_opt.conv2d_variant != 1) {
         bool taken = false;
         const hipError_t e = launch_conv2d_mfma(gy, wgt, gx, N, Cout, Ho, Wo, Cin, H, W, kh, kw, 1, 1, kh - 1 - ph,
-                                                kw - 1 - pw, 1, 1, s, &taken, 1);
+                                                kw - 1 - pw, 1, 1, s, &taken, 1, ws);
         if (taken || e != hipSuccess) return e;
     }
     if ((sh > 1 || sw > 1) && N > 0 && g_opt.conv2d_variant != 1) {
@@ -621,7 +621,7 @@ hipError_t launch_conv2d_grad_input(const float *gy, const float *wgt, float *gx
         }
         bool taken = false;
         const hipError_t e = launch_conv2d_grad_input_phases(gy, wgt, gx, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph,
-                                                             pw, s, &taken);
+                                                             pw, s, &taken, ws);
         if (taken || e != hipSuccess) return e;
     }
     int64_t grid = (N * Cin * H * W + kThreads - 1) / kThreads;
@@ -677,14 +677,15 @@ hipError_t launch_conv2d_grad_weight(const float *x, const float *gy, float *gw,
 
 hipError_t launch_conv1d_grad_input(const float *gy, const float *wgt, float *gx, int64_t B, int64_t Cin, int64_t L,
                                     int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad,
-                                    int32_t dilation, int32_t groups, hipStream_t s)
+                                    int32_t dilation, int32_t groups, hipStream_t s, Workspace ws)
 {
     const int64_t back_pad = (int64_t)dilation * (k - 1) - pad;
+    if (g_opt.conv1d_variant != 0) ws = {};
     if (stride == 1 && back_pad >= 0 && g_opt.conv1d_variant != 1) {
         // the adjoint as a forward call: Cout channels of length Lo in, Cin channels of length L out
         bool taken = false;
         const hipError_t e = launch_conv1d(gy, wgt, gx, B, Cout, Lo, Cin, L, k, 1, (int32_t)back_pad, dilation, groups, s,
-                                           1, &taken);
+                                           1, &taken, ws);
         if (taken || e != hipSuccess) return e;
     }
     if (stride > 1 && dilation == 1 && groups == 1 && Cin >= 2 && B > 0 && g_opt.conv1d_variant != 1) {
@@ -697,7 +698,7 @@ hipError_t launch_conv1d_grad_input(const float *gy, const float *wgt, float *gx
         }
         bool taken = false;
         const hipError_t e = launch_conv2d_grad_input_phases(gy, wgt, gx, B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad,
-                                                             s, &taken);
+                                                             s, &taken, ws);
         if (taken || e != hipSuccess) return e;
     }
     int64_t grid = (B * Cin * L + kThreads - 1) / kThreads;

@@ -652,6 +652,24 @@ hipError_t c8_launch(const C8Launch &L, const float *x, const float *wgt, float 
 
 }  // namespace
 
+// The layer as taps for the split-operand kernel (conv_split.hip), weights plain or through the adjoint view.
+hipError_t launch_conv2d_split(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H, int64_t W,
+                               int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh, int32_t sw,
+                               int32_t ph, int32_t pw, int32_t dh, int32_t dw, hipStream_t s, bool *taken, int wadj, Workspace ws)
+{
+    *taken = false;
+    const int64_t KT = (int64_t)kh * kw;
+    if (!ws.p || KT > 64 || (g_opt.conv2d_variant != 0 && g_opt.conv2d_variant < 100)) return hipSuccess;
+    int th[64], tw[64], wt[64];
+    for (int t = 0; t < KT; ++t) {
+        th[t] = t / kw * dh - ph;
+        tw[t] = t % kw * dw - pw;
+        wt[t] = wadj ? (int)KT - 1 - t : t;
+    }
+    return launch_conv_split(x, wgt, y, N, Cin, H, W, Cout, Ho, Wo, Ho, Wo, sh, sw, (int)KT, th, tw, wt, nullptr,
+                             wadj ? KT : Cin * KT, wadj ? Cout * KT : KT, ws, s, taken);
+}
+
 // groups = 1 convolution on the matrix cores.  The channel-fastest kernel takes strides and tap
 // spacing, and kernels of more than 9 taps run as a chain of launches over chunks of taps (whole
 // kernel rows, or runs of taps of a one-row kernel), each adding to what the earlier ones left in
@@ -660,7 +678,7 @@ hipError_t c8_launch(const C8Launch &L, const float *x, const float *wgt, float 
 hipError_t launch_conv2d_mfma(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,
                               int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
                               int32_t sw, int32_t ph, int32_t pw, int32_t dh, int32_t dw, hipStream_t s, bool *taken,
-                              int wadj)
+                              int wadj, Workspace ws)
 {
     *taken = false;
     const bool plain = sh == 1 && sw == 1 && dh == 1 && dw == 1;
@@ -671,6 +689,18 @@ hipError_t launch_conv2d_mfma(const float *x, const float *wgt, float *y, int64_
     if (KT == 1 && plain && ph == 0 && pw == 0 && H > 1) {
         W *= H; H = 1;
         Wo *= Ho; Ho = 1;
+    }
+    // With a workspace: the split-operand kernel, except 64 -> 64 channels, 3 x 3, with enough position blocks for the
+    // streaming kernel's split form, whose weights stay in registers and whose runs leave no last wave:
+    // [32,64,56,56] 50 / 56 us, [64,64,56,56] 94 / 110, [128,64,28,28] 54 / 60 (with 128 output channels 113 / 108, with
+    // half the positions 54 / 33).
+    if (ws.p && plain && Cin == 64 && Cout == 64 && g_opt.conv2d_variant == 0) {
+        const hipError_t e = launch_conv2d_stream(x, wgt, y, N, Cin, H, W, Cout, Ho, Wo, kh, kw, ph, pw, s, taken, wadj, true);
+        if (*taken || e != hipSuccess) return e;
+    }
+    if (ws.p) {
+        const hipError_t e = launch_conv2d_split(x, wgt, y, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw, dh, dw, s, taken, wadj, ws);
+        if (*taken || e != hipSuccess) return e;
     }
     // the weight-stationary streaming kernel where it applies (option conv2d_variant 16 switches it off,
     // 17 takes it for small problems too)
@@ -759,10 +789,29 @@ hipError_t launch_conv2d_mfma(const float *x, const float *wgt, float *y, int64_
 hipError_t launch_conv2d_grad_input_phases(const float *gy, const float *wgt, float *gx, int64_t N, int64_t Cin,
                                            int64_t H, int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh,
                                            int32_t kw, int32_t sh, int32_t sw, int32_t ph, int32_t pw, hipStream_t s,
-                                           bool *taken)
+                                           bool *taken, Workspace ws)
 {
     *taken = false;
     const int KTF = kh * kw;
+    // stride 2 on both axes (or along rows of height 1) with a workspace: all four phases in one launch.  Cell
+    // h = 2 i + er is reached by the taps a with (er + ph - a) even, from row i + (er + ph - a) / 2 of gy.
+    if (ws.p && KTF <= 64 && (sh == 2 || (H == 1 && kh == 1 && ph == 0)) && sw == 2 &&
+        (g_opt.conv2d_variant == 0 || g_opt.conv2d_variant >= 100)) {
+        int th[64], tw[64], wt[64], phase[64], n = 0;
+        for (int f = 0; f < 4; ++f)
+            for (int a = 0; a < kh; ++a)
+                for (int b = 0; b < kw; ++b) {
+                    const int er = f >> 1, ec = f & 1;
+                    if (((er + ph - a) & 1) || ((ec + pw - b) & 1)) continue;
+                    th[n] = (er + ph - a) / 2;
+                    tw[n] = (ec + pw - b) / 2;
+                    wt[n] = a * kw + b;
+                    phase[n++] = f;
+                }
+        const hipError_t e = launch_conv_split(gy, wgt, gx, N, Cout, Ho, Wo, Cin, (H + 1) / 2, (W + 1) / 2, H, W, 1, 1, KTF, th, tw, wt,
+                                               phase, KTF, Cin * KTF, ws, s, taken);
+        if (*taken || e != hipSuccess) return e;
+    }
     if (H * W > 2147483647LL / 2 || Cout * Cin * KTF > 2147483647LL / 2 || sh * sw > 16) return hipSuccess;
     constexpr int kMaxLaunch = 64;
     C8Launch L[kMaxLaunch];

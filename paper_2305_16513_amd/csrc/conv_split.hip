@@ -1,0 +1,747 @@
+// Dense-channel convolution (Section 2.5) on the bf16 matrix cores with exactly split fp32 operands: any
+// kernel of up to 64 taps, stride 1 or 2, any channel counts, one or two dimensions, forward and the adjoint with
+// respect to the input.
+//
+//   y[n][co][p] = sum over taps t, input channels ci of  W_t[co][ci] * X[n][ci][p * s + t]
+//
+// is a sum of matrix products over shifted views of the same input, the sliding sum over taps.  An fp32 number
+// is the exact sum of three bf16 numbers and a product of two bf16 numbers is exact in fp32; of the nine piece
+// products of x * w the three smallest are below 2^-23 of the product, the other six are accumulated in fp32 by
+// v_mfma_f32_32x32x16_bf16: 6 instructions of 32 cycles per 16 channels, tap and 32 x 32 outputs where the fp32
+// matrix instruction needs 8 of 64 cycles.
+//
+// Two launches.  split_weights_kernel writes the weights' pieces into the caller's workspace in the order in which
+// the matrix instruction wants them (1 KB per piece of a 32 x 16 block, lane after lane), whatever view they are
+// read through (plain, adjoint, output phases of a strided adjoint).  Splitting them inside the main kernel would
+// be repeated by every workgroup, and their LDS traffic would double; from the workspace they go
+// straight into registers, one 128-bit load per lane and operand, served by L2.
+// conv_split_kernel: a workgroup computes 32*MB*WM output channels x 32*NB*WN output positions (each wavefront
+// MB x NB blocks of 32 x 32; WK wavefronts share a block's contraction).  Per chunk of 16*NC input
+// channels the input lines that the tile's windows meet are loaded once, zero-padded, split and written to LDS as
+// 16-byte units of eight channels of one position and piece, positions contiguous; a tap's B operand is that tile
+// read at a shifted address, so nothing is staged per tap and no column matrix exists.  Strided layers
+// store the columns of a line by residue, so that the positions of a tap are contiguous there too.
+//
+// Tiles.  Output rows of all images are numbered through (virtual rows) and cut into strips of TW columns; the
+// positions of a strip are numbered row after row and a tile is a run of them, so that small planes fill whole
+// tiles.  Where runs that start at row ends stage fewer lines, a tile takes whole rows of the strip instead.
+//
+// Output phases (NPH = 4): the adjoint of a stride-2 layer computes the four cells (2i + er, 2j + ec) of gx from
+// the same staged gradients; every tap belongs to one phase, so the work is that of the forward pass, and the two
+// cells of a row leave as one store.
+#include "sws_internal.h"
+
+#include <type_traits>
+
+namespace sws {
+
+namespace {
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef v2f v2f_u __attribute__((aligned(4)));
+
+constexpr int kMaxSteps = 64;                         // contraction steps per chunk and wavefront (one lane holds one)
+constexpr int kStepBytes = 3 * 1024;                  // a step's weights of 32 output channels: 3 pieces x 64 lanes x 16 bytes
+constexpr int kPadSteps = 4;                          // steps behind the last one that the prefetch may touch
+
+struct SplitGeom {
+    int N, Cin, H, W, HW, Cout, Ho, NR;               // input planes; NR = N * Ho virtual output rows
+    int KT, S, NC, nchunk, KS;                        // taps; steps per chunk and wavefront; 16-channel groups, chunks; steps per wavefront
+    int ls, LPI, SH, sh, sw, dh0, dw0;                // lines: per output row, per image, per window; strides, first row / column offset
+    int CW, LW, TW, TWl, nstrips;                     // columns per residue, positions per line, strip widths
+    int bnp, bnpl, tpf, tiles, cot;                   // positions per tile (last strip), tiles per full strip, all tiles, channel tiles
+    int PS, bufs;                                     // staged positions; bytes from one LDS buffer to the other
+    int yHW, yH, yW, ys;                              // output planes; cells per position and axis (1, or 2 for phases)
+    int nt[4];                                        // phases: taps of each
+    float inv_tw, inv_twl, inv_Ho, inv_LPI, inv_LW, inv_CW, inv_PS, inv_KT;
+    unsigned short tapoff[kMaxSteps];                 // tap -> staged positions from a position's base
+};
+
+struct PrepGeom {
+    int Cin, Cout, KT, G, WK;                         // contraction channels, output channels, taps, 16-channel groups (padded), K split
+    int wco, wci;                                     // elements from one output / contraction channel to the next
+    unsigned short wtap[kMaxSteps];                   // tap -> element
+};
+
+__device__ __forceinline__ int fdiv(int x, float inv_d) { return (int)(((float)x + 0.5f) * inv_d); }    // 0 <= x < 2^20
+
+// the upper halves of two floats as one register of two bf16 (lo in the low half)
+__device__ __forceinline__ unsigned pack_hi(float lo, float hi)
+{
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+
+// One wavefront per (32 output channels, 16 contraction channels, tap): lane (l32, half) writes W[co = l32][8 half + e].
+// Rounding to nearest in every piece: the pieces sum to the weight exactly and the dropped products are smallest.
+__global__ __launch_bounds__(256) void split_weights_kernel(const float *__restrict__ wgt, v4u *__restrict__ ws, PrepGeom g)
+{
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    const int t = blockIdx.z * 4 + (int)(threadIdx.x >> 6);
+    if (t >= g.KT) return;
+    const int grp = blockIdx.x, cb = blockIdx.y;
+    const int co = cb * 32 + l32, ci0 = grp * 16 + half * 8;
+    const float *src = wgt + (int64_t)(co < g.Cout ? co : 0) * g.wco + g.wtap[t];
+    unsigned p[3][4];
+    float f[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        // an octet that reaches beyond the last channel holds the last eight; those that the octet before it holds
+        // too count as zero there (fewer than eight channels in all: the slots behind the last)
+        const int cs = ci0 < g.Cin - 8 ? ci0 : (g.Cin > 8 ? g.Cin - 8 : 0), c = cs + e;
+        const bool ok = co < g.Cout && c >= ci0 && c < g.Cin;
+        const float v = src[(int64_t)(c < g.Cin ? c : 0) * g.wci];
+        f[e] = ok ? v : 0.0f;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        unsigned short h[3][2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const float v = f[e + u];
+            const __bf16 f1 = (__bf16)v;
+            const float r1 = v - (float)f1;
+            const __bf16 f2 = (__bf16)r1;
+            const __bf16 f3 = (__bf16)(r1 - (float)f2);
+            h[0][u] = __builtin_bit_cast(unsigned short, f1);
+            h[1][u] = __builtin_bit_cast(unsigned short, f2);
+            h[2][u] = __builtin_bit_cast(unsigned short, f3);
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) p[q][e / 2] = (unsigned)h[q][0] | (unsigned)h[q][1] << 16;
+    }
+    // a wavefront's groups are consecutive: group grp belongs to wavefront grp % WK of the K split
+    const int64_t step = ((int64_t)cb * g.G + (grp % g.WK) * (g.G / g.WK) + grp / g.WK) * g.KT + t;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) ws[step * (kStepBytes / 16) + q * 64 + lane] = (v4u){p[q][0], p[q][1], p[q][2], p[q][3]};
+}
+
+// One buffer descriptor: loads beyond `bytes` return zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+
+constexpr unsigned kNowhere = 0x80000000u;            // beyond every descriptor
+
+// U: staged units (eight channels of one position) per thread.  S: steps per chunk and wavefront when that number is
+// compiled in (the chunk is then straight-line code: the next chunk's loads go out between the first products and
+// their splitting runs between the last ones; with a loop over the steps the wait counters have to assume
+// the worst order of the two kinds of loads), 0: any number.  R: steps of weights held, R - 1 of them in flight.
+// WPE: wavefronts per SIMD that the registers are meant for.
+template <int MB, int NB, int WM, int WN, int WK, int U, int NPH, int WPE, int S>
+__global__ __launch_bounds__(64 * WM * WN * WK) __attribute__((amdgpu_waves_per_eu(WPE)))
+void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, float *__restrict__ y, SplitGeom g)
+{
+    constexpr int T = 64 * WM * WN * WK;
+    constexpr int R = S ? (S % 3 == 0 ? 3 : 4) : 2;
+    static_assert(S == 0 || (S % R == 0 && NPH == 1), "the ring of weights closes over a chunk");
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave / (WM * WN), wmn = wave - wk * (WM * WN), wn = wmn / WM, wm = wmn - wn * WM;
+
+    // XCD-aware: workgroup b runs on XCD b mod 8; each XCD takes a contiguous run of tiles, the channel tiles of one
+    // position tile next to each other (they read the same input lines)
+    const int Gx = (int)gridDim.x;                    // a multiple of 8
+    const int id = (int)(blockIdx.x & 7) * (Gx >> 3) + (int)(blockIdx.x >> 3);
+    if (id >= g.tiles * g.cot) return;
+    const int pt = id / g.cot, ct = id - pt * g.cot;
+    int strip = pt / g.tpf;
+    strip = strip < g.nstrips - 1 ? strip : g.nstrips - 1;
+    const bool last = strip == g.nstrips - 1;
+    const int tw = last ? g.TWl : g.TW, bnp = last ? g.bnpl : g.bnp;
+    const float inv_tw = last ? g.inv_twl : g.inv_tw;
+    const int q0 = (pt - strip * g.tpf) * bnp;
+    const int R0 = q0 / tw, c_0 = q0 - R0 * tw;
+    const int n0 = R0 / g.Ho, oh0 = R0 - n0 * g.Ho;
+    const int colbase = strip * g.TW;
+
+    // ---- where my output positions start in the staged tile
+    auto place = [&](int b, int &Rr, int &c, int &dn, int &oh) {
+        const int jj = c_0 + (wn * NB + b) * 32 + l32;
+        Rr = fdiv(jj, inv_tw);
+        c = jj - Rr * tw;
+        const int tt = oh0 + Rr;
+        dn = fdiv(tt, g.inv_Ho);
+        oh = tt - dn * g.Ho;
+        return (wn * NB + b) * 32 + l32 < bnp && R0 + Rr < g.NR;
+    };
+    int posb[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        int Rr, c, dn, oh;
+        posb[b] = place(b, Rr, c, dn, oh) ? ((dn * g.LPI + oh * g.ls - oh0 * g.ls) * g.LW + c) * 16 : 0;
+    }
+
+    // ---- my staged units: where they come from, where they go
+    const int noct = 2 * g.NC;
+    int jl = bnp - 1;                                 // the tile's last position decides how many lines it needs
+    {
+        const int64_t left = (int64_t)g.NR * tw - q0 - 1;
+        if (left < jl) jl = (int)left;
+    }
+    const int Rl = fdiv(c_0 + jl, inv_tw), tl = oh0 + Rl, dl = fdiv(tl, g.inv_Ho);
+    const int nlines = dl * g.LPI + (tl - dl * g.Ho) * g.ls - oh0 * g.ls + g.SH;
+    unsigned voff[U];                                 // bytes from image n0 to the position, channel 0; cells that do not exist: kNowhere
+    int dst[U], c8[U];                                // place in the staged tile; first channel inside the chunk
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+        const int u = tid + i * T;
+        const int oct = fdiv(u, g.inv_PS), pos = u - oct * g.PS;
+        const int lr = fdiv(pos, g.inv_LW), cc = pos - lr * g.LW;
+        const int cph = fdiv(cc, g.inv_CW), cq = cc - cph * g.CW;
+        const int col = (colbase + cq) * g.sw + cph + g.dw0;
+        const int l = oh0 * g.ls + lr, dn = fdiv(l, g.inv_LPI), r = l - dn * g.LPI;
+        const int row = (g.SH >= g.sh ? r : r * g.sh) + g.dh0;
+        const bool in = oct < noct;
+        const bool ok = in && lr < nlines && n0 + dn < g.N && (unsigned)row < (unsigned)g.H && (unsigned)col < (unsigned)g.W;
+        voff[i] = ok ? 4u * (unsigned)(dn * g.Cin * g.HW + row * g.W + col) : kNowhere;
+        c8[i] = oct * 8;
+        dst[i] = in ? (oct * 3 * g.PS + pos) * 16 : -1;
+    }
+    const int units = noct * g.PS;
+    const int64_t x_left = 4 * (int64_t)(g.N - n0) * g.Cin * g.HW;
+    const __amdgpu_buffer_rsrc_t xrs = rsrc(x + (int64_t)n0 * g.Cin * g.HW, x_left < 0x7fffffff ? (unsigned)x_left : 0x7fffffffu);
+    const int cmax = g.Cin > 8 ? g.Cin - 8 : 0;       // the last eight channels: an octet that reaches beyond them starts there
+    float xr[U][8];
+    auto issue = [&](int i, int ch) {                 // unit i of chunk ch (no branches: the wait counters stay exact)
+        int c = ch * (16 * g.NC) + c8[i];
+        c = c < cmax ? c : cmax;
+        const unsigned at = voff[i] == kNowhere ? kNowhere : voff[i] + 4u * (unsigned)(c * g.HW);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int se = e < g.Cin ? e : g.Cin - 1;
+            xr[i][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrs, at, 4 * se * g.HW, 0));
+        }
+    };
+    auto commit = [&](int i, char *buf) {
+        if (i * T >= units) return;
+        unsigned p[3][4];
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            float r1[2], r2[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float v = xr[i][e + u];
+                r1[u] = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);
+                r2[u] = r1[u] - __uint_as_float(__float_as_uint(r1[u]) & 0xffff0000u);
+            }
+            p[0][e / 2] = pack_hi(xr[i][e], xr[i][e + 1]);
+            p[1][e / 2] = pack_hi(r1[0], r1[1]);
+            p[2][e / 2] = pack_hi(r2[0], r2[1]);
+        }
+        if (dst[i] >= 0) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) *(v4u *)(buf + dst[i] + q * (g.PS * 16)) = (v4u){p[q][0], p[q][1], p[q][2], p[q][3]};
+        }
+    };
+    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    // ---- my steps' places in the staged tile, one per lane (relative to my wavefront's first channel group)
+    int steptab;
+    {
+        const int s = lane < g.S ? lane : 0;
+        const int gl = fdiv(s, g.inv_KT), t = s - gl * g.KT;
+        steptab = gl * (WK * 6 * g.PS * 16) + g.tapoff[t] * 16;
+    }
+    const int bpiece = g.PS * 16;
+    const int bbase = (2 * wk + half) * 3 * bpiece;
+
+    // ---- weights: my MB blocks of 32 output channels, steps in order
+    const int ncb = (g.Cout + 31) >> 5;
+    __amdgpu_buffer_rsrc_t ars[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        int cb = (ct * WM + wm) * MB + m;
+        cb = cb < ncb ? cb : ncb - 1;                 // blocks beyond the last are computed from it and not stored
+        ars[m] = rsrc((const char *)ws + ((int64_t)cb * WK + wk) * g.KS * kStepBytes, (unsigned)(g.KS * kStepBytes));
+    }
+    v4u A[R][MB][3];
+    auto aload = [&](v4u (&a)[MB][3], int ks) {       // (beyond the last step: zeros that nothing uses)
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                a[m][q] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(ars[m], lane * 16 + q * 1024, ks * kStepBytes, 0));
+    };
+    v4u Bq[2][NB][3];
+    auto bload = [&](v4u (&b)[NB][3], const char *buf, int s) {
+        const int off = __builtin_amdgcn_readlane(steptab, s) + bbase;
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) b[j][q] = *(const v4u *)(buf + (off + posb[j]) + q * bpiece);
+    };
+
+    v16f acc[NPH][MB][NB];
+#pragma unroll
+    for (int f = 0; f < NPH; ++f)
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[f][m][b][v] = 0.0f;
+    // Products of the leading pieces go to one accumulator, the other five (at most 2^-8 of them) to another, added
+    // once at the end (phases: once per chunk): an output then takes one rounding of its own size per 16 channels and tap
+    // instead of six.
+    v16f lo[MB][NB];
+    auto clear_lo = [&]() {
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) lo[m][b][v] = 0.0f;
+    };
+    auto fold_lo = [&](v16f (&c)[MB][NB]) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) c[m][b] += lo[m][b];
+    };
+    clear_lo();
+    auto products = [&](v16f (&c)[MB][NB], const v4u (&a)[MB][3], const v4u (&b)[NB][3]) {
+        constexpr int PA[6] = {2, 0, 1, 0, 1, 0}, PB[6] = {0, 0, 1, 2, 0, 1};      // (the leading product second: the chains alternate)
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    v16f &d = k == 1 ? c[m][j] : lo[m][j];
+                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a[m][PA[k]]),
+                                                                __builtin_bit_cast(v8bf, b[j][PB[k]]), d, 0, 0, 0);
+                }
+    };
+
+#pragma unroll
+    for (int i = 0; i < U; ++i) issue(i, 0);
+#pragma unroll
+    for (int r = 0; r < R - 1; ++r) aload(A[r], r);
+#pragma unroll
+    for (int i = 0; i < U; ++i) commit(i, lds);
+    barrier();
+    int ks = 0;                                       // my step
+    char *cur = lds;
+    if constexpr (S != 0) {
+        // a chunk: on entry the weights of its first R - 1 steps are in slots 0 .. R - 2, on exit those of the next
+        auto chunk = [&](auto more, int ch) {
+            char *nxt = cur == lds ? lds + g.bufs : lds;
+            bload(Bq[0], cur, 0);
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                aload(A[(s + R - 1) % R], ks + s + R - 1);
+                if (s + 1 < S) bload(Bq[(s + 1) & 1], cur, s + 1);
+                if constexpr (more.value) {
+#pragma unroll
+                    for (int i = 0; i < U; ++i)
+                        if (i * (S / 2) / U == s) issue(i, ch + 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (more.value) {
+#pragma unroll
+                    for (int i = 0; i < U; ++i)
+                        if (S - U + i == s || (S < U && s == S - 1)) commit(i, nxt);
+                }
+                products(acc[0], A[s % R], Bq[s & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            ks += S;
+            if constexpr (more.value) {
+                cur = nxt;
+                barrier();
+            }
+        };
+        for (int ch = 0; ch + 1 < g.nchunk; ++ch) chunk(std::true_type{}, ch);
+        chunk(std::false_type{}, 0);
+    } else {
+        for (int ch = 0; ch < g.nchunk; ++ch) {
+            const bool more = ch + 1 < g.nchunk;
+            if (more) {
+#pragma unroll
+                for (int i = 0; i < U; ++i) issue(i, ch + 1);
+            }
+            bload(Bq[0], cur, 0);
+            // steps s0 .. s1 - 1; on entry the weights of step s0 are in slot 0 and its inputs in Bq[0], on exit likewise
+            auto step = [&](v16f (&c)[MB][NB], int r, int s) {
+                aload(A[r ^ 1], ks + 1);
+                bload(Bq[r ^ 1], cur, s + 1 < g.S ? s + 1 : 0);
+                __builtin_amdgcn_sched_barrier(0);
+                products(c, A[r], Bq[r]);
+                __builtin_amdgcn_sched_barrier(0);
+                ++ks;
+            };
+            auto run = [&](v16f (&c)[MB][NB], int s0, int s1) {
+                int s = s0;
+                for (; s + 2 <= s1; s += 2) {
+                    step(c, 0, s);
+                    step(c, 1, s + 1);
+                }
+                if (s < s1) {
+                    step(c, 0, s);
+#pragma unroll
+                    for (int m = 0; m < MB; ++m)
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) A[0][m][q] = A[1][m][q];
+#pragma unroll
+                    for (int j = 0; j < NB; ++j)
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) Bq[0][j][q] = Bq[1][j][q];
+                }
+            };
+            if constexpr (NPH == 1) {
+                run(acc[0], 0, g.S);
+            } else {
+                int s = 0;                            // phases: NC = WK, the chunk's steps are its taps, phase after phase
+#pragma unroll
+                for (int f = 0; f < NPH; ++f) {
+                    if (g.nt[f] == 0) continue;
+                    clear_lo();
+                    run(acc[f], s, s + g.nt[f]);
+                    fold_lo(acc[f]);
+                    s += g.nt[f];
+                }
+            }
+            if (more) {
+                cur = cur == lds ? lds + g.bufs : lds;
+#pragma unroll
+                for (int i = 0; i < U; ++i) commit(i, cur);
+                barrier();
+            }
+        }
+    }
+    if constexpr (NPH == 1) fold_lo(acc[0]);
+
+    // ---- the wavefronts that share a block add up through LDS
+    if constexpr (WK > 1) {
+        v4f *red = (v4f *)lds;
+        constexpr int BLK = NPH * MB * NB * 4 * 64;   // v4f per wavefront
+        for (int k = WK - 1; k >= 1; --k) {
+            barrier();
+            if (wk == k) {
+#pragma unroll
+                for (int f = 0; f < NPH; ++f)
+#pragma unroll
+                    for (int m = 0; m < MB; ++m)
+#pragma unroll
+                        for (int b = 0; b < NB; ++b)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                red[wmn * BLK + (((f * MB + m) * NB + b) * 4 + v) * 64 + lane] =
+                                    (v4f){acc[f][m][b][4 * v], acc[f][m][b][4 * v + 1], acc[f][m][b][4 * v + 2], acc[f][m][b][4 * v + 3]};
+            }
+            barrier();
+            if (wk == 0) {
+#pragma unroll
+                for (int f = 0; f < NPH; ++f)
+#pragma unroll
+                    for (int m = 0; m < MB; ++m)
+#pragma unroll
+                        for (int b = 0; b < NB; ++b)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                const v4f q = red[wmn * BLK + (((f * MB + m) * NB + b) * 4 + v) * 64 + lane];
+#pragma unroll
+                                for (int u = 0; u < 4; ++u) acc[f][m][b][4 * v + u] += q[u];
+                            }
+            }
+        }
+        if (wk != 0) return;
+    }
+
+    // ---- out: register v of lane (l32, half) is output channel 8*(v/4) + 4*half + v%4 of the block, position l32
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        int Rr, c, dn, oh;
+        if (!place(b, Rr, c, dn, oh)) continue;
+        const int col = colbase + c;
+        float *yb = y + (int64_t)(n0 + dn) * g.Cout * g.yHW + (int64_t)(oh * g.ys) * g.yW + col * g.ys;
+        const bool pcol1 = 2 * col + 1 < g.yW, prow1 = 2 * oh + 1 < g.yH;      // phases: the second column / row exists
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+            const int co0 = ((ct * WM + wm) * MB + m) * 32 + 4 * half;
+            float *yp = yb + (int64_t)co0 * g.yHW;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int dc = 8 * (v / 4) + v % 4;
+                if (co0 + dc >= g.Cout) continue;
+                float *d = yp + (int64_t)dc * g.yHW;
+                if constexpr (NPH == 1) {
+                    *d = acc[0][m][b][v];
+                } else {
+                    if (pcol1) *(v2f_u *)d = (v2f){acc[0][m][b][v], acc[1][m][b][v]};
+                    else *d = acc[0][m][b][v];
+                    if (prow1) {
+                        if (pcol1) *(v2f_u *)(d + g.yW) = (v2f){acc[2][m][b][v], acc[3][m][b][v]};
+                        else d[g.yW] = acc[2][m][b][v];
+                    }
+                }
+            }
+        }
+    }
+}
+
+struct Cfg { int mb, nb, wm, wn, wk, u, nph, wpe; };
+// wavefront block x wavefronts x K split; staged units per thread; phases; wavefronts per SIMD
+constexpr Cfg kCfg[] = {
+    {2, 2, 2, 2, 1, 3, 1, 1},     // 0: 128 x 128
+    {2, 2, 1, 4, 1, 4, 1, 1},     // 1:  64 x 256
+    {1, 2, 2, 2, 1, 4, 1, 2},     // 2:  64 x 128
+    {1, 2, 2, 2, 2, 3, 1, 2},     // 3:  64 x 128, two wavefronts per block
+    {1, 2, 1, 4, 1, 4, 1, 2},     // 4:  32 x 256
+    {1, 2, 4, 1, 1, 4, 1, 2},     // 5: 128 x 64
+    {1, 2, 2, 1, 2, 4, 1, 2},     // 6:  64 x 64, two wavefronts per block
+    {1, 2, 1, 2, 2, 4, 1, 2},     // 7:  32 x 128, two wavefronts per block
+    {1, 2, 1, 1, 4, 4, 1, 2},     // 8:  32 x 64, four wavefronts per block
+    {1, 1, 1, 1, 4, 4, 1, 2},     // 9:  32 x 32, four wavefronts per block
+    {1, 2, 2, 2, 1, 3, 4, 1},     // 10: 64 x 128 positions x 4 phases
+    {1, 1, 2, 2, 1, 4, 4, 2},     // 11:  64 x 64 x 4
+    {1, 1, 2, 2, 2, 3, 4, 2},     // 12:  64 x 64 x 4, two
+    {1, 1, 1, 2, 2, 4, 4, 2},     // 13:  32 x 64 x 4, two wavefronts per block
+};
+constexpr int kNumCfg = sizeof(kCfg) / sizeof(kCfg[0]);
+
+template <int I, int S>
+hipError_t launch_steps(const float *x, const v4u *ws, float *y, const SplitGeom &g, int grid, size_t lds, hipStream_t s)
+{
+    constexpr Cfg c = kCfg[I];
+    auto k = conv_split_kernel<c.mb, c.nb, c.wm, c.wn, c.wk, c.u, c.nph, c.wpe, S>;
+    if (lds > 64 * 1024) {
+        static std::atomic<bool> raised{false};       // (the attribute is per function; setting it twice does no harm)
+        if (!raised.load(std::memory_order_relaxed)) {
+            const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return e;
+            raised.store(true, std::memory_order_relaxed);
+        }
+    }
+    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * c.wm * c.wn * c.wk), lds, s, x, ws, y, g);
+    return hipGetLastError();
+}
+
+template <int I>
+hipError_t launch_cfg(const float *x, const v4u *ws, float *y, const SplitGeom &g, int grid, size_t lds, hipStream_t s)
+{
+    if constexpr (kCfg[I].nph == 1) {
+        switch (g.S) {
+        case 6: return launch_steps<I, 6>(x, ws, y, g, grid, lds, s);
+        case 8: return launch_steps<I, 8>(x, ws, y, g, grid, lds, s);
+        case 9: return launch_steps<I, 9>(x, ws, y, g, grid, lds, s);
+        case 12: return launch_steps<I, 12>(x, ws, y, g, grid, lds, s);
+        default: break;
+        }
+    }
+    return launch_steps<I, 0>(x, ws, y, g, grid, lds, s);
+}
+
+// A tile geometry for one configuration; cost: estimated cycles of the launch.
+struct Tiling {
+    int nstrips, TW, TWl, CW, LW, bnp, bnpl, tpf, tiles, cot, PS, NC, nchunk, S, KS, bufs, need;
+    double cost;
+};
+
+// The cheapest tiling of configuration c; false: none fits.  (32-bit divisions: this runs on every call.)
+bool plan(const SplitGeom &g, const Cfg &c, int Wo, int SW, int cus, Tiling *best)
+{
+    const int BN = 32 * c.nb * c.wn, BM = 32 * c.mb * c.wm, T = 64 * c.wm * c.wn * c.wk;
+    const int SWc = SW < g.sw ? SW : g.sw;            // column residues that are read
+    const unsigned groups = (unsigned)(g.Cin + 15) / 16;
+    bool found = false;
+    Tiling h;
+    h.cot = (int)((unsigned)(g.Cout + BM - 1) / BM);
+    const int whole = (int)((unsigned)(Wo + BN - 1) / BN);      // strips of at most BN columns
+    for (int ns = 1; ns <= Wo; ns = ns < 4 ? ns + 1 : (ns < whole ? whole : Wo + 1)) {
+        for (int aligned = 0; aligned < 2; ++aligned) {
+            int tw = (int)((unsigned)(Wo + ns - 1) / ns);
+            if (ns >= 4 && aligned && tw < BN) tw = BN < Wo ? BN : Wo;
+            if (tw > 16384) continue;
+            h.nstrips = (int)((unsigned)(Wo + tw - 1) / tw);
+            h.TW = tw;
+            h.TWl = Wo - (h.nstrips - 1) * tw;
+            h.CW = tw + (int)((unsigned)(SW - 1) / g.sw);
+            h.LW = SWc * h.CW;
+            int lines = 0;
+            unsigned tl[2];
+            bool ok = true;
+            for (int e = h.nstrips > 1 ? 0 : 1; e < 2; ++e) {       // full strips, last strip
+                const int w = e ? h.TWl : h.TW;
+                int bnp = BN;
+                int rows = (int)((unsigned)(BN + w - 2) / w) + 1;
+                const int fit = (int)((unsigned)BN / w);
+                if (aligned) {
+                    if (fit == 0) { ok = false; break; }
+                    rows = fit;
+                    bnp = rows * w;
+                } else if (fit * w == BN) {
+                    rows = fit;
+                }
+                if (rows > g.NR) rows = g.NR;
+                const int crossings = (int)((unsigned)(rows - 1 + g.Ho - 1) / g.Ho);
+                const int nl = (rows - 1) * g.ls + g.SH + crossings * (g.SH - g.ls);
+                if (nl > lines) lines = nl;
+                (e ? h.bnpl : h.bnp) = bnp;
+                tl[e] = ((unsigned)g.NR * (unsigned)w + (unsigned)bnp - 1) / (unsigned)bnp;
+            }
+            if (!ok || lines > 4096 || lines * h.LW > 4096) continue;
+            if (h.nstrips == 1) { h.bnp = h.bnpl; tl[0] = tl[1]; }
+            h.PS = lines * h.LW;
+            const int64_t tiles = (int64_t)tl[0] * (h.nstrips - 1) + tl[1];
+            if (tiles * h.cot > (1 << 30)) continue;
+            h.tpf = (int)tl[0];
+            h.tiles = (int)tiles;
+            // channel groups per chunk: enough steps to pass a chunk's loads behind (kernels of few taps), whole rounds of the K split
+            int nc = c.wk, per = 1;                   // per = nc / wk
+            if (c.nph == 1)
+                while (per * g.KT < 8 && (unsigned)(2 * nc) <= (groups + c.wk - 1) / c.wk * c.wk && 2 * per * g.KT <= kMaxSteps &&
+                       4 * nc * h.PS <= c.u * T) {
+                    nc *= 2;
+                    per *= 2;
+                }
+            if (2 * nc * h.PS > c.u * T) continue;
+            h.NC = nc;
+            h.nchunk = (int)((groups + nc - 1) / nc);
+            h.S = per * g.KT;
+            if (h.S > kMaxSteps) continue;
+            h.KS = h.nchunk * h.S;
+            const int buf = 2 * nc * 3 * h.PS * 16;
+            h.bufs = h.nchunk > 1 ? buf : 0;
+            h.need = buf + h.bufs;
+            const int red = c.wk > 1 ? c.nph * c.mb * c.nb * 4 * 64 * 16 * c.wm * c.wn : 0;
+            if (h.need < red) h.need = red;
+            if (h.need > 156 * 1024) continue;
+            // Estimated time, in cycles: a workgroup alone takes `alone`, res of them share a compute unit at one per
+            // `shared`.  The constants are fitted to 1900 measured launches (104 layers, both directions, all
+            // configurations): the choice they give is on average 1 % slower than the best configuration of each layer.
+            const double wpw = T / 256.0;             // wavefronts per SIMD and workgroup
+            double res = c.wpe / wpw;                 // workgroups per compute unit: registers, 160 KB of LDS
+            const int by_lds = 160 * 1024 / h.need;
+            if (by_lds < res) res = by_lds;
+            if (res < 1) res = 1;
+            const bool line = c.nph == 1 && (h.S == 6 || h.S == 8 || h.S == 9 || h.S == 12);      // straight-line chunks
+            const double mfma = (double)h.KS * c.mb * c.nb * 6 * 32 * wpw * (c.nph == 1 ? 1.0 : 1.106);
+            const double wld = (double)h.KS * (T / 64) * c.mb * 48;       // weights through the vector cache, 64 bytes per cycle
+            const double stage = h.nchunk * (890 + 375 * wpw * ((2 * nc * h.PS + T - 1) / T)) * (line ? 1.0 : 1.105);
+            const double m = 1.419 * mfma, l = 0.157 * wld;
+            const double shared = (m > l ? m : l) + 0.625 * stage;
+            const double alone = 0.958 * mfma + 0.516 * wld + stage + 6979 + (c.wk > 1 ? 466 * c.mb * c.nb * c.nph : 0);
+            const double n = (double)tiles * h.cot / cus;
+            const double full = __builtin_floor(n / res), rem = n - full * res;
+            double t = full * (res * shared > alone ? res * shared : alone);
+            if (rem > 0) t += __builtin_ceil(rem) * shared > alone ? __builtin_ceil(rem) * shared : alone;
+            if (!found || t < best->cost) {
+                found = true;
+                h.cost = t;
+                *best = h;
+            }
+        }
+    }
+    return found;
+}
+
+}  // namespace
+
+// One short contraction: the extra launch and the longer start cost more than the products save, the fp32 kernels
+// are ahead.  Measured (them / here, us): 1 x 1 of 32 channels [8,32,362] -> 384 6.3 / 9.1, [32,32,40,17] -> 256
+// 12.4 / 14.8, but [64,32,29,29] -> 259 35.6 / 29.6; of 64 channels [64,64,8,8] -> 80 7.5 / 8.9, but
+// [32,64,26,26] -> 80 13.4 / 11.0.
+static bool short_contraction(int64_t Cin, int64_t Cout, int64_t KT, int64_t positions)
+{
+    const double flop = 2.0 * (double)positions * (double)Cout * (double)Cin;
+    return KT == 1 && ((Cin == 32 && flop < 4e8) || (Cin == 64 && flop < 1e8));
+}
+
+// Bytes of workspace for a dense layer of Cin contraction channels, Cout result channels and KT taps; 0: not used.
+int64_t conv_split_workspace(int64_t Cin, int64_t Cout, int64_t KT, int64_t positions)
+{
+    if (KT > kMaxSteps || short_contraction(Cin, Cout, KT, positions)) return 0;
+    // the contraction is padded to whole chunks, and a chunk is at most the contraction rounded up to four groups
+    const int64_t groups = (Cin + 15) / 16, cb = (Cout + 31) / 32;
+    const int64_t padded = 2 * groups + 4 < groups + 32 ? 2 * groups + 4 : groups + 32;
+    return (cb * padded * KT + kPadSteps) * kStepBytes;
+}
+
+// A dense layer given by its taps: tap t reads input row oh*sh + dh[t], column ow*sw + dw[t] with the weights at
+// wgt + co*wco + ci*wci + wt[t]; output cell (oh, ow) of Ho x Wo.  phases: ph[t] = 2*er + ec, output cell (2 oh + er,
+// 2 ow + ec) of yH x yW, taps in ascending order of phase, sh = sw = 1.
+hipError_t launch_conv_split(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H, int64_t W,
+                             int64_t Cout, int64_t Ho, int64_t Wo, int64_t yH, int64_t yW, int sh, int sw, int KT,
+                             const int *dh, const int *dw, const int *wt, const int *ph, int64_t wco, int64_t wci, Workspace ws,
+                             hipStream_t s, bool *taken)
+{
+    *taken = false;
+    if (!ws.p || ((uintptr_t)ws.p & 15) || KT < 1 || KT > kMaxSteps || sh > 2 || sw > 2 || N < 1) return hipSuccess;
+    if (N * Ho >= (1LL << 30) || H >= (1 << 18) || Ho >= (1 << 18) || W >= (1LL << 28) || Wo >= (1LL << 28) || Cout * wco >= (1LL << 31) ||
+        Cin * wci >= (1LL << 31) || Cin * H * W >= (1LL << 27) || yH * yW >= (1LL << 30) || N * Ho * Wo >= (1LL << 31) - 65536)
+        return hipSuccess;
+    // ... likewise 1-D of 32 channels, k = 3 (conv1d_split.hip): [32,32,235] -> 64 8.0 / 9.8, but [32,32,283] -> 188 12.9 / 11.8
+    const bool forced = g_opt.conv2d_variant >= 100;
+    if (!forced && (short_contraction(Cin, Cout, KT, N * Ho * Wo) ||
+                    (KT == 3 && Cin == 32 && H == 1 && !ph && wci == KT && sw == 1 && 192.0 * N * Wo * Cout < 1e8)))
+        return hipSuccess;
+    SplitGeom g;
+    g.N = (int)N; g.Cin = (int)Cin; g.H = (int)H; g.W = (int)W; g.HW = (int)(H * W); g.Cout = (int)Cout; g.Ho = (int)Ho;
+    g.NR = (int)(N * Ho);
+    g.KT = KT; g.sh = sh; g.sw = sw;
+    g.yH = (int)yH; g.yW = (int)yW; g.yHW = (int)(yH * yW); g.ys = ph ? 2 : 1;
+    int h0 = dh[0], h1 = dh[0], w0 = dw[0], w1 = dw[0];
+    for (int t = 1; t < KT; ++t) {
+        h0 = dh[t] < h0 ? dh[t] : h0; h1 = dh[t] > h1 ? dh[t] : h1;
+        w0 = dw[t] < w0 ? dw[t] : w0; w1 = dw[t] > w1 ? dw[t] : w1;
+    }
+    g.dh0 = h0; g.dw0 = w0; g.SH = h1 - h0 + 1;
+    const int SW = w1 - w0 + 1;
+    if (g.SH > 1024 || SW > 4096) return hipSuccess;
+    g.ls = g.SH < sh ? g.SH : sh;
+    g.LPI = (int)(Ho - 1) * g.ls + g.SH;
+    for (int f = 0; f < 4; ++f) g.nt[f] = 0;
+    if (ph)
+        for (int t = 0; t < KT; ++t) ++g.nt[ph[t]];
+    const int cus = device_cus();
+    // the configuration whose estimated time is smallest
+    int bi = -1;
+    Tiling b;
+    const int force = forced ? g_opt.conv2d_variant - 100 : -1;       // A/B and tests: this configuration
+    for (int i = 0; i < kNumCfg; ++i) {
+        if ((kCfg[i].nph > 1) != (ph != nullptr) || (force >= 0 && force < kNumCfg && force != i)) continue;
+        Tiling h;
+        if (!plan(g, kCfg[i], (int)Wo, SW, cus, &h)) continue;
+        // a tile's images, and a wavefront's weights, within 32-bit offsets
+        const int64_t imgs = (int64_t)(h.bnp > h.bnpl ? h.bnp : h.bnpl) / (h.TWl * Ho) + 2;
+        if (imgs * Cin * H * W >= (1LL << 29) || (int64_t)h.KS * kStepBytes >= (1LL << 31)) continue;
+        if (bi < 0 || h.cost < b.cost) { bi = i; b = h; }
+    }
+    if (bi < 0) return hipSuccess;
+    const Cfg &c = kCfg[bi];
+    const int ncb = (int)((Cout + 31) / 32);
+    const int64_t G = (int64_t)b.nchunk * b.NC;
+    if (((int64_t)ncb * G * KT + kPadSteps) * kStepBytes > ws.bytes || G > 65535 || ncb > 65535) return hipSuccess;
+    g.nstrips = b.nstrips; g.TW = b.TW; g.TWl = b.TWl; g.CW = b.CW; g.LW = b.LW; g.bnp = b.bnp; g.bnpl = b.bnpl; g.tpf = b.tpf;
+    g.tiles = b.tiles; g.cot = b.cot; g.PS = b.PS; g.NC = b.NC; g.nchunk = b.nchunk; g.S = b.S; g.KS = b.KS; g.bufs = b.bufs;
+    g.inv_tw = 1.0f / g.TW; g.inv_twl = 1.0f / g.TWl; g.inv_Ho = 1.0f / g.Ho; g.inv_LPI = 1.0f / g.LPI;
+    g.inv_LW = 1.0f / g.LW; g.inv_CW = 1.0f / g.CW; g.inv_PS = 1.0f / g.PS; g.inv_KT = 1.0f / g.KT;
+    for (int t = 0; t < KT; ++t) {
+        const int a = dh[t] - h0, b = dw[t] - w0;
+        g.tapoff[t] = (unsigned short)(a * g.LW + b % sw * g.CW + b / sw);
+    }
+    for (int t = KT; t < kMaxSteps; ++t) g.tapoff[t] = 0;
+    PrepGeom p;
+    p.Cin = (int)Cin; p.Cout = (int)Cout; p.KT = KT; p.G = (int)G; p.WK = c.wk; p.wco = (int)wco; p.wci = (int)wci;
+    for (int t = 0; t < kMaxSteps; ++t) p.wtap[t] = (unsigned short)(t < KT ? wt[t] : 0);
+    const int grid = (int)xcd_grid((int64_t)g.tiles * g.cot);
+    *taken = true;
+    hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)G, (unsigned)ncb, (unsigned)((KT + 3) / 4)), dim3(256), 0, s, wgt,
+                       (v4u *)ws.p, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+#define SWS_CFG(I) case I: return launch_cfg<I>(x, (const v4u *)ws.p, y, g, grid, (size_t)b.need, s)
+    switch (bi) {
+        SWS_CFG(0); SWS_CFG(1); SWS_CFG(2); SWS_CFG(3); SWS_CFG(4); SWS_CFG(5); SWS_CFG(6); SWS_CFG(7); SWS_CFG(8); SWS_CFG(9);
+        SWS_CFG(10); SWS_CFG(11); SWS_CFG(12);
+    default: return launch_cfg<13>(x, (const v4u *)ws.p, y, g, grid, (size_t)b.need, s);
+    }
+#undef SWS_CFG
+}
+
+}  // namespace sws

@@ -615,7 +615,7 @@ hipError_t launch_stream(const float *x, const float *wgt, float *y, const Strea
 // not one of these, or too little work to fill the device — nothing was launched.
 hipError_t launch_conv2d_stream(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H, int64_t W,
                                 int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t ph, int32_t pw,
-                                hipStream_t s, bool *taken, int wadj)
+                                hipStream_t s, bool *taken, int wadj, bool split_only)
 {
     *taken = false;
     if (Cin != 64 || Cout % 64 != 0 || Cout < 64 || kw != 3 || (kh != 3 && kh != 1) || ph < 0 || pw < 0 ||
@@ -678,11 +678,13 @@ hipError_t launch_conv2d_stream(const float *x, const float *wgt, float *y, int6
     const int64_t lines_per_run = (g.T / cus + 2) / g.BPI * g.LPI + 2LL * g.LPI;
     if ((g.T * kh * kw < 60LL * cus && g_opt.conv2d_variant != 17 && g_opt.conv2d_variant != 18) || lines_per_run >= (1 << 20))
         return hipSuccess;
-    *taken = true;
     // the split-operand instance: images, forward weights, and its larger ring must fit
     size_t lds3 = (size_t)g.R * g.LW * kPitch3 + 4 * (kScratchFloats / 2 + kSpareFloats);
     if (lds3 < 2 * wtmp) lds3 = 2 * wtmp;             // the whole weight tile passes through LDS at once
-    if (!mode_b && g_opt.conv2d_variant != 17 && lds3 <= 160 * 1024) {
+    const bool x3 = !mode_b && g_opt.conv2d_variant != 17 && lds3 <= 160 * 1024;
+    if (split_only && !x3) return hipSuccess;
+    *taken = true;
+    if (x3) {
         if (wadj) {
             if (cgs == 0) return launch_stream1<64, 3, 3, false, 0, true, true>(x, wgt, y, g, lds3, cus, s);
             if (cgs == 1) return launch_stream1<64, 3, 3, false, 1, true, true>(x, wgt, y, g, lds3, cus, s);

@@ -279,9 +279,18 @@ sws_status sws_pool2d_padded(sws_op op, const float *x, float *y, int64_t N, int
                                                pad_bottom, pad_right, (int)mode, scale, (hipStream_t)stream));
 }
 
-sws_status sws_conv1d(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
+int64_t sws_conv_workspace(int64_t Cin, int64_t Cout, int64_t taps, int64_t positions)
+{
+    if (Cin < 1 || Cout < 1 || taps < 1 || positions < 1 || Cin > kMaxDim || Cout > kMaxDim) return 0;
+    int64_t n;
+    if (!mul3(Cin + 1024, Cout + 1024, taps, &n) || n > kMaxDim) return 0;       // (no kernel asks for one of this size)
+    return sws::conv_split_workspace(Cin, Cout, taps, positions);
+}
+
+sws_status sws_conv1d_ws(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
                       int64_t Cout, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
-                      int32_t groups, sws_stream_t stream)
+                      int32_t groups, void *workspace, int64_t workspace_bytes,
+                         sws_stream_t stream)
 {
     if (B < 0 || Cin < 1 || L < 0 || Cout < 1 || k < 1 || stride < 1 || pad < 0 || dilation < 1 || groups < 1)
         return SWS_ERR_INVALID_ARG;
@@ -295,12 +304,21 @@ sws_status sws_conv1d(const float *x, const float *wgt, float *y, int64_t B, int
     if (B == 0) return SWS_OK;
     if (!x || !wgt || !y) return SWS_ERR_INVALID_ARG;
     return SWS_LAUNCH(sws::launch_conv1d(x, wgt, y, B, Cin, L, Cout, Lo, k, stride, pad, dilation, groups,
-                                       (hipStream_t)stream));
+                                       (hipStream_t)stream, 0, nullptr, sws::Workspace{workspace, workspace_bytes}));
 }
 
-sws_status sws_conv1d_padded(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
+sws_status sws_conv1d(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
+                      int64_t Cout, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
+                      int32_t groups, sws_stream_t stream)
+{
+    return sws_conv1d_ws(x, wgt, y, B, Cin, L, Cout, k, stride, pad, dilation, groups, nullptr, 0, stream);
+}
+
+sws_status sws_conv1d_padded_ws(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
                              int64_t Cout, int32_t k, int32_t stride, int32_t pad_left, int32_t pad_right,
-                             int32_t dilation, int32_t groups, sws_pad_mode mode, sws_stream_t stream)
+                             int32_t dilation, int32_t groups, sws_pad_mode mode,
+                                void *workspace, int64_t workspace_bytes,
+                                sws_stream_t stream)
 {
     if (B < 0 || Cin < 1 || L < 1 || Cout < 1 || k < 1 || stride < 1 || pad_left < 0 || pad_right < 0 || dilation < 1 ||
         groups < 1)
@@ -319,7 +337,14 @@ sws_status sws_conv1d_padded(const float *x, const float *wgt, float *y, int64_t
     if (B == 0) return SWS_OK;
     if (!x || !wgt || !y) return SWS_ERR_INVALID_ARG;
     return SWS_LAUNCH(sws::launch_conv1d_padded(x, wgt, y, B, Cin, L, Cout, Lo, k, stride, pad_left, pad_right, dilation,
-                                               groups, (int)mode, (hipStream_t)stream));
+                                               groups, (int)mode, (hipStream_t)stream, sws::Workspace{workspace, workspace_bytes}));
+}
+
+sws_status sws_conv1d_padded(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
+                             int64_t Cout, int32_t k, int32_t stride, int32_t pad_left, int32_t pad_right,
+                             int32_t dilation, int32_t groups, sws_pad_mode mode, sws_stream_t stream)
+{
+    return sws_conv1d_padded_ws(x, wgt, y, B, Cin, L, Cout, k, stride, pad_left, pad_right, dilation, groups, mode, nullptr, 0, stream);
 }
 
 sws_status sws_conv1d_16(sws_dtype dtype, const void *x, const float *wgt, void *y, int64_t B, int64_t Cin, int64_t L,
@@ -362,9 +387,10 @@ sws_status check_conv1d(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int32_t
 
 }  // namespace
 
-sws_status sws_conv1d_grad_input(const float *gy, const float *wgt, float *gx, int64_t B, int64_t Cin, int64_t L,
+sws_status sws_conv1d_grad_input_ws(const float *gy, const float *wgt, float *gx, int64_t B, int64_t Cin, int64_t L,
                                  int64_t Cout, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
-                                 int32_t groups, sws_stream_t stream)
+                                 int32_t groups, void *workspace, int64_t workspace_bytes,
+                                    sws_stream_t stream)
 {
     int64_t Lo;
     const sws_status st = check_conv1d(B, Cin, L, Cout, k, stride, pad, dilation, groups, &Lo);
@@ -372,7 +398,14 @@ sws_status sws_conv1d_grad_input(const float *gy, const float *wgt, float *gx, i
     if (B == 0) return SWS_OK;
     if (!gy || !wgt || !gx) return SWS_ERR_INVALID_ARG;
     return SWS_LAUNCH(sws::launch_conv1d_grad_input(gy, wgt, gx, B, Cin, L, Cout, Lo, k, stride, pad, dilation, groups,
-                                                  (hipStream_t)stream));
+                                                  (hipStream_t)stream, sws::Workspace{workspace, workspace_bytes}));
+}
+
+sws_status sws_conv1d_grad_input(const float *gy, const float *wgt, float *gx, int64_t B, int64_t Cin, int64_t L,
+                                 int64_t Cout, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
+                                 int32_t groups, sws_stream_t stream)
+{
+    return sws_conv1d_grad_input_ws(gy, wgt, gx, B, Cin, L, Cout, k, stride, pad, dilation, groups, nullptr, 0, stream);
 }
 
 sws_status sws_conv1d_grad_weight(const float *x, const float *gy, float *gw, int64_t B, int64_t Cin, int64_t L,
@@ -408,9 +441,10 @@ sws_status check_conv2d(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Co
 
 }  // namespace
 
-sws_status sws_conv2d_grad_input(const float *gy, const float *wgt, float *gx, int64_t N, int64_t Cin, int64_t H,
+sws_status sws_conv2d_grad_input_ws(const float *gy, const float *wgt, float *gx, int64_t N, int64_t Cin, int64_t H,
                                  int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t ph,
-                                 int32_t pw, sws_stream_t stream)
+                                 int32_t pw, void *workspace, int64_t workspace_bytes,
+                                    sws_stream_t stream)
 {
     int64_t Ho, Wo;
     const sws_status st = check_conv2d(N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw, &Ho, &Wo);
@@ -418,7 +452,14 @@ sws_status sws_conv2d_grad_input(const float *gy, const float *wgt, float *gx, i
     if (N == 0) return SWS_OK;
     if (!gy || !wgt || !gx) return SWS_ERR_INVALID_ARG;
     return SWS_LAUNCH(sws::launch_conv2d_grad_input(gy, wgt, gx, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw,
-                                                  (hipStream_t)stream));
+                                                  (hipStream_t)stream, sws::Workspace{workspace, workspace_bytes}));
+}
+
+sws_status sws_conv2d_grad_input(const float *gy, const float *wgt, float *gx, int64_t N, int64_t Cin, int64_t H,
+                                 int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t ph,
+                                 int32_t pw, sws_stream_t stream)
+{
+    return sws_conv2d_grad_input_ws(gy, wgt, gx, N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw, nullptr, 0, stream);
 }
 
 sws_status sws_conv2d_grad_weight(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H,
@@ -433,9 +474,10 @@ sws_status sws_conv2d_grad_weight(const float *x, const float *gy, float *gw, in
                                                    (hipStream_t)stream));
 }
 
-sws_status sws_conv2d(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,
+sws_status sws_conv2d_ws(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,
                       int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t ph,
-                      int32_t pw, sws_stream_t stream)
+                      int32_t pw, void *workspace, int64_t workspace_bytes,
+                         sws_stream_t stream)
 {
     if (N < 0 || Cin < 1 || H < 0 || W < 0 || Cout < 1) return SWS_ERR_INVALID_ARG;
     if (kh < 1 || kw < 1 || sh < 1 || sw < 1 || ph < 0 || pw < 0) return SWS_ERR_INVALID_ARG;
@@ -450,13 +492,21 @@ sws_status sws_conv2d(const float *x, const float *wgt, float *y, int64_t N, int
     if (N == 0) return SWS_OK;
     if (!x || !wgt || !y) return SWS_ERR_INVALID_ARG;
     return SWS_LAUNCH(sws::launch_conv2d(x, wgt, y, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw,
-                                       (hipStream_t)stream));
+                                       (hipStream_t)stream, sws::Workspace{workspace, workspace_bytes}));
 }
 
-sws_status sws_conv2d_padded(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,
+sws_status sws_conv2d(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,
+                      int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t ph,
+                      int32_t pw, sws_stream_t stream)
+{
+    return sws_conv2d_ws(x, wgt, y, N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw, nullptr, 0, stream);
+}
+
+sws_status sws_conv2d_padded_ws(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,
                              int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t pad_top,
                              int32_t pad_left, int32_t pad_bottom, int32_t pad_right, sws_pad_mode mode,
-                             sws_stream_t stream)
+                                void *workspace, int64_t workspace_bytes,
+                                sws_stream_t stream)
 {
     if (N < 0 || Cin < 1 || H < 1 || W < 1 || Cout < 1) return SWS_ERR_INVALID_ARG;
     if (kh < 1 || kw < 1 || sh < 1 || sw < 1) return SWS_ERR_INVALID_ARG;
@@ -478,7 +528,15 @@ sws_status sws_conv2d_padded(const float *x, const float *wgt, float *y, int64_t
     if (N == 0) return SWS_OK;
     if (!x || !wgt || !y) return SWS_ERR_INVALID_ARG;
     return SWS_LAUNCH(sws::launch_conv2d_padded(x, wgt, y, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, pad_top, pad_left,
-                                               pad_bottom, pad_right, (int)mode, (hipStream_t)stream));
+                                               pad_bottom, pad_right, (int)mode, (hipStream_t)stream, sws::Workspace{workspace, workspace_bytes}));
+}
+
+sws_status sws_conv2d_padded(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,
+                             int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t pad_top,
+                             int32_t pad_left, int32_t pad_bottom, int32_t pad_right, sws_pad_mode mode,
+                             sws_stream_t stream)
+{
+    return sws_conv2d_padded_ws(x, wgt, y, N, Cin, H, W, Cout, kh, kw, sh, sw, pad_top, pad_left, pad_bottom, pad_right, mode, nullptr, 0, stream);
 }
 
 }  // extern "C"

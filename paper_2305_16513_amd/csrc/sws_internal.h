@@ -127,6 +127,12 @@ inline int max_origin_shift(int64_t lo, int line)
     return line - b;
 }
 
+// Device memory a caller lends a dense convolution for the duration of the call (stream-ordered); empty: none.
+struct Workspace {
+    void *p = nullptr;
+    int64_t bytes = 0;
+};
+
 // Compute units of the current device (256 on MI355X), asked once.
 int device_cus();
 
@@ -189,11 +195,11 @@ hipError_t launch_pool2d_16(int op, int dtype, const void *x, void *y, int64_t p
                             float scale, hipStream_t s);
 hipError_t launch_conv1d(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
                          int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad,
-                         int32_t dilation, int32_t groups, hipStream_t s, int wadj = 0, bool *taken = nullptr);
+                         int32_t dilation, int32_t groups, hipStream_t s, int wadj = 0, bool *taken = nullptr, Workspace ws = {});
 // Rows extended by pad_left / pad_right elements under a boundary rule (mirror, periodic, edge; conv1d.hip).
 hipError_t launch_conv1d_padded(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
                                 int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad_left, int32_t pad_right,
-                                int32_t dilation, int32_t groups, int mode, hipStream_t s);
+                                int32_t dilation, int32_t groups, int mode, hipStream_t s, Workspace ws = {});
 // Dense 1-D layers of 32 / 64 input channels on the bf16 matrix cores with split fp32 operands (conv1d_split.hip);
 // *taken = false: not one of its shapes, nothing launched.
 hipError_t launch_conv1d_split(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L, int64_t Cout,
@@ -205,24 +211,24 @@ hipError_t launch_conv1d_16(int dtype, const void *x, const float *wgt, void *y,
 // Adjoints of the 1-D convolution (conv_grad.hip).
 hipError_t launch_conv1d_grad_input(const float *gy, const float *wgt, float *gx, int64_t B, int64_t Cin, int64_t L,
                                     int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad,
-                                    int32_t dilation, int32_t groups, hipStream_t s);
+                                    int32_t dilation, int32_t groups, hipStream_t s, Workspace ws = {});
 hipError_t launch_conv1d_grad_weight(const float *x, const float *gy, float *gw, int64_t B, int64_t Cin, int64_t L,
                                      int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad,
                                      int32_t dilation, int32_t groups, hipStream_t s);
 hipError_t launch_conv2d_grad_input(const float *gy, const float *wgt, float *gx, int64_t N, int64_t Cin, int64_t H,
                                     int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
-                                    int32_t sw, int32_t ph, int32_t pw, hipStream_t s);
+                                    int32_t sw, int32_t ph, int32_t pw, hipStream_t s, Workspace ws = {});
 hipError_t launch_conv2d_grad_weight(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H,
                                      int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
                                      int32_t sw, int32_t ph, int32_t pw, hipStream_t s);
 hipError_t launch_conv2d(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,
                          int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw,
-                         int32_t sh, int32_t sw, int32_t ph, int32_t pw, hipStream_t s);
+                         int32_t sh, int32_t sw, int32_t ph, int32_t pw, hipStream_t s, Workspace ws = {});
 
 // Planes extended on four sides under a boundary rule (conv2d_padded.hip).
 hipError_t launch_conv2d_padded(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H, int64_t W,
                                 int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh, int32_t sw,
-                                int32_t pt, int32_t pl, int32_t pb, int32_t pr, int mode, hipStream_t s);
+                                int32_t pt, int32_t pl, int32_t pb, int32_t pr, int mode, hipStream_t s, Workspace ws = {});
 
 // Dense grad-weight on the bf16 matrix cores with split fp32 operands (conv_gw_split.hip): 3 x 3, horizontal
 // stride 1, channel counts in multiples of 32; gw must hold zeros; *taken = false: not its case, nothing launched.
@@ -239,18 +245,28 @@ hipError_t launch_conv1d_gw_split(const float *x, const float *gy, float *gw, in
 hipError_t launch_conv2d_mfma(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,
                               int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
                               int32_t sw, int32_t ph, int32_t pw, int32_t dh, int32_t dw, hipStream_t s,
-                              bool *taken, int wadj = 0);
+                              bool *taken, int wadj = 0, Workspace ws = {});
+// Dense layers on the bf16 matrix cores with split fp32 operands, weights split into the caller's workspace first
+// (conv_split.hip); *taken = false: not its case or the workspace is too small, nothing launched.
+int64_t conv_split_workspace(int64_t Cin, int64_t Cout, int64_t KT, int64_t positions);
+hipError_t launch_conv_split(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H, int64_t W,
+                             int64_t Cout, int64_t Ho, int64_t Wo, int64_t yH, int64_t yW, int sh, int sw, int KT,
+                             const int *dh, const int *dw, const int *wt, const int *ph, int64_t wco, int64_t wci, Workspace ws,
+                             hipStream_t s, bool *taken);
+hipError_t launch_conv2d_split(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H, int64_t W,
+                               int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh, int32_t sw,
+                               int32_t ph, int32_t pw, int32_t dh, int32_t dw, hipStream_t s, bool *taken, int wadj, Workspace ws);
 // Weight-stationary streaming kernel (conv_stream.hip): 64 input channels, 3 x 3 on narrow images and
 // 1 x 3 on 1-D rows, stride 1; *taken = false: not its case, nothing launched.
 hipError_t launch_conv2d_stream(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H, int64_t W,
                                 int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t ph, int32_t pw,
-                                hipStream_t s, bool *taken, int wadj);
+                                hipStream_t s, bool *taken, int wadj, bool split_only = false);
 // Strided adjoint with respect to the input, one stride-1 launch chain per output phase; phases no
 // tap reaches are NOT written (the caller clears gx first when kh < sh or kw < sw).
 hipError_t launch_conv2d_grad_input_phases(const float *gy, const float *wgt, float *gx, int64_t N, int64_t Cin,
                                            int64_t H, int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh,
                                            int32_t kw, int32_t sh, int32_t sw, int32_t ph, int32_t pw, hipStream_t s,
-                                           bool *taken);
+                                           bool *taken, Workspace ws = {});
 
 // Direct-evaluation fallbacks (naive_kernels.hip).
 hipError_t launch_slide1d_naive(int op, const float *x, float *y, int64_t rows, int64_t len, int32_t w,

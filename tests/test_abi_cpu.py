@@ -271,3 +271,16 @@ def test_conv2d_padded_argument_checks(L):
     assert c(mode=4) == 1 and c(mode=-1) == 1 and c(H=0) == 1 and c(pt=-1) == 1 and c(Cin=0) == 1
     assert c(pt=8) == 1 and c(pr=6) == 1 and c(mode=2, pb=9) == 1 and c(mode=2, pl=7) == 1
     assert c(kh=11) == 1 and c(kw=9) == 1 and c(sh=0) == 1 and c(y=nul) == 1 and c(w=nul) == 1
+
+
+def test_conv_workspace_and_argument_checks_of_the_ws_entries(L):
+    one, nul = ctypes.c_void_p(16), ctypes.c_void_p(0)
+    assert L.sws_conv_workspace(64, 64, 9, 1000) >= 6 * 64 * 64 * 9         # three bf16 pieces per weight
+    assert L.sws_conv_workspace(64, 64, 65, 1000) == 0 and L.sws_conv_workspace(0, 64, 9, 1000) == 0
+    assert L.sws_conv_workspace(2 ** 31, 2 ** 31, 9, 1000) == 0 and L.sws_conv_workspace(64, 64, 9, 0) == 0
+    assert L.sws_conv_workspace(32, 64, 1, 1000) == 0                       # a contraction too short for it
+    assert L.sws_conv2d_ws(one, one, one, 0, 3, 10, 10, 4, 3, 3, 1, 1, 1, 1, one, 64, nul) == 0     # no images: nothing to do
+    assert L.sws_conv2d_ws(nul, one, one, 1, 3, 10, 10, 4, 3, 3, 1, 1, 1, 1, one, 64, nul) == 1
+    assert L.sws_conv2d_grad_input_ws(one, one, one, 1, 3, 2, 2, 4, 5, 5, 1, 1, 1, 1, one, 64, nul) == 1
+    assert L.sws_conv1d_ws(one, one, one, 1, 3, 10, 4, 11, 1, 0, 1, 1, one, 64, nul) == 1
+    assert L.sws_conv1d_grad_input_ws(one, one, nul, 1, 3, 10, 4, 3, 1, 0, 1, 1, one, 64, nul) == 1

@@ -1,0 +1,189 @@
+"""The split-operand convolution kernel for any dense layer (conv_split.hip): every tile configuration at the edges of
+its tiles, against the C oracle.
+
+Tolerance: an output is a sum of n = Cin*kh*kw products, each evaluated as six exact piece products (what is dropped is
+below 2^-23 of it), accumulated with one rounding of the running sum per 16 products: |err| <= (2^-23 + (n/16 + 8) *
+2^-24) * sum|terms|, and below 2e-6 of it for the n <= 500 used here.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2305_16513_amd import workloads
+from tests.parity_util import assert_bit_exact, assert_within_tol, to_gpu, to_host
+
+pytestmark = pytest.mark.gpu
+SPLIT_TOL = 2e-6
+FORWARD, PHASES = range(10), range(10, 14)
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2305_16513_amd import binding
+    return binding
+
+
+@pytest.fixture(autouse=True)
+def automatic(B):
+    yield
+    B.sws_set_option("conv2d_variant", 0)
+
+
+def _guarded(shape):
+    """A contiguous tensor between two bands of a value that no output takes."""
+    import torch
+    n = int(np.prod(shape))
+    flat = torch.full((n + 128,), 12345.0, device="cuda")
+    return flat, flat[64:64 + n].view(shape)
+
+
+def _check(B, case, seed, integer, forward=True, adjoint=True):
+    n, cin, cout, h, w, kh, kw, s, p = case
+    ph, pw = (p if h > 1 else 0), p
+    if integer:                                       # sums below 2^24: exact in any order
+        x = workloads.integer_valued((n, cin, h, w), -3, 3, seed)
+        wgt = workloads.integer_valued((cout, cin, kh, kw), -3, 3, seed + 1)
+    else:
+        rng = np.random.default_rng(seed)
+        x = rng.standard_normal((n, cin, h, w)).astype(np.float32)
+        wgt = rng.standard_normal((cout, cin, kh, kw)).astype(np.float32)
+    sh = s if h > 1 else 1
+    ref, mag = oracle.conv2d(x, wgt, sh, s, ph, pw)
+    if forward:
+        flat, y = _guarded(ref.shape)
+        B.sws_conv2d(to_gpu(x), to_gpu(wgt), sh, s, ph, pw, y=y)
+        if integer:
+            assert_bit_exact(to_host(y), ref, "y %s" % (case,))
+        else:
+            assert_within_tol(to_host(y), ref, mag, "y %s" % (case,), tol=SPLIT_TOL)
+        assert (flat[:64] == 12345.0).all() and (flat[-64:] == 12345.0).all()
+    if adjoint:
+        gy = workloads.integer_valued(ref.shape, -3, 3, seed + 2) if integer else \
+            np.random.default_rng(seed + 2).standard_normal(ref.shape).astype(np.float32)
+        gref, gmag = oracle.conv2d_grad_input(gy, wgt, h, w, sh, s, ph, pw)
+        flat, gx = _guarded(gref.shape)
+        B.sws_conv2d_grad_input(to_gpu(gy), to_gpu(wgt), h, w, sh, s, ph, pw, gx=gx)
+        if integer:
+            assert_bit_exact(to_host(gx), gref, "gx %s" % (case,))
+        else:
+            assert_within_tol(to_host(gx), gref, gmag, "gx %s" % (case,), tol=SPLIT_TOL)
+        assert (flat[:64] == 12345.0).all() and (flat[-64:] == 12345.0).all()
+
+
+# n, cin, cout, h, w, kh, kw, stride, pad: channels below, at and beyond blocks of 8, 16, 32 and 64; planes smaller than a
+# tile, tiles across images, rows longer than a tile, strips; every residue of the strides
+CASES = [
+    (1, 1, 1, 1, 1, 1, 1, 1, 0),
+    (2, 7, 33, 5, 6, 3, 3, 1, 1),
+    (3, 24, 65, 7, 7, 3, 3, 1, 1),
+    (5, 19, 31, 4, 3, 3, 3, 1, 0),
+    (2, 40, 129, 14, 13, 3, 3, 1, 1),
+    (1, 16, 32, 3, 300, 3, 3, 1, 1),
+    (2, 33, 20, 1, 257, 1, 3, 1, 1),
+    (1, 50, 64, 1, 1030, 1, 5, 1, 0),
+    (2, 130, 40, 9, 11, 1, 1, 1, 0),
+    (3, 17, 34, 8, 9, 5, 5, 1, 2),
+    (2, 20, 48, 15, 18, 3, 3, 2, 1),
+    (4, 9, 32, 7, 8, 3, 3, 2, 1),
+    (3, 40, 24, 6, 5, 1, 1, 2, 0),
+    (2, 12, 36, 11, 12, 2, 2, 2, 0),
+    (2, 5, 40, 12, 9, 5, 5, 2, 2),
+    (1, 6, 10, 9, 9, 7, 7, 2, 3),
+    (2, 30, 18, 1, 77, 1, 3, 2, 1),
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_chosen_configuration(B, case):
+    for integer in (True, False):
+        _check(B, case, 11, integer)
+
+
+@pytest.mark.parametrize("cfg", FORWARD)
+def test_every_forward_configuration(B, cfg):
+    """(A configuration whose tile does not fit a shape leaves it to the kernels without a workspace.)"""
+    B.sws_set_option("conv2d_variant", 100 + cfg)
+    for i, case in enumerate(CASES):
+        _check(B, case, 20 + i, i % 2 == 0, adjoint=case[7] == 1)
+
+
+@pytest.mark.parametrize("cfg", PHASES)
+def test_every_phase_configuration(B, cfg):
+    B.sws_set_option("conv2d_variant", 100 + cfg)
+    for i, case in enumerate(CASES):
+        if case[7] == 2:
+            _check(B, case, 50 + i, i % 2 == 0, forward=False)
+
+
+def test_many_chunks_and_large_tiles(B):
+    """Several chunks of input channels through both staging buffers, tiles of every configuration filled."""
+    for cfg in FORWARD:
+        B.sws_set_option("conv2d_variant", 100 + cfg)
+        _check(B, (2, 150, 130, 17, 19, 3, 3, 1, 1), 70, True)
+    B.sws_set_option("conv2d_variant", 0)
+    _check(B, (2, 100, 70, 21, 18, 3, 3, 2, 1), 71, True)
+
+
+def test_information_in_the_third_piece(B):
+    """Values 1 + i 2^-23: their low bits live in the third bf16 piece; differences of neighbouring channels show them."""
+    rng = np.random.default_rng(3)
+    x = (1.0 + rng.integers(0, 1 << 23, (1, 32, 6, 40)) * 2.0 ** -23).astype(np.float32)
+    wgt = np.zeros((32, 32, 3, 3), np.float32)
+    for co in range(32):
+        wgt[co, co, 1, 1], wgt[co, (co + 1) % 32, 1, 1] = 1.0, -1.0
+    ref, _ = oracle.conv2d(x, wgt, 1, 1, 1, 1)
+    y = to_host(B.sws_conv2d(to_gpu(x), to_gpu(wgt), 1, 1, 1, 1)).astype(np.float64)
+    assert np.abs(y - ref).max() <= 2.0 ** -23
+
+
+def test_without_workspace_and_with_one_too_small(B):
+    """The C entries take a NULL or a small workspace: the same result by the kernels that need none."""
+    import ctypes
+    import torch
+    x = workloads.integer_valued((2, 24, 9, 10), -3, 3, 5)
+    wgt = workloads.integer_valued((40, 24, 3, 3), -3, 3, 6)
+    ref, _ = oracle.conv2d(x, wgt, 1, 1, 1, 1)
+    xd, wd = to_gpu(x), to_gpu(wgt)
+    small = torch.empty(4096, dtype=torch.uint8, device="cuda")
+    for ws, size in ((None, 0), (small.data_ptr(), small.numel())):
+        y = torch.full(ref.shape, 7.0, device="cuda")
+        rc = B.lib().sws_conv2d_ws(xd.data_ptr(), wd.data_ptr(), y.data_ptr(), 2, 24, 9, 10, 40, 3, 3, 1, 1, 1, 1, ws, size,
+                                   ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+        assert_bit_exact(to_host(y), ref, "workspace of %d bytes" % size)
+
+
+def test_graph_replay(B):
+    """Captured in a HIP graph (the workspace comes from the graph's pool) and replayed with eager work between."""
+    import torch
+    x = to_gpu(workloads.integer_valued((3, 40, 13, 11), -3, 3, 8))
+    wgt = to_gpu(workloads.integer_valued((48, 40, 3, 3), -3, 3, 9))
+    g = to_gpu(workloads.integer_valued((3, 48, 7, 6), -3, 3, 10))
+    y, gx = torch.empty(3, 48, 7, 6, device="cuda"), torch.empty_like(x)
+
+    def both():
+        B.sws_conv2d(x, wgt, 2, 2, 1, 1, y=y)
+        B.sws_conv2d_grad_input(g, wgt, 13, 11, 2, 2, 1, 1, gx=gx)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        both()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        both()
+    for rep in range(4):
+        wgt.copy_(to_gpu(workloads.integer_valued((48, 40, 3, 3), -3, 3, 30 + rep)))
+        y.fill_(7.0)
+        gx.fill_(7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = y.clone(), gx.clone()
+        both()
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], y) and torch.equal(got[1], gx), "replay %d" % rep
+        ref, _ = oracle.conv2d(to_host(x), to_host(wgt), 2, 2, 1, 1)
+        assert_bit_exact(to_host(y), ref, "replay %d" % rep)
