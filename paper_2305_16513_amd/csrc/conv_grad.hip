@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kThreads) void conv1d_grad_weight_naive_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Thin channels (one input channel per output channel), stride 1, taps adjacent, k <= 64.
+// Thin channels (one input channel per output channel), stride 1, k <= 64, taps up to 16 apart.
 // ---------------------------------------------------------------------------------------------
 // LDS layout of a staged tile: element q at q + 4*(q >> 4), so that a lane's window (from 16*lane)
 // starts 20 floats after its neighbour's and the 128-bit reads of eight lanes hit eight bank quads.
@@ -137,53 +137,102 @@ __device__ __forceinline__ void stage_row(float *dst, const float *__restrict__ 
     for (int j = 0; j < STRIPS; ++j) *(v4f *)(dst + gpos(256 * j + 4 * lane)) = g4[j];
 }
 
-template <int KB4>
+// The same for taps spaced d apart: element q at phase q % d, index q / d inside it, a phase PP floats long, so that a
+// window with spacing d is contiguous; `count` elements.  Four strips' loads in flight at a time.
+__device__ __forceinline__ void stage_row_phases(float *dst, const float *__restrict__ src, int p0, int n, int count, int d,
+                                                 float inv_d, int PP, int lane)
+{
+    for (int s0 = 0; s0 < count; s0 += 1024) {
+        v4f g4[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int at = p0 + s0 + 256 * j, q = at + 4 * lane;
+            g4[j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+            if (s0 + 256 * j < count) {
+                if (at >= 0 && at + 256 <= n) {
+                    g4[j] = *(const v4f_u *)(src + q);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) g4[j][c] = (q + c >= 0 && q + c < n) ? src[q + c] : 0.0f;
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int q = s0 + 256 * j + 4 * lane;
+            int idx = (int)(((float)q + 0.5f) * inv_d), ph = q - idx * d;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (q + c < count) dst[ph * PP + gpos(idx)] = g4[j][c];
+                if (++ph == d) { ph = 0; ++idx; }
+            }
+        }
+    }
+}
+
+// A workgroup takes one output channel and a run of its tiles (all images' rows, `per` of parts runs).
+// DIL: taps d apart; a lane's 16 outputs are then d apart too (phase lane % d, 16 consecutive indices of it) and a tile
+// is 16 * d * (64 / d) outputs.
+template <int KB4, bool DIL>
 __global__ __launch_bounds__(kThreads) void conv1d_thin_grad_weight_kernel(
     const float *__restrict__ x, const float *__restrict__ gy, float *__restrict__ gw, int B, int Cin, int L,
-    int Cout, int Lo, int k, int pad, int cog, int tiles_per_row, int bgroup, int64_t n_units)
+    int Cout, int Lo, int k, int pad, int cog, int tiles_per_row, int64_t per, int d, int PPX, int PPG)
 {
     constexpr int K4 = 4 * KB4;
     constexpr int XS = (kTileOut + K4 + 255) / 256;  // strips of x per tile
     constexpr int XREG = (gpos(256 * XS) + 63) / 64 * 64;
     constexpr int GREG = (gpos(kTileOut) + 63) / 64 * 64;
     constexpr int NG = KB4 + 4;                      // 4-float groups in a lane's window of x
-    __shared__ __attribute__((aligned(16))) float lds[kWavesPerWg * (XREG + GREG)];
+    extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ float red[kWavesPerWg][K4];
 
-    const int64_t unit = blockIdx.x;
-    if (unit >= n_units) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    float *X = lds + wave * (XREG + GREG), *G = X + XREG;
+    const int xreg = DIL ? d * PPX : XREG, greg = DIL ? d * PPG : GREG;
+    float *X = lds + wave * (xreg + greg), *G = X + xreg;
     // consecutive workgroups take consecutive channels of the same images: adjacent rows of memory
-    const int co = (int)(unit % Cout);
-    const int b0 = (int)(unit / Cout) * bgroup;
-    int b1 = b0 + bgroup;
-    if (b1 > B) b1 = B;
+    const int co = (int)(blockIdx.x % (unsigned)Cout);
+    const int64_t j0 = (int64_t)(blockIdx.x / (unsigned)Cout) * per, total = (int64_t)B * tiles_per_row;
+    const int64_t j1 = j0 + per < total ? j0 + per : total;
     const int ci = co / cog;
+    const float inv_d = 1.0f / (float)d;
+    const int blocks = DIL ? 64 / d : 64;            // runs of 16 indices per phase
+    const int TO = DIL ? 16 * d * blocks : kTileOut;
+    const int blk = DIL ? (int)(((float)lane + 0.5f) * inv_d) : lane, ph = lane - blk * d;
+    const bool on = !DIL || blk < blocks;
+    const float *Xw = X + (DIL && on ? ph * PPX + 20 * blk : 20 * (DIL ? 0 : lane));
+    const float *Gw = G + (DIL && on ? ph * PPG + 20 * blk : 20 * (DIL ? 0 : lane));
 
     float acc[K4];
 #pragma unroll
     for (int t = 0; t < K4; ++t) acc[t] = 0.0f;
 
-    const int n_tiles = (b1 - b0) * tiles_per_row;
-    for (int j = wave; j < n_tiles; j += kWavesPerWg) {
-        const int b = b0 + j / tiles_per_row;
-        const int t0 = (j % tiles_per_row) * kTileOut;
-        const float *xr = x + ((int64_t)b * Cin + ci) * L;
-        const float *gr = gy + ((int64_t)b * Cout + co) * Lo;
-        stage_row<XS>(X, xr, t0 - pad, L, lane);
-        stage_row<kTileOut / 256>(G, gr, t0, Lo, lane);
+    for (int64_t j = j0 + wave; j < j1; j += kWavesPerWg) {
+        const int64_t b = j / tiles_per_row;
+        const int t0 = (int)(j - b * tiles_per_row) * TO;
+        const float *xr = x + (b * Cin + ci) * (int64_t)L;
+        const float *gr = gy + (b * Cout + co) * (int64_t)Lo;
+        if constexpr (DIL) {
+            stage_row_phases(X, xr, t0 - pad, L, TO + (k - 1) * d, d, inv_d, PPX, lane);
+            stage_row_phases(G, gr, t0, Lo, TO, d, inv_d, PPG, lane);
+        } else {
+            stage_row<XS>(X, xr, t0 - pad, L, lane);
+            stage_row<kTileOut / 256>(G, gr, t0, Lo, lane);
+        }
         wave_lds_sync();
         float gv[16], xw[4 * NG];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const v4f g = *(const v4f *)(G + 20 * lane + 4 * u);
+            const v4f g = *(const v4f *)(Gw + 4 * u);
             gv[4 * u] = g.x; gv[4 * u + 1] = g.y; gv[4 * u + 2] = g.z; gv[4 * u + 3] = g.w;
+        }
+        if (DIL && !on) {                            // 64 % d lanes have no outputs of their own
+#pragma unroll
+            for (int e = 0; e < 16; ++e) gv[e] = 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < NG; ++u) {
-            const v4f g = *(const v4f *)(X + 20 * lane + 20 * (u >> 2) + 4 * (u & 3));
+            const v4f g = *(const v4f *)(Xw + 20 * (u >> 2) + 4 * (u & 3));
             xw[4 * u] = g.x; xw[4 * u + 1] = g.y; xw[4 * u + 2] = g.z; xw[4 * u + 3] = g.w;
         }
 #pragma unroll
@@ -428,20 +477,47 @@ __global__ __launch_bounds__(kThreads) void conv1d_dense_grad_weight_kernel(
     }
 }
 
+constexpr int kGwMaxDilation = 16;                   // the phase-major tile of larger spacings would not fit LDS at 64 taps
+
+template <int KB4, bool DIL>
+hipError_t launch_thin_gw1(const float *x, const float *gy, float *gw, int B, int Cin, int L, int Cout, int Lo, int k,
+                           int pad, int cog, int d, hipStream_t s)
+{
+    const int TO = DIL ? 16 * d * (64 / d) : kTileOut;
+    const int tiles_per_row = (Lo + TO - 1) / TO;
+    const int64_t total = (int64_t)B * tiles_per_row;
+    // Runs per channel: a few thousand workgroups in all, at least 32 tiles each (8 per wavefront; the reduction at the end
+    // costs about one tile's work), at most 512 runs (each ends in one atomic add per tap, and adds to one
+    // cache line serialise, about 0.1 us each).  A run may end inside a row: [1,1,1048576], k = 31 is 1024 tiles of one row.
+    int64_t parts = (total + 31) / 32, cap = (2048 + Cout - 1) / Cout;
+    if (cap > 512) cap = 512;
+    if (parts > cap) parts = cap;
+    if (parts < 1) parts = 1;
+    const int64_t per = (total + parts - 1) / parts;
+    parts = (total + per - 1) / per;
+    if (Cout * parts > 2147483647LL) return kNotTaken;
+    constexpr int K4 = 4 * KB4, XS = (kTileOut + K4 + 255) / 256;
+    // a phase's length: its indices in 16 + 4 layout, an odd number of 16-byte groups (eight lanes of eight phases then
+    // read eight bank quads)
+    const int PPX = (gpos(TO / d + K4 + 16) / 8 * 8) + 4, PPG = (gpos(TO / d + 16) / 8 * 8) + 4;
+    const size_t xreg = DIL ? (size_t)d * PPX : (gpos(256 * XS) + 63) / 64 * 64, greg = DIL ? (size_t)d * PPG : (gpos(kTileOut) + 63) / 64 * 64;
+    const size_t lds = kWavesPerWg * (xreg + greg) * sizeof(float);
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)conv1d_thin_grad_weight_kernel<KB4, DIL>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((conv1d_thin_grad_weight_kernel<KB4, DIL>), dim3((unsigned)(Cout * parts)), dim3(kThreads), lds, s, x, gy, gw,
+                       B, Cin, L, Cout, Lo, k, pad, cog, tiles_per_row, per, d, PPX, PPG);
+    return hipGetLastError();
+}
+
 template <int KB4>
 hipError_t launch_thin_gw(const float *x, const float *gy, float *gw, int B, int Cin, int L, int Cout, int Lo, int k,
-                          int pad, int cog, hipStream_t s)
+                          int pad, int cog, int d, hipStream_t s)
 {
-    const int tiles_per_row = (Lo + kTileOut - 1) / kTileOut;
-    // images per workgroup: at least 16 tiles per wavefront (the reduction at the end costs about
-    // one tile's worth of work), but keep a few thousand workgroups when the problem allows
-    int bgroup = (64 + tiles_per_row - 1) / tiles_per_row;
-    while (bgroup > 1 && (int64_t)Cout * ((B + bgroup - 1) / bgroup) < 2048) bgroup = (bgroup + 1) / 2;
-    const int64_t n_units = (int64_t)Cout * ((B + bgroup - 1) / bgroup);
-    if (n_units > 2147483647LL) return kNotTaken;
-    hipLaunchKernelGGL((conv1d_thin_grad_weight_kernel<KB4>), dim3((unsigned)n_units), dim3(kThreads), 0, s, x, gy, gw,
-                       B, Cin, L, Cout, Lo, k, pad, cog, tiles_per_row, bgroup, n_units);
-    return hipGetLastError();
+    return d == 1 ? launch_thin_gw1<KB4, false>(x, gy, gw, B, Cin, L, Cout, Lo, k, pad, cog, 1, s)
+                  : launch_thin_gw1<KB4, true>(x, gy, gw, B, Cin, L, Cout, Lo, k, pad, cog, d, s);
 }
 
 template <int KT, int SW>
@@ -716,7 +792,7 @@ hipError_t launch_conv1d_grad_weight(const float *x, const float *gy, float *gw,
     const int64_t n_gw = Cout * cig * k;
     const int variant = g_opt.conv1d_variant;        // 1 forces direct evaluation (A/B and tests)
     if (n_gw > 2147483647LL) return kNotTaken;
-    const bool thin_ok = B > 0 && cig == 1 && stride == 1 && dilation == 1 && k <= 64 && B <= 2147483647LL && variant != 1;
+    const bool thin_ok = B > 0 && cig == 1 && stride == 1 && dilation <= kGwMaxDilation && k <= 64 && B <= 2147483647LL && variant != 1;
     const bool dense_ok = B > 0 && groups == 1 && stride <= 2 && Cin >= 2 && variant != 1;
     if (thin_ok || dense_ok) {
         int64_t fg = (n_gw + kThreads - 1) / kThreads;
@@ -726,7 +802,7 @@ hipError_t launch_conv1d_grad_weight(const float *x, const float *gy, float *gw,
     if (thin_ok) {
 #define SWS_TGW(KB)                                                                                              \
     case KB:                                                                                                     \
-        return launch_thin_gw<KB>(x, gy, gw, (int)B, (int)Cin, (int)L, (int)Cout, (int)Lo, k, pad, cog, s)
+        return launch_thin_gw<KB>(x, gy, gw, (int)B, (int)Cin, (int)L, (int)Cout, (int)Lo, k, pad, cog, dilation, s)
         switch ((k + 3) / 4) {
             SWS_TGW(1); SWS_TGW(2); SWS_TGW(3); SWS_TGW(4); SWS_TGW(5); SWS_TGW(6); SWS_TGW(7); SWS_TGW(8);
             SWS_TGW(9); SWS_TGW(10); SWS_TGW(11); SWS_TGW(12); SWS_TGW(13); SWS_TGW(14); SWS_TGW(15); SWS_TGW(16);

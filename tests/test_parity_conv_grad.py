@@ -463,3 +463,17 @@ def test_split_operand_grad_weight_rows_at_full_size_on_sampled_channels(B):
     ref2, mag2 = oracle.conv2d_grad_weight(np.ascontiguousarray(x2[:, cis2]), np.ascontiguousarray(g2[:, cos]), 1, 1, 1, 1, 0, 0)
     worst = assert_within_tol(gw2[np.ix_(cos, cis2)], ref2, mag2, "1 x 1 layer, sampled channel pairs")
     assert worst < 2e-6, worst
+
+
+# b, channels, length, k, dilation, pad: spacings that do and do not divide a wavefront, rows shorter than a tile,
+# rows and tiles that end inside a phase, several runs of tiles per channel inside one row, several output channels per input channel
+THIN_SPACED_GW = [(2, 3, 700, 5, 2, 4), (1, 2, 2500, 36, 4, 70), (3, 1, 1900, 9, 3, 0), (1, 2, 5003, 64, 8, 11), (2, 2, 1200, 7, 5, 15),
+                  (1, 1, 3000, 63, 16, 496), (2, 1, 1100, 4, 7, 3), (1, 1, 90, 3, 11, 5), (1, 1, 70000, 12, 1, 5), (1, 1, 70000, 12, 6, 33)]
+
+
+@pytest.mark.parametrize("integer", [True, False])
+@pytest.mark.parametrize("b,c,length,k,dil,pad", THIN_SPACED_GW)
+def test_grad_weight_one_channel_per_output_spaced_taps(B, b, c, length, k, dil, pad, integer):
+    """One input channel per output channel with spaced taps (phase-major tiles) and runs of tiles that end inside a row."""
+    for cog in (1, 2):
+        _check_gw(B, (b, c, length, c * cog, k, 1, pad, dil, c), 90 + k, integer)
