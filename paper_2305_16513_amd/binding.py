@@ -21,7 +21,7 @@ _lib = None
 
 _i64, _i32, _f32, _vp = ctypes.c_int64, ctypes.c_int32, ctypes.c_float, ctypes.c_void_p
 
-EXPORTS = ("sws_slide1d", "sws_slide1d_16", "sws_slide1d_padded", "sws_slide1d_pair", "sws_pool2d", "sws_maxpool2d_grad", "sws_avgpool2d_grad", "sws_pool2d_16", "sws_pool2d_ex", "sws_pool2d_padded", "sws_conv1d", "sws_conv1d_padded", "sws_conv1d_16", "sws_conv1d_grad_input", "sws_conv1d_grad_weight", "sws_conv2d", "sws_conv2d_padded", "sws_conv2d_grad_input", "sws_conv2d_grad_weight", "sws_conv_workspace", "sws_conv1d_ws", "sws_conv1d_grad_input_ws", "sws_conv2d_ws", "sws_conv2d_grad_input_ws", "sws_conv1d_padded_ws", "sws_conv2d_padded_ws", "sws_copy", "sws_out_len",
+EXPORTS = ("sws_slide1d", "sws_slide1d_16", "sws_slide1d_padded", "sws_slide1d_pair", "sws_pool2d", "sws_maxpool2d_grad", "sws_avgpool2d_grad", "sws_pool2d_16", "sws_pool2d_ex", "sws_pool2d_padded", "sws_conv1d", "sws_conv1d_padded", "sws_conv1d_16", "sws_conv1d_grad_input", "sws_conv1d_grad_weight", "sws_conv2d", "sws_conv2d_padded", "sws_conv2d_grad_input", "sws_conv2d_grad_weight", "sws_conv_workspace", "sws_conv1d_ws", "sws_conv1d_grad_input_ws", "sws_conv2d_ws", "sws_conv2d_grad_input_ws", "sws_conv1d_padded_ws", "sws_conv2d_padded_ws", "sws_conv_grad_weight_workspace", "sws_conv1d_grad_weight_ws", "sws_conv2d_grad_weight_ws", "sws_copy", "sws_out_len",
            "sws_status_string", "sws_set_option", "sws_version")
 
 
@@ -83,11 +83,14 @@ def lib():
         for f in (L.sws_conv2d_grad_input, L.sws_conv2d_grad_weight):
             f.restype = ctypes.c_int
             f.argtypes = [_vp, _vp, _vp, _i64, _i64, _i64, _i64, _i64, _i32, _i32, _i32, _i32, _i32, _i32, _vp]
+        L.sws_conv_grad_weight_workspace.restype = _i64
+        L.sws_conv_grad_weight_workspace.argtypes = [_i64, _i64, _i32, _i32]
         L.sws_conv_workspace.restype = _i64
         L.sws_conv_workspace.argtypes = [_i64, _i64, _i64, _i64]
         for f, plain in ((L.sws_conv1d_ws, L.sws_conv1d), (L.sws_conv1d_grad_input_ws, L.sws_conv1d_grad_input),
                          (L.sws_conv2d_ws, L.sws_conv2d), (L.sws_conv2d_grad_input_ws, L.sws_conv2d_grad_input),
-                         (L.sws_conv1d_padded_ws, L.sws_conv1d_padded), (L.sws_conv2d_padded_ws, L.sws_conv2d_padded)):
+                         (L.sws_conv1d_padded_ws, L.sws_conv1d_padded), (L.sws_conv2d_padded_ws, L.sws_conv2d_padded),
+                         (L.sws_conv1d_grad_weight_ws, L.sws_conv1d_grad_weight), (L.sws_conv2d_grad_weight_ws, L.sws_conv2d_grad_weight)):
             f.restype = ctypes.c_int
             f.argtypes = plain.argtypes[:-1] + [_vp, _i64, _vp]
         L.sws_copy.restype = ctypes.c_int
@@ -140,18 +143,26 @@ def _workspace_bytes(cin, cout, taps, positions):
     return lib().sws_conv_workspace(cin, cout, taps, positions)
 
 
-def _workspace(wgt, cin, cout, taps, positions, stream):
-    """Device memory for the split weights of a dense layer that reads cin and writes cout channels, allocated on
-    the stream that the call runs on: (tensor, address, bytes), or (None, None, 0) where no kernel uses one."""
-    n = _workspace_bytes(cin, cout, taps, positions)
+@functools.lru_cache(maxsize=1024)
+def _grad_weight_bytes(cin, cout, kh, kw):
+    return lib().sws_conv_grad_weight_workspace(cin, cout, kh, kw)
+
+
+def _scratch(n, like, stream):
+    """n bytes of device memory allocated on the stream that the call runs on: (tensor, address, bytes)."""
     if n == 0:
         return None, None, 0
     if stream is None:
-        t = torch.empty(n, dtype=torch.uint8, device=wgt.device)
+        t = torch.empty(n, dtype=torch.uint8, device=like.device)
     else:
         with torch.cuda.stream(stream):
-            t = torch.empty(n, dtype=torch.uint8, device=wgt.device)
+            t = torch.empty(n, dtype=torch.uint8, device=like.device)
     return t, t.data_ptr(), n
+
+
+def _workspace(wgt, cin, cout, taps, positions, stream):
+    """For the split weights of a dense layer that reads cin and writes cout channels (none where no kernel uses it)."""
+    return _scratch(_workspace_bytes(cin, cout, taps, positions), wgt, stream)
 
 
 def _out(y, shape, like, name="y"):
@@ -420,8 +431,9 @@ def sws_conv1d_grad_weight(x, gy, k, stride=1, pad=0, dilation=1, groups=1, gw=N
     if b2 != b or cin % groups or lo != sws_out_len(length, k, stride, pad, dilation):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d_grad_weight")
     gw = _out(gw, (cout, cin // groups, k), x, "gw")
-    _check(lib().sws_conv1d_grad_weight(x.data_ptr(), gy.data_ptr(), gw.data_ptr(), b, cin, length, cout, k, stride,
-                                        pad, dilation, groups, _stream(stream)), "sws_conv1d_grad_weight")
+    keep, ws, ws_bytes = _scratch(_grad_weight_bytes(cin, cout, 1, k) if groups == 1 and cin > 1 else 0, x, stream)
+    _check(lib().sws_conv1d_grad_weight_ws(x.data_ptr(), gy.data_ptr(), gw.data_ptr(), b, cin, length, cout, k, stride,
+                                        pad, dilation, groups, ws, ws_bytes, _stream(stream)), "sws_conv1d_grad_weight")
     return gw
 
 
@@ -485,8 +497,9 @@ def sws_conv2d_grad_weight(x, gy, kh, kw, sh=1, sw=1, ph=0, pw=0, gw=None, strea
     if n2 != n or ho != sws_out_len(h, kh, sh, ph) or wo != sws_out_len(wd, kw, sw, pw):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d_grad_weight")
     gw = _out(gw, (cout, cin, kh, kw), x, "gw")
-    _check(lib().sws_conv2d_grad_weight(x.data_ptr(), gy.data_ptr(), gw.data_ptr(), n, cin, h, wd, cout, kh, kw,
-                                        sh, sw, ph, pw, _stream(stream)), "sws_conv2d_grad_weight")
+    keep, ws, ws_bytes = _scratch(_grad_weight_bytes(cin, cout, kh, kw), x, stream)
+    _check(lib().sws_conv2d_grad_weight_ws(x.data_ptr(), gy.data_ptr(), gw.data_ptr(), n, cin, h, wd, cout, kh, kw,
+                                        sh, sw, ph, pw, ws, ws_bytes, _stream(stream)), "sws_conv2d_grad_weight")
     return gw
 
 

@@ -709,10 +709,21 @@ hipError_t launch_conv2d_grad_input(const float *gy, const float *wgt, float *gx
 
 hipError_t launch_conv2d_grad_weight(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H,
                                      int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
-                                     int32_t sw, int32_t ph, int32_t pw, hipStream_t s)
+                                     int32_t sw, int32_t ph, int32_t pw, hipStream_t s, Workspace ws)
 {
     const int64_t n_gw = Cout * Cin * kh * kw;
     if (n_gw > 2147483647LL) return kNotTaken;
+    // With a workspace: the tiled split-operand kernel.  3 x 3 at stride 2 on channels in multiples of 32 and rows of whole
+    // 16-byte groups stays on the kernel that reads its operands straight from memory (its tile here would be four
+    // fifths halo): [32,128,56,56] -> 128 93 us there, 97 here; at stride 1 [32,256,14,14] -> 256 88 / 75, [3,128,10,97] -> 472 150 / 46.
+    const bool direct = kh == 3 && kw == 3 && sh == 2 && sw == 2 && Cin % 32 == 0 && Cout % 32 == 0 && W % 4 == 0 && Wo % 4 == 0;
+    if (ws.p && N > 0 && ((g_opt.conv2d_variant == 0 && !direct) || g_opt.conv2d_variant == 100)) {
+        bool taken = false;
+        const bool flat = kh == 1 && kw == 1 && sh == 1 && sw == 1 && ph == 0 && pw == 0;      // does not see the rows
+        const hipError_t e = flat ? launch_conv_gw_tile(x, gy, gw, N, Cin, 1, H * W, Cout, 1, Ho * Wo, 1, 1, 1, 1, 0, 0, 1, ws, s, &taken)
+                                  : launch_conv_gw_tile(x, gy, gw, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw, 1, ws, s, &taken);
+        if (taken || e != hipSuccess) return e;
+    }
     if (N > 0 && sw <= 2 && Cin >= 2 && g_opt.conv2d_variant != 1 && H * W <= 2147483647LL && Ho * Wo <= 2147483647LL) {
         int64_t fg = (n_gw + kThreads - 1) / kThreads;
         if (fg > 4096) fg = 4096;
@@ -786,12 +797,17 @@ hipError_t launch_conv1d_grad_input(const float *gy, const float *wgt, float *gx
 
 hipError_t launch_conv1d_grad_weight(const float *x, const float *gy, float *gw, int64_t B, int64_t Cin, int64_t L,
                                      int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad,
-                                     int32_t dilation, int32_t groups, hipStream_t s)
+                                     int32_t dilation, int32_t groups, hipStream_t s, Workspace ws)
 {
     const int cig = (int)(Cin / groups), cog = (int)(Cout / groups);
     const int64_t n_gw = Cout * cig * k;
     const int variant = g_opt.conv1d_variant;        // 1 forces direct evaluation (A/B and tests)
     if (n_gw > 2147483647LL) return kNotTaken;
+    if (ws.p && B > 0 && groups == 1 && Cin >= 2 && variant == 0 && (g_opt.conv2d_variant == 0 || g_opt.conv2d_variant == 100)) {
+        bool taken = false;
+        const hipError_t e = launch_conv_gw_tile(x, gy, gw, B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad, dilation, ws, s, &taken);
+        if (taken || e != hipSuccess) return e;
+    }
     const bool thin_ok = B > 0 && cig == 1 && stride == 1 && dilation <= kGwMaxDilation && k <= 64 && B <= 2147483647LL && variant != 1;
     const bool dense_ok = B > 0 && groups == 1 && stride <= 2 && Cin >= 2 && variant != 1;
     if (thin_ok || dense_ok) {

@@ -1,0 +1,460 @@
+// The adjoint of a dense convolution with respect to its weights, any kernel of up to 64 taps, strides 1 and 2, any channel
+// counts, one or two dimensions, on the bf16 matrix cores with exactly split fp32 operands:
+//
+//   gw[co][ci][t] = sum over positions p of  gy[n][co][p] * x[n][ci][p * s + t]
+//
+// is, per tap, a matrix product whose contraction index is the position.  v_mfma_f32_32x32x16_bf16 wants eight
+// consecutive contraction indices of one channel per lane, while one staged tile of x should serve every tap, i.e. be read at
+// any shift of the position.  Both hold with the tile stored position by position (16-byte units of eight channels of
+// one position and bf16 piece) and read with the transposing LDS load ds_read_b64_tr_b16: sixteen lanes point at four
+// positions x sixteen channels and receive four positions of one channel each.  The positions of a read are arbitrary
+// addresses, so strides, odd shifts and rows that end inside a run cost nothing; no column matrix, no permutes.
+//
+// A workgroup owns 64 output x 64 input channels x up to nine taps (whole kernel rows, or a run of one) and a run of
+// tiles of up to 128 positions: eight wavefronts, 32 x 32 channels x all its taps each, two wavefronts per block that take
+// alternate groups of 16 positions.  A tile is rpt whole rows of a strip of TW columns; rows are numbered through all
+// images, so small planes fill it.  The next tile's lines of x and gy are loaded into registers before the products of
+// the current one and split into LDS after them.  The dropped piece products are below 2^-23 of a term.
+//
+// Sums leave as partial blocks in the caller's workspace, lane after lane, and gw_reduce_kernel adds them in a fixed order:
+// the result does not depend on the order in which workgroups end.  (Atomic adds to gw instead, 36864 per workgroup,
+// take 27 us on 64 x 64 channels, 3 x 3; the two passes over 38 MB of partial blocks 13.)
+#include "sws_internal.h"
+
+namespace sws {
+
+namespace {
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef short v8s __attribute__((ext_vector_type(8)));
+
+constexpr int kThreads = 512;
+constexpr int kMaxTaps = 64, kMaxGroups = 64;
+constexpr int kBN = 128;                              // positions per tile
+constexpr int kPG = 140;                              // positions per staged plane of gy: >= kBN, = 12 mod 16 (see PS below)
+constexpr int kOctG = 3 * kPG * 16;                   // bytes from one octet of gy's channels to the next
+
+struct GwTile {
+    int N, Cin, H, W, HW, Cout, Ho, Wo, HoWo, NR;     // NR = N * Ho virtual rows of gy
+    int KT, ls, LPI, SH, sh, sw;                      // taps; lines per output row, per image, per window; strides
+    int CW, LW, TW, nstrips, rpt, tps, tiles;         // columns per residue, positions per line, strip width; rows per tile, tiles per strip
+    int PS;                                           // positions per staged plane of x, = 12 mod 16: the octets' planes
+                                                      // then start 16 banks apart, and a transposing read of four of them meets each bank twice
+    int ksteps, per, nsplit, cob, cib, ng;            // groups of 16 positions per tile; tiles per workgroup, runs; channel blocks, tap groups
+    float inv_TW, inv_Ho, inv_LPI, inv_LW, inv_CW, inv_PS;
+    short gdh[kMaxGroups], gdw[kMaxGroups];           // tap group: row and column of its first tap, relative to the position
+    unsigned char gt0[kMaxGroups], gnt[kMaxGroups];   // first tap, taps
+    unsigned short tapoff[kMaxTaps];                  // tap -> staged positions from a position's base
+};
+
+__device__ __forceinline__ int fdiv(int x, float inv_d) { return (int)(((float)x + 0.5f) * inv_d); }    // 0 <= x < 2^20
+
+__device__ __forceinline__ unsigned pack_hi(float lo, float hi)
+{
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+
+constexpr unsigned kNowhere = 0x80000000u;            // beyond every descriptor: such loads return zero
+
+// a 16-byte unit: eight channels' values, split into three pieces, to dst, dst + step, dst + 2 step
+__device__ __forceinline__ void put_unit(char *dst, int step, const float (&v)[8])
+{
+    unsigned p[3][4];
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        float r1[2], r2[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            r1[u] = v[e + u] - __uint_as_float(__float_as_uint(v[e + u]) & 0xffff0000u);
+            r2[u] = r1[u] - __uint_as_float(__float_as_uint(r1[u]) & 0xffff0000u);
+        }
+        p[0][e / 2] = pack_hi(v[e], v[e + 1]);
+        p[1][e / 2] = pack_hi(r1[0], r1[1]);
+        p[2][e / 2] = pack_hi(r2[0], r2[1]);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *(v4u *)(dst + q * step) = (v4u){p[q][0], p[q][1], p[q][2], p[q][3]};
+}
+
+// eight positions of this lane's channel: two transposing reads of four
+__device__ __forceinline__ v8bf tr8(const char *p0, const char *p1)
+{
+    typedef __attribute__((address_space(3))) v4s lds_v4s;
+    const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)p0);
+    const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)p1);
+    return __builtin_bit_cast(v8bf, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// TB: taps per group at most, FULL: in every group; WM x WN blocks of 32 x 32 channels, WK wavefronts each; UX: staged units
+// of x per thread (gy has WM).  The places of a thread's units are worked out anew for every tile (opaque): kept in registers
+// they push the accumulators into scratch memory, whose reloads would wait for the loads in flight.
+template <int TB, int WM, int WN, int UX, bool FULL>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void conv_gw_tile_kernel(const float *__restrict__ x, const float *__restrict__ gy, float *__restrict__ ws, GwTile g)
+{
+    constexpr int WK = 8 / (WM * WN), OG = 4 * WM, OX = 4 * WN;      // octets of channels
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    char *const G = lds, *const X = lds + OG * kOctG;
+    const int pieceX = g.PS * 16, octX = 3 * pieceX;
+    int *const tab = (int *)(X + OX * octX);          // position -> byte offset of its base in a plane of x
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WM, wn = wave / WM % WN, wk = wave / (WM * WN);
+
+    const int Gx = (int)gridDim.x;                    // a multiple of 8: each XCD takes a contiguous run
+    const int id = (int)(blockIdx.x & 7) * (Gx >> 3) + (int)(blockIdx.x >> 3);
+    const int nblk = g.cob * g.cib * g.ng;
+    if (id >= g.nsplit * nblk) return;
+    const int split = id / nblk, blk = id - split * nblk;
+    const int grp = blk % g.ng, cb = blk / g.ng, cob = cb / g.cib, cib = cb - cob * g.cib;
+    const int nt = g.gnt[grp], t0 = g.gt0[grp], dh = g.gdh[grp], dw = g.gdw[grp];
+    const int co0 = cob * (32 * WM), ci0 = cib * (32 * WN);
+    const int first = split * g.per, end = first + g.per < g.tiles ? first + g.per : g.tiles;
+
+    // ---- staged units.  gy: octet of channels, position; x: octet, line and column of the tile
+    const int gmax = g.Cout > 8 ? g.Cout - 8 : 0, xmax = g.Cin > 8 ? g.Cin - 8 : 0;
+    const int units = OX * g.PS;
+    float gr[WM][8], xr[UX][8];
+    int tabv = 0;
+    auto issue = [&](int tile) {
+        const int strip = tile / g.tps, R0 = (tile - strip * g.tps) * g.rpt, cb0 = strip * g.TW;
+        const int n0 = R0 / g.Ho, oh0 = R0 - n0 * g.Ho;
+        const int64_t xl_ = 4 * (int64_t)(g.N - n0) * g.Cin * g.HW, gl_ = 4 * (int64_t)(g.N - n0) * g.Cout * g.HoWo;
+        const __amdgpu_buffer_rsrc_t xs = rsrc(x + (int64_t)n0 * g.Cin * g.HW, xl_ < 0x7fffffff ? (unsigned)xl_ : 0x7fffffffu);
+        const __amdgpu_buffer_rsrc_t gs = rsrc(gy + (int64_t)n0 * g.Cout * g.HoWo, gl_ < 0x7fffffff ? (unsigned)gl_ : 0x7fffffffu);
+        int me = tid;
+        asm volatile("" : "+v"(me));
+        {
+            const int R = fdiv(me & 127, g.inv_TW), c = (me & 127) - R * g.TW;
+            const int t = oh0 + R, dn = fdiv(t, g.inv_Ho), oh = t - dn * g.Ho;
+            const bool in = R < g.rpt, ok = in && R0 + R < g.NR && cb0 + c < g.Wo;
+            tabv = in ? ((dn * g.LPI + (oh - oh0) * g.ls) * g.LW + c) * 16 : 0;
+#pragma unroll
+            for (int i = 0; i < WM; ++i) {
+                const int ch = co0 + 8 * ((me >> 7) + 4 * i), cc = ch < gmax ? ch : gmax;
+                const unsigned at = ok && ch < g.Cout ? 4u * (unsigned)((dn * g.Cout + cc) * g.HoWo + oh * g.Wo + cb0 + c) : kNowhere;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int se = e < g.Cout ? e : g.Cout - 1;
+                    gr[i][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(gs, at, 4 * se * g.HoWo, 0));
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < UX; ++i) {
+            if (i * kThreads >= units) continue;
+            const int u = me + i * kThreads, oct = fdiv(u, g.inv_PS), pos = u - oct * g.PS;
+            const int ln = fdiv(pos, g.inv_LW), c0 = pos - ln * g.LW, cph = fdiv(c0, g.inv_CW);
+            const int col = (cb0 + c0 - cph * g.CW) * g.sw + cph + dw;
+            const int l = oh0 * g.ls + ln, dn = fdiv(l, g.inv_LPI), r = l - dn * g.LPI;
+            const int row = (g.SH >= g.sh ? r : r * g.sh) + dh;
+            const int ch = ci0 + oct * 8, cc = ch < xmax ? ch : xmax;
+            const bool ok = oct < OX && ch < g.Cin && n0 + dn < g.N && (unsigned)row < (unsigned)g.H && (unsigned)col < (unsigned)g.W;
+            const unsigned at = ok ? 4u * (unsigned)((dn * g.Cin + cc) * g.HW + row * g.W + col) : kNowhere;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int se = e < g.Cin ? e : g.Cin - 1;
+                xr[i][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xs, at, 4 * se * g.HW, 0));
+            }
+        }
+    };
+    auto commit = [&]() {
+        int me = tid;
+        asm volatile("" : "+v"(me));
+#pragma unroll
+        for (int i = 0; i < WM; ++i) put_unit(G + ((me >> 7) + 4 * i) * kOctG + (me & 127) * 16, kPG * 16, gr[i]);
+#pragma unroll
+        for (int i = 0; i < UX; ++i) {
+            if (i * kThreads >= units) continue;
+            const int u = me + i * kThreads, oct = fdiv(u, g.inv_PS), pos = u - oct * g.PS;
+            if (oct < OX) put_unit(X + oct * octX + pos * 16, pieceX, xr[i]);
+        }
+        if (me < kBN) tab[me] = tabv;
+    };
+    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    // ---- operand reads: lane 16 b + m points at octet 2 (b & 1) + (m & 3) / 2, half (m & 1), position 8 (b >> 1) + m / 4
+    const int b = lane >> 4, m = lane & 15;
+    const int oct = 2 * (b & 1) + ((m & 3) >> 1), pj = 8 * (b >> 1) + (m >> 2);
+    const char *const Ga = G + (4 * wm + oct) * kOctG + (m & 1) * 8 + pj * 16;
+    const char *const Xa = X + (4 * wn + oct) * octX + (m & 1) * 8;
+    v16f acc[TB];
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.0f;
+
+    if (first < end) issue(first);
+    for (int tile = first; tile < end; ++tile) {
+        commit();
+        barrier();
+        if (tile + 1 < end) issue(tile + 1);
+        for (int s = wk; s < g.ksteps; s += WK) {
+            const int p0 = tab[16 * s + pj], p1 = tab[16 * s + pj + 4];
+            v8bf a[3], bb[2][3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) a[q] = tr8(Ga + s * 256 + q * (kPG * 16), Ga + s * 256 + 64 + q * (kPG * 16));
+            auto xread = [&](int t, v8bf (&o)[3]) {
+                const int off = g.tapoff[t0 + t] * 16;
+                const char *q0 = Xa + p0 + off, *q1 = Xa + p1 + off;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) o[q] = tr8(q0 + q * pieceX, q1 + q * pieceX);
+            };
+            xread(0, bb[0]);
+#pragma unroll
+            for (int t = 0; t < TB; ++t) {
+                if (!FULL && t >= nt) continue;
+                if (FULL ? t + 1 < TB : t + 1 < nt) xread(t + 1, bb[(t + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                const v8bf (&B)[3] = bb[t & 1];
+                v16f c = acc[t];                      // smallest products first
+                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], B[0], c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], B[1], c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], B[2], c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], B[0], c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], B[1], c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], B[0], c, 0, 0, 0);
+                acc[t] = c;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        barrier();                                    // everybody has read the tile
+    }
+
+    // ---- the wavefronts of a block add up through LDS, three taps at a time; then to the workspace:
+    //      ws[split][block][tap][wm, wn][register][lane]
+    constexpr int BLK = WM * WN, ROWS = TB < 3 ? TB : 3;
+    float *const out = ws + ((int64_t)split * nblk + blk) * (TB * BLK * 1024) + (wave % BLK) * 1024 + lane;
+    v4f *const red = (v4f *)lds + lane;
+#pragma unroll
+    for (int q = 0; q < TB; q += 3) {
+        if (wk > 0) {
+#pragma unroll
+            for (int t = q; t < q + 3 && t < TB; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    red[((wave - BLK) * (4 * ROWS) + (t - q) * 4 + v) * 64] =
+                        (v4f){acc[t][4 * v], acc[t][4 * v + 1], acc[t][4 * v + 2], acc[t][4 * v + 3]};
+        }
+        barrier();
+        if (wk == 0) {
+#pragma unroll
+            for (int t = q; t < q + 3 && t < TB; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    v4f r = {acc[t][4 * v], acc[t][4 * v + 1], acc[t][4 * v + 2], acc[t][4 * v + 3]};
+                    for (int k = 0; k < WK - 1; ++k) r += red[((k * BLK + wave) * (4 * ROWS) + (t - q) * 4 + v) * 64];
+                    if (FULL || t < nt) {
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) out[t * (BLK * 1024) + (4 * v + u) * 64] = r[u];
+                    }
+                }
+        }
+        barrier();
+    }
+}
+
+// gw from the partial blocks: a workgroup adds 64 lanes of one (block, tap, wavefront, register), its four wavefronts
+// every fourth run; register v of lane (l32, half) is output channel 8*(v/4) + 4*half + v%4, input channel l32 of the
+// block of 32.  An octet of channels that reached beyond the last one held the last eight (see the staging).
+__global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
+{
+    __shared__ float part[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nblk = g.cob * g.cib * g.ng, BLK = WM * WN;
+    const int v = blockIdx.x & 15, rest = (int)(blockIdx.x >> 4), w = rest % BLK, t = rest / BLK % TB, blk = rest / (BLK * TB);
+    const int grp = blk % g.ng, cb = blk / g.ng, cob = cb / g.cib, cib = cb - cob * g.cib;
+    if (t >= g.gnt[grp]) return;
+    const int64_t step = (int64_t)nblk * (TB * BLK * 1024);
+    const float *p = ws + (int64_t)blk * (TB * BLK * 1024) + t * (BLK * 1024) + w * 1024 + v * 64 + lane;
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    int k = wave;
+    for (; k + 12 < g.nsplit; k += 16) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s[u] += p[(k + 4 * u) * step];
+    }
+    for (; k < g.nsplit; k += 4) s[0] += p[k * step];
+    part[wave][lane] = (s[0] + s[1]) + (s[2] + s[3]);
+    __syncthreads();
+    if (wave != 0) return;
+    const float sum = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    auto channel = [](int slot, int n) {              // the channel a slot holds; -1: none, or one that another slot holds
+        const int o = slot & ~7, c0 = o < n - 8 ? o : (n > 8 ? n - 8 : 0), c = c0 + (slot & 7);
+        return o < n && c >= o && c < n ? c : -1;
+    };
+    const int co = channel(cob * (32 * WM) + w % WM * 32 + 8 * (v / 4) + 4 * (lane >> 5) + v % 4, g.Cout);
+    const int ci = channel(cib * (32 * WN) + w / WM * 32 + (lane & 31), g.Cin);
+    if (co >= 0 && ci >= 0) gw[((int64_t)co * g.Cin + ci) * g.KT + g.gt0[grp] + t] = sum;
+}
+
+template <int TB, int WM, int WN, bool FULL>
+hipError_t launch_gw1(const float *x, const float *gy, float *gw, float *ws, const GwTile &g, size_t lds, hipStream_t s)
+{
+    constexpr int UX = 4;
+    const int nblk = g.cob * g.cib * g.ng;
+    if (lds > 64 * 1024) {
+        static std::atomic<bool> raised{false};       // (the attribute is per function; setting it twice does no harm)
+        if (!raised.load(std::memory_order_relaxed)) {
+            const hipError_t e = hipFuncSetAttribute((const void *)conv_gw_tile_kernel<TB, WM, WN, UX, FULL>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return e;
+            raised.store(true, std::memory_order_relaxed);
+        }
+    }
+    hipLaunchKernelGGL((conv_gw_tile_kernel<TB, WM, WN, UX, FULL>), dim3((unsigned)xcd_grid((int64_t)g.nsplit * nblk)), dim3(kThreads), lds,
+                       s, x, gy, ws, g);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(gw_reduce_kernel, dim3((unsigned)(nblk * TB * WM * WN * 16)), dim3(256), 0, s, ws, gw, g, TB, WM, WN);
+    return hipGetLastError();
+}
+
+template <int TB>
+hipError_t launch_gw(const float *x, const float *gy, float *gw, float *ws, const GwTile &g, int WM, int WN, size_t lds, hipStream_t s)
+{
+    bool full = true;
+    for (int k = 0; k < g.ng; ++k) full = full && g.gnt[k] == TB;
+#define SWS_GW(M, N) return full ? launch_gw1<TB, M, N, true>(x, gy, gw, ws, g, lds, s) : launch_gw1<TB, M, N, false>(x, gy, gw, ws, g, lds, s)
+    if (WM == 2 && WN == 2) SWS_GW(2, 2);
+    if (WM == 2) SWS_GW(2, 1);
+    if (WN == 2) SWS_GW(1, 2);
+    SWS_GW(1, 1);
+#undef SWS_GW
+}
+
+struct Groups { int rows, taps, ng, tb; };            // kernel rows and taps per row of a group; groups; taps rounded to an instance
+
+Groups tap_groups(int kh, int kw)
+{
+    Groups q;
+    q.taps = kw <= 9 ? kw : 9;
+    q.rows = kw <= 9 ? 9 / kw : 1;
+    if (q.rows > kh) q.rows = kh;
+    q.rows = (kh + (kh + q.rows - 1) / q.rows - 1) / ((kh + q.rows - 1) / q.rows);      // evenly
+    q.ng = (kh + q.rows - 1) / q.rows * ((kw + q.taps - 1) / q.taps);
+    const int n = q.rows * q.taps;
+    q.tb = n <= 1 ? 1 : n <= 3 ? 3 : n <= 5 ? 5 : 9;
+    return q;
+}
+
+// Runs per block of gw: one workgroup per compute unit, two rounds where that leaves a block few runs.
+int gw_splits(int64_t nblk, int64_t tiles)
+{
+    int64_t n = (256 + nblk - 1) / nblk;
+    if (nblk > 128) n = nblk >= 512 ? 1 : 512 / nblk;
+    return (int)(n < tiles ? n : tiles);
+}
+
+}  // namespace
+
+// Bytes of workspace: every run's partial sums.
+int64_t conv_gw_workspace(int64_t Cin, int64_t Cout, int kh, int kw)
+{
+    if ((int64_t)kh * kw > kMaxTaps || kh > 64 || kw > 64) return 0;
+    const Groups q = tap_groups(kh, kw);
+    const int64_t nblk = ((Cin + 63) / 64) * ((Cout + 63) / 64) * q.ng, small = ((Cin + 31) / 32) * ((Cout + 31) / 32) * q.ng;
+    const int64_t a = (nblk + 512) * 4, b = small + 512;      // 32 x 32 blocks; (64 x 32 lie between)
+    return (a > 2 * b ? a : 2 * b) * q.tb * 1024 * 4;
+}
+
+hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Cout,
+                               int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t ph, int32_t pw, int32_t dil,
+                               Workspace ws, hipStream_t s, bool *taken)
+{
+    *taken = false;
+    if (!ws.p || ((uintptr_t)ws.p & 15) || (int64_t)kh * kw > kMaxTaps || sh > 2 || sw > 2 || N < 1) return hipSuccess;
+    if (N * Ho >= (1LL << 30) || H >= (1 << 18) || Ho >= (1 << 18) || W >= (1LL << 27) || Wo >= (1LL << 27) || Cin * H * W >= (1LL << 27) ||
+        Cout * Ho * Wo >= (1LL << 27))
+        return hipSuccess;
+    const Groups q = tap_groups(kh, kw);
+    GwTile g;
+    g.N = (int)N; g.Cin = (int)Cin; g.H = (int)H; g.W = (int)W; g.HW = (int)(H * W); g.Cout = (int)Cout; g.Ho = (int)Ho; g.Wo = (int)Wo;
+    g.HoWo = (int)(Ho * Wo); g.NR = (int)(N * Ho); g.KT = kh * kw; g.sh = sh; g.sw = sw;
+    g.SH = q.rows; g.ls = g.SH < sh ? g.SH : sh;
+    if (g.SH < sh && g.SH != 1) return hipSuccess;
+    g.LPI = (int)(Ho - 1) * g.ls + g.SH;
+    const int SW = (q.taps - 1) * dil + 1, SWc = SW < sw ? SW : sw;
+    g.ng = q.ng;
+    const int runs = (kw + q.taps - 1) / q.taps;
+    for (int k = 0; k < q.ng; ++k) {
+        const int a0 = k / runs * q.rows, b0 = k % runs * q.taps;
+        const int na = kh - a0 < q.rows ? kh - a0 : q.rows, nb = kw - b0 < q.taps ? kw - b0 : q.taps;
+        if (na > 1 && nb != kw) return hipSuccess;
+        g.gdh[k] = (short)(a0 - ph); g.gdw[k] = (short)(b0 * dil - pw);
+        g.gt0[k] = (unsigned char)(a0 * kw + b0); g.gnt[k] = (unsigned char)(na * nb);
+    }
+    if (ph > 16384 || pw > 16384 || kw * (int64_t)dil > 16384) return hipSuccess;
+    // Channel blocks of a workgroup, strip width and rows per tile: the smallest estimated time of the longest run (products
+    // on two wavefronts per SIMD, staging per unit, a run's end), in cycles.
+    constexpr int kUX = 4;
+    bool found = false;
+    double best = 0;
+    GwTile bg = g;
+    int WM = 0, WN = 0;
+    size_t lds = 0;
+    const int nt = q.rows * q.taps;
+    for (int wmn = 0; wmn < 4; ++wmn) {
+        const int wm = 1 + (wmn & 1), wn = 1 + (wmn >> 1), wk = 8 / (wm * wn);
+        if ((wm == 2 && Cout <= 32) || (wn == 2 && Cin <= 32)) continue;
+        const int64_t cob = (Cout + 32 * wm - 1) / (32 * wm), cib = (Cin + 32 * wn - 1) / (32 * wn), nblk = cob * cib * g.ng;
+        if (nblk * 16 * wm * wn * q.tb >= (1LL << 30)) continue;
+        for (int ns = (int)((Wo + kBN - 1) / kBN), last = ns + 3; ns <= last && ns <= Wo; ++ns) {
+            const int TW = (int)((unsigned)(Wo + ns - 1) / ns), nstrips = (int)((unsigned)(Wo + TW - 1) / TW);
+            const int CW = TW + (int)((unsigned)(SW - 1) / sw), LW = SWc * CW;
+            for (int rpt = kBN / TW < g.NR ? kBN / TW : g.NR; rpt >= 1; rpt = rpt > 4 ? rpt * 3 / 4 : rpt - 1) {
+                const int crossings = (int)((unsigned)(rpt - 1 + g.Ho - 1) / g.Ho);
+                const int64_t lines = (int64_t)(rpt - 1) * g.ls + g.SH + crossings * (g.SH - g.ls);
+                if (lines * LW > 1024) continue;
+                const int PS = ((int)(lines * LW) + 3) / 16 * 16 + 12;
+                const size_t stage = (size_t)4 * 3 * 16 * (wn * PS + wm * kPG) + kBN * 4;
+                const size_t red = (size_t)(8 - wm * wn) * 4 * (q.tb < 3 ? q.tb : 3) * 1024;
+                if (4 * wn * PS > kUX * kThreads || stage > 158 * 1024) continue;
+                const int tps = (int)((unsigned)(g.NR + rpt - 1) / rpt), tiles = tps * nstrips, ksteps = (rpt * TW + 15) / 16;
+                int nsplit = gw_splits(nblk, tiles);
+                const int per = (int)((unsigned)(tiles + nsplit - 1) / nsplit);
+                nsplit = (int)((unsigned)(tiles + per - 1) / per);
+                if (nblk * nsplit * q.tb * wm * wn * 4096 > ws.bytes) continue;
+                const double rounds = (double)((nblk * nsplit + 255) / 256);
+                const double tile = (ksteps + wk - 1) / wk * (double)nt * 6 * 32 * 2 * 1.2 + 1200 + 500.0 * ((4 * wn * PS + kThreads - 1) / kThreads + wm);
+                const double cost = rounds * (per * tile + 4000 + 6.0 * q.tb * wm * wn * nblk * nsplit / 64);
+                if (!found || cost < best) {
+                    found = true;
+                    best = cost;
+                    WM = wm; WN = wn;
+                    lds = stage > red ? stage : red;
+                    bg.TW = TW; bg.nstrips = nstrips; bg.CW = CW; bg.LW = LW; bg.rpt = rpt; bg.PS = PS; bg.tps = tps; bg.tiles = tiles;
+                    bg.ksteps = ksteps; bg.per = per; bg.nsplit = nsplit; bg.cob = (int)cob; bg.cib = (int)cib;
+                }
+            }
+        }
+    }
+    if (!found) return hipSuccess;
+    g = bg;
+    const int64_t imgs = g.rpt / Ho + 2;
+    if (imgs * Cin * H * W >= (1LL << 29) || imgs * Cout * Ho * Wo >= (1LL << 29)) return hipSuccess;
+    for (int t = 0; t < g.KT; ++t) {
+        const int a = t / kw % q.rows, bcol = t % kw % q.taps * dil;
+        g.tapoff[t] = (unsigned short)(a * g.LW + bcol % sw * g.CW + bcol / sw);
+    }
+    for (int t = g.KT; t < kMaxTaps; ++t) g.tapoff[t] = 0;
+    g.inv_TW = 1.0f / g.TW; g.inv_Ho = 1.0f / g.Ho; g.inv_LPI = 1.0f / g.LPI; g.inv_LW = 1.0f / g.LW; g.inv_CW = 1.0f / g.CW;
+    g.inv_PS = 1.0f / g.PS;
+    float *w = (float *)ws.p;
+    *taken = true;
+    switch (q.tb) {
+    case 1: return launch_gw<1>(x, gy, gw, w, g, WM, WN, lds, s);
+    case 3: return launch_gw<3>(x, gy, gw, w, g, WM, WN, lds, s);
+    case 5: return launch_gw<5>(x, gy, gw, w, g, WM, WN, lds, s);
+    default: return launch_gw<9>(x, gy, gw, w, g, WM, WN, lds, s);
+    }
+}
+
+}  // namespace sws

@@ -287,6 +287,12 @@ int64_t sws_conv_workspace(int64_t Cin, int64_t Cout, int64_t taps, int64_t posi
     return sws::conv_split_workspace(Cin, Cout, taps, positions);
 }
 
+int64_t sws_conv_grad_weight_workspace(int64_t Cin, int64_t Cout, int32_t kh, int32_t kw)
+{
+    if (Cin < 1 || Cout < 1 || kh < 1 || kw < 1 || Cin > (1 << 20) || Cout > (1 << 20)) return 0;
+    return sws::conv_gw_workspace(Cin, Cout, kh, kw);
+}
+
 sws_status sws_conv1d_ws(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
                       int64_t Cout, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
                       int32_t groups, void *workspace, int64_t workspace_bytes,
@@ -408,16 +414,25 @@ sws_status sws_conv1d_grad_input(const float *gy, const float *wgt, float *gx, i
     return sws_conv1d_grad_input_ws(gy, wgt, gx, B, Cin, L, Cout, k, stride, pad, dilation, groups, nullptr, 0, stream);
 }
 
-sws_status sws_conv1d_grad_weight(const float *x, const float *gy, float *gw, int64_t B, int64_t Cin, int64_t L,
+sws_status sws_conv1d_grad_weight_ws(const float *x, const float *gy, float *gw, int64_t B, int64_t Cin, int64_t L,
                                   int64_t Cout, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
-                                  int32_t groups, sws_stream_t stream)
+                                  int32_t groups,
+                                     void *workspace, int64_t workspace_bytes,
+                                     sws_stream_t stream)
 {
     int64_t Lo;
     const sws_status st = check_conv1d(B, Cin, L, Cout, k, stride, pad, dilation, groups, &Lo);
     if (st != SWS_OK) return st;
     if (!gw || (B > 0 && (!x || !gy))) return SWS_ERR_INVALID_ARG;      // with no images gw is all zeros
     return SWS_LAUNCH(sws::launch_conv1d_grad_weight(x, gy, gw, B, Cin, L, Cout, Lo, k, stride, pad, dilation, groups,
-                                                   (hipStream_t)stream));
+                                                   (hipStream_t)stream, sws::Workspace{workspace, workspace_bytes}));
+}
+
+sws_status sws_conv1d_grad_weight(const float *x, const float *gy, float *gw, int64_t B, int64_t Cin, int64_t L,
+                                  int64_t Cout, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
+                                  int32_t groups, sws_stream_t stream)
+{
+    return sws_conv1d_grad_weight_ws(x, gy, gw, B, Cin, L, Cout, k, stride, pad, dilation, groups, nullptr, 0, stream);
 }
 
 namespace {
@@ -462,16 +477,25 @@ sws_status sws_conv2d_grad_input(const float *gy, const float *wgt, float *gx, i
     return sws_conv2d_grad_input_ws(gy, wgt, gx, N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw, nullptr, 0, stream);
 }
 
-sws_status sws_conv2d_grad_weight(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H,
+sws_status sws_conv2d_grad_weight_ws(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H,
                                   int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t ph,
-                                  int32_t pw, sws_stream_t stream)
+                                  int32_t pw,
+                                     void *workspace, int64_t workspace_bytes,
+                                     sws_stream_t stream)
 {
     int64_t Ho, Wo;
     const sws_status st = check_conv2d(N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw, &Ho, &Wo);
     if (st != SWS_OK) return st;
     if (!gw || (N > 0 && (!x || !gy))) return SWS_ERR_INVALID_ARG;      // with no images gw is all zeros
     return SWS_LAUNCH(sws::launch_conv2d_grad_weight(x, gy, gw, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw,
-                                                   (hipStream_t)stream));
+                                                   (hipStream_t)stream, sws::Workspace{workspace, workspace_bytes}));
+}
+
+sws_status sws_conv2d_grad_weight(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H,
+                                  int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t ph,
+                                  int32_t pw, sws_stream_t stream)
+{
+    return sws_conv2d_grad_weight_ws(x, gy, gw, N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw, nullptr, 0, stream);
 }
 
 sws_status sws_conv2d_ws(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,

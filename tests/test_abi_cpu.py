@@ -284,3 +284,11 @@ def test_conv_workspace_and_argument_checks_of_the_ws_entries(L):
     assert L.sws_conv2d_grad_input_ws(one, one, one, 1, 3, 2, 2, 4, 5, 5, 1, 1, 1, 1, one, 64, nul) == 1
     assert L.sws_conv1d_ws(one, one, one, 1, 3, 10, 4, 11, 1, 0, 1, 1, one, 64, nul) == 1
     assert L.sws_conv1d_grad_input_ws(one, one, nul, 1, 3, 10, 4, 3, 1, 0, 1, 1, one, 64, nul) == 1
+
+
+def test_grad_weight_workspace_and_argument_checks(L):
+    one, nul = ctypes.c_void_p(16), ctypes.c_void_p(0)
+    assert L.sws_conv_grad_weight_workspace(64, 64, 3, 3) >= 4 * 64 * 64 * 9
+    assert L.sws_conv_grad_weight_workspace(64, 64, 9, 9) == 0 and L.sws_conv_grad_weight_workspace(64, 0, 3, 3) == 0
+    assert L.sws_conv2d_grad_weight_ws(one, one, nul, 1, 3, 10, 10, 4, 3, 3, 1, 1, 1, 1, one, 64, nul) == 1
+    assert L.sws_conv1d_grad_weight_ws(nul, one, one, 1, 3, 10, 4, 3, 1, 0, 1, 1, one, 64, nul) == 1

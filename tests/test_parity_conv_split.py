@@ -187,3 +187,44 @@ def test_graph_replay(B):
         assert torch.equal(got[0], y) and torch.equal(got[1], gx), "replay %d" % rep
         ref, _ = oracle.conv2d(to_host(x), to_host(wgt), 2, 2, 1, 1)
         assert_bit_exact(to_host(y), ref, "replay %d" % rep)
+
+
+# (pad below the kernel; strides beyond 2 and more than 64 taps are other kernels' cases)
+GW_CASES = CASES + [
+    (2, 70, 33, 10, 9, 3, 3, 1, 1),                   # blocks of 64 and 32 channels, both ends ragged
+    (1, 20, 70, 1, 700, 1, 11, 1, 5),                 # two runs of taps of one row
+    (20, 33, 9, 7, 7, 3, 3, 1, 1),                    # tiles across images
+    (2, 3, 5, 130, 140, 3, 3, 1, 1),                  # strips, fewer than eight channels
+    (1, 40, 40, 2, 600, 2, 3, 2, 0),
+]
+
+
+@pytest.mark.parametrize("integer", [True, False])
+@pytest.mark.parametrize("case", GW_CASES)
+def test_grad_weight_through_transposing_reads(B, case, integer):
+    n, cin, cout, h, w, kh, kw, s, p = case
+    ph, sh = (p, s) if h > 1 else (0, 1)
+    rng = np.random.default_rng(41)
+    x = workloads.integer_valued((n, cin, h, w), -3, 3, 42) if integer else rng.standard_normal((n, cin, h, w)).astype(np.float32)
+    ho, wo = (h + 2 * ph - kh) // sh + 1, (w + 2 * p - kw) // s + 1
+    gy = workloads.integer_valued((n, cout, ho, wo), -3, 3, 43) if integer else \
+        rng.standard_normal((n, cout, ho, wo)).astype(np.float32)
+    ref, mag = oracle.conv2d_grad_weight(x, gy, kh, kw, sh, s, ph, p)
+    flat, gw = _guarded(ref.shape)
+    B.sws_set_option("conv2d_variant", 100)           # (also where another kernel is preferred)
+    B.sws_conv2d_grad_weight(to_gpu(x), to_gpu(gy), kh, kw, sh, s, ph, p, gw=gw)
+    if integer:
+        assert_bit_exact(to_host(gw), ref, "gw %s" % (case,))
+    else:
+        # sums of up to n*ho*wo = 18200 products: a rounding of the running sum per 16 products and run of tiles
+        assert_within_tol(to_host(gw), ref, mag, "gw %s" % (case,), tol=SPLIT_TOL)
+    assert (flat[:64] == 12345.0).all() and (flat[-64:] == 12345.0).all()
+
+
+def test_grad_weight_is_reproducible(B):
+    """Partial sums are added in a fixed order: two calls give the same bits."""
+    rng = np.random.default_rng(7)
+    x, gy = (to_gpu(rng.standard_normal(s).astype(np.float32)) for s in ((8, 40, 30, 30), (8, 48, 30, 30)))
+    a = to_host(B.sws_conv2d_grad_weight(x, gy, 3, 3, 1, 1, 1, 1))
+    for _ in range(3):
+        assert_bit_exact(to_host(B.sws_conv2d_grad_weight(x, gy, 3, 3, 1, 1, 1, 1)), a)
