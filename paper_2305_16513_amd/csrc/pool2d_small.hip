@@ -18,8 +18,8 @@ constexpr int kStage = 4096;                         // floats of LDS per workgr
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-template <int OP>
-__global__ __launch_bounds__(kThreads) void pool2d_small_kernel(const float *__restrict__ x, float *__restrict__ y,
+template <int OP, typename T>
+__global__ __launch_bounds__(kThreads) void pool2d_small_kernel(const T *__restrict__ x, T *__restrict__ y,
                                                                 int64_t planes, int H, int W, int Ho, int Wo, int kh,
                                                                 int kw, int sh, int sw, int ph, int pw, float scale,
                                                                 int div_valid, int G, unsigned rcp_q, unsigned rcp_wo)
@@ -30,17 +30,21 @@ __global__ __launch_bounds__(kThreads) void pool2d_small_kernel(const float *__r
     const int P = H * W, Q = Ho * Wo;
     const int64_t p0 = (int64_t)blockIdx.x * G;
     const int g = planes - p0 < G ? (int)(planes - p0) : G;
-    const float *src = x + p0 * P;
+    typedef T v4t __attribute__((ext_vector_type(4)));
+    const T *src = x + p0 * P;
     const int n = g * P;
-    if (((uintptr_t)src & 15) == 0) {
+    if (((uintptr_t)src & (4 * sizeof(T) - 1)) == 0) {
         const int n4 = n >> 2;
-        for (int i = tid; i < n4; i += kThreads) *(v4f *)(lds + 4 * i) = *(const v4f *)(src + 4 * i);
-        for (int i = 4 * n4 + tid; i < n; i += kThreads) lds[i] = src[i];
+        for (int i = tid; i < n4; i += kThreads) {
+            const v4t q = *(const v4t *)(src + 4 * i);
+            *(v4f *)(lds + 4 * i) = (v4f){(float)q[0], (float)q[1], (float)q[2], (float)q[3]};
+        }
+        for (int i = 4 * n4 + tid; i < n; i += kThreads) lds[i] = (float)src[i];
     } else {
-        for (int i = tid; i < n; i += kThreads) lds[i] = src[i];
+        for (int i = tid; i < n; i += kThreads) lds[i] = (float)src[i];
     }
     __syncthreads();
-    float *dst = y + p0 * Q;
+    T *dst = y + p0 * Q;
     const int m = g * Q;
     for (int o = tid; o < m; o += kThreads) {
         // o = (plane, ho, wo); the quotients by multiplication with 2^32 / d + 1 (exact: o < 2^16, d < 2^12)
@@ -62,14 +66,15 @@ __global__ __launch_bounds__(kThreads) void pool2d_small_kernel(const float *__r
             const int cells = (a_hi > a_lo ? a_hi - a_lo : 0) * (b_hi > b_lo ? b_hi - b_lo : 0);
             acc *= div_valid ? scale / (float)cells : scale;
         }
-        dst[o] = acc;
+        dst[o] = (T)acc;
     }
 }
 
 }  // namespace
 
 // Planes of at most kStage / 4 elements.  *taken = false: not this kernel's case.
-hipError_t launch_pool2d_small(int op, const float *x, float *y, int64_t planes, int H, int W, int Ho, int Wo, int kh,
+template <typename T>
+hipError_t launch_pool2d_small(int op, const T *x, T *y, int64_t planes, int H, int W, int Ho, int Wo, int kh,
                                int kw, int sh, int sw, int ph, int pw, float scale, int div_valid, hipStream_t s,
                                bool *taken)
 {
@@ -78,14 +83,16 @@ hipError_t launch_pool2d_small(int op, const float *x, float *y, int64_t planes,
     if (P < 1 || P > kStage / 4 || Q < 1 || Q > 4095 || Wo > 4095) return hipSuccess;
     // whole planes per workgroup, a multiple of four so that every workgroup's range starts on a
     // 16-byte boundary when x does
-    const int G = (int)(kStage / P) & ~3;
-    if ((int64_t)G * Q >= 65536) return hipSuccess;
+    int G = (int)(kStage / P) & ~3;
+    // ... and at most 4096 outputs: windows that spread a plane (the adjoint of a global average: 1 x 1 -> 7 x 7, 65536
+    // planes) would otherwise leave too few workgroups, or outputs beyond the reach of the quotient below
+    if (G * Q > 4096) G = Q < 1024 ? (int)(4096 / Q) & ~3 : 4;
     const int64_t grid = (planes + G - 1) / G;
     if (grid > 2147483647LL) return hipSuccess;
     *taken = true;
     const unsigned rcp_q = (unsigned)(4294967296ULL / (uint64_t)Q + 1), rcp_wo = (unsigned)(4294967296ULL / (uint64_t)Wo + 1);
 #define SWS_PS(OPV)                                                                                                \
-    hipLaunchKernelGGL((pool2d_small_kernel<OPV>), dim3((unsigned)grid), dim3(kThreads), 0, s, x, y, planes, H, W, Ho, Wo, \
+    hipLaunchKernelGGL((pool2d_small_kernel<OPV, T>), dim3((unsigned)grid), dim3(kThreads), 0, s, x, y, planes, H, W, Ho, Wo, \
                        kh, kw, sh, sw, ph, pw, scale, div_valid, G, rcp_q, rcp_wo)
     switch (op) {
     case SWS_OP_ADD: SWS_PS(SWS_OP_ADD); break;
@@ -95,5 +102,12 @@ hipError_t launch_pool2d_small(int op, const float *x, float *y, int64_t planes,
 #undef SWS_PS
     return hipGetLastError();
 }
+
+template hipError_t launch_pool2d_small<float>(int, const float *, float *, int64_t, int, int, int, int, int, int, int, int, int, int,
+                                               float, int, hipStream_t, bool *);
+template hipError_t launch_pool2d_small<__bf16>(int, const __bf16 *, __bf16 *, int64_t, int, int, int, int, int, int, int, int, int,
+                                                int, float, int, hipStream_t, bool *);
+template hipError_t launch_pool2d_small<_Float16>(int, const _Float16 *, _Float16 *, int64_t, int, int, int, int, int, int, int, int,
+                                                  int, int, float, int, hipStream_t, bool *);
 
 }  // namespace sws

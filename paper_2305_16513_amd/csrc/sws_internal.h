@@ -158,7 +158,9 @@ hipError_t launch_slide1d_reg(int op, const float *x, float *y, int64_t rows, in
 // several rows per wavefront.  hipErrorInvalidValue: not taken (w or grid beyond its reach).
 // 2-D pooling on planes of a few hundred elements: several whole planes per workgroup through LDS.
 // *taken = false: not its case (the caller goes on to the other kernels).
-hipError_t launch_pool2d_small(int op, const float *x, float *y, int64_t planes, int H, int W, int Ho, int Wo, int kh,
+// (T: float, or 16-bit storage with fp32 arithmetic)
+template <typename T>
+hipError_t launch_pool2d_small(int op, const T *x, T *y, int64_t planes, int H, int W, int Ho, int Wo, int kh,
                                int kw, int sh, int sw, int ph, int pw, float scale, int div_valid, hipStream_t s,
                                bool *taken);
 int slide1d_rows_max_w();
@@ -188,6 +190,9 @@ hipError_t launch_avgpool2d_grad(const float *gy, float *gx, int64_t planes, int
 // Row-streaming adjoints of 3 x 3 pooling (pool_grad_rows.hip); *taken = false: shape not covered, nothing launched.
 hipError_t launch_maxpool2d_grad_rows(const float *x, const float *gy, float *gx, int64_t planes, int H, int W, int Ho,
                                       int Wo, int kh, int kw, int sh, int sw, int ph, int pw, hipStream_t s, bool *taken);
+// Large windows (pool_grad_large.hip); *taken = false: not its case, nothing launched.
+hipError_t launch_maxpool2d_grad_large(const float *x, const float *gy, float *gx, int64_t planes, int64_t H, int64_t W, int64_t Ho,
+                                       int64_t Wo, int kh, int kw, int sh, int sw, int ph, int pw, hipStream_t s, bool *taken);
 hipError_t launch_avgpool2d_grad_rows(const float *gy, float *gx, int64_t planes, int H, int W, int Ho, int Wo, int kh,
                                       int kw, int sh, int sw, int ph, int pw, float scale, hipStream_t s, bool *taken);
 hipError_t launch_pool2d_16(int op, int dtype, const void *x, void *y, int64_t planes, int64_t H, int64_t W, int64_t Ho,

@@ -197,3 +197,11 @@ def test_windows_longer_than_a_tile_in_one_pass(B, kind, op, w, length):
             _check(B, op, kind, x, w, scale=1.0 / w, what="%s %s w=%d variant %d" % (kind, op, w, variant))
         finally:
             B.sws_set_option("slide_variant", 0)
+
+
+@pytest.mark.parametrize("kind", ["bf16", "f16"])
+@pytest.mark.parametrize("op", ["add", "max"])
+@pytest.mark.parametrize("geom,shape", [((3, 3, 2, 2, 1, 1), (45, 9, 13, 8)), ((3, 3, 1, 1, 1, 1), (7, 5, 7, 9)), ((7, 7, 1, 1, 0, 0), (33, 3, 7, 7)),
+                                        ((2, 2, 2, 2, 0, 0), (3, 11, 5, 5)), ((9, 9, 1, 1, 8, 8), (3, 3, 1, 1))])
+def test_pool2d_16_on_small_planes(B, kind, op, geom, shape):
+    test_pool2d_16(B, kind, op, geom, shape)
