@@ -426,6 +426,17 @@ hipError_t launch_maxpool2d_grad(const float *x, const float *gy, float *gx, int
                                                         ph, pw, s, &taken);
         if (taken) return e;
     }
+    // Large windows: the band kernel below scans kh * kw cells for every window, pool_grad_large.hip a logarithm of that for
+    // every cell.  us, scan / doubling: 13 x 13 on [371,32,37,19] 945 / 175; 7 x 7 on [2000,32,7,7] 294 / 59; 5 x 5 on
+    // [2000,32,10,9] 279 / 74, [374,32,90,14] 299 / 199, but [100,64,56,56] 306 / 334; 5 x 5 stride 2 on [40,64,112,112] 200 / 358.
+    // (pool2d_variant 256: for every window)
+    const double scan = (double)kh * kw / ((double)sh * sw);         // cells looked at per cell of the plane
+    const bool doubling = scan >= 36.0 || (scan >= 16.0 && H * W <= 2048);
+    if (g_opt.pool2d_variant == 256 || (g_opt.pool2d_variant == 0 && doubling)) {
+        bool taken = false;
+        const hipError_t e = launch_maxpool2d_grad_large(x, gy, gx, planes, H, W, Ho, Wo, kh, kw, sh, sw, ph, pw, s, &taken);
+        if (taken) return e;
+    }
     PgGeom g;
     g.H = (int)H; g.W = (int)W; g.Ho = (int)Ho; g.Wo = (int)Wo; g.kh = kh; g.kw = kw; g.sh = sh; g.sw = sw; g.ph = ph; g.pw = pw;
     g.pwl = pw;
@@ -480,6 +491,11 @@ hipError_t launch_maxpool2d_grad(const float *x, const float *gy, float *gx, int
 #undef SWS_PG
             return hipGetLastError();
         }
+    }
+    if (g_opt.pool2d_variant == 0 && kh * (int64_t)kw > 1) {         // (bands that do not fit LDS: still far ahead of direct evaluation)
+        bool taken = false;
+        const hipError_t e = launch_maxpool2d_grad_large(x, gy, gx, planes, H, W, Ho, Wo, kh, kw, sh, sw, ph, pw, s, &taken);
+        if (taken) return e;
     }
     int64_t grid = (planes * H * W + kThreads - 1) / kThreads;
     if (grid > 1048576) grid = 1048576;

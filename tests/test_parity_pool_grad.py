@@ -281,3 +281,49 @@ def test_row_streaming_avgpool_grad_2x2_stride_2(B, shape, variant):
     finally:
         B.sws_set_option("pool2d_variant", 0)
     assert np.array_equal(gx.astype(np.float64), ref)
+
+
+# windows of 16 cells and more (maximum and position in one double): planes of one wavefront and tiles of larger ones, tiles
+# that end inside a window, strides that divide the window and that do not, windows as large as the plane
+LARGE = [((13, 13, 1, 1, 6, 6), (3, 2, 37, 19)), ((13, 13, 1, 1, 6, 6), (1, 2, 72, 183)), ((5, 5, 1, 1, 2, 2), (2, 3, 90, 14)),
+         ((7, 7, 1, 1, 3, 3), (5, 3, 7, 7)), ((11, 6, 2, 3, 5, 2), (2, 2, 60, 71)), ((8, 8, 8, 8, 0, 0), (2, 2, 64, 50)),
+         ((1, 40, 1, 1, 0, 20), (1, 2, 9, 700)), ((40, 1, 3, 1, 7, 0), (1, 2, 300, 9)), ((20, 20, 1, 1, 0, 0), (2, 1, 20, 20)),
+         ((4, 4, 5, 5, 1, 1), (2, 2, 33, 31)), ((13, 13, 1, 1, 6, 6), (1, 1, 224, 224))]
+
+
+@pytest.mark.parametrize("geom,shape", LARGE)
+def test_large_windows(B, geom, shape):
+    kh, kw, sh, sw, ph, pw = geom
+    ho, wo = (shape[2] + 2 * ph - kh) // sh + 1, (shape[3] + 2 * pw - kw) // sw + 1
+    r = np.random.Generator(np.random.PCG64(5))
+    x = r.standard_normal(shape, dtype=np.float32)
+    gy = r.standard_normal((shape[0], shape[1], ho, wo), dtype=np.float32)
+    a, _ = _check(B, x, gy, geom, "%s %s" % (geom, shape))
+    assert np.array_equal(a, to_host(B.sws_maxpool2d_grad(to_gpu(x), to_gpu(gy), *geom)))            # reproducible
+    # ties of both signs, and zeros: the first cell
+    x, gy = workloads.integer_valued(shape, -1, 1, 6), workloads.integer_valued(gy.shape, -3, 3, 7)
+    for v in (x, x - 5.0, x + 5.0):
+        a, ref = _check(B, v, gy, geom, "ties %s %s" % (geom, shape))
+        assert np.array_equal(a.astype(np.float64), ref)
+    # the extremes of the type
+    x = np.where(x > 0, np.float32(3.4028235e38), np.where(x < 0, np.float32(-3.4028235e38), np.float32(1e-45))).astype(np.float32)
+    a, ref = _check(B, x, gy, geom, "extremes")
+    assert np.array_equal(a.astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("geom", GEOMS)
+def test_every_geometry_on_the_large_window_kernel(B, geom):
+    B.sws_set_option("pool2d_variant", 256)
+    try:
+        test_geometries(B, geom, (2, 3, 37, 53))
+        test_geometries(B, geom, (1, 2, 16, 200))
+    finally:
+        B.sws_set_option("pool2d_variant", 0)
+
+
+@pytest.mark.parametrize("shape", [(70, 7, 7, 7), (3, 5, 13, 11), (2, 3, 24, 40)])
+def test_global_average_adjoint(B, shape):
+    """One window per plane: its gradient goes to every cell (few inputs, many outputs per plane)."""
+    gy = workloads.integer_valued((shape[0], shape[1], 1, 1), -3, 3, 8)
+    gx = to_host(B.sws_avgpool2d_grad(to_gpu(gy), shape[2], shape[3], shape[2], shape[3], 1, 1, 0, 0, B.SWS_DIV_SCALE, 0.5))
+    assert np.array_equal(gx, np.broadcast_to(gy * np.float32(0.5), shape))
