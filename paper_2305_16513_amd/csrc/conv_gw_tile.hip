@@ -17,8 +17,15 @@
 // the current one and split into LDS after them.  The dropped piece products are below 2^-23 of a term.
 //
 // Sums leave as partial blocks in the caller's workspace, lane after lane, and gw_reduce_kernel adds them in a fixed order:
-// the result does not depend on the order in which workgroups end.  (Atomic adds to gw instead, 36864 per workgroup,
-// take 27 us on 64 x 64 channels, 3 x 3; the two passes over 38 MB of partial blocks 13.)
+// the result does not depend on the order in which workgroups end (6 - 13 us; the atomic adds of conv_gw_split.hip, 36864 per
+// workgroup, take 27 us on 64 x 64 channels, 3 x 3).
+//
+// Measured, us, this kernel with its second pass / the kernels without a workspace: [58,32,23,27] -> 128, 5 x 5 75 / 433,
+// [3,128,10,97] -> 472, 3 x 3 46 / 150, [32,256,14,14] -> 256, 3 x 3 75 / 88, [32,64,56,56] -> 64 75 / 74, [16,64,4096] -> 64, k = 3
+// 27 / 31; 40 layers 1.7 x on average.  What it spends its time on ([32,64,56,56]): products 28 us at the clock that the
+// matrix cores hold, splitting 15, second pass and launches 10, the rest waits between the phases of a tile.  Two LDS buffers with
+// tiles of 64 positions, one wavefront of a SIMD splitting while the other multiplies, came out even at nine taps (68 - 70 us there)
+// and behind at one (174 against 127 us on [19,96,87,87] -> 256): not taken.
 #include "sws_internal.h"
 
 namespace sws {

@@ -3,18 +3,21 @@
 // The segment prefix / suffix scheme of the fp32 kernel (the block form of Section 3's
 // Algorithm 2): a wavefront owns a tile of 1024 consecutive inputs cut into segments of
 // S = w - 1 elements, builds the in-segment prefix sums Pre and suffix sums Suf, and every output
-// costs one more (+): y[q] = Suf[q] (+) Pre[q+S].  Elements are 16 bits wide in memory only: a
-// lane's strip element is EIGHT of them (one 128-bit load), widened exactly to fp32 on the way
-// into LDS; the scans and the combine are fp32; the eight results of a strip element are rounded
-// to nearest even once and leave as one 128-bit non-temporal store.  With half the bytes per
-// element the kernel is bound by instruction issue and latency rather than by HBM, hence the wide
-// strips (half as many staging and combine steps per element as the fp32 kernel's four-element
-// strips) and the software prefetch of the next tile.
+// costs one more (+): y[q] = Suf[q] (+) Pre[q+S].  A lane loads and stores EIGHT elements at a time (128 bits) and scans
+// sixteen consecutive ones; scans and the combine are fp32, the results are rounded to nearest even once.  With half the
+// bytes per element the kernel is bound by instruction issue and latency rather than by HBM, so LDS carries as little
+// as it can: the inputs as they are (16 bits), the prefix sums, the 16-bit results — the suffix sums stay in the registers
+// of the lane whose outputs need them.  17 KB of LDS traffic and 4 KB of LDS per 1024 elements; with inputs staged as
+// fp32 and both scans in LDS (26 and 8 KB) [900,30000] w = 64 took 28.9 us against 24.0, [186479,422] w = 39 192
+// against 151, [8192,16384] w = 64 129.1 against 127.9 (more wavefronts per SIMD than the four that 124 registers
+// leave: spills, 365 us).  The next tile is requested before the current one is worked on.
 // Windows up to 33 also have a kernel on shifted loads (eight outputs per lane straight from
 // 128-bit loads, no LDS); it serves the windows up to 9 everywhere, and the others on short rows
 // and small tensors, where 1024-element wave tiles fit badly.
 // Plain rows only (no boundary rules, no chains of windows).
 #include "sws_internal.h"
+
+#include <type_traits>
 
 namespace sws {
 
@@ -38,13 +41,14 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// LDS layout of a wave tile: 256 groups of 4 floats, group g stored at
+// LDS layout of a wave tile of prefix sums: 256 groups of 4 floats, group g stored at
 //     g ^ ((g >> 3) & 3) ^ (((g >> 5) & 1) << 3).
-// Conflict-free for the three 128-bit access shapes used here: chunks (lane l reads groups
-// 4l .. 4l+3), strip halves on the way in and out (lane l touches group 2l, then 2l+1: eight
-// consecutive lanes cover the groups {0,2,4,6,9,11,13,15} mod 16 — eight different bank quads) and
-// the shifted Pre groups.  Only bits 0-3 of g change, so adding 128 groups (a strip) commutes.
+// Conflict-free for chunks (lane l writes groups 4l .. 4l+3) and for the shifted groups 4l + S/4 .. of the combine.
 __device__ __forceinline__ int lds_group(int g) { return g ^ ((g >> 3) & 3) ^ (((g >> 5) & 1) << 3); }
+
+// 16-bit units (eight elements, 16 bytes) of the same memory: lane l touches units 64 j + l on the way in and out and units
+// 2l, 2l + 1 as its chunk; exchanging even and odd units in every other run of sixteen keeps both conflict-free.
+__device__ __forceinline__ int lds_unit(int u) { return u ^ ((u >> 4) & 1); }
 
 // In-segment scan step, the reset folded into arithmetic (one VALU op for ADD, two for MAX / MIN).
 template <int OP> struct SegStep;
@@ -72,6 +76,8 @@ template <typename T> struct Io {
     static __device__ __forceinline__ v8f load8(const T *p) { return widen(load_raw(p)); }
     static __device__ __forceinline__ float load1(const T *p) { return (float)*p; }
     static __device__ __forceinline__ void store1(T *p, float v) { *p = (T)v; }
+    static __device__ __forceinline__ v8 narrow(v8f o) { return __builtin_convertvector(o, v8); }
+    static __device__ __forceinline__ void store_raw(T *p, v8 o) { __builtin_nontemporal_store(o, (v8_u *)p); }
     static __device__ __forceinline__ void store8(T *p, v8f o)
     {
         __builtin_nontemporal_store(__builtin_convertvector(o, v8), (v8_u *)p);
@@ -88,13 +94,13 @@ __global__ __launch_bounds__(kThreads) void slide16_scan_kernel(const T *__restr
     using G = SegStep<OP>;
     using IO = Io<T>;
     constexpr int C = kC, N = kN;
-    __shared__ __attribute__((aligned(16))) float lds[kWavesPerWg * 2 * N];
+    __shared__ __attribute__((aligned(16))) float lds[kWavesPerWg * N];
 
     const int64_t unit = remap ? xcd_unit(n_units) : (int64_t)blockIdx.x;
     if (unit < 0) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float *Bf = lds + wave * 2 * N;                  // Suf
-    float *A = Bf + N;                               // staged inputs, later Pre
+    float *A = lds + wave * N;                       // staged 16-bit inputs, then Pre in fp32, then the 16-bit results
+    typename IO::v8 *const A16 = (typename IO::v8 *)A;       // ... as units of eight 16-bit elements, unit u at lds_unit(u)
     int64_t gt = unit * group + wave;
     int64_t gt_end = (unit + 1) * group;
     if (gt_end > n_tiles) gt_end = n_tiles;
@@ -129,11 +135,11 @@ __global__ __launch_bounds__(kThreads) void slide16_scan_kernel(const T *__restr
     const int sh = S & 3;                           // misalignment of Pre[q+S] against groups
     const int s4 = (S - sh) >> 2;
     const int chunk_pos = 4 * lds_group(4 * lane);  // my chunk: group u of it sits at chunk_pos ^ (4*u)
-    // strip element of lane l: local positions 512*j + 8*l .. +7, i.e. groups 128*j + 2l, 2l+1
-    const int sp0 = 4 * lds_group(2 * lane), sp1 = 4 * lds_group(2 * lane + 1);
-    // the three aligned groups that hold Pre[q+S .. q+S+7+sh] (past the tile: wrapped, discarded lanes only)
-    const int pp0 = 4 * lds_group((2 * lane + s4) & 255), pp1 = 4 * lds_group((2 * lane + s4 + 1) & 255),
-              pp2 = 4 * lds_group((2 * lane + s4 + 2) & 255);
+    // Pre[q+S] for my 16 outputs: the five aligned groups from element 16*lane + S - sh on (past the tile: wrapped,
+    // discarded lanes only)
+    int pp[5];
+#pragma unroll
+    for (int u = 0; u < 5; ++u) pp[u] = 4 * lds_group((4 * lane + s4 + u) & 255);
 
     // The strips of my next tile are requested before the current tile is worked on (raw 16-bit
     // registers, widened when their turn comes): with 2 KB per tile a wavefront would otherwise
@@ -162,11 +168,11 @@ __global__ __launch_bounds__(kThreads) void slide16_scan_kernel(const T *__restr
         const int qlo = t0 < 0 ? -t0 : 0;
         const T *xt = xr + t0;
         T *yt = y + r * (int64_t)lo + t0;
-        // ---- stage: two strips of 512 elements -> LDS as fp32
-        v8f g8[2];
+        // ---- stage: two strips of 512 elements -> LDS as they are
+        typename IO::v8 g8[2];
         if (have0) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) g8[j] = IO::widen(raw0[j]);
+            for (int j = 0; j < 2; ++j) g8[j] = raw0[j];
         } else {
             // a tile at an end of its row: whole strips inside the row are still 128-bit loads,
             // strips wholly outside hold the identity (wave-uniform tests)
@@ -174,15 +180,12 @@ __global__ __launch_bounds__(kThreads) void slide16_scan_kernel(const T *__restr
             for (int j = 0; j < 2; ++j) {
                 const int s0 = t0 + 512 * j;
                 if (s0 >= 0 && s0 + 512 <= len) {
-                    g8[j] = IO::load8(xt + 512 * j + 8 * lane);
-                } else if (s0 >= len || s0 + 512 <= 0) {
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) g8[j][c] = O::id();
+                    g8[j] = IO::load_raw(xt + 512 * j + 8 * lane);
                 } else {
 #pragma unroll
                     for (int c = 0; c < 8; ++c) {
                         const int e = s0 + 8 * lane + c;
-                        g8[j][c] = (e >= 0 && e < len) ? IO::load1(xr + e) : O::id();
+                        g8[j][c] = (e >= 0 && e < len) ? xr[e] : (T)O::id();
                     }
                 }
             }
@@ -190,17 +193,15 @@ __global__ __launch_bounds__(kThreads) void slide16_scan_kernel(const T *__restr
         // ---- my next tile: request it now
         have0 = request(r1, t1, gt + kWavesPerWg, raw0);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            *(v4f *)(A + sp0 + 512 * j) = (v4f){g8[j][0], g8[j][1], g8[j][2], g8[j][3]};
-            *(v4f *)(A + sp1 + 512 * j) = (v4f){g8[j][4], g8[j][5], g8[j][6], g8[j][7]};
-        }
+        for (int j = 0; j < 2; ++j) A16[lds_unit(64 * j + lane)] = g8[j];
         wave_lds_sync();
         // ---- my chunk of C consecutive elements
         float v[C];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const v4f g = *(const v4f *)(A + (chunk_pos ^ (4 * u)));
-            v[4 * u] = g.x; v[4 * u + 1] = g.y; v[4 * u + 2] = g.z; v[4 * u + 3] = g.w;
+        for (int u = 0; u < 2; ++u) {
+            const v8f g = IO::widen(A16[lds_unit(2 * lane + u)]);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) v[8 * u + c] = g[c];
         }
         // ---- pass 1: lane totals (tail: my last segment's part, head: my first segment's part)
         float tail = v[0], head = v[C - 1];
@@ -225,41 +226,53 @@ __global__ __launch_bounds__(kThreads) void slide16_scan_kernel(const T *__restr
         v[0] = G::f(e, m[0], v[0]);
 #pragma unroll
         for (int k = 1; k < C; ++k) v[k] = G::f(v[k - 1], m[k], v[k]);
+        wave_lds_sync();                             // (everybody has read the staged inputs)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < 4; ++u)
             *(v4f *)(A + (chunk_pos ^ (4 * u))) = (v4f){v[4 * u], v[4 * u + 1], v[4 * u + 2], v[4 * u + 3]};
-            *(v4f *)(Bf + (chunk_pos ^ (4 * u))) = (v4f){suf[4 * u], suf[4 * u + 1], suf[4 * u + 2], suf[4 * u + 3]};
+        wave_lds_sync();
+        // ---- combine: y[q] = Suf[q] (+) Pre[q+S] for my own 16 outputs, one rounding
+        {
+            float p[20];
+#pragma unroll
+            for (int u = 0; u < 5; ++u) {
+                const v4f q = *(const v4f *)(A + pp[u]);
+                p[4 * u] = q.x; p[4 * u + 1] = q.y; p[4 * u + 2] = q.z; p[4 * u + 3] = q.w;
+            }
+            v8f o[2];
+            auto add = [&](auto shift) {
+#pragma unroll
+                for (int c = 0; c < C; ++c) o[c / 8][c % 8] = O::f(suf[c], p[c + decltype(shift)::value]);
+            };
+            switch (sh) {                            // wave-uniform
+            case 0: add(std::integral_constant<int, 0>{}); break;
+            case 1: add(std::integral_constant<int, 1>{}); break;
+            case 2: add(std::integral_constant<int, 2>{}); break;
+            default: add(std::integral_constant<int, 3>{}); break;
+            }
+            if (OP == SWS_OP_ADD) {
+                o[0] *= scale;
+                o[1] *= scale;
+            }
+            wave_lds_sync();                         // (everybody has read Pre)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) A16[lds_unit(2 * lane + u)] = IO::narrow(o[u]);
         }
         wave_lds_sync();
-        // ---- combine on strips of eight: y[q] = Suf[q] (+) Pre[q+S], one rounding, 128-bit stores
+        // ---- out: strips of eight results, 128-bit stores
         int lim = lo - t0;
         if (lim > tout) lim = tout;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int q = 512 * j + 8 * lane;
             if (q >= lim) continue;
-            const v4f sa = *(const v4f *)(Bf + sp0 + 512 * j), sb = *(const v4f *)(Bf + sp1 + 512 * j);
-            const v4f p0 = *(const v4f *)(A + ((pp0 + 512 * j) & (N - 1)));
-            const v4f p1 = *(const v4f *)(A + ((pp1 + 512 * j) & (N - 1)));
-            const v4f p2 = *(const v4f *)(A + ((pp2 + 512 * j) & (N - 1)));
-            v8f pn;
-            switch (sh) {                            // wave-uniform
-            case 0: pn = (v8f){p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w}; break;
-            case 1: pn = (v8f){p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w, p2.x}; break;
-            case 2: pn = (v8f){p0.z, p0.w, p1.x, p1.y, p1.z, p1.w, p2.x, p2.y}; break;
-            default: pn = (v8f){p0.w, p1.x, p1.y, p1.z, p1.w, p2.x, p2.y, p2.z}; break;
-            }
-            const v8f sv = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, sb.w};
-            v8f o;
-#pragma unroll
-            for (int c = 0; c < 8; ++c) o[c] = O::f(sv[c], pn[c]);
-            if (OP == SWS_OP_ADD) o *= scale;
+            const typename IO::v8 o = A16[lds_unit(64 * j + lane)];
             if (q >= qlo && q + 8 <= lim) {
-                IO::store8(yt + q, o);
+                IO::store_raw(yt + q, o);
             } else {
 #pragma unroll
                 for (int c = 0; c < 8; ++c)
-                    if (q + c >= qlo && q + c < lim) IO::store1(yt + q + c, o[c]);
+                    if (q + c >= qlo && q + c < lim) yt[q + c] = o[c];
             }
         }
         wave_lds_sync();                             // the next tile overwrites A
