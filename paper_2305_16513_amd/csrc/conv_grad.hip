@@ -707,6 +707,15 @@ hipError_t launch_conv2d_grad_input(const float *gy, const float *wgt, float *gx
     return hipGetLastError();
 }
 
+// Few channels and up to three taps: gw is a few thousand long sums, and the rounding of the bf16 matrix instruction shows in
+// them — error against 64 bits, tiled split-operand / fp32 kernels: [16,24,5574] -> 32, k = 1 6.2e-7 / 3.6e-7, [8,32,3564] -> 20, k = 3
+// 4.0e-7 / 2.5e-7, [32,48,4376] -> 32, k = 3 5.0e-7 / 3.5e-7 — at 0.96 - 1.3 times the speed: these layers keep their kernels.
+// (Over 90 random layers the error of a layer's three results is otherwise below the fp32 kernels'.)
+static bool few_long_sums(int64_t Cin, int64_t Cout, int64_t taps)
+{
+    return taps <= 3 && (Cin < Cout ? Cin : Cout) <= 48 && (Cin < Cout ? Cout : Cin) <= 64;
+}
+
 hipError_t launch_conv2d_grad_weight(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H,
                                      int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
                                      int32_t sw, int32_t ph, int32_t pw, hipStream_t s, Workspace ws)
@@ -717,7 +726,7 @@ hipError_t launch_conv2d_grad_weight(const float *x, const float *gy, float *gw,
     // 16-byte groups stays on the kernel that reads its operands straight from memory (its tile here would be four
     // fifths halo): [32,128,56,56] -> 128 93 us there, 97 here; at stride 1 [32,256,14,14] -> 256 88 / 75, [3,128,10,97] -> 472 150 / 46.
     const bool direct = kh == 3 && kw == 3 && sh == 2 && sw == 2 && Cin % 32 == 0 && Cout % 32 == 0 && W % 4 == 0 && Wo % 4 == 0;
-    if (ws.p && N > 0 && ((g_opt.conv2d_variant == 0 && !direct) || g_opt.conv2d_variant == 100)) {
+    if (ws.p && N > 0 && ((g_opt.conv2d_variant == 0 && !direct && !few_long_sums(Cin, Cout, (int64_t)kh * kw)) || g_opt.conv2d_variant == 100)) {
         bool taken = false;
         const bool flat = kh == 1 && kw == 1 && sh == 1 && sw == 1 && ph == 0 && pw == 0;      // does not see the rows
         const hipError_t e = flat ? launch_conv_gw_tile(x, gy, gw, N, Cin, 1, H * W, Cout, 1, Ho * Wo, 1, 1, 1, 1, 0, 0, 1, ws, s, &taken)
@@ -803,7 +812,8 @@ hipError_t launch_conv1d_grad_weight(const float *x, const float *gy, float *gw,
     const int64_t n_gw = Cout * cig * k;
     const int variant = g_opt.conv1d_variant;        // 1 forces direct evaluation (A/B and tests)
     if (n_gw > 2147483647LL) return kNotTaken;
-    if (ws.p && B > 0 && groups == 1 && Cin >= 2 && variant == 0 && (g_opt.conv2d_variant == 0 || g_opt.conv2d_variant == 100)) {
+    if (ws.p && B > 0 && groups == 1 && Cin >= 2 && variant == 0 &&
+        ((g_opt.conv2d_variant == 0 && !few_long_sums(Cin, Cout, k)) || g_opt.conv2d_variant == 100)) {
         bool taken = false;
         const hipError_t e = launch_conv_gw_tile(x, gy, gw, B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad, dilation, ws, s, &taken);
         if (taken || e != hipSuccess) return e;
