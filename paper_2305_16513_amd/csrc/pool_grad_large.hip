@@ -57,14 +57,14 @@ __global__ __launch_bounds__(64 * NW) void maxpool_grad_large_kernel(const float
     const int nw = w1 - w0 + 1, nv = v1 - v0 + 1;     // may be 0 or less: no window covers the tile
     const int xr0 = w0 * g.sh - g.ph, xc0 = v0 * g.sw - g.pw;
     const int XR = nw > 0 ? (nw - 1) * g.sh + g.kh : 0, XC = nv > 0 ? (nv - 1) * g.sw + g.kw : 0;
+    auto wave_sync = [&]() {                          // what my wavefront's other lanes wrote to LDS
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
     auto sync = [&]() {
-        if constexpr (NW == 1) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        } else {
-            __syncthreads();
-        }
+        if constexpr (NW == 1) wave_sync();
+        else __syncthreads();
     };
 
     for (int e = tid; e < NW * g.TB * g.TC; e += T) acc[e] = 0.0f;
@@ -96,8 +96,24 @@ __global__ __launch_bounds__(64 * NW) void maxpool_grad_large_kernel(const float
         // ---- kw columns: row by row, in place
         {
             const int rpw = (XR + NW - 1) / NW, i0 = wave * rpw, i1 = i0 + rpw < XR ? i0 + rpw : XR;
+            // A step reads what other lanes left in the step before (a row belongs to one wavefront, which waits for itself only),
+            // and inside a step everything is read before anything behind it is written.  (Past the end of a wavefront's rows
+            // lie another's, or padding: what is read there reaches columns that start no window.)
+            const int end = i1 * g.P;
             auto pass = [&](int m) {
-                for (int e = i0 * g.P + lane; e < i1 * g.P; e += 64) key[e] = __builtin_fmax(key[e], key[e + m]);
+                for (int e0 = i0 * g.P + lane; e0 < end; e0 += 256) {
+                    double v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int e = e0 + 64 * u < end ? e0 + 64 * u : e0;
+                        v[u] = __builtin_fmax(key[e], key[e + m]);
+                    }
+                    wave_sync();
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (e0 + 64 * u < end) key[e0 + 64 * u] = v[u];
+                    wave_sync();
+                }
             };
             int m = 1;
             for (; 2 * m <= g.kw; m *= 2) pass(m);
@@ -110,9 +126,23 @@ __global__ __launch_bounds__(64 * NW) void maxpool_grad_large_kernel(const float
             for (int b = b0; b < b1; b += 64) {
                 const int cw = b1 - b < 64 ? b1 - b : 64, rb = 64 / cw;
                 const int rr = fdiv(lane, 1.0f / (float)cw), col = (b + lane - rr * cw) * g.sw;
+                const int top = rr < rb ? XR : 0;     // (64 % cw lanes stand by)
                 auto pass = [&](int m) {
-                    for (int i = rr; i + m < XR; i += rb)
-                        if (rr < rb) key[i * g.P + col] = __builtin_fmax(key[i * g.P + col], key[(i + m) * g.P + col]);
+                    for (int i0 = 0; i0 + m < XR; i0 += 4 * rb) {
+                        double v[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int i = i0 + u * rb + rr, r = i + m < top ? i : 0;
+                            v[u] = __builtin_fmax(key[r * g.P + col], key[(r + m) * g.P + col]);
+                        }
+                        wave_sync();
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int i = i0 + u * rb + rr;
+                            if (i + m < top) key[i * g.P + col] = v[u];
+                        }
+                        wave_sync();
+                    }
                 };
                 int m = 1;
                 for (; 2 * m <= g.kh; m *= 2) pass(m);

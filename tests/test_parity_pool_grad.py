@@ -327,3 +327,21 @@ def test_global_average_adjoint(B, shape):
     gy = workloads.integer_valued((shape[0], shape[1], 1, 1), -3, 3, 8)
     gx = to_host(B.sws_avgpool2d_grad(to_gpu(gy), shape[2], shape[3], shape[2], shape[3], 1, 1, 0, 0, B.SWS_DIV_SCALE, 0.5))
     assert np.array_equal(gx, np.broadcast_to(gy * np.float32(0.5), shape))
+
+
+# every number of doubling steps, with and without a last overlapping one, along rows and along columns: what a lane reads in a step
+# other lanes have written in the step before
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 33])
+@pytest.mark.parametrize("shape", [(3, 5, 41, 43), (1, 3, 90, 150)])          # one wavefront per plane, four per tile
+def test_doubling_steps_of_large_windows(B, k, shape):
+    r = np.random.Generator(np.random.PCG64(k))
+    B.sws_set_option("pool2d_variant", 256)
+    try:
+        for kh, kw in ((k, 1), (1, k), (k, k), (k, 40 - k)):
+            geom = (kh, kw, 1, 1, kh // 2, kw // 2)
+            x = r.standard_normal(shape, dtype=np.float32)
+            gy = workloads.integer_valued((shape[0], shape[1], shape[2] + 2 * (kh // 2) - kh + 1, shape[3] + 2 * (kw // 2) - kw + 1), -3, 3, k)
+            a, ref = _check(B, x, gy, geom, "%s %s" % (geom, shape))
+            assert np.array_equal(a.astype(np.float64), ref)
+    finally:
+        B.sws_set_option("pool2d_variant", 0)
