@@ -29,8 +29,9 @@ __device__ __forceinline__ int fdiv(int x, float inv_d) { return (int)(((float)x
 
 constexpr unsigned kPosMask = (1u << 27) - 1;         // row << 12 | column inside the tile
 
-// NW wavefronts per tile
-template <int NW>
+// NW wavefronts per tile; U runs of 64 keys in flight: four, but one where the staged tile is no more than four of them
+// (7 x 7 on [2000,32,7,7] 56 us against 61; 13 x 13 on [371,32,37,19] 174 against 157).
+template <int NW, int U>
 __global__ __launch_bounds__(64 * NW) void maxpool_grad_large_kernel(const float *__restrict__ x, const float *__restrict__ gy,
                                                                      float *__restrict__ gx, PgLarge g, int64_t n_units)
 {
@@ -101,16 +102,16 @@ __global__ __launch_bounds__(64 * NW) void maxpool_grad_large_kernel(const float
             // lie another's, or padding: what is read there reaches columns that start no window.)
             const int end = i1 * g.P;
             auto pass = [&](int m) {
-                for (int e0 = i0 * g.P + lane; e0 < end; e0 += 256) {
-                    double v[4];
+                for (int e0 = i0 * g.P + lane; e0 < end; e0 += 64 * U) {
+                    double v[U];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
+                    for (int u = 0; u < U; ++u) {
                         const int e = e0 + 64 * u < end ? e0 + 64 * u : e0;
                         v[u] = __builtin_fmax(key[e], key[e + m]);
                     }
                     wave_sync();
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
+                    for (int u = 0; u < U; ++u)
                         if (e0 + 64 * u < end) key[e0 + 64 * u] = v[u];
                     wave_sync();
                 }
@@ -128,16 +129,16 @@ __global__ __launch_bounds__(64 * NW) void maxpool_grad_large_kernel(const float
                 const int rr = fdiv(lane, 1.0f / (float)cw), col = (b + lane - rr * cw) * g.sw;
                 const int top = rr < rb ? XR : 0;     // (64 % cw lanes stand by)
                 auto pass = [&](int m) {
-                    for (int i0 = 0; i0 + m < XR; i0 += 4 * rb) {
-                        double v[4];
+                    for (int i0 = 0; i0 + m < XR; i0 += U * rb) {
+                        double v[U];
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) {
+                        for (int u = 0; u < U; ++u) {
                             const int i = i0 + u * rb + rr, r = i + m < top ? i : 0;
                             v[u] = __builtin_fmax(key[r * g.P + col], key[(r + m) * g.P + col]);
                         }
                         wave_sync();
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) {
+                        for (int u = 0; u < U; ++u) {
                             const int i = i0 + u * rb + rr;
                             if (i + m < top) key[i * g.P + col] = v[u];
                         }
@@ -187,46 +188,47 @@ hipError_t launch_maxpool2d_grad_large(const float *x, const float *gy, float *g
     // four per tile.  Tiles: the fewest staged cells per cell with at least two workgroups per compute unit.
     const bool wave = H * W <= 2048;
     const int NW = wave ? 1 : 4;
-    size_t lds = 0;
-    bool found = false;
-    double best = 0;
-    auto seen = [](int t, int k, int st, int64_t n, int64_t no) {       // cells that the windows over t cells of a row of n see
-        int64_t win = (t + k - 2) / st + 1;
-        win = win < no ? win : no;
-        (void)n;
-        return (int)((win - 1) * st + k);
+    // (this runs on every call: only the tile heights and widths that differ are tried, [224,224] 29 x 29 of 64 x 64 cuts)
+    struct Cut { int parts, t, span; };               // parts of an axis, cells of one, cells that its windows see
+    auto cuts = [](Cut *c, int n, int no, int k, int st) {
+        int m = 0;
+        for (int parts = 1; parts <= 64 && parts <= n; ++parts) {
+            const int t = (int)((unsigned)(n + parts - 1) / (unsigned)parts);
+            if (t > 1024 || (m > 0 && t == c[m - 1].t)) continue;
+            int win = (int)((unsigned)(t + k - 2) / (unsigned)st) + 1;
+            win = win < no ? win : no;
+            if ((win - 1) * st + k < 4096) c[m++] = {parts, t, (win - 1) * st + k};
+        }
+        return m;
     };
-    for (int bands = 1; bands <= 64 && bands <= H; ++bands)
-        for (int cols = 1; cols <= 64 && cols <= W; ++cols) {
-            const int TB = (int)((H + bands - 1) / bands), TC = (int)((W + cols - 1) / cols);
-            if (TB > 1024 || TC > 1024) continue;
-            const int XR = seen(TB, kh, sh, H, Ho), P = seen(TC, kw, sw, W, Wo);
-            const int64_t D = (int64_t)XR * P + kw + 64;
-            const size_t need = (size_t)D * 8 + (size_t)NW * TB * TC * 4;
-            if (XR >= 4096 || P >= 4096 || need > 78 * 1024) continue;
-            const double cost = (double)((int64_t)XR * P + 512) * bands * cols;
-            if (!found || cost < best) {
-                found = true;
+    Cut rows[64], cols[64];
+    const int nr = cuts(rows, (int)H, (int)(Ho < (1 << 20) ? Ho : 1 << 20), kh, sh), nc = cuts(cols, (int)W, (int)(Wo < (1 << 20) ? Wo : 1 << 20), kw, sw);
+    int need = 0;
+    int64_t best = 0;
+    for (int i = 0; i < nr; ++i)
+        for (int j = 0; j < nc; ++j) {
+            const int cells = rows[i].span * cols[j].span;
+            const int D = cells + kw + 64, bytes = D * 8 + NW * rows[i].t * cols[j].t * 4;
+            if (cells > 10240 || bytes > 78 * 1024) continue;
+            const int64_t cost = (int64_t)(cells + 512) * (rows[i].parts * cols[j].parts);
+            if (need == 0 || cost < best) {
+                need = bytes;
                 best = cost;
-                lds = need;
-                g.TB = TB; g.TC = TC; g.nb = (int)((H + TB - 1) / TB); g.nc = (int)((W + TC - 1) / TC); g.P = P; g.D = (int)((D + 1) / 2 * 2);
+                g.TB = rows[i].t; g.TC = cols[j].t; g.nb = rows[i].parts; g.nc = cols[j].parts; g.P = cols[j].span; g.D = (D + 1) / 2 * 2;
             }
         }
-    if (!found) return hipSuccess;
-    lds += 16;
+    if (need == 0) return hipSuccess;
+    const size_t lds = (size_t)need + 16;
     const int64_t units = planes * g.nb * g.nc;
     if (units > 2147483647LL) return hipSuccess;
     g.inv_P = 1.0f / g.P; g.inv_TC = 1.0f / g.TC;
     *taken = true;
+    const auto k = !wave ? maxpool_grad_large_kernel<4, 4> : g.D <= 256 + kw + 64 ? maxpool_grad_large_kernel<1, 1> : maxpool_grad_large_kernel<1, 4>;
     if (lds > 64 * 1024) {
-        const hipError_t e = wave ? hipFuncSetAttribute((const void *)maxpool_grad_large_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024)
-                                  : hipFuncSetAttribute((const void *)maxpool_grad_large_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+        const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
         if (e != hipSuccess) return e;
     }
-    if (wave)
-        hipLaunchKernelGGL(maxpool_grad_large_kernel<1>, dim3((unsigned)units), dim3(64), lds, s, x, gy, gx, g, units);
-    else
-        hipLaunchKernelGGL(maxpool_grad_large_kernel<4>, dim3((unsigned)units), dim3(256), lds, s, x, gy, gx, g, units);
+    hipLaunchKernelGGL(k, dim3((unsigned)units), dim3(64 * NW), lds, s, x, gy, gx, g, units);
     return hipGetLastError();
 }
 

@@ -292,3 +292,26 @@ def test_grad_weight_workspace_and_argument_checks(L):
     assert L.sws_conv_grad_weight_workspace(64, 64, 9, 9) == 0 and L.sws_conv_grad_weight_workspace(64, 0, 3, 3) == 0
     assert L.sws_conv2d_grad_weight_ws(one, one, nul, 1, 3, 10, 10, 4, 3, 3, 1, 1, 1, 1, one, 64, nul) == 1
     assert L.sws_conv1d_grad_weight_ws(nul, one, one, 1, 3, 10, 4, 3, 1, 0, 1, 1, one, 64, nul) == 1
+
+
+def test_planning_of_a_launch_takes_microseconds(L):
+    """Host time of an entry whose launcher looks for the best tiling, beside one that does not: without a GPU the launch itself
+    is refused, so what is timed is the checks and the plan."""
+    import time
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("made-up pointers")
+    one, nul = ctypes.c_void_p(4096), ctypes.c_void_p(0)
+
+    def us(hw, k):
+        best = 1e9
+        for _ in range(9):
+            t = time.perf_counter()
+            for _ in range(60):
+                assert L.sws_maxpool2d_grad(one, one, one, 1, 1, hw, hw, k, k, 1, 1, k // 2, k // 2, nul) != 0
+            best = min(best, (time.perf_counter() - t) / 60 * 1e6)
+        return best
+
+    plain = us(112, 3)
+    for hw, k in ((112, 7), (224, 13)):
+        assert us(hw, k) < plain + 15, (hw, k, plain)       # 1 - 2 us; every pair of 64 x 64 cuts: 45 us
