@@ -383,10 +383,17 @@ sws_status sws_conv2d_padded_ws(const float *x, const float *wgt, float *y, int6
                              int32_t pad_top, int32_t pad_left, int32_t pad_bottom, int32_t pad_right,
                              sws_pad_mode mode, void *workspace, int64_t workspace_bytes, sws_stream_t stream);
 
-/* The adjoints with respect to the weights with memory lent in the same way: with sws_conv_grad_weight_workspace() bytes of
- * it, dense layers (groups = 1, at least two input channels, up to 64 taps, strides 1 and 2) leave their partial sums there and a
- * second kernel adds them in a fixed order; a product is six exact products of bf16 pieces (inputs must be finite). 1-D
- * layers: kh = 1, kw = k. */
+/* The adjoints with respect to the weights with memory lent in the same way: dense layers (groups = 1, at least two input
+ * channels, up to 64 taps, strides 1 and 2) leave their partial sums there and a second kernel adds them in a fixed order; a
+ * product is six exact products of bf16 pieces (inputs must be finite).
+ * sws_conv1d_grad_weight_workspace(), sws_conv2d_grad_weight_workspace(): the bytes that the call with the same arguments uses, 0 if
+ * none (or if the arguments are invalid).  With less the call uses what there is, or none.
+ * sws_conv_grad_weight_workspace(Cin, Cout, kh, kw): enough for most layers of these channels and taps whatever their planes (1-D
+ * layers: kh = 1, kw = k). */
+int64_t sws_conv1d_grad_weight_workspace(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int32_t k, int32_t stride,
+                                         int32_t pad, int32_t dilation, int32_t groups);
+int64_t sws_conv2d_grad_weight_workspace(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int32_t kh,
+                                         int32_t kw, int32_t sh, int32_t sw, int32_t ph, int32_t pw);
 int64_t sws_conv_grad_weight_workspace(int64_t Cin, int64_t Cout, int32_t kh, int32_t kw);
 sws_status sws_conv1d_grad_weight_ws(const float *x, const float *gy, float *gw, int64_t B,
                                   int64_t Cin, int64_t L, int64_t Cout, int32_t k, int32_t stride,

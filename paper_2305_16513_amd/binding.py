@@ -7,7 +7,6 @@ to the C ABI.  There is no fallback: a missing library or a non-zero status rais
 """
 import ctypes
 import functools
-import math
 import os
 
 import torch
@@ -21,7 +20,7 @@ _lib = None
 
 _i64, _i32, _f32, _vp = ctypes.c_int64, ctypes.c_int32, ctypes.c_float, ctypes.c_void_p
 
-EXPORTS = ("sws_slide1d", "sws_slide1d_16", "sws_slide1d_padded", "sws_slide1d_pair", "sws_pool2d", "sws_maxpool2d_grad", "sws_avgpool2d_grad", "sws_pool2d_16", "sws_pool2d_ex", "sws_pool2d_padded", "sws_conv1d", "sws_conv1d_padded", "sws_conv1d_16", "sws_conv1d_grad_input", "sws_conv1d_grad_weight", "sws_conv2d", "sws_conv2d_padded", "sws_conv2d_grad_input", "sws_conv2d_grad_weight", "sws_conv_workspace", "sws_conv1d_ws", "sws_conv1d_grad_input_ws", "sws_conv2d_ws", "sws_conv2d_grad_input_ws", "sws_conv1d_padded_ws", "sws_conv2d_padded_ws", "sws_conv_grad_weight_workspace", "sws_conv1d_grad_weight_ws", "sws_conv2d_grad_weight_ws", "sws_copy", "sws_out_len",
+EXPORTS = ("sws_slide1d", "sws_slide1d_16", "sws_slide1d_padded", "sws_slide1d_pair", "sws_pool2d", "sws_maxpool2d_grad", "sws_avgpool2d_grad", "sws_pool2d_16", "sws_pool2d_ex", "sws_pool2d_padded", "sws_conv1d", "sws_conv1d_padded", "sws_conv1d_16", "sws_conv1d_grad_input", "sws_conv1d_grad_weight", "sws_conv2d", "sws_conv2d_padded", "sws_conv2d_grad_input", "sws_conv2d_grad_weight", "sws_conv_workspace", "sws_conv1d_ws", "sws_conv1d_grad_input_ws", "sws_conv2d_ws", "sws_conv2d_grad_input_ws", "sws_conv1d_padded_ws", "sws_conv2d_padded_ws", "sws_conv_grad_weight_workspace", "sws_conv1d_grad_weight_workspace", "sws_conv2d_grad_weight_workspace", "sws_conv1d_grad_weight_ws", "sws_conv2d_grad_weight_ws", "sws_copy", "sws_out_len",
            "sws_status_string", "sws_set_option", "sws_version")
 
 
@@ -85,6 +84,10 @@ def lib():
             f.argtypes = [_vp, _vp, _vp, _i64, _i64, _i64, _i64, _i64, _i32, _i32, _i32, _i32, _i32, _i32, _vp]
         L.sws_conv_grad_weight_workspace.restype = _i64
         L.sws_conv_grad_weight_workspace.argtypes = [_i64, _i64, _i32, _i32]
+        L.sws_conv1d_grad_weight_workspace.restype = _i64
+        L.sws_conv1d_grad_weight_workspace.argtypes = [_i64, _i64, _i64, _i64, _i32, _i32, _i32, _i32, _i32]
+        L.sws_conv2d_grad_weight_workspace.restype = _i64
+        L.sws_conv2d_grad_weight_workspace.argtypes = [_i64, _i64, _i64, _i64, _i64, _i32, _i32, _i32, _i32, _i32, _i32]
         L.sws_conv_workspace.restype = _i64
         L.sws_conv_workspace.argtypes = [_i64, _i64, _i64, _i64]
         for f, plain in ((L.sws_conv1d_ws, L.sws_conv1d), (L.sws_conv1d_grad_input_ws, L.sws_conv1d_grad_input),
@@ -120,6 +123,8 @@ def sws_out_len(length, w, stride=1, pad=0, dilation=1):
 
 def sws_set_option(key, value):
     rc = lib().sws_set_option(key.encode(), int(value))
+    for f in (_workspace_bytes, _conv1d_gw_bytes, _conv2d_gw_bytes):     # an option may take a layer to another kernel
+        f.cache_clear()
     if rc:
         raise SwsError(rc, "sws_set_option(%r)" % key)
 
@@ -151,20 +156,28 @@ def _workspace_bytes(cin, cout, taps, positions):
 
 
 @functools.lru_cache(maxsize=1024)
-def _grad_weight_bytes(cin, cout, kh, kw):
-    return lib().sws_conv_grad_weight_workspace(cin, cout, kh, kw)
+def _conv1d_gw_bytes(*layer):
+    return lib().sws_conv1d_grad_weight_workspace(*layer)
+
+
+@functools.lru_cache(maxsize=1024)
+def _conv2d_gw_bytes(*layer):
+    return lib().sws_conv2d_grad_weight_workspace(*layer)
 
 
 def _scratch(n, like, stream):
     """n bytes (a multiple of 4) of device memory beside the fp32 tensor `like`, allocated on the stream that the call runs on:
-    (tensor, address, bytes)."""
+    (tensor, address, bytes).  None where that much is not to be had: the call then runs on the kernels that need none."""
     if n == 0:
         return None, None, 0
-    if stream is None:
-        t = like.new_empty(n // 4)
-    else:
-        with torch.cuda.stream(stream):
+    try:
+        if stream is None:
             t = like.new_empty(n // 4)
+        else:
+            with torch.cuda.stream(stream):
+                t = like.new_empty(n // 4)
+    except torch.cuda.OutOfMemoryError:
+        return None, None, 0
     return t, t.data_ptr(), n
 
 
@@ -365,7 +378,7 @@ def sws_conv1d_padded(x, wgt, stride=1, pad_left=0, pad_right=0, dilation=1, gro
     if lo < 1 or cig * groups != cin or pad_left < 0 or pad_right < 0:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d_padded")
     y = _out(y, (b, cout, lo), x)
-    keep, ws, ws_bytes = _workspace(wgt, cig, cout, k, b * lo, stream) if groups == 1 else (None, None, 0)
+    keep, ws, ws_bytes = _workspace(wgt, cig, cout, k, b * lo, stream) if groups == 1 and stride <= 2 and mode == 0 and pad_left == pad_right else (None, None, 0)
     _check(lib().sws_conv1d_padded_ws(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), b, cin, length, cout, k, stride, pad_left,
                                    pad_right, dilation, groups, mode, ws, ws_bytes, _stream(stream)), "sws_conv1d_padded")
     return y
@@ -383,7 +396,7 @@ def sws_conv1d(x, wgt, stride=1, pad=0, dilation=1, groups=1, y=None, stream=Non
     if lo < 1:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d")
     y = _out(y, (b, cout, lo), x)
-    keep, ws, ws_bytes = _workspace(wgt, cig, cout, k, b * lo, stream) if groups == 1 else (None, None, 0)
+    keep, ws, ws_bytes = _workspace(wgt, cig, cout, k, b * lo, stream) if groups == 1 and stride <= 2 else (None, None, 0)
     _check(lib().sws_conv1d_ws(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), b, cin, length, cout, k, stride,
                             pad, dilation, groups, ws, ws_bytes, _stream(stream)), "sws_conv1d")
     return y
@@ -424,7 +437,7 @@ def sws_conv1d_grad_input(gy, wgt, length, stride=1, pad=0, dilation=1, groups=1
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d_grad_input")
     cin = cig * groups
     gx = _out(gx, (b, cin, length), gy, "gx")
-    keep, ws, ws_bytes = _workspace(wgt, cout, cig, k, b * lo, stream) if groups == 1 else (None, None, 0)
+    keep, ws, ws_bytes = _workspace(wgt, cout, cig, k, b * lo, stream) if groups == 1 and stride <= 2 else (None, None, 0)
     _check(lib().sws_conv1d_grad_input_ws(gy.data_ptr(), wgt.data_ptr(), gx.data_ptr(), b, cin, length, cout, k, stride,
                                        pad, dilation, groups, ws, ws_bytes, _stream(stream)), "sws_conv1d_grad_input")
     return gx
@@ -439,7 +452,7 @@ def sws_conv1d_grad_weight(x, gy, k, stride=1, pad=0, dilation=1, groups=1, gw=N
     if b2 != b or cin % groups or lo != sws_out_len(length, k, stride, pad, dilation):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d_grad_weight")
     gw = _out(gw, (cout, cin // groups, k), x, "gw")
-    keep, ws, ws_bytes = _scratch(_grad_weight_bytes(cin, cout, 1, k) if groups == 1 and cin > 1 else 0, x, stream)
+    keep, ws, ws_bytes = _scratch(_conv1d_gw_bytes(b, cin, length, cout, k, stride, pad, dilation, groups), x, stream)
     _check(lib().sws_conv1d_grad_weight_ws(x.data_ptr(), gy.data_ptr(), gw.data_ptr(), b, cin, length, cout, k, stride,
                                         pad, dilation, groups, ws, ws_bytes, _stream(stream)), "sws_conv1d_grad_weight")
     return gw
@@ -457,7 +470,8 @@ def sws_conv2d_padded(x, wgt, sh=1, sw=1, pads=(0, 0, 0, 0), mode=0, y=None, str
     if cin2 != cin or ho < 1 or wo < 1 or min(pads) < 0:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d_padded")
     y = _out(y, (n, cout, ho, wo), x)
-    keep, ws, ws_bytes = _workspace(wgt, cin, cout, kh * kw, n * ho * wo, stream)
+    even = (pt, pl) == (pb, pr)
+    keep, ws, ws_bytes = _workspace(wgt, cin, cout, kh * kw, n * ho * wo, stream) if sh <= 2 and sw <= 2 and even else (None, None, 0)
     _check(lib().sws_conv2d_padded_ws(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), n, cin, h, wd, cout, kh, kw, sh, sw,
                                    pt, pl, pb, pr, mode, ws, ws_bytes, _stream(stream)), "sws_conv2d_padded")
     return y
@@ -475,7 +489,7 @@ def sws_conv2d(x, wgt, sh=1, sw=1, ph=0, pw=0, y=None, stream=None):
     if ho < 1 or wo < 1:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d")
     y = _out(y, (n, cout, ho, wo), x)
-    keep, ws, ws_bytes = _workspace(wgt, cin, cout, kh * kw, n * ho * wo, stream)
+    keep, ws, ws_bytes = _workspace(wgt, cin, cout, kh * kw, n * ho * wo, stream) if sh <= 2 and sw <= 2 else (None, None, 0)
     _check(lib().sws_conv2d_ws(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), n, cin, h, wd, cout, kh, kw,
                             sh, sw, ph, pw, ws, ws_bytes, _stream(stream)), "sws_conv2d")
     return y
@@ -490,7 +504,7 @@ def sws_conv2d_grad_input(gy, wgt, h, wd, sh=1, sw=1, ph=0, pw=0, gx=None, strea
     if cout2 != cout or ho != sws_out_len(h, kh, sh, ph) or wo != sws_out_len(wd, kw, sw, pw):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d_grad_input")
     gx = _out(gx, (n, cin, h, wd), gy, "gx")
-    keep, ws, ws_bytes = _workspace(wgt, cout, cin, kh * kw, n * ho * wo, stream)
+    keep, ws, ws_bytes = _workspace(wgt, cout, cin, kh * kw, n * ho * wo, stream) if sh <= 2 and sw <= 2 else (None, None, 0)
     _check(lib().sws_conv2d_grad_input_ws(gy.data_ptr(), wgt.data_ptr(), gx.data_ptr(), n, cin, h, wd, cout, kh, kw,
                                        sh, sw, ph, pw, ws, ws_bytes, _stream(stream)), "sws_conv2d_grad_input")
     return gx
@@ -505,7 +519,7 @@ def sws_conv2d_grad_weight(x, gy, kh, kw, sh=1, sw=1, ph=0, pw=0, gw=None, strea
     if n2 != n or ho != sws_out_len(h, kh, sh, ph) or wo != sws_out_len(wd, kw, sw, pw):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d_grad_weight")
     gw = _out(gw, (cout, cin, kh, kw), x, "gw")
-    keep, ws, ws_bytes = _scratch(_grad_weight_bytes(cin, cout, kh, kw), x, stream)
+    keep, ws, ws_bytes = _scratch(_conv2d_gw_bytes(n, cin, h, wd, cout, kh, kw, sh, sw, ph, pw), x, stream)
     _check(lib().sws_conv2d_grad_weight_ws(x.data_ptr(), gy.data_ptr(), gw.data_ptr(), n, cin, h, wd, cout, kh, kw,
                                         sh, sw, ph, pw, ws, ws_bytes, _stream(stream)), "sws_conv2d_grad_weight")
     return gw

@@ -707,6 +707,14 @@ hipError_t launch_conv2d_grad_input(const float *gy, const float *wgt, float *gx
     return hipGetLastError();
 }
 
+// A layer as the tiled kernel sees it; a 1 x 1 kernel does not see the rows.
+static GwLayer gw_layer(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int kh, int kw, int sh, int sw,
+                        int ph, int pw, int dil)
+{
+    if (kh == 1 && kw == 1 && sh == 1 && sw == 1 && ph == 0 && pw == 0) return {N, Cin, 1, H * W, Cout, 1, Ho * Wo, 1, 1, 1, 1, 0, 0, 1};
+    return {N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw, dil};
+}
+
 // Few channels and up to three taps: gw is a few thousand long sums, and the rounding of the bf16 matrix instruction shows in
 // them — error against 64 bits, tiled split-operand / fp32 kernels: [16,24,5574] -> 32, k = 1 6.2e-7 / 3.6e-7, [8,32,3564] -> 20, k = 3
 // 4.0e-7 / 2.5e-7, [32,48,4376] -> 32, k = 3 5.0e-7 / 3.5e-7 — at 0.96 - 1.3 times the speed: these layers keep their kernels.
@@ -716,22 +724,44 @@ static bool few_long_sums(int64_t Cin, int64_t Cout, int64_t taps)
     return taps <= 3 && (Cin < Cout ? Cin : Cout) <= 48 && (Cin < Cout ? Cout : Cin) <= 64;
 }
 
+// Layers that run on the tiled kernel, given a workspace.  3 x 3 at stride 2 on channels in multiples of 32 and rows of whole
+// 16-byte groups stays on the kernel that reads its operands straight from memory (its tile here would be four
+// fifths halo): [32,128,56,56] -> 128 93 us there, 97 here; at stride 1 [32,256,14,14] -> 256 88 / 75, [3,128,10,97] -> 472 150 / 46.
+static bool tile_wanted(const GwLayer &l)
+{
+    if (g_opt.conv2d_variant == 100) return true;
+    const bool direct = l.kh == 3 && l.kw == 3 && l.sh == 2 && l.sw == 2 && l.Cin % 32 == 0 && l.Cout % 32 == 0 && l.W % 4 == 0 && l.Wo % 4 == 0;
+    return !direct && !few_long_sums(l.Cin, l.Cout, (int64_t)l.kh * l.kw);
+}
+
+int64_t conv2d_gw_workspace(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
+                            int32_t sw, int32_t ph, int32_t pw)
+{
+    const GwLayer l = gw_layer(N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw, 1);
+    return tile_wanted(l) ? conv_gw_tile_workspace(l) : 0;
+}
+
+int64_t conv1d_gw_workspace(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
+                            int32_t groups)
+{
+    if (groups != 1 || Cin < 2) return 0;
+    const GwLayer l = gw_layer(B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad, dilation);
+    return tile_wanted(l) ? conv_gw_tile_workspace(l) : 0;
+}
+
 hipError_t launch_conv2d_grad_weight(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H,
                                      int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
                                      int32_t sw, int32_t ph, int32_t pw, hipStream_t s, Workspace ws)
 {
     const int64_t n_gw = Cout * Cin * kh * kw;
     if (n_gw > 2147483647LL) return kNotTaken;
-    // With a workspace: the tiled split-operand kernel.  3 x 3 at stride 2 on channels in multiples of 32 and rows of whole
-    // 16-byte groups stays on the kernel that reads its operands straight from memory (its tile here would be four
-    // fifths halo): [32,128,56,56] -> 128 93 us there, 97 here; at stride 1 [32,256,14,14] -> 256 88 / 75, [3,128,10,97] -> 472 150 / 46.
-    const bool direct = kh == 3 && kw == 3 && sh == 2 && sw == 2 && Cin % 32 == 0 && Cout % 32 == 0 && W % 4 == 0 && Wo % 4 == 0;
-    if (ws.p && N > 0 && ((g_opt.conv2d_variant == 0 && !direct && !few_long_sums(Cin, Cout, (int64_t)kh * kw)) || g_opt.conv2d_variant == 100)) {
+    if (ws.p && N > 0 && (g_opt.conv2d_variant == 0 || g_opt.conv2d_variant == 100)) {
+        const GwLayer l = gw_layer(N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw, 1);
         bool taken = false;
-        const bool flat = kh == 1 && kw == 1 && sh == 1 && sw == 1 && ph == 0 && pw == 0;      // does not see the rows
-        const hipError_t e = flat ? launch_conv_gw_tile(x, gy, gw, N, Cin, 1, H * W, Cout, 1, Ho * Wo, 1, 1, 1, 1, 0, 0, 1, ws, s, &taken)
-                                  : launch_conv_gw_tile(x, gy, gw, N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw, 1, ws, s, &taken);
-        if (taken || e != hipSuccess) return e;
+        if (tile_wanted(l)) {
+            const hipError_t e = launch_conv_gw_tile(x, gy, gw, l, ws, s, &taken);
+            if (taken || e != hipSuccess) return e;
+        }
     }
     if (N > 0 && sw <= 2 && Cin >= 2 && g_opt.conv2d_variant != 1 && H * W <= 2147483647LL && Ho * Wo <= 2147483647LL) {
         int64_t fg = (n_gw + kThreads - 1) / kThreads;
@@ -812,11 +842,13 @@ hipError_t launch_conv1d_grad_weight(const float *x, const float *gy, float *gw,
     const int64_t n_gw = Cout * cig * k;
     const int variant = g_opt.conv1d_variant;        // 1 forces direct evaluation (A/B and tests)
     if (n_gw > 2147483647LL) return kNotTaken;
-    if (ws.p && B > 0 && groups == 1 && Cin >= 2 && variant == 0 &&
-        ((g_opt.conv2d_variant == 0 && !few_long_sums(Cin, Cout, k)) || g_opt.conv2d_variant == 100)) {
+    if (ws.p && B > 0 && groups == 1 && Cin >= 2 && variant == 0 && (g_opt.conv2d_variant == 0 || g_opt.conv2d_variant == 100)) {
+        const GwLayer l = gw_layer(B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad, dilation);
         bool taken = false;
-        const hipError_t e = launch_conv_gw_tile(x, gy, gw, B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad, dilation, ws, s, &taken);
-        if (taken || e != hipSuccess) return e;
+        if (tile_wanted(l)) {
+            const hipError_t e = launch_conv_gw_tile(x, gy, gw, l, ws, s, &taken);
+            if (taken || e != hipSuccess) return e;
+        }
     }
     const bool thin_ok = B > 0 && cig == 1 && stride == 1 && dilation <= kGwMaxDilation && k <= 64 && B <= 2147483647LL && variant != 1;
     const bool dense_ok = B > 0 && groups == 1 && stride <= 2 && Cin >= 2 && variant != 1;

@@ -377,54 +377,38 @@ int gw_splits(int64_t nblk, int64_t tiles)
     return (int)(n < tiles ? n : tiles);
 }
 
-}  // namespace
+// A layer's plan: the geometry but for its taps' offsets; channel blocks of a workgroup; LDS and workspace bytes.
+struct GwPlan {
+    GwTile g;
+    int WM, WN;
+    size_t lds;
+    int64_t bytes;
+};
 
-// Bytes of workspace: every run's partial sums.
-int64_t conv_gw_workspace(int64_t Cin, int64_t Cout, int kh, int kw)
+// The cheapest plan of at most `limit` bytes of workspace; false: the layer is not this kernel's.
+bool plan_gw(const GwLayer &l, int64_t limit, GwPlan *best)
 {
-    if ((int64_t)kh * kw > kMaxTaps || kh > 64 || kw > 64) return 0;
-    const Groups q = tap_groups(kh, kw);
-    const int64_t nblk = ((Cin + 63) / 64) * ((Cout + 63) / 64) * q.ng, small = ((Cin + 31) / 32) * ((Cout + 31) / 32) * q.ng;
-    const int64_t a = (nblk + 512) * 4, b = small + 512;      // 32 x 32 blocks; (64 x 32 lie between)
-    return (a > 2 * b ? a : 2 * b) * q.tb * 1024 * 4;
-}
-
-hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Cout,
-                               int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t ph, int32_t pw, int32_t dil,
-                               Workspace ws, hipStream_t s, bool *taken)
-{
-    *taken = false;
-    if (!ws.p || ((uintptr_t)ws.p & 15) || (int64_t)kh * kw > kMaxTaps || sh > 2 || sw > 2 || N < 1) return hipSuccess;
+    const int64_t N = l.N, Cin = l.Cin, H = l.H, W = l.W, Cout = l.Cout, Ho = l.Ho, Wo = l.Wo;
+    const int kh = l.kh, kw = l.kw, sh = l.sh, sw = l.sw, dil = l.dil;
+    if ((int64_t)kh * kw > kMaxTaps || sh > 2 || sw > 2 || N < 1) return false;
     if (N * Ho >= (1LL << 30) || H >= (1 << 18) || Ho >= (1 << 18) || W >= (1LL << 27) || Wo >= (1LL << 27) || Cin * H * W >= (1LL << 27) ||
         Cout * Ho * Wo >= (1LL << 27))
-        return hipSuccess;
+        return false;
+    if (l.ph > 16384 || l.pw > 16384 || kw * (int64_t)dil > 16384) return false;
     const Groups q = tap_groups(kh, kw);
-    GwTile g;
+    GwTile &g = best->g;
     g.N = (int)N; g.Cin = (int)Cin; g.H = (int)H; g.W = (int)W; g.HW = (int)(H * W); g.Cout = (int)Cout; g.Ho = (int)Ho; g.Wo = (int)Wo;
     g.HoWo = (int)(Ho * Wo); g.NR = (int)(N * Ho); g.KT = kh * kw; g.sh = sh; g.sw = sw;
     g.SH = q.rows; g.ls = g.SH < sh ? g.SH : sh;
-    if (g.SH < sh && g.SH != 1) return hipSuccess;
+    if (g.SH < sh && g.SH != 1) return false;
     g.LPI = (int)(Ho - 1) * g.ls + g.SH;
     const int SW = (q.taps - 1) * dil + 1, SWc = SW < sw ? SW : sw;
     g.ng = q.ng;
-    const int runs = (kw + q.taps - 1) / q.taps;
-    for (int k = 0; k < q.ng; ++k) {
-        const int a0 = k / runs * q.rows, b0 = k % runs * q.taps;
-        const int na = kh - a0 < q.rows ? kh - a0 : q.rows, nb = kw - b0 < q.taps ? kw - b0 : q.taps;
-        if (na > 1 && nb != kw) return hipSuccess;
-        g.gdh[k] = (short)(a0 - ph); g.gdw[k] = (short)(b0 * dil - pw);
-        g.gt0[k] = (unsigned char)(a0 * kw + b0); g.gnt[k] = (unsigned char)(na * nb);
-    }
-    if (ph > 16384 || pw > 16384 || kw * (int64_t)dil > 16384) return hipSuccess;
-    // Channel blocks of a workgroup, strip width and rows per tile: the smallest estimated time of the longest run (products
+    // Channel blocks of a workgroup, strip width, rows per tile and runs: the smallest estimated time of the longest run (products
     // on two wavefronts per SIMD, staging per unit, a run's end), in cycles.
     constexpr int kUX = 4;
     bool found = false;
-    double best = 0;
-    GwTile bg = g;
-    int WM = 0, WN = 0;
-    size_t lds = 0;
-    const int nt = q.rows * q.taps;
+    double cost = 0;
     for (int wmn = 0; wmn < 4; ++wmn) {
         const int wm = 1 + (wmn & 1), wn = 1 + (wmn >> 1), wk = 8 / (wm * wn);
         if ((wm == 2 && Cout <= 32) || (wn == 2 && Cin <= 32)) continue;
@@ -437,36 +421,82 @@ hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, int64
                 const int crossings = (int)((unsigned)(rpt - 1 + g.Ho - 1) / g.Ho);
                 const int64_t lines = (int64_t)(rpt - 1) * g.ls + g.SH + crossings * (g.SH - g.ls);
                 if (lines * LW > 1024) continue;
+                const int64_t imgs = rpt / Ho + 2;    // a tile's images within 32-bit offsets
+                if (imgs * Cin * H * W >= (1LL << 29) || imgs * Cout * Ho * Wo >= (1LL << 29)) continue;
                 const int PS = ((int)(lines * LW) + 3) / 16 * 16 + 12;
                 const size_t stage = (size_t)4 * 3 * 16 * (wn * PS + wm * kPG) + kBN * 4;
                 const size_t red = (size_t)(8 - wm * wn) * 4 * (q.tb < 3 ? q.tb : 3) * 1024;
                 if (4 * wn * PS > kUX * kThreads || stage > 158 * 1024) continue;
-                const int tps = (int)((unsigned)(g.NR + rpt - 1) / rpt), tiles = tps * nstrips, ksteps = (rpt * TW + 15) / 16;
-                int nsplit = gw_splits(nblk, tiles);
-                const int per = (int)((unsigned)(tiles + nsplit - 1) / nsplit);
-                nsplit = (int)((unsigned)(tiles + per - 1) / per);
-                if (nblk * nsplit * q.tb * wm * wn * 4096 > ws.bytes) continue;
+                const int tps = (int)((unsigned)(g.NR + rpt - 1) / rpt), ksteps = (rpt * TW + 15) / 16, steps = (ksteps + wk - 1) / wk;
+                if ((int64_t)tps * nstrips >= (1LL << 30)) continue;
+                const int tiles = tps * nstrips;
+                const double tile = steps * (double)(q.rows * q.taps) * 6 * 32 * 2 * 1.2 + 1200 + 500.0 * ((4 * wn * PS + kThreads - 1) / kThreads + wm);
+                const int runs = gw_splits(nblk, tiles);
+                const int per = (int)((unsigned)(tiles + runs - 1) / (unsigned)runs), nsplit = (int)((unsigned)(tiles + per - 1) / per);
+                const int64_t bytes = nblk * nsplit * q.tb * wm * wn * 4096;
+                if (bytes > limit) continue;
                 const double rounds = (double)((nblk * nsplit + 255) / 256);
-                const double tile = (ksteps + wk - 1) / wk * (double)nt * 6 * 32 * 2 * 1.2 + 1200 + 500.0 * ((4 * wn * PS + kThreads - 1) / kThreads + wm);
-                const double cost = rounds * (per * tile + 4000 + 6.0 * q.tb * wm * wn * nblk * nsplit / 64);
-                if (!found || cost < best) {
+                const double c = rounds * (per * tile + 4000 + 6.0 * q.tb * wm * wn * nblk * nsplit / 64);
+                if (!found || c < cost) {
                     found = true;
-                    best = cost;
-                    WM = wm; WN = wn;
-                    lds = stage > red ? stage : red;
-                    bg.TW = TW; bg.nstrips = nstrips; bg.CW = CW; bg.LW = LW; bg.rpt = rpt; bg.PS = PS; bg.tps = tps; bg.tiles = tiles;
-                    bg.ksteps = ksteps; bg.per = per; bg.nsplit = nsplit; bg.cob = (int)cob; bg.cib = (int)cib;
+                    cost = c;
+                    best->WM = wm; best->WN = wn;
+                    best->lds = stage > red ? stage : red;
+                    best->bytes = bytes;
+                    g.TW = TW; g.nstrips = nstrips; g.CW = CW; g.LW = LW; g.rpt = rpt; g.PS = PS; g.tps = tps; g.tiles = tiles;
+                    g.ksteps = ksteps; g.per = per; g.nsplit = nsplit; g.cob = (int)cob; g.cib = (int)cib;
                 }
             }
         }
     }
-    if (!found) return hipSuccess;
-    g = bg;
-    const int64_t imgs = g.rpt / Ho + 2;
-    if (imgs * Cin * H * W >= (1LL << 29) || imgs * Cout * Ho * Wo >= (1LL << 29)) return hipSuccess;
+    return found;
+}
+
+}  // namespace
+
+// Bytes that suffice for a layer of these channels and taps whatever its planes: two rounds of runs on every compute unit.
+int64_t conv_gw_tile_most(int64_t Cin, int64_t Cout, int kh, int kw)
+{
+    if ((int64_t)kh * kw > kMaxTaps || kh > 64 || kw > 64) return 0;
+    const Groups q = tap_groups(kh, kw);
+    int64_t most = 0;
+    for (int wmn = 0; wmn < 4; ++wmn) {
+        const int wm = 1 + (wmn & 1), wn = 1 + (wmn >> 1);
+        if ((wm == 2 && Cout <= 32) || (wn == 2 && Cin <= 32)) continue;
+        const int64_t nblk = ((Cout + 32 * wm - 1) / (32 * wm)) * ((Cin + 32 * wn - 1) / (32 * wn)) * q.ng;
+        const int64_t bytes = (nblk > 512 ? nblk : 512) * q.tb * wm * wn * 4096;
+        most = bytes > most ? bytes : most;
+    }
+    return most;
+}
+
+// Bytes of workspace of a layer; 0: not this kernel's.
+int64_t conv_gw_tile_workspace(const GwLayer &l)
+{
+    GwPlan p;
+    return plan_gw(l, INT64_MAX, &p) ? p.bytes : 0;
+}
+
+hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, const GwLayer &l, Workspace ws, hipStream_t s, bool *taken)
+{
+    *taken = false;
+    if (!ws.p || ((uintptr_t)ws.p & 15)) return hipSuccess;
+    GwPlan p;
+    if (!plan_gw(l, ws.bytes, &p)) return hipSuccess;
+    GwTile &g = p.g;
+    const int WM = p.WM, WN = p.WN;
+    const size_t lds = p.lds;
+    const Groups q = tap_groups(l.kh, l.kw);
+    const int runs = (l.kw + q.taps - 1) / q.taps;
+    for (int k = 0; k < q.ng; ++k) {
+        const int a0 = k / runs * q.rows, b0 = k % runs * q.taps;
+        const int na = l.kh - a0 < q.rows ? l.kh - a0 : q.rows, nb = l.kw - b0 < q.taps ? l.kw - b0 : q.taps;
+        g.gdh[k] = (short)(a0 - l.ph); g.gdw[k] = (short)(b0 * l.dil - l.pw);
+        g.gt0[k] = (unsigned char)(a0 * l.kw + b0); g.gnt[k] = (unsigned char)(na * nb);
+    }
     for (int t = 0; t < g.KT; ++t) {
-        const int a = t / kw % q.rows, bcol = t % kw % q.taps * dil;
-        g.tapoff[t] = (unsigned short)(a * g.LW + bcol % sw * g.CW + bcol / sw);
+        const int a = t / l.kw % q.rows, bcol = t % l.kw % q.taps * l.dil;
+        g.tapoff[t] = (unsigned short)(a * g.LW + bcol % l.sw * g.CW + bcol / l.sw);
     }
     for (int t = g.KT; t < kMaxTaps; ++t) g.tapoff[t] = 0;
     g.inv_TW = 1.0f / g.TW; g.inv_Ho = 1.0f / g.Ho; g.inv_LPI = 1.0f / g.LPI; g.inv_LW = 1.0f / g.LW; g.inv_CW = 1.0f / g.CW;

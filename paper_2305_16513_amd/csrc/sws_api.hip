@@ -290,7 +290,7 @@ int64_t sws_conv_workspace(int64_t Cin, int64_t Cout, int64_t taps, int64_t posi
 int64_t sws_conv_grad_weight_workspace(int64_t Cin, int64_t Cout, int32_t kh, int32_t kw)
 {
     if (Cin < 1 || Cout < 1 || kh < 1 || kw < 1 || Cin > (1 << 20) || Cout > (1 << 20)) return 0;
-    return sws::conv_gw_workspace(Cin, Cout, kh, kw);
+    return sws::conv_gw_tile_most(Cin, Cout, kh, kw);
 }
 
 sws_status sws_conv1d_ws(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L,
@@ -414,6 +414,14 @@ sws_status sws_conv1d_grad_input(const float *gy, const float *wgt, float *gx, i
     return sws_conv1d_grad_input_ws(gy, wgt, gx, B, Cin, L, Cout, k, stride, pad, dilation, groups, nullptr, 0, stream);
 }
 
+int64_t sws_conv1d_grad_weight_workspace(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int32_t k, int32_t stride, int32_t pad,
+                                         int32_t dilation, int32_t groups)
+{
+    int64_t Lo;
+    if (check_conv1d(B, Cin, L, Cout, k, stride, pad, dilation, groups, &Lo) != SWS_OK) return 0;
+    return sws::conv1d_gw_workspace(B, Cin, L, Cout, Lo, k, stride, pad, dilation, groups);
+}
+
 sws_status sws_conv1d_grad_weight_ws(const float *x, const float *gy, float *gw, int64_t B, int64_t Cin, int64_t L,
                                   int64_t Cout, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
                                   int32_t groups,
@@ -475,6 +483,14 @@ sws_status sws_conv2d_grad_input(const float *gy, const float *wgt, float *gx, i
                                  int32_t pw, sws_stream_t stream)
 {
     return sws_conv2d_grad_input_ws(gy, wgt, gx, N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw, nullptr, 0, stream);
+}
+
+int64_t sws_conv2d_grad_weight_workspace(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh,
+                                         int32_t sw, int32_t ph, int32_t pw)
+{
+    int64_t Ho, Wo;
+    if (check_conv2d(N, Cin, H, W, Cout, kh, kw, sh, sw, ph, pw, &Ho, &Wo) != SWS_OK) return 0;
+    return sws::conv2d_gw_workspace(N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw);
 }
 
 sws_status sws_conv2d_grad_weight_ws(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H,

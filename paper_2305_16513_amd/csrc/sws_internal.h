@@ -263,10 +263,18 @@ hipError_t launch_conv2d_split(const float *x, const float *wgt, float *y, int64
                                int32_t ph, int32_t pw, int32_t dh, int32_t dw, hipStream_t s, bool *taken, int wadj, Workspace ws);
 // Dense grad-weight on the bf16 matrix cores through transposing LDS reads, partial sums in the caller's workspace (conv_gw_tile.hip);
 // gw need not hold zeros; *taken = false: not its case or the workspace is too small, nothing launched.
-int64_t conv_gw_workspace(int64_t Cin, int64_t Cout, int kh, int kw);
-hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Cout,
-                               int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t ph, int32_t pw, int32_t dil,
-                               Workspace ws, hipStream_t s, bool *taken);
+struct GwLayer {
+    int64_t N, Cin, H, W, Cout, Ho, Wo;
+    int kh, kw, sh, sw, ph, pw, dil;                  // (dil: along rows)
+};
+int64_t conv_gw_tile_most(int64_t Cin, int64_t Cout, int kh, int kw);
+int64_t conv_gw_tile_workspace(const GwLayer &l);
+hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, const GwLayer &l, Workspace ws, hipStream_t s, bool *taken);
+// Bytes that the adjoints with respect to the weights use, 0: none (conv_grad.hip).
+int64_t conv2d_gw_workspace(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
+                            int32_t sw, int32_t ph, int32_t pw);
+int64_t conv1d_gw_workspace(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
+                            int32_t groups);
 // Weight-stationary streaming kernel (conv_stream.hip): 64 input channels, 3 x 3 on narrow images and
 // 1 x 3 on 1-D rows, stride 1; *taken = false: not its case, nothing launched.
 hipError_t launch_conv2d_stream(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H, int64_t W,

@@ -286,6 +286,33 @@ def test_conv_workspace_and_argument_checks_of_the_ws_entries(L):
     assert L.sws_conv1d_grad_input_ws(one, one, nul, 1, 3, 10, 4, 3, 1, 0, 1, 1, one, 64, nul) == 1
 
 
+def test_grad_weight_workspace_goes_with_the_work(L):
+    """Partial sums of as many runs as the layer has tiles for, and none where no kernel uses them."""
+    conv2, conv1 = L.sws_conv2d_grad_weight_workspace, L.sws_conv1d_grad_weight_workspace
+    gw = 4 * 64 * 64 * 9
+    assert conv2(32, 64, 56, 56, 64, 3, 3, 1, 1, 1, 1) >= 64 * gw            # one block of gw, runs for the whole chip
+    assert 0 < conv2(2, 64, 8, 8, 64, 3, 3, 1, 1, 1, 1) <= 8 * gw            # a few tiles (75 MB for any layer of these channels before)
+    assert 0 < conv2(2, 8, 8, 8, 8, 3, 3, 1, 1, 1, 1) <= 8 * 4 * 32 * 32 * 9
+    assert 0 < conv1(16, 64, 4096, 64, 3, 1, 0, 1, 1) <= 512 * 4 * 64 * 64 * 3
+    assert conv2(32, 64, 56, 56, 64, 3, 3, 3, 3, 1, 1) == 0 and conv1(16, 64, 4096, 64, 3, 3, 0, 1, 1) == 0       # strides beyond 2
+    assert conv2(32, 128, 56, 56, 128, 3, 3, 2, 2, 1, 1) == 0                # the kernel that reads its operands from memory
+    assert conv1(16, 64, 4096, 64, 3, 1, 0, 1, 2) == 0 and conv1(16, 1, 4096, 64, 3, 1, 0, 1, 1) == 0
+    assert conv2(1, 64, 30, 30, 64, 9, 9, 1, 1, 0, 0) == 0 and conv1(1, 64, 30, 64, 31, 1, 0, 1, 1) == 0          # 81 taps; invalid
+    assert conv2(0, 64, 30, 30, 64, 3, 3, 1, 1, 0, 0) == 0
+
+
+def test_no_memory_for_a_workspace_is_no_error():
+    import torch
+    from paper_2305_16513_amd import binding as B
+
+    class Full:
+        def new_empty(self, n):
+            raise torch.cuda.OutOfMemoryError("no %d floats" % n)
+
+    assert B._scratch(1 << 20, Full(), None) == (None, None, 0)
+    assert B._scratch(0, Full(), None) == (None, None, 0)
+
+
 def test_grad_weight_workspace_and_argument_checks(L):
     one, nul = ctypes.c_void_p(16), ctypes.c_void_p(0)
     assert L.sws_conv_grad_weight_workspace(64, 64, 3, 3) >= 4 * 64 * 64 * 9
