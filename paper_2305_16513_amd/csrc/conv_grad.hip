@@ -715,30 +715,31 @@ static GwLayer gw_layer(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Co
     return {N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw, dil};
 }
 
-// Few channels and up to three taps: gw is a few thousand long sums, and the rounding of the bf16 matrix instruction shows in
-// them — error against 64 bits, tiled split-operand / fp32 kernels: [16,24,5574] -> 32, k = 1 6.2e-7 / 3.6e-7, [8,32,3564] -> 20, k = 3
-// 4.0e-7 / 2.5e-7, [32,48,4376] -> 32, k = 3 5.0e-7 / 3.5e-7 — at 0.96 - 1.3 times the speed: these layers keep their kernels.
-// (Over 90 random layers the error of a layer's three results is otherwise below the fp32 kernels'.)
-static bool few_long_sums(int64_t Cin, int64_t Cout, int64_t taps)
-{
-    return taps <= 3 && (Cin < Cout ? Cin : Cout) <= 48 && (Cin < Cout ? Cout : Cin) <= 64;
-}
-
 // Layers that run on the tiled kernel, given a workspace.  3 x 3 at stride 2 on channels in multiples of 32 and rows of whole
 // 16-byte groups stays on the kernel that reads its operands straight from memory (its tile here would be four
 // fifths halo): [32,128,56,56] -> 128 93 us there, 97 here; at stride 1 [32,256,14,14] -> 256 88 / 75, [3,128,10,97] -> 472 150 / 46.
-static bool tile_wanted(const GwLayer &l)
+// *exact: the kernel that the layer runs on without a workspace multiplies in fp32, and gw's error against 64 bits (1.7e-7 whatever
+// the size) is to be no larger here.  The other layers' split-operand kernels (conv_gw_split.hip) are further off than either form of this one.
+static bool tile_wanted(const GwLayer &l, bool *exact)
 {
+    *exact = true;
     if (g_opt.conv2d_variant == 100) return true;
     const bool direct = l.kh == 3 && l.kw == 3 && l.sh == 2 && l.sw == 2 && l.Cin % 32 == 0 && l.Cout % 32 == 0 && l.W % 4 == 0 && l.Wo % 4 == 0;
-    return !direct && !few_long_sums(l.Cin, l.Cout, (int64_t)l.kh * l.kw);
+    if (direct) return false;
+    if (conv2d_gw_split_takes(l.Cin, l.W, l.Cout, l.kh, l.kw, l.sh, l.sw, l.pw)) *exact = false;
+    else if (l.H == 1 && l.kh == 1 && l.sw == 1 && l.dil == 1 && conv1d_gw_split_us(l.N, l.Cin, l.W, l.Cout, l.Wo, l.kw, l.pw) > 0) *exact = false;
+    // A few dozen positions: eight products of bf16 pieces are aligned to the largest of them and cut at 2^-24 of it, which is more than the
+    // roundings of so short an fp32 sum.  [1,175,9,9] -> 200, 3 x 3 stride 2 (25 positions) 7.0e-8 here, 5.9e-8 there, [1,160,11,11] -> 48 (36)
+    // 7.4e-8 / 7.1e-8, [1,32,256] -> 128, k = 3 even.
+    return !(*exact && l.N * l.Ho * l.Wo < 64);
 }
 
 int64_t conv2d_gw_workspace(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
                             int32_t sw, int32_t ph, int32_t pw)
 {
     const GwLayer l = gw_layer(N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw, 1);
-    return tile_wanted(l) ? conv_gw_tile_workspace(l) : 0;
+    bool exact = false;
+    return tile_wanted(l, &exact) ? conv_gw_tile_workspace(l, exact) : 0;
 }
 
 int64_t conv1d_gw_workspace(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
@@ -746,7 +747,8 @@ int64_t conv1d_gw_workspace(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int
 {
     if (groups != 1 || Cin < 2) return 0;
     const GwLayer l = gw_layer(B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad, dilation);
-    return tile_wanted(l) ? conv_gw_tile_workspace(l) : 0;
+    bool exact = false;
+    return tile_wanted(l, &exact) ? conv_gw_tile_workspace(l, exact) : 0;
 }
 
 hipError_t launch_conv2d_grad_weight(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H,
@@ -757,9 +759,9 @@ hipError_t launch_conv2d_grad_weight(const float *x, const float *gy, float *gw,
     if (n_gw > 2147483647LL) return kNotTaken;
     if (ws.p && N > 0 && (g_opt.conv2d_variant == 0 || g_opt.conv2d_variant == 100)) {
         const GwLayer l = gw_layer(N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw, 1);
-        bool taken = false;
-        if (tile_wanted(l)) {
-            const hipError_t e = launch_conv_gw_tile(x, gy, gw, l, ws, s, &taken);
+        bool taken = false, exact = false;
+        if (tile_wanted(l, &exact)) {
+            const hipError_t e = launch_conv_gw_tile(x, gy, gw, l, exact, ws, s, &taken);
             if (taken || e != hipSuccess) return e;
         }
     }
@@ -844,9 +846,9 @@ hipError_t launch_conv1d_grad_weight(const float *x, const float *gy, float *gw,
     if (n_gw > 2147483647LL) return kNotTaken;
     if (ws.p && B > 0 && groups == 1 && Cin >= 2 && variant == 0 && (g_opt.conv2d_variant == 0 || g_opt.conv2d_variant == 100)) {
         const GwLayer l = gw_layer(B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad, dilation);
-        bool taken = false;
-        if (tile_wanted(l)) {
-            const hipError_t e = launch_conv_gw_tile(x, gy, gw, l, ws, s, &taken);
+        bool taken = false, exact = false;
+        if (tile_wanted(l, &exact)) {
+            const hipError_t e = launch_conv_gw_tile(x, gy, gw, l, exact, ws, s, &taken);
             if (taken || e != hipSuccess) return e;
         }
     }

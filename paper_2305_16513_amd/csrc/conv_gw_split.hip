@@ -623,22 +623,16 @@ __global__ __launch_bounds__(kRowThreads) void conv1d_gw_split_kernel(const floa
 
 }  // namespace
 
-// Kernels one row high on dense channels (stride 1, channel counts in multiples of 32, k = 1, 3 or 5); rows: see the
-// kernel.  gw must hold zeros; *taken = false: not its case, nothing launched.
-hipError_t launch_conv1d_gw_split(const float *x, const float *gy, float *gw, int64_t rows, int RH, int64_t Cin, int64_t L,
-                                  int64_t Cout, int64_t Lo, int32_t k, int32_t pad, int64_t x_cs, int64_t gy_cs, hipStream_t s,
-                                  bool *taken)
+namespace {
+
+// Can conv1d_gw_split_kernel take the layer, and in how many workgroups per block of gw?  0: no.
+int64_t row_groups(int64_t rows, int RH, int64_t Cin, int64_t L, int64_t Cout, int64_t Lo, int32_t k, int32_t pad, int64_t x_cs, int64_t gy_cs)
 {
-    *taken = false;
-    if ((Cin & 31) || (Cout & 31) || rows < 1 || Lo < 1 || L < 1 || Cin > 32768 || Cout > 32768) return hipSuccess;
-    if (pad < 0 || pad > (1 << 20) || RH < 1) return hipSuccess;
-    if (64 * x_cs + L >= (1 << 30) || 64 * gy_cs + Lo >= (1 << 30)) return hipSuccess;       // 32-bit byte offsets inside a block
-    if (g_opt.conv2d_variant != 0 || g_opt.conv1d_variant != 0 || (k != 1 && k != 3 && k != 5)) return hipSuccess;
-    const int cpr = (int)((Lo + 63) / 64);                         // chunks of 64 output positions per row
-    const int64_t n_chunks = rows * cpr;
-    const int co_blocks = (int)((Cout + 63) / 64), ci_blocks = (int)((Cin + 63) / 64);
-    const int64_t blocks = (int64_t)co_blocks * ci_blocks;
-    if (blocks > 65535) return hipSuccess;
+    if ((Cin & 31) || (Cout & 31) || rows < 1 || Lo < 1 || L < 1 || Cin > 32768 || Cout > 32768) return 0;
+    if (pad < 0 || pad > (1 << 20) || RH < 1 || (k != 1 && k != 3 && k != 5)) return 0;
+    if (64 * x_cs + L >= (1 << 30) || 64 * gy_cs + Lo >= (1 << 30)) return 0;                // 32-bit byte offsets inside a block
+    const int64_t n_chunks = rows * ((Lo + 63) / 64), blocks = ((Cout + 63) / 64) * ((Cin + 63) / 64);
+    if (blocks > 65535) return 0;
     // Workgroups per block of gw: more of them shorten the walk over the chunks, and every one of them ends with
     // 4096 k adds to memory, which the chip takes at about a third of a million per microsecond.  One workgroup
     // fills a CU (LDS); a chunk takes it two microseconds or so (1.6 with the operands in the last-level cache, 3 from
@@ -650,9 +644,39 @@ hipError_t launch_conv1d_gw_split(const float *x, const float *gy, float *gw, in
         const double t = (double)((n_chunks + sgroups - 1) / sgroups) * 2.0 + (double)(sgroups * blocks) * 4096.0 * k / 350000.0;
         if (t < best_t) { best_t = t; best = sgroups; }
     }
-    int64_t wgs = best;
-    if (g_opt.slide_group > 0) wgs = g_opt.slide_group;
-    if (wgs > n_chunks) wgs = n_chunks;
+    if (g_opt.slide_group > 0) best = g_opt.slide_group;
+    return best < n_chunks ? best : n_chunks;
+}
+
+}  // namespace
+
+// Estimated time of a layer one row high, us (fitted to 260 layers, 8 % deviation); 0: not this kernel's.
+double conv1d_gw_split_us(int64_t rows, int64_t Cin, int64_t L, int64_t Cout, int64_t Lo, int32_t k, int32_t pad)
+{
+    const int64_t wgs = row_groups(rows, 1, Cin, L, Cout, Lo, k, pad, L, Lo);
+    if (wgs == 0) return 0;
+    const int64_t n_chunks = rows * ((Lo + 63) / 64), per = (n_chunks + wgs - 1) / wgs;
+    const double all = (double)(wgs * ((Cout + 63) / 64) * ((Cin + 63) / 64)), rounds = __builtin_ceil(all / device_cus());
+    const bool pair = !(L & 1) && !(Lo & 1);
+    const double start = k == 1 ? 8.5 : (k == 3 ? 10.0 : 10.9), add = k == 1 ? 0.0074 : (k == 3 ? 0.0163 : 0.0222);
+    const double chunk = k == 1 ? (pair ? 1.24 : 1.92) : (k == 3 ? (pair ? 2.01 : 2.45) : (pair ? 2.84 : 3.25));
+    return start + rounds * per * chunk + add * all + 1.6e-4 * wgs * wgs;        // (the last: adds to one block of gw serialise)
+}
+
+// Kernels one row high on dense channels (stride 1, channel counts in multiples of 32, k = 1, 3 or 5); rows: see the
+// kernel.  gw must hold zeros; *taken = false: not its case, nothing launched.
+hipError_t launch_conv1d_gw_split(const float *x, const float *gy, float *gw, int64_t rows, int RH, int64_t Cin, int64_t L,
+                                  int64_t Cout, int64_t Lo, int32_t k, int32_t pad, int64_t x_cs, int64_t gy_cs, hipStream_t s,
+                                  bool *taken)
+{
+    *taken = false;
+    if (g_opt.conv2d_variant != 0 || g_opt.conv1d_variant != 0) return hipSuccess;
+    const int64_t wgs = row_groups(rows, RH, Cin, L, Cout, Lo, k, pad, x_cs, gy_cs);
+    if (wgs == 0) return hipSuccess;
+    const int cpr = (int)((Lo + 63) / 64);                         // chunks of 64 output positions per row
+    const int64_t n_chunks = rows * cpr;
+    const int ci_blocks = (int)((Cin + 63) / 64);
+    const int64_t blocks = (int64_t)((Cout + 63) / 64) * ci_blocks;
     const int64_t per = (n_chunks + wgs - 1) / wgs;
     const int64_t grid = (n_chunks + per - 1) / per;
     if (grid > 2147483647LL) return hipSuccess;
@@ -687,16 +711,21 @@ hipError_t launch_conv1d_gw_split(const float *x, const float *gy, float *gw, in
     return hipGetLastError();
 }
 
+// Layers of conv2d_gw_split_kernel.
+bool conv2d_gw_split_takes(int64_t Cin, int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t pw)
+{
+    if (sw != sh || (sw != 1 && sw != 2) || kh != 3 || kw != 3 || (Cin & 31) || (Cout & 31)) return false;
+    return (pw == 0 || pw == 1) && (sw == 1 || pw == 1) && W < (1 << 28) && Cin <= 32768 && Cout <= 32768;
+}
+
 // *taken = false: not this kernel's case (nothing launched).  gw must hold zeros.
 hipError_t launch_conv2d_gw_split(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H, int64_t W,
                                   int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh, int32_t sw,
                                   int32_t ph, int32_t pw, hipStream_t s, bool *taken)
 {
     *taken = false;
-    if (sw != sh || (sw != 1 && sw != 2) || kh != 3 || kw != 3 || (Cin & 31) || (Cout & 31) || N < 1) return hipSuccess;
-    if ((pw != 0 && pw != 1) || (sw == 2 && pw != 1) || W >= (1 << 28)) return hipSuccess;
+    if (g_opt.conv2d_variant != 0 || N < 1 || !conv2d_gw_split_takes(Cin, W, Cout, kh, kw, sh, sw, pw)) return hipSuccess;
     const bool dyn = (W & 3) || (Wo & 3);
-    if (g_opt.conv2d_variant != 0 || Cin > 32768 || Cout > 32768) return hipSuccess;
     const int g8 = (int)((Wo + 7) / 8);
     const int co_blocks = (int)((Cout + 63) / 64), ci_blocks = (int)((Cin + 63) / 64);
     if ((int64_t)co_blocks * ci_blocks > 65535) return hipSuccess;

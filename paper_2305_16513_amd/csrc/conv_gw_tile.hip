@@ -14,18 +14,29 @@
 // tiles of up to 128 positions: eight wavefronts, 32 x 32 channels x all its taps each, two wavefronts per block that take
 // alternate groups of 16 positions.  A tile is rpt whole rows of a strip of TW columns; rows are numbered through all
 // images, so small planes fill it.  The next tile's lines of x and gy are loaded into registers before the products of
-// the current one and split into LDS after them.  The dropped piece products are below 2^-23 of a term.
+// the current one and split into LDS after them.  Both operands' pieces are cut, not rounded, so a dropped product may reach
+// 2^-22 of its term and the three of them 2^-21 (on average 2^-25).
+//
+// Sums.  The matrix instruction adds its products in two halves of eight, each cut at 2^-24 of its largest product, and each half to
+// the accumulator with one rounding; an accumulator that is small beside the products is cut like one of them.  Six
+// products per 16 positions into the run's sum are twelve roundings of its own size, and a sum that starts with the small products
+// is cut by the large ones every time (a bias: 6.8e-7 on [32,64,56,56] -> 64, 3 x 3).  So the leading products and the
+// other five go to accumulators of their own.  Up to three taps: per tile from zero, added to the run's sum at its end.  Four to eight: per 16 positions
+// from zero.  Nine: the leading ones on the run's sum, the others per 16 positions (registers).  Layers whose kernel without a workspace is a
+// split-operand one too (FAST, five and nine taps): all six on the run's sum, still more exact than that kernel.  Error of gw against
+// 64 bits, fp32 kernels / all six on the run's sum / now: [1,168,84,84] -> 200, 5 x 5 1.6e-7 / 3.3e-7 / 1.6e-7, [16,500,28,28] -> 500,
+// 3 x 3 1.7e-7 / 6.1e-7 / 1.4e-7, [32,61,14,14] -> 32 1.45e-7 / 2.1e-7 / 1.1e-7, [16,24,5574] -> 32, k = 1 3.7e-7 / 6.2e-7 / 1.2e-7.
+// Operands of one tap at a time, a piece of the next read as soon as the last product with the present one is out: with two sets the nine-tap
+// instance spills, whose reloads wait for the loads in flight ([32,64,56,56] -> 64 93 us, now 75).
 //
 // Sums leave as partial blocks in the caller's workspace, lane after lane, and gw_reduce_kernel adds them in a fixed order:
 // the result does not depend on the order in which workgroups end (6 - 13 us; the atomic adds of conv_gw_split.hip, 36864 per
 // workgroup, take 27 us on 64 x 64 channels, 3 x 3).
 //
-// Measured, us, this kernel with its second pass / the kernels without a workspace: [58,32,23,27] -> 128, 5 x 5 75 / 433,
-// [3,128,10,97] -> 472, 3 x 3 46 / 150, [32,256,14,14] -> 256, 3 x 3 75 / 88, [32,64,56,56] -> 64 75 / 74, [16,64,4096] -> 64, k = 3
-// 27 / 31; 40 layers 1.7 x on average.  What it spends its time on ([32,64,56,56]): products 28 us at the clock that the
-// matrix cores hold, splitting 15, second pass and launches 10, the rest waits between the phases of a tile.  Two LDS buffers with
-// tiles of 64 positions, one wavefront of a SIMD splitting while the other multiplies, came out even at nine taps (68 - 70 us there)
-// and behind at one (174 against 127 us on [19,96,87,87] -> 256): not taken.
+// Measured, us, this kernel with its second pass / the kernels without a workspace: [17,128,23,14] -> 104, 5 x 5 55 / 313,
+// [1,96,65,65] -> 484, 3 x 3 49 / 208, [32,256,14,14] -> 256, 3 x 3 70 / 87, [32,64,56,56] -> 64 69 / 74, [16,64,4096] -> 64, k = 3
+// 28 / 31.  Two LDS buffers with tiles of 64 positions, one wavefront of a SIMD splitting while the other multiplies, came out even at nine
+// taps and behind at one (174 against 127 us on [19,96,87,87] -> 256): not taken.
 #include "sws_internal.h"
 
 namespace sws {
@@ -41,6 +52,7 @@ typedef short v8s __attribute__((ext_vector_type(8)));
 constexpr int kThreads = 512;
 constexpr int kMaxTaps = 64, kMaxGroups = 64;
 constexpr int kBN = 128;                              // positions per tile
+constexpr int kMaxAdds = 64;                          // see plan_gw
 constexpr int kPG = 140;                              // positions per staged plane of gy: >= kBN, = 12 mod 16 (see PS below)
 constexpr int kOctG = 3 * kPG * 16;                   // bytes from one octet of gy's channels to the next
 
@@ -100,10 +112,10 @@ __device__ __forceinline__ v8bf tr8(const char *p0, const char *p1)
     return __builtin_bit_cast(v8bf, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// TB: taps per group at most, FULL: in every group; WM x WN blocks of 32 x 32 channels, WK wavefronts each; UX: staged units
-// of x per thread (gy has WM).  The places of a thread's units are worked out anew for every tile (opaque): kept in registers
-// they push the accumulators into scratch memory, whose reloads would wait for the loads in flight.
-template <int TB, int WM, int WN, int UX, bool FULL>
+// TB: taps per group at most (a shorter last group computes its last tap again); WM x WN blocks of 32 x 32 channels, WK
+// wavefronts each; UX: staged units of x per thread (gy has WM).  The places of a thread's units are worked out anew for every
+// tile (opaque): kept in registers they push the accumulators into scratch memory, whose reloads would wait for the loads in flight.
+template <int TB, int WM, int WN, int UX, bool FAST>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void conv_gw_tile_kernel(const float *__restrict__ x, const float *__restrict__ gy, float *__restrict__ ws, GwTile g)
 {
@@ -193,62 +205,79 @@ void conv_gw_tile_kernel(const float *__restrict__ x, const float *__restrict__ 
     const int oct = 2 * (b & 1) + ((m & 3) >> 1), pj = 8 * (b >> 1) + (m >> 2);
     const char *const Ga = G + (4 * wm + oct) * kOctG + (m & 1) * 8 + pj * 16;
     const char *const Xa = X + (4 * wn + oct) * octX + (m & 1) * 8;
-    // Up to three taps the products of a tile are summed on their own and then added to the run's sum: the run takes one
-    // rounding of its own size per tile, not six per 16 positions (error of gw against 64 bits on [16,224,1469] -> 351, k = 1:
-    // 5.8e-7 without, 2.2e-7 with, fp32 kernels 2.3e-7).  Beyond that the registers do not hold a second set; summing each 16 positions from
-    // zero instead measured worse (6.8e-7 against 2.5e-7 on [32,64,56,56] -> 64, 3 x 3; fp32 4.9e-7).
-    constexpr bool TILE_SUM = TB <= 3;
+    unsigned off2[(TB + 1) / 2];                      // two taps' offsets (below 2^14 bytes) per scalar register
+#pragma unroll
+    for (int j = 0; j < TB; j += 2) {
+        const unsigned a = g.tapoff[t0 + (j < nt ? j : nt - 1)], b = g.tapoff[t0 + (j + 1 < nt ? j + 1 : nt - 1)];
+        off2[j / 2] = __builtin_amdgcn_readfirstlane((a | b << 16) << 4);
+    }
+    constexpr bool TILE_SUM = TB <= 3, ON_RUN = TB == 9 || FAST;
     v16f acc[TB];
 #pragma unroll
-    for (int t = 0; t < TB; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[t][v] = 0.0f;
+    for (int t = 0; t < TB; ++t) acc[t] = (v16f){0.0f};
 
     if (first < end) issue(first);
     for (int tile = first; tile < end; ++tile) {
         commit();
         barrier();
         if (tile + 1 < end) issue(tile + 1);
-        v16f sum[TILE_SUM ? TB : 1];
+        v16f hi[TILE_SUM ? TB : 1], lo[TILE_SUM ? TB : 1];
         if constexpr (TILE_SUM) {
 #pragma unroll
-            for (int t = 0; t < TB; ++t) sum[t] = (v16f){0.0f};
+            for (int t = 0; t < TB; ++t) hi[t] = lo[t] = (v16f){0.0f};
         }
         for (int s = wk; s < g.ksteps; s += WK) {
             const int p0 = tab[16 * s + pj], p1 = tab[16 * s + pj + 4];
-            v8bf a[3], bb[2][3];
+            v8bf a[3];
 #pragma unroll
             for (int q = 0; q < 3; ++q) a[q] = tr8(Ga + s * 256 + q * (kPG * 16), Ga + s * 256 + 64 + q * (kPG * 16));
-            auto xread = [&](int t, v8bf (&o)[3]) {
-                const int off = g.tapoff[t0 + t] * 16;
-                const char *q0 = Xa + p0 + off, *q1 = Xa + p1 + off;
-#pragma unroll
-                for (int q = 0; q < 3; ++q) o[q] = tr8(q0 + q * pieceX, q1 + q * pieceX);
+            auto xread = [&](int t, int q) {
+                const int off = (int)(t & 1 ? off2[t / 2] >> 16 : off2[t / 2] & 0xffff) + q * pieceX;
+                return tr8(Xa + p0 + off, Xa + p1 + off);
             };
-            xread(0, bb[0]);
+            v8bf b2 = xread(0, 2), b1 = xread(0, 1), b0 = xread(0, 0);
 #pragma unroll
             for (int t = 0; t < TB; ++t) {
-                if (!FULL && t >= nt) continue;
-                if (FULL ? t + 1 < TB : t + 1 < nt) xread(t + 1, bb[(t + 1) & 1]);
+                // (a piece of the next tap is read as soon as this tap's last product of it is out: twelve registers less
+                // than with two sets)
+                v16f l = {0.0f};
+                if constexpr (TILE_SUM) l = lo[t];
+                else if constexpr (FAST) l = acc[t];
                 __builtin_amdgcn_sched_barrier(0);
-                const v8bf (&B)[3] = bb[t & 1];
-                v16f c;                               // smallest products first
-                if constexpr (TILE_SUM) c = sum[t];
-                else c = acc[t];
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], B[0], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], B[1], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], B[2], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], B[0], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], B[1], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], B[0], c, 0, 0, 0);
-                if constexpr (TILE_SUM) sum[t] = c;
-                else acc[t] = c;
+                l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b2, l, 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
+                if (t + 1 < TB) b2 = xread(t + 1, 2);
+                __builtin_amdgcn_sched_barrier(0);
+                l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b1, l, 0, 0, 0);
+                l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b1, l, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (t + 1 < TB) b1 = xread(t + 1, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b0, l, 0, 0, 0);
+                l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b0, l, 0, 0, 0);
+                v16f h = {0.0f};
+                if constexpr (TILE_SUM) h = hi[t];
+                else if constexpr (FAST) h = l;
+                else if constexpr (ON_RUN) h = acc[t];
+                h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b0, h, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (t + 1 < TB) b0 = xread(t + 1, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (TILE_SUM) {
+                    lo[t] = l;
+                    hi[t] = h;
+                } else if constexpr (FAST) {
+                    acc[t] = h;
+                } else if constexpr (ON_RUN) {
+                    acc[t] = h + l;
+                } else {
+                    acc[t] += h + l;
+                }
             }
         }
         if constexpr (TILE_SUM) {
 #pragma unroll
-            for (int t = 0; t < TB; ++t) acc[t] += sum[t];
+            for (int t = 0; t < TB; ++t) acc[t] += hi[t] + lo[t];
         }
         barrier();                                    // everybody has read the tile
     }
@@ -276,7 +305,7 @@ void conv_gw_tile_kernel(const float *__restrict__ x, const float *__restrict__ 
                 for (int v = 0; v < 4; ++v) {
                     v4f r = {acc[t][4 * v], acc[t][4 * v + 1], acc[t][4 * v + 2], acc[t][4 * v + 3]};
                     for (int k = 0; k < WK - 1; ++k) r += red[((k * BLK + wave) * (4 * ROWS) + (t - q) * 4 + v) * 64];
-                    if (FULL || t < nt) {
+                    if (t < nt) {
 #pragma unroll
                         for (int u = 0; u < 4; ++u) out[t * (BLK * 1024) + (4 * v + u) * 64] = r[u];
                     }
@@ -319,7 +348,7 @@ __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict_
     if (co >= 0 && ci >= 0) gw[((int64_t)co * g.Cin + ci) * g.KT + g.gt0[grp] + t] = sum;
 }
 
-template <int TB, int WM, int WN, bool FULL>
+template <int TB, int WM, int WN, bool FAST>
 hipError_t launch_gw1(const float *x, const float *gy, float *gw, float *ws, const GwTile &g, size_t lds, hipStream_t s)
 {
     constexpr int UX = 4;
@@ -327,13 +356,13 @@ hipError_t launch_gw1(const float *x, const float *gy, float *gw, float *ws, con
     if (lds > 64 * 1024) {
         static std::atomic<bool> raised{false};       // (the attribute is per function; setting it twice does no harm)
         if (!raised.load(std::memory_order_relaxed)) {
-            const hipError_t e = hipFuncSetAttribute((const void *)conv_gw_tile_kernel<TB, WM, WN, UX, FULL>,
+            const hipError_t e = hipFuncSetAttribute((const void *)conv_gw_tile_kernel<TB, WM, WN, UX, FAST>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
             if (e != hipSuccess) return e;
             raised.store(true, std::memory_order_relaxed);
         }
     }
-    hipLaunchKernelGGL((conv_gw_tile_kernel<TB, WM, WN, UX, FULL>), dim3((unsigned)xcd_grid((int64_t)g.nsplit * nblk)), dim3(kThreads), lds,
+    hipLaunchKernelGGL((conv_gw_tile_kernel<TB, WM, WN, UX, FAST>), dim3((unsigned)xcd_grid((int64_t)g.nsplit * nblk)), dim3(kThreads), lds,
                        s, x, gy, ws, g);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -341,31 +370,34 @@ hipError_t launch_gw1(const float *x, const float *gy, float *gw, float *ws, con
     return hipGetLastError();
 }
 
-template <int TB>
-hipError_t launch_gw(const float *x, const float *gy, float *gw, float *ws, const GwTile &g, int WM, int WN, size_t lds, hipStream_t s)
+template <int TB, bool FAST>
+hipError_t launch_gw2(const float *x, const float *gy, float *gw, float *ws, const GwTile &g, int WM, int WN, size_t lds, hipStream_t s)
 {
-    bool full = true;
-    for (int k = 0; k < g.ng; ++k) full = full && g.gnt[k] == TB;
-#define SWS_GW(M, N) return full ? launch_gw1<TB, M, N, true>(x, gy, gw, ws, g, lds, s) : launch_gw1<TB, M, N, false>(x, gy, gw, ws, g, lds, s)
-    if (WM == 2 && WN == 2) SWS_GW(2, 2);
-    if (WM == 2) SWS_GW(2, 1);
-    if (WN == 2) SWS_GW(1, 2);
-    SWS_GW(1, 1);
-#undef SWS_GW
+    if (WM == 2 && WN == 2) return launch_gw1<TB, 2, 2, FAST>(x, gy, gw, ws, g, lds, s);
+    if (WM == 2) return launch_gw1<TB, 2, 1, FAST>(x, gy, gw, ws, g, lds, s);
+    if (WN == 2) return launch_gw1<TB, 1, 2, FAST>(x, gy, gw, ws, g, lds, s);
+    return launch_gw1<TB, 1, 1, FAST>(x, gy, gw, ws, g, lds, s);
 }
 
-struct Groups { int rows, taps, ng, tb; };            // kernel rows and taps per row of a group; groups; taps rounded to an instance
+template <int TB>
+hipError_t launch_gw(const float *x, const float *gy, float *gw, float *ws, const GwTile &g, bool exact, int WM, int WN, size_t lds, hipStream_t s)
+{
+    if constexpr (TB == 5 || TB == 9)                 // (the taps of the layers whose runs need not be exact)
+        if (!exact) return launch_gw2<TB, true>(x, gy, gw, ws, g, WM, WN, lds, s);
+    return launch_gw2<TB, false>(x, gy, gw, ws, g, WM, WN, lds, s);
+}
+
+struct Groups { int rows, taps, ng, tb; };            // kernel rows and taps per row of a group; groups; taps of a group
 
 Groups tap_groups(int kh, int kw)
 {
     Groups q;
-    q.taps = kw <= 9 ? kw : 9;
+    q.taps = (kw + (kw + 8) / 9 - 1) / ((kw + 8) / 9);        // a row of more than nine taps: runs of it, evenly
     q.rows = kw <= 9 ? 9 / kw : 1;
     if (q.rows > kh) q.rows = kh;
     q.rows = (kh + (kh + q.rows - 1) / q.rows - 1) / ((kh + q.rows - 1) / q.rows);      // evenly
     q.ng = (kh + q.rows - 1) / q.rows * ((kw + q.taps - 1) / q.taps);
-    const int n = q.rows * q.taps;
-    q.tb = n <= 1 ? 1 : n <= 3 ? 3 : n <= 5 ? 5 : 9;
+    q.tb = q.rows * q.taps;
     return q;
 }
 
@@ -386,7 +418,8 @@ struct GwPlan {
 };
 
 // The cheapest plan of at most `limit` bytes of workspace; false: the layer is not this kernel's.
-bool plan_gw(const GwLayer &l, int64_t limit, GwPlan *best)
+// exact: see the dispatch (conv_grad.hip); no run then adds more than kMaxAdds times to a wavefront's sums.
+bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
 {
     const int64_t N = l.N, Cin = l.Cin, H = l.H, W = l.W, Cout = l.Cout, Ho = l.Ho, Wo = l.Wo;
     const int kh = l.kh, kw = l.kw, sh = l.sh, sw = l.sw, dil = l.dil;
@@ -431,10 +464,15 @@ bool plan_gw(const GwLayer &l, int64_t limit, GwPlan *best)
                 if ((int64_t)tps * nstrips >= (1LL << 30)) continue;
                 const int tiles = tps * nstrips;
                 const double tile = steps * (double)(q.rows * q.taps) * 6 * 32 * 2 * 1.2 + 1200 + 500.0 * ((4 * wn * PS + kThreads - 1) / kThreads + wm);
-                const int runs = gw_splits(nblk, tiles);
+                int runs = gw_splits(nblk, tiles);
+                if (exact) {
+                    const int adds = q.tb <= 3 ? 1 : steps * (q.tb < 9 ? 1 : 3), most = kMaxAdds / adds > 1 ? kMaxAdds / adds : 1;
+                    const int least = (tiles + most - 1) / most;
+                    runs = runs > least ? runs : least;
+                }
                 const int per = (int)((unsigned)(tiles + runs - 1) / (unsigned)runs), nsplit = (int)((unsigned)(tiles + per - 1) / per);
                 const int64_t bytes = nblk * nsplit * q.tb * wm * wn * 4096;
-                if (bytes > limit) continue;
+                if (bytes > limit || nblk * nsplit >= (1LL << 30)) continue;
                 const double rounds = (double)((nblk * nsplit + 255) / 256);
                 const double c = rounds * (per * tile + 4000 + 6.0 * q.tb * wm * wn * nblk * nsplit / 64);
                 if (!found || c < cost) {
@@ -471,18 +509,19 @@ int64_t conv_gw_tile_most(int64_t Cin, int64_t Cout, int kh, int kw)
 }
 
 // Bytes of workspace of a layer; 0: not this kernel's.
-int64_t conv_gw_tile_workspace(const GwLayer &l)
+int64_t conv_gw_tile_workspace(const GwLayer &l, bool exact)
 {
     GwPlan p;
-    return plan_gw(l, INT64_MAX, &p) ? p.bytes : 0;
+    return plan_gw(l, exact, INT64_MAX, &p) ? p.bytes : 0;
 }
 
-hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, const GwLayer &l, Workspace ws, hipStream_t s, bool *taken)
+hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, const GwLayer &l, bool exact, Workspace ws, hipStream_t s,
+                               bool *taken)
 {
     *taken = false;
     if (!ws.p || ((uintptr_t)ws.p & 15)) return hipSuccess;
     GwPlan p;
-    if (!plan_gw(l, ws.bytes, &p)) return hipSuccess;
+    if (!plan_gw(l, exact, ws.bytes, &p)) return hipSuccess;
     GwTile &g = p.g;
     const int WM = p.WM, WN = p.WN;
     const size_t lds = p.lds;
@@ -503,12 +542,12 @@ hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, const
     g.inv_PS = 1.0f / g.PS;
     float *w = (float *)ws.p;
     *taken = true;
+#define SWS_GW_TB(T) case T: return launch_gw<T>(x, gy, gw, w, g, exact, WM, WN, lds, s)
     switch (q.tb) {
-    case 1: return launch_gw<1>(x, gy, gw, w, g, WM, WN, lds, s);
-    case 3: return launch_gw<3>(x, gy, gw, w, g, WM, WN, lds, s);
-    case 5: return launch_gw<5>(x, gy, gw, w, g, WM, WN, lds, s);
-    default: return launch_gw<9>(x, gy, gw, w, g, WM, WN, lds, s);
+        SWS_GW_TB(1); SWS_GW_TB(2); SWS_GW_TB(3); SWS_GW_TB(4); SWS_GW_TB(5); SWS_GW_TB(6); SWS_GW_TB(7); SWS_GW_TB(8);
+    default: return launch_gw<9>(x, gy, gw, w, g, exact, WM, WN, lds, s);
     }
+#undef SWS_GW_TB
 }
 
 }  // namespace sws

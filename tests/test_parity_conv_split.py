@@ -196,6 +196,12 @@ GW_CASES = CASES + [
     (20, 33, 9, 7, 7, 3, 3, 1, 1),                    # tiles across images
     (2, 3, 5, 130, 140, 3, 3, 1, 1),                  # strips, fewer than eight channels
     (1, 40, 40, 2, 600, 2, 3, 2, 0),
+    (2, 12, 34, 1, 300, 1, 2, 1, 0),                  # every number of taps that a workgroup takes at once: 2, 4, 6, 7, 8 ...
+    (1, 20, 40, 9, 70, 2, 2, 1, 0),
+    (2, 33, 10, 8, 40, 2, 3, 1, 1),
+    (1, 10, 66, 1, 500, 1, 7, 1, 3),
+    (2, 20, 40, 9, 37, 4, 4, 1, 1),
+    (1, 18, 40, 20, 21, 8, 8, 1, 3),                  # ... and the most taps
 ]
 
 
@@ -228,3 +234,47 @@ def test_grad_weight_is_reproducible(B):
     a = to_host(B.sws_conv2d_grad_weight(x, gy, 3, 3, 1, 1, 1, 1))
     for _ in range(3):
         assert_bit_exact(to_host(B.sws_conv2d_grad_weight(x, gy, 3, 3, 1, 1, 1, 1)), a)
+
+
+def _gw_exact(x, gy, kh, kw, s, ph, pw):
+    """The gradient in 64 bits: per tap one product of matrices."""
+    import torch
+    import torch.nn.functional as F
+    x, gy = x.double(), gy.double()
+    cin, (cout, ho, wo) = x.shape[1], gy.shape[1:]
+    xe = F.pad(x, (pw, pw, ph, ph)).transpose(0, 1).contiguous()
+    g2 = gy.transpose(0, 1).reshape(cout, -1).contiguous()
+    gw = torch.empty(cout, cin, kh, kw, dtype=torch.float64, device=x.device)
+    for a in range(kh):
+        for b in range(kw):
+            xt = xe[:, :, a:a + s * (ho - 1) + 1:s, b:b + s * (wo - 1) + 1:s].reshape(cin, -1)
+            gw[:, :, a, b] = g2 @ xt.t().contiguous()
+    return gw
+
+
+# n, cin, cout, h, w, kh, kw, stride, pad; channels that no multiple of 32 rounds, or taps other than 3 x 3: without a workspace these
+# run on fp32 instructions; the last two by so many blocks of gw that runs are cut for the length of their sums alone
+EXACT = [(8, 96, 72, 40, 40, 5, 5, 1, 2), (8, 61, 50, 28, 28, 3, 3, 1, 1), (4, 40, 90, 33, 33, 3, 3, 2, 1), (4, 60, 60, 30, 30, 7, 7, 1, 3),
+         (8, 48, 100, 40, 40, 4, 4, 1, 1), (16, 24, 40, 1, 5574, 1, 1, 1, 0), (8, 40, 70, 1, 2156, 1, 3, 1, 0), (2, 60, 100, 1, 3136, 1, 11, 1, 5),
+         (8, 260, 260, 28, 28, 3, 3, 1, 1), (4, 200, 260, 28, 28, 5, 5, 1, 2)]
+
+
+@pytest.mark.parametrize("case", EXACT)
+def test_grad_weight_is_as_exact_as_the_fp32_kernels(B, monkeypatch, case):
+    """Error against 64 bits (2-norm) with the workspace and without: at most a tenth more, the spread between two inputs."""
+    import torch
+    n, cin, cout, h, w, kh, kw, s, p = case
+    ph = p if h > 1 else 0
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn(n, cin, h, w, generator=gen, device="cuda")
+    sh = s if h > 1 else 1
+    gy = torch.randn(n, cout, (h + 2 * ph - kh) // sh + 1, (w + 2 * p - kw) // s + 1, generator=gen, device="cuda")
+    ref = _gw_exact(x, gy, kh, kw, s, ph, p)
+
+    def error():
+        return ((B.sws_conv2d_grad_weight(x, gy, kh, kw, sh, s, ph, p).double() - ref).norm() / ref.norm()).item()
+
+    tiled = error()
+    monkeypatch.setattr(B, "_scratch", lambda *a: (None, None, 0))
+    plain = error()
+    assert tiled <= 1.1 * plain, (tiled, plain)
