@@ -720,14 +720,26 @@ static GwLayer gw_layer(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Co
 // fifths halo): [32,128,56,56] -> 128 93 us there, 97 here; at stride 1 [32,256,14,14] -> 256 88 / 75, [3,128,10,97] -> 472 150 / 46.
 // *exact: the kernel that the layer runs on without a workspace multiplies in fp32, and gw's error against 64 bits (1.7e-7 whatever
 // the size) is to be no larger here.  The other layers' split-operand kernels (conv_gw_split.hip) are further off than either form of this one.
-static bool tile_wanted(const GwLayer &l, bool *exact)
+// *other_us: what the kernel would take that serves the layer otherwise.  Layers one row high of k = 1, 3 and 5 have one of their own, whose pipeline
+// splits one chunk while it multiplies another (conv1d_gw_split_kernel): [32,256,3136] -> 256, k = 3 250 us there, 296 here, [16,544,6024] -> 128,
+// k = 1 139 / 191, but [16,64,4096] -> 64, k = 3 31 / 28, [64,544,1029] -> 32, k = 5 156 / 98.  Both sides estimate (8 % deviation), and
+// this one, the more exact, is taken up to a tenth more: of 260 random layers it serves two thirds, 0.93 of that kernel's time.
+static bool tile_wanted(const GwLayer &l, bool *exact, double *other_us)
 {
     *exact = true;
+    *other_us = 1e30;
     if (g_opt.conv2d_variant == 100) return true;
     const bool direct = l.kh == 3 && l.kw == 3 && l.sh == 2 && l.sw == 2 && l.Cin % 32 == 0 && l.Cout % 32 == 0 && l.W % 4 == 0 && l.Wo % 4 == 0;
     if (direct) return false;
-    if (conv2d_gw_split_takes(l.Cin, l.W, l.Cout, l.kh, l.kw, l.sh, l.sw, l.pw)) *exact = false;
-    else if (l.H == 1 && l.kh == 1 && l.sw == 1 && l.dil == 1 && conv1d_gw_split_us(l.N, l.Cin, l.W, l.Cout, l.Wo, l.kw, l.pw) > 0) *exact = false;
+    if (conv2d_gw_split_takes(l.Cin, l.W, l.Cout, l.kh, l.kw, l.sh, l.sw, l.pw)) {
+        *exact = false;
+    } else if (l.H == 1 && l.kh == 1 && l.sw == 1 && l.dil == 1) {
+        const double us = conv1d_gw_split_us(l.N, l.Cin, l.W, l.Cout, l.Wo, l.kw, l.pw);
+        if (us > 0) {
+            *exact = false;
+            *other_us = 1.1 * us;
+        }
+    }
     // A few dozen positions: eight products of bf16 pieces are aligned to the largest of them and cut at 2^-24 of it, which is more than the
     // roundings of so short an fp32 sum.  [1,175,9,9] -> 200, 3 x 3 stride 2 (25 positions) 7.0e-8 here, 5.9e-8 there, [1,160,11,11] -> 48 (36)
     // 7.4e-8 / 7.1e-8, [1,32,256] -> 128, k = 3 even.
@@ -739,7 +751,8 @@ int64_t conv2d_gw_workspace(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_
 {
     const GwLayer l = gw_layer(N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw, 1);
     bool exact = false;
-    return tile_wanted(l, &exact) ? conv_gw_tile_workspace(l, exact) : 0;
+    double other_us = 0;
+    return tile_wanted(l, &exact, &other_us) ? conv_gw_tile_workspace(l, exact, other_us) : 0;
 }
 
 int64_t conv1d_gw_workspace(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Lo, int32_t k, int32_t stride, int32_t pad, int32_t dilation,
@@ -748,7 +761,8 @@ int64_t conv1d_gw_workspace(int64_t B, int64_t Cin, int64_t L, int64_t Cout, int
     if (groups != 1 || Cin < 2) return 0;
     const GwLayer l = gw_layer(B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad, dilation);
     bool exact = false;
-    return tile_wanted(l, &exact) ? conv_gw_tile_workspace(l, exact) : 0;
+    double other_us = 0;
+    return tile_wanted(l, &exact, &other_us) ? conv_gw_tile_workspace(l, exact, other_us) : 0;
 }
 
 hipError_t launch_conv2d_grad_weight(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H,
@@ -760,8 +774,9 @@ hipError_t launch_conv2d_grad_weight(const float *x, const float *gy, float *gw,
     if (ws.p && N > 0 && (g_opt.conv2d_variant == 0 || g_opt.conv2d_variant == 100)) {
         const GwLayer l = gw_layer(N, Cin, H, W, Cout, Ho, Wo, kh, kw, sh, sw, ph, pw, 1);
         bool taken = false, exact = false;
-        if (tile_wanted(l, &exact)) {
-            const hipError_t e = launch_conv_gw_tile(x, gy, gw, l, exact, ws, s, &taken);
+        double other_us = 0;
+        if (tile_wanted(l, &exact, &other_us)) {
+            const hipError_t e = launch_conv_gw_tile(x, gy, gw, l, exact, other_us, ws, s, &taken);
             if (taken || e != hipSuccess) return e;
         }
     }
@@ -847,8 +862,9 @@ hipError_t launch_conv1d_grad_weight(const float *x, const float *gy, float *gw,
     if (ws.p && B > 0 && groups == 1 && Cin >= 2 && variant == 0 && (g_opt.conv2d_variant == 0 || g_opt.conv2d_variant == 100)) {
         const GwLayer l = gw_layer(B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad, dilation);
         bool taken = false, exact = false;
-        if (tile_wanted(l, &exact)) {
-            const hipError_t e = launch_conv_gw_tile(x, gy, gw, l, exact, ws, s, &taken);
+        double other_us = 0;
+        if (tile_wanted(l, &exact, &other_us)) {
+            const hipError_t e = launch_conv_gw_tile(x, gy, gw, l, exact, other_us, ws, s, &taken);
             if (taken || e != hipSuccess) return e;
         }
     }

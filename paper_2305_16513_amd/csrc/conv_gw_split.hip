@@ -11,8 +11,8 @@
 // channel, and the 7s + KW consecutive inputs of its input channel that those positions meet under
 // the KW taps of one kernel row (every s-th of them per tap); nothing is staged in LDS and no column matrix is built.  Every fp32
 // value is split into three bf16 pieces by truncation (8 + 8 + 8 bits of mantissa; the pieces sum to
-// the value exactly) and six of the nine piece products are kept — what is dropped is below 2^-23 of
-// the term — so the result has fp32 accuracy at 6/16 of the fp32 matrix instruction's time.
+// the value exactly) and six of the nine piece products are kept — what is dropped is below 2^-21 of
+// the term, on average 2^-25 — so the result has fp32 accuracy at 6/16 of the fp32 matrix instruction's time.
 //
 // A workgroup owns a 64 x 64 block of (co, ci) — one 32 x 32 block and all KH*KW taps per wavefront,
 // 16 accumulator registers per tap — and a share of the positions, cut into tasks of a column of 8
@@ -329,8 +329,9 @@ constexpr int kRowLds = 2 * kStage * 4;                          // bytes: two b
 // slices between the groups of six matrix instructions (one group per tap and 16 positions), so that the vector
 // unit works on the next chunk while the matrix unit works on this one; issue_loads() refills (vx, vg) and is called
 // once they are split, a few groups before the end.  SH: the staged row starts one position early (an even
-// position: pairs loaded as one 64-bit access, PAIR); NA sets of accumulators take turns, so that a matrix
-// instruction seldom waits for the one before it.
+// position: pairs loaded as one 64-bit access, PAIR).  With NA = 2 the leading product of a step goes to one set of accumulators and
+// the other five to the other: the run's sum then takes two roundings of its own size per 16 positions instead of twelve per 32 (error of gw
+// on [32,256,3136] -> 256, k = 3 8.7e-7 -> 3.6e-7, with halved runs 2.6e-7; the time is the same).  k = 5 has the registers for one set.
 template <int KW, int SH, bool PAIR, int NA, int NX, int NG, class Loads>
 __device__ __forceinline__ void row_phase(const unsigned *__restrict__ xc, const unsigned *__restrict__ gc,
                                           unsigned *__restrict__ xn, unsigned *__restrict__ gn, v16f (&acc)[NA][KW],
@@ -408,14 +409,25 @@ __device__ __forceinline__ void row_phase(const unsigned *__restrict__ xc, const
                     Bp[p][i] = ((b + SH) & 1) ? __builtin_amdgcn_perm(d[cur][p][(b + SH) / 2 + i + 1], d[cur][p][(b + SH) / 2 + i], 0x05040302u)
                                               : d[cur][p][(b + SH) / 2 + i];
             const v8bf b1 = __builtin_bit_cast(v8bf, Bp[0]), b2 = __builtin_bit_cast(v8bf, Bp[1]), b3 = __builtin_bit_cast(v8bf, Bp[2]);
-            v16f cc = acc[ks % NA][b];                           // smallest products first
-            cc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3, b1, cc, 0, 0, 0);
-            cc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b2, cc, 0, 0, 0);
-            cc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b3, cc, 0, 0, 0);
-            cc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b1, cc, 0, 0, 0);
-            cc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b2, cc, 0, 0, 0);
-            cc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, cc, 0, 0, 0);
-            acc[ks % NA][b] = cc;
+            v16f hi = acc[0][b];
+            if constexpr (NA == 2) {                             // the leading products to one set, the others to the other
+                v16f lo = acc[NA - 1][b];
+                lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3, b1, lo, 0, 0, 0);
+                lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b2, lo, 0, 0, 0);
+                hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, hi, 0, 0, 0);
+                lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b3, lo, 0, 0, 0);
+                lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b1, lo, 0, 0, 0);
+                lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b2, lo, 0, 0, 0);
+                acc[NA - 1][b] = lo;
+            } else {                                             // smallest products first
+                hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3, b1, hi, 0, 0, 0);
+                hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b2, hi, 0, 0, 0);
+                hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b3, hi, 0, 0, 0);
+                hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b1, hi, 0, 0, 0);
+                hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b2, hi, 0, 0, 0);
+                hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, hi, 0, 0, 0);
+            }
+            acc[0][b] = hi;
             // this group's slice of the splitting, issued behind its matrix instructions
             const int g = ks * KW + b;
 #pragma unroll
@@ -644,6 +656,10 @@ int64_t row_groups(int64_t rows, int RH, int64_t Cin, int64_t L, int64_t Cout, i
         const double t = (double)((n_chunks + sgroups - 1) / sgroups) * 2.0 + (double)(sgroups * blocks) * 4096.0 * k / 350000.0;
         if (t < best_t) { best_t = t; best = sgroups; }
     }
+    // The rounding of a run's sum goes with the root of its length: long runs are halved, a second round of workgroups
+    // (error of gw on [32,512,784] -> 512, k = 3: 3.5e-7 in runs of 104 chunks, 2.5e-7 in runs of 52).  k = 5 has no registers for a sum
+    // of its own for the lesser products, so its runs end sooner.
+    if ((n_chunks + best - 1) / best > (k == 5 ? 32 : 64) && blocks <= cus) best = 2 * cus / blocks;
     if (g_opt.slide_group > 0) best = g_opt.slide_group;
     return best < n_chunks ? best : n_chunks;
 }

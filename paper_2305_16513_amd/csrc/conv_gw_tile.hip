@@ -401,20 +401,13 @@ Groups tap_groups(int kh, int kw)
     return q;
 }
 
-// Runs per block of gw: one workgroup per compute unit, two rounds where that leaves a block few runs.
-int gw_splits(int64_t nblk, int64_t tiles)
-{
-    int64_t n = (256 + nblk - 1) / nblk;
-    if (nblk > 128) n = nblk >= 512 ? 1 : 512 / nblk;
-    return (int)(n < tiles ? n : tiles);
-}
-
-// A layer's plan: the geometry but for its taps' offsets; channel blocks of a workgroup; LDS and workspace bytes.
+// A layer's plan: the geometry but for its taps' offsets; channel blocks of a workgroup; LDS and workspace bytes; estimated us.
 struct GwPlan {
     GwTile g;
     int WM, WN;
     size_t lds;
     int64_t bytes;
+    double us;
 };
 
 // The cheapest plan of at most `limit` bytes of workspace; false: the layer is not this kernel's.
@@ -435,7 +428,7 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
     g.SH = q.rows; g.ls = g.SH < sh ? g.SH : sh;
     if (g.SH < sh && g.SH != 1) return false;
     g.LPI = (int)(Ho - 1) * g.ls + g.SH;
-    const int SW = (q.taps - 1) * dil + 1, SWc = SW < sw ? SW : sw;
+    const int SW = (q.taps - 1) * dil + 1, SWc = SW < sw ? SW : sw, cus = device_cus();
     g.ng = q.ng;
     // Channel blocks of a workgroup, strip width, rows per tile and runs: the smallest estimated time of the longest run (products
     // on two wavefronts per SIMD, staging per unit, a run's end), in cycles.
@@ -463,30 +456,43 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
                 const int tps = (int)((unsigned)(g.NR + rpt - 1) / rpt), ksteps = (rpt * TW + 15) / 16, steps = (ksteps + wk - 1) / wk;
                 if ((int64_t)tps * nstrips >= (1LL << 30)) continue;
                 const int tiles = tps * nstrips;
-                const double tile = steps * (double)(q.rows * q.taps) * 6 * 32 * 2 * 1.2 + 1200 + 500.0 * ((4 * wn * PS + kThreads - 1) / kThreads + wm);
-                int runs = gw_splits(nblk, tiles);
-                if (exact) {
-                    const int adds = q.tb <= 3 ? 1 : steps * (q.tb < 9 ? 1 : 3), most = kMaxAdds / adds > 1 ? kMaxAdds / adds : 1;
-                    const int least = (tiles + most - 1) / most;
-                    runs = runs > least ? runs : least;
-                }
-                const int per = (int)((unsigned)(tiles + runs - 1) / (unsigned)runs), nsplit = (int)((unsigned)(tiles + per - 1) / per);
-                const int64_t bytes = nblk * nsplit * q.tb * wm * wn * 4096;
-                if (bytes > limit || nblk * nsplit >= (1LL << 30)) continue;
-                const double rounds = (double)((nblk * nsplit + 255) / 256);
-                const double c = rounds * (per * tile + 4000 + 6.0 * q.tb * wm * wn * nblk * nsplit / 64);
-                if (!found || c < cost) {
-                    found = true;
-                    cost = c;
-                    best->WM = wm; best->WN = wn;
-                    best->lds = stage > red ? stage : red;
-                    best->bytes = bytes;
-                    g.TW = TW; g.nstrips = nstrips; g.CW = CW; g.LW = LW; g.rpt = rpt; g.PS = PS; g.tps = tps; g.tiles = tiles;
-                    g.ksteps = ksteps; g.per = per; g.nsplit = nsplit; g.cob = (int)cob; g.cib = (int)cib;
+                const int units = (4 * wn * PS + kThreads - 1) / kThreads + wm;
+                const double tile = steps * (double)q.tb * 6 * 32 * 2 * 1.2 + 1200 + 500.0 * units;
+                // Runs per block of gw: a workgroup fills a compute unit (LDS), so as many as there are units, or twice as many,
+                // and never a few more: those would be a round of their own ([4,288,4658] -> 448, k = 1, 18 runs of 15 blocks: 132 us,
+                // 17 runs: 66).
+                for (int r = 1; r <= 2; ++r) {
+                    int64_t least = 1;
+                    if (exact) {
+                        const int adds = q.tb <= 3 ? 1 : steps * (q.tb < 9 ? 1 : 3), most = kMaxAdds / adds > 1 ? kMaxAdds / adds : 1;
+                        least = (tiles + most - 1) / most;
+                    }
+                    int64_t whole = (least * nblk + cus - 1) / cus;      // rounds
+                    if (whole < r) whole = r;
+                    int64_t n = whole * cus / nblk;
+                    if (n < least) n = least;
+                    if (n > tiles) n = tiles;
+                    const int per = (int)((unsigned)(tiles + n - 1) / (unsigned)n), nsplit = (int)((unsigned)(tiles + per - 1) / per);
+                    const int64_t bytes = nblk * nsplit * q.tb * wm * wn * 4096;
+                    if (bytes > limit || nblk * nsplit >= (1LL << 30)) continue;
+                    const double rounds = (double)((nblk * nsplit + cus - 1) / cus);
+                    const double end = q.tb * wm * wn * (double)(nblk * nsplit);
+                    const double c = rounds * (per * tile + 4000 + 6.0 * end / 64);
+                    if (!found || c < cost) {
+                        found = true;
+                        cost = c;
+                        best->WM = wm; best->WN = wn;
+                        best->lds = stage > red ? stage : red;
+                        best->bytes = bytes;
+                        best->us = 6.9 + rounds * (per * (0.269 * steps * q.tb + 1.67 + 0.09 * units) + 0.75) + 0.0026 * end;
+                        g.TW = TW; g.nstrips = nstrips; g.CW = CW; g.LW = LW; g.rpt = rpt; g.PS = PS; g.tps = tps; g.tiles = tiles;
+                        g.ksteps = ksteps; g.per = per; g.nsplit = nsplit; g.cob = (int)cob; g.cib = (int)cib;
+                    }
                 }
             }
         }
     }
+    if (found) best->us += 12e-8 * (double)(N * (Cin * H * W + Cout * Ho * Wo));
     return found;
 }
 
@@ -502,26 +508,26 @@ int64_t conv_gw_tile_most(int64_t Cin, int64_t Cout, int kh, int kw)
         const int wm = 1 + (wmn & 1), wn = 1 + (wmn >> 1);
         if ((wm == 2 && Cout <= 32) || (wn == 2 && Cin <= 32)) continue;
         const int64_t nblk = ((Cout + 32 * wm - 1) / (32 * wm)) * ((Cin + 32 * wn - 1) / (32 * wn)) * q.ng;
-        const int64_t bytes = (nblk > 512 ? nblk : 512) * q.tb * wm * wn * 4096;
+        const int64_t bytes = (nblk > 2 * device_cus() ? nblk : 2 * device_cus()) * q.tb * wm * wn * 4096;
         most = bytes > most ? bytes : most;
     }
     return most;
 }
 
-// Bytes of workspace of a layer; 0: not this kernel's.
-int64_t conv_gw_tile_workspace(const GwLayer &l, bool exact)
+// Bytes of workspace of a layer; 0: not this kernel's, or estimated to take longer than other_us.
+int64_t conv_gw_tile_workspace(const GwLayer &l, bool exact, double other_us)
 {
     GwPlan p;
-    return plan_gw(l, exact, INT64_MAX, &p) ? p.bytes : 0;
+    return plan_gw(l, exact, INT64_MAX, &p) && p.us <= other_us ? p.bytes : 0;
 }
 
-hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, const GwLayer &l, bool exact, Workspace ws, hipStream_t s,
-                               bool *taken)
+hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, const GwLayer &l, bool exact, double other_us, Workspace ws,
+                               hipStream_t s, bool *taken)
 {
     *taken = false;
     if (!ws.p || ((uintptr_t)ws.p & 15)) return hipSuccess;
     GwPlan p;
-    if (!plan_gw(l, exact, ws.bytes, &p)) return hipSuccess;
+    if (!plan_gw(l, exact, ws.bytes, &p) || p.us > other_us) return hipSuccess;
     GwTile &g = p.g;
     const int WM = p.WM, WN = p.WN;
     const size_t lds = p.lds;

@@ -270,9 +270,9 @@ struct GwLayer {
     int kh, kw, sh, sw, ph, pw, dil;                  // (dil: along rows)
 };
 int64_t conv_gw_tile_most(int64_t Cin, int64_t Cout, int kh, int kw);
-int64_t conv_gw_tile_workspace(const GwLayer &l, bool exact);
-hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, const GwLayer &l, bool exact, Workspace ws, hipStream_t s,
-                               bool *taken);
+int64_t conv_gw_tile_workspace(const GwLayer &l, bool exact, double other_us);
+hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, const GwLayer &l, bool exact, double other_us, Workspace ws,
+                               hipStream_t s, bool *taken);
 // Bytes that the adjoints with respect to the weights use, 0: none (conv_grad.hip).
 int64_t conv2d_gw_workspace(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
                             int32_t sw, int32_t ph, int32_t pw);

@@ -301,6 +301,18 @@ def test_grad_weight_workspace_goes_with_the_work(L):
     assert conv2(0, 64, 30, 30, 64, 3, 3, 1, 1, 0, 0) == 0
 
 
+def test_grad_weight_runs_fill_whole_rounds_and_one_row_layers_go_to_the_faster_kernel(L):
+    """A workgroup of the tiled kernel fills a compute unit: a few more workgroups than there are units would be a second round.  (Counted from
+    the partial sums: 64 x 64 channels x 9 taps each.)"""
+    for cin, cout in ((320, 192), (192, 320), (576, 192), (448, 448), (704, 192), (192, 192)):
+        groups = L.sws_conv2d_grad_weight_workspace(32, cin, 56, 56, cout, 3, 3, 1, 1, 1, 1) / (4.0 * 64 * 64 * 9)
+        assert 0 < groups <= 256 or 420 <= groups <= 512, (cin, cout, groups)
+    conv1 = L.sws_conv1d_grad_weight_workspace
+    assert conv1(32, 256, 3136, 256, 3, 1, 1, 1, 1) == 0 and conv1(16, 544, 6024, 128, 1, 1, 0, 1, 1) == 0
+    assert conv1(16, 64, 4096, 64, 3, 1, 0, 1, 1) > 0 and conv1(64, 544, 1029, 32, 5, 1, 2, 1, 1) > 0
+    assert conv1(32, 256, 3136, 250, 3, 1, 1, 1, 1) > 0                      # (channels that kernel does not take)
+
+
 def test_no_memory_for_a_workspace_is_no_error():
     import torch
     from paper_2305_16513_amd import binding as B
