@@ -170,6 +170,8 @@ __device__ __forceinline__ void stage_row_phases(float *dst, const float *__rest
     }
 }
 
+constexpr int kSumTiles = 16 * kWavesPerWg;          // tiles of a workgroup between two totals
+
 // A workgroup takes one output channel and a run of its tiles (all images' rows, `per` of parts runs).
 // DIL: taps d apart; a lane's 16 outputs are then d apart too (phase lane % d, 16 consecutive indices of it) and a tile
 // is 16 * d * (64 / d) outputs.
@@ -203,52 +205,56 @@ __global__ __launch_bounds__(kThreads) void conv1d_thin_grad_weight_kernel(
     const float *Xw = X + (DIL && on ? ph * PPX + 20 * blk : 20 * (DIL ? 0 : lane));
     const float *Gw = G + (DIL && on ? ph * PPG + 20 * blk : 20 * (DIL ? 0 : lane));
 
-    float acc[K4];
+    // Totals are taken every 16 tiles of a wavefront: a lane's sum is then at most 256 terms long however long the run (one sum over a run
+    // of 342 tiles: twice the error on [1024,768,512], which goes with the root of the length; 16 tiles cost as much as 17).
+    for (int64_t js = j0; js < j1; js += kSumTiles) {
+        const int64_t je = js + kSumTiles < j1 ? js + kSumTiles : j1;
+        float acc[K4];
 #pragma unroll
-    for (int t = 0; t < K4; ++t) acc[t] = 0.0f;
-
-    for (int64_t j = j0 + wave; j < j1; j += kWavesPerWg) {
-        const int64_t b = j / tiles_per_row;
-        const int t0 = (int)(j - b * tiles_per_row) * TO;
-        const float *xr = x + (b * Cin + ci) * (int64_t)L;
-        const float *gr = gy + (b * Cout + co) * (int64_t)Lo;
-        if constexpr (DIL) {
-            stage_row_phases(X, xr, t0 - pad, L, TO + (k - 1) * d, d, inv_d, PPX, lane);
-            stage_row_phases(G, gr, t0, Lo, TO, d, inv_d, PPG, lane);
-        } else {
-            stage_row<XS>(X, xr, t0 - pad, L, lane);
-            stage_row<kTileOut / 256>(G, gr, t0, Lo, lane);
-        }
-        wave_lds_sync();
-        float gv[16], xw[4 * NG];
+        for (int t = 0; t < K4; ++t) acc[t] = 0.0f;
+        for (int64_t j = js + wave; j < je; j += kWavesPerWg) {
+            const int64_t b = j / tiles_per_row;
+            const int t0 = (int)(j - b * tiles_per_row) * TO;
+            const float *xr = x + (b * Cin + ci) * (int64_t)L;
+            const float *gr = gy + (b * Cout + co) * (int64_t)Lo;
+            if constexpr (DIL) {
+                stage_row_phases(X, xr, t0 - pad, L, TO + (k - 1) * d, d, inv_d, PPX, lane);
+                stage_row_phases(G, gr, t0, Lo, TO, d, inv_d, PPG, lane);
+            } else {
+                stage_row<XS>(X, xr, t0 - pad, L, lane);
+                stage_row<kTileOut / 256>(G, gr, t0, Lo, lane);
+            }
+            wave_lds_sync();
+            float gv[16], xw[4 * NG];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const v4f g = *(const v4f *)(Gw + 4 * u);
-            gv[4 * u] = g.x; gv[4 * u + 1] = g.y; gv[4 * u + 2] = g.z; gv[4 * u + 3] = g.w;
-        }
-        if (DIL && !on) {                            // 64 % d lanes have no outputs of their own
+            for (int u = 0; u < 4; ++u) {
+                const v4f g = *(const v4f *)(Gw + 4 * u);
+                gv[4 * u] = g.x; gv[4 * u + 1] = g.y; gv[4 * u + 2] = g.z; gv[4 * u + 3] = g.w;
+            }
+            if (DIL && !on) {                            // 64 % d lanes have no outputs of their own
 #pragma unroll
-            for (int e = 0; e < 16; ++e) gv[e] = 0.0f;
-        }
+                for (int e = 0; e < 16; ++e) gv[e] = 0.0f;
+            }
 #pragma unroll
-        for (int u = 0; u < NG; ++u) {
-            const v4f g = *(const v4f *)(Xw + 20 * (u >> 2) + 4 * (u & 3));
-            xw[4 * u] = g.x; xw[4 * u + 1] = g.y; xw[4 * u + 2] = g.z; xw[4 * u + 3] = g.w;
+            for (int u = 0; u < NG; ++u) {
+                const v4f g = *(const v4f *)(Xw + 20 * (u >> 2) + 4 * (u & 3));
+                xw[4 * u] = g.x; xw[4 * u + 1] = g.y; xw[4 * u + 2] = g.z; xw[4 * u + 3] = g.w;
+            }
+#pragma unroll
+            for (int t = 0; t < K4; ++t) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[t] = __builtin_fmaf(gv[e], xw[e + t], acc[t]);
+            }
+            wave_lds_sync();                             // the next tile overwrites X and G
         }
+        // ---- one total per tap: across lanes, then across the workgroup's wavefronts, then to memory
 #pragma unroll
         for (int t = 0; t < K4; ++t) {
+            float v = acc[t];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[t] = __builtin_fmaf(gv[e], xw[e + t], acc[t]);
+            for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+            if (lane == 0) red[wave][t] = js == j0 ? v : red[wave][t] + v;
         }
-        wave_lds_sync();                             // the next tile overwrites X and G
-    }
-    // ---- one total per tap: across lanes, then across the workgroup's wavefronts, then to memory
-#pragma unroll
-    for (int t = 0; t < K4; ++t) {
-        float v = acc[t];
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-        if (lane == 0) red[wave][t] = v;
     }
     __syncthreads();
     if ((int)threadIdx.x < k) {

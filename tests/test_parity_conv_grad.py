@@ -477,3 +477,16 @@ def test_grad_weight_one_channel_per_output_spaced_taps(B, b, c, length, k, dil,
     """One input channel per output channel with spaced taps (phase-major tiles) and runs of tiles that end inside a row."""
     for cog in (1, 2):
         _check_gw(B, (b, c, length, c * cog, k, 1, pad, dil, c), 90 + k, integer)
+
+
+@pytest.mark.parametrize("dil", [1, 2])
+def test_grad_weight_of_thin_layers_sums_long_runs_in_parts(B, dil):
+    """512 rows of 16 positions per channel in one run, every product 1 + 3 * 2^-16: below 2^8 such terms add up exactly in fp32, and one sum over
+    the run (2048 terms per lane) drifts by 2e-5.  Bound: half an ulp for each of the 8 totals of a wavefront, the 4 wavefronts and memory."""
+    import torch
+    x = torch.ones(512, 2048, 16 * dil, device="cuda")
+    gy = torch.zeros(512, 2048, 16 * dil, device="cuda")
+    gy[:, :, :16] = 1.0 + 3 * 2.0 ** -16
+    gw = B.sws_conv1d_grad_weight(x, gy, 1, 1, 0, dil, 2048).double()
+    want = 512 * 16 * (1.0 + 3 * 2.0 ** -16)
+    assert ((gw - want).abs() <= 13 * 2.0 ** -24 * want).all(), ((gw - want).abs().max() / want).item()
