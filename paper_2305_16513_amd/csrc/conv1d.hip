@@ -608,8 +608,10 @@ hipError_t launch_conv1d(const float *x, const float *wgt, float *y, int64_t B, 
             const hipError_t e = launch_conv2d_split(x, wgt, y, B, Cin, 1, L, Cout, 1, Lo, 1, k, 1, stride, 0, pad, 1, dilation, s,
                                                      &taken_s, wadj, ws);
             if (taken_s || e != hipSuccess) return e;
+            // refused (less memory than it asks for, rows beyond its offsets): the call is the one without a workspace
+            if (split_ok && valu_ok && prefer_few(Cin, Cout, k, stride > 1, false)) variant = few_ok ? 6 : 7;
         }
-        if (!wadj && stride == 1 && dilation == 1) {
+        if (variant == 3 && !wadj && stride == 1 && dilation == 1) {
             // a few dozen channels: the split-operand kernel that streams the input straight from memory
             const hipError_t e = launch_conv1d_split(x, wgt, y, B, Cin, L, Cout, Lo, k, pad, s, &taken_s);
             if (taken_s || e != hipSuccess) return e;

@@ -153,6 +153,30 @@ def test_without_workspace_and_with_one_too_small(B):
         assert_bit_exact(to_host(y), ref, "workspace of %d bytes" % size)
 
 
+@pytest.mark.parametrize("cin,cout,k,stride", [(60, 32, 3, 1), (60, 32, 3, 2), (20, 24, 9, 1), (64, 64, 3, 1), (32, 64, 5, 1), (9, 70, 31, 1), (18, 33, 7, 3)])
+@pytest.mark.parametrize("adjoint", [False, True])
+def test_a_workspace_too_small_gives_the_bits_of_none(B, cin, cout, k, stride, adjoint):
+    """1-D layers, where another kernel is preferred when there is no workspace: lending too little or at a crooked address takes that one too."""
+    import ctypes
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(cin + k)
+    b, length = 3, 700
+    lo = (length - k) // stride + 1
+    x = torch.randn(b, cout if adjoint else cin, lo if adjoint else length, generator=gen, device="cuda")
+    wgt = torch.randn(cout, cin, k, generator=gen, device="cuda")
+    lent = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    entry = B.lib().sws_conv1d_grad_input_ws if adjoint else B.lib().sws_conv1d_ws
+    got = []
+    for at, size in ((None, 0), (lent.data_ptr(), 64), (lent.data_ptr() + 4, lent.numel() - 4)):
+        y = torch.full((b, cin if adjoint else cout, length if adjoint else lo), 7.0, device="cuda")
+        rc = entry(x.data_ptr(), wgt.data_ptr(), y.data_ptr(), b, cin, length, cout, k, stride, 0, 1, 1, at, size,
+                   ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+        got.append(to_host(y))
+    assert_bit_exact(got[1], got[0], "64 bytes")
+    assert_bit_exact(got[2], got[0], "not on a 16-byte boundary")
+
+
 def test_graph_replay(B):
     """Captured in a HIP graph (the workspace comes from the graph's pool) and replayed with eager work between."""
     import torch
