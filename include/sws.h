@@ -282,7 +282,7 @@ sws_status sws_conv1d_16(sws_dtype dtype, const void *x, const float *wgt, void 
  * gy).  gx and gw are overwritten, not accumulated into.  gw is summed with atomic adds whose
  * order is not fixed: its last bits may differ between runs.  On dense layers (groups = 1, stride and
  * dilation 1, k = 1, 3 or 5, channel counts in multiples of 32) a product of gw is evaluated as six
- * exact products of bf16 pieces of its fp32 operands, which drops less than 2^-23 of it (inputs
+ * exact products of bf16 pieces of its fp32 operands, which drops less than 2^-21 of it, on average 2^-25 (inputs
  * must be finite there: an infinite operand splits into inf and NaN).
  *   gy : device [B,Cout,Lo]   wgt, gw : device [Cout,Cin/groups,k]   x, gx : device [B,Cin,L]
  * Errors: as sws_conv1d. */
@@ -302,7 +302,7 @@ sws_status sws_conv1d_grad_weight(const float *x, const float *gy, float *gw, in
  * Accumulation is fp32 and the summation order is unspecified; every output is within
  * 1e-5 * sum|terms| of the exact sum.  On some layers (64 input channels, 3 x 3, stride 1) a product
  * x * w is evaluated as six exact products of bf16 pieces of the fp32 operands, which drops less than
- * 2^-23 of it; products of integers below 2^8 stay exact.  (The same holds for sws_conv1d on dense
+ * 2^-21 of it, on average 2^-25; products of integers below 2^8 stay exact.  (The same holds for sws_conv1d on dense
  * layers of 32 / 64 input channels.)
  * Errors: as sws_conv1d. */
 sws_status sws_conv2d(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin,
@@ -337,7 +337,7 @@ sws_status sws_conv2d_padded(const float *x, const float *wgt, float *y, int64_t
  * whose order is not fixed.  Accuracy as for sws_conv2d; on some layers (3 x 3 at stride 1 or 2, and
  * 1 x 1, 1 x 3, 1 x 5 at stride 1 without padding above and below, channel counts in multiples of 32)
  * a product of gw is evaluated as six exact products of bf16 pieces of its fp32
- * operands, which drops less than 2^-23 of it (inputs must be finite there: an infinite operand splits
+ * operands, which drops less than 2^-21 of it, on average 2^-25 (inputs must be finite there: an infinite operand splits
  * into inf and NaN).
  *   gy : device [N,Cout,Ho,Wo]   wgt, gw : device [Cout,Cin,kh,kw]   x, gx : device [N,Cin,H,W]
  * Errors: as sws_conv2d. */

@@ -8,7 +8,7 @@
 // the streaming operand and is never staged: a lane owns one output position and eight input channels, so its
 // operand is eight loads of one element each, coalesced across the 32 lanes of a half-wavefront; all loads of a
 // tile of 32 positions are issued up front and converted (split, packed with v_perm) as they arrive.  Six of the
-// nine piece products are kept — what is dropped is below 2^-23 of a term — so the result has fp32 accuracy at
+// nine piece products are kept — what is dropped is below 2^-21 of a term, on average 2^-25 — so the result has fp32 accuracy at
 // 6/16 of the fp32 matrix instruction's time.  Output registers hold one output channel and 32 consecutive
 // positions: stores are 128-byte runs.
 #include "sws_internal.h"

@@ -6,7 +6,7 @@
 //
 // is a sum of matrix products over shifted views of the same input, the sliding sum over taps.  An fp32 number
 // is the exact sum of three bf16 numbers and a product of two bf16 numbers is exact in fp32; of the nine piece
-// products of x * w the three smallest are below 2^-23 of the product, the other six are accumulated in fp32 by
+// products of x * w the three smallest are below 2^-22 of the product in all, the other six are accumulated in fp32 by
 // v_mfma_f32_32x32x16_bf16: 6 instructions of 32 cycles per 16 channels, tap and 32 x 32 outputs where the fp32
 // matrix instruction needs 8 of 64 cycles.
 //
@@ -107,7 +107,8 @@ __global__ __launch_bounds__(256) void split_weights_kernel(const float *__restr
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const float v = f[e + u];
-            const __bf16 f1 = (__bf16)v;
+            // (to nearest, but cut where that would be infinity)
+            const __bf16 f1 = (__bf16)(__builtin_fabsf(v) < 0x1.ffp127f ? v : __uint_as_float(__float_as_uint(v) & 0xffff0000u));
             const float r1 = v - (float)f1;
             const __bf16 f2 = (__bf16)r1;
             const __bf16 f3 = (__bf16)(r1 - (float)f2);

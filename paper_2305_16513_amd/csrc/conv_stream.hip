@@ -38,7 +38,7 @@
 // Split operands (template flag X3, images only).  An fp32 number is the exact sum of three bf16
 // numbers (the leading, middle and last 8 bits of its mantissa, each the upper half of an fp32 word),
 // and a product of two bf16 numbers is exact in fp32.  Of the nine piece products of x * w the three
-// smallest are below 2^-23 of the product; the other six, accumulated in fp32 by
+// smallest are below 2^-22 of the product in all (the weights' pieces are rounded, the input's cut); the other six, accumulated in fp32 by
 // v_mfma_f32_32x32x16_bf16, give the fp32 result to within less than one fp32 rounding per term — in
 // 6 instructions of 32 cycles per 16 channels and tap instead of 8 of 64 cycles.  The input is split when
 // a line is written to the ring (three bf16 planes per position, 384 bytes for 64 channels, 16-byte
@@ -286,7 +286,8 @@ __global__ __launch_bounds__(kThreads) void conv_stream_kernel(const float *__re
 #pragma unroll
                 for (int t = 0; t < KT; ++t) {
                     const float f = rd[WADJ ? KT - 1 - t : t];
-                    const __bf16 f1 = (__bf16)f;
+                    // (to nearest, but cut where that would be infinity)
+                    const __bf16 f1 = (__bf16)(__builtin_fabsf(f) < 0x1.ffp127f ? f : __uint_as_float(__float_as_uint(f) & 0xffff0000u));
                     const float r1 = f - (float)f1;
                     const __bf16 f2 = (__bf16)r1;
                     w3[t][0][e] = f1;

@@ -1,9 +1,10 @@
 """The split-operand convolution kernel for any dense layer (conv_split.hip): every tile configuration at the edges of
 its tiles, against the C oracle.
 
-Tolerance: an output is a sum of n = Cin*kh*kw products, each evaluated as six exact piece products (what is dropped is
-below 2^-23 of it), accumulated with one rounding of the running sum per 16 products: |err| <= (2^-23 + (n/16 + 8) *
-2^-24) * sum|terms|, and below 2e-6 of it for the n <= 500 used here.
+Tolerance: an output is a sum of n products (Cin*kh*kw, adjoint Cout*kh*kw, at most 1170 here), each evaluated as six exact piece
+products (what is dropped is below 2^-22 of it), accumulated with two roundings of the running sum per 16 products and a few at the
+end.  Each is at most 2^-24 of sum|terms| and their signs differ, so twice the root of their number counts:
+|err| <= (2^-22 + 2 sqrt(n/8 + 8) 2^-24) * sum|terms|, 0.6e-6 of it for n = 9 and 1.8e-6 for 1170; 2e-6 is used throughout.
 """
 import numpy as np
 import pytest
@@ -134,6 +135,50 @@ def test_information_in_the_third_piece(B):
     ref, _ = oracle.conv2d(x, wgt, 1, 1, 1, 1)
     y = to_host(B.sws_conv2d(to_gpu(x), to_gpu(wgt), 1, 1, 1, 1)).astype(np.float64)
     assert np.abs(y - ref).max() <= 2.0 ** -23
+
+
+def test_weights_at_the_end_of_the_range(B):
+    """Weights up to the largest finite number (their leading piece must not round to infinity) against small inputs."""
+    # (both the kernel for any layer and, with 64 channels and enough positions, the one that keeps its weights in registers)
+    big = np.array([3.4028235e38, -3.4028235e38, 3.3961775e38, 3.39e38, -1.0, 2.0 ** 127, float.fromhex("0x1.ff0001p127"), float.fromhex("-0x1.feffffp127")], np.float32)
+    rng = np.random.default_rng(4)
+    for c, (n, h, w) in ((32, (2, 9, 11)), (64, (2, 56, 56))):
+        wgt = np.zeros((c, c, 3, 3), np.float32)
+        for co in range(c):
+            wgt[co, co, co % 3, 1] = big[co % 8]
+        x = (rng.standard_normal((n, c, h, w)) * 2.0 ** -110).astype(np.float32)
+        for var in (0, 18 if c == 64 else 0):         # (18: the streaming kernel on a small problem)
+            B.sws_set_option("conv2d_variant", var)
+            for ref, got in ((oracle.conv2d(x, wgt, 1, 1, 1, 1)[0], B.sws_conv2d(to_gpu(x), to_gpu(wgt), 1, 1, 1, 1)),
+                             (oracle.conv2d_grad_input(x, wgt, h, w, 1, 1, 1, 1)[0], B.sws_conv2d_grad_input(to_gpu(x), to_gpu(wgt), h, w, 1, 1, 1, 1))):
+                assert np.abs(to_host(got).astype(np.float64) - ref).max() <= 2.0 ** -21 * np.abs(ref).max(), (c, var)
+
+
+def test_what_the_dropped_products_may_reach(B):
+    """One product per output: three of the nine piece products are dropped, below 2^-21 of it where both operands are cut and 2^-22
+    where the weights are rounded to nearest, and the rest takes a rounding or two.  Mantissas whose second and third pieces are
+    as large as they can be, and random ones."""
+    rng = np.random.default_rng(6)
+    v = np.concatenate([[1 + 2.0 ** -7 - 2.0 ** -23, 1 + 2.0 ** -8 - 2.0 ** -23, 2 - 2.0 ** -23, 1 + 2.0 ** -7 - 2.0 ** -15 - 2.0 ** -23],
+                        1.0 + rng.integers(0, 1 << 23, 4092) * 2.0 ** -23]).astype(np.float32)
+    exact = v.astype(np.float64)
+    # gw[co][0] = gy[co] * x for one position (kernel 100: the tiled one also for so few)
+    B.sws_set_option("conv2d_variant", 100)
+    for first in v[:4]:
+        x = np.full((1, 2, 1, 1), first, np.float32)
+        gw = to_host(B.sws_conv2d_grad_weight(to_gpu(x), to_gpu(v[:2048].reshape(1, 2048, 1, 1)), 1, 1)).astype(np.float64)[:, 0, 0, 0]
+        off = np.abs(gw / (exact[:2048] * np.float64(first)) - 1)
+        assert off.max() <= 2.0 ** -21 + 2.0 ** -23, off.max() * 2.0 ** 23
+    B.sws_set_option("conv2d_variant", 0)
+    # y[co] = wgt[co][c] * x[c], one non-zero input channel of 64, 3 x 3 so that the split-operand kernel takes it
+    for first in v[:4]:
+        x = np.zeros((1, 64, 1, 40), np.float32)
+        x[0, 5] = first
+        wgt = np.zeros((2048, 64, 1, 3), np.float32)
+        wgt[:, 5, 0, 1] = v[:2048]
+        y = to_host(B.sws_conv2d(to_gpu(x), to_gpu(wgt), 1, 1, 0, 1)).astype(np.float64)[0, :, 0, 7]
+        off = np.abs(y / (exact[:2048] * np.float64(first)) - 1)
+        assert off.max() <= 2.0 ** -22 + 2.0 ** -23, off.max() * 2.0 ** 23
 
 
 def test_without_workspace_and_with_one_too_small(B):
