@@ -166,12 +166,10 @@ hipError_t launch_split(const float *x, const float *wgt, float *y, int64_t B, i
     const int64_t cap = (int64_t)device_cus() / co_blocks > 0 ? (int64_t)device_cus() / co_blocks : 1;
     if (wgs > cap) wgs = cap;
     if (wgs < 1) wgs = 1;
-    static std::atomic<int> raised{0};
-    if (lds > 64 * 1024 && !raised.load(std::memory_order_relaxed)) {
-        const hipError_t e = hipFuncSetAttribute((const void *)conv1d_split_kernel<NC, K>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (lds > 64 * 1024) {
+        static std::atomic<uint64_t> raised{0};
+        const hipError_t e = raise_lds((const void *)conv1d_split_kernel<NC, K>, 160 * 1024, raised);
         if (e != hipSuccess) return e;
-        raised.store(1, std::memory_order_relaxed);
     }
     hipLaunchKernelGGL((conv1d_split_kernel<NC, K>), dim3((unsigned)wgs, (unsigned)co_blocks), dim3(kThreads), lds, s, x, wgt, y,
                        L, Cout, Lo, pad, tiles_per_row, n_tiles);

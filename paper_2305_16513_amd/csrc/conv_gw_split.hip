@@ -702,13 +702,9 @@ hipError_t launch_conv1d_gw_split(const float *x, const float *gy, float *gw, in
     const int shift = pair ? (pad & 1) : 0;
 #define SWS_GW1(KW_, SH_, PAIR_)                                                                                   \
     do {                                                                                                           \
-        static std::atomic<int> raised{0};                                                                         \
-        if (!raised.load(std::memory_order_relaxed)) {                                                             \
-            const hipError_t e = hipFuncSetAttribute((const void *)conv1d_gw_split_kernel<KW_, SH_, PAIR_>,        \
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kRowLds);         \
-            if (e != hipSuccess) return e;                                                                         \
-            raised.store(1, std::memory_order_relaxed);                                                            \
-        }                                                                                                          \
+        static std::atomic<uint64_t> raised{0};                                                                    \
+        const hipError_t e = raise_lds((const void *)conv1d_gw_split_kernel<KW_, SH_, PAIR_>, kRowLds, raised);     \
+        if (e != hipSuccess) return e;                                                                             \
         hipLaunchKernelGGL((conv1d_gw_split_kernel<KW_, SH_, PAIR_>), dim3((unsigned)grid, (unsigned)blocks), dim3(kRowThreads), \
                            kRowLds, s, x, gy, gw, (int)Cin, (int)L, (int)Cout, (int)Lo, pad, RH, x_cs, gy_cs, cpr, n_chunks, per, \
                            ci_blocks);                                                                             \

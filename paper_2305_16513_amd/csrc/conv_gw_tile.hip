@@ -354,13 +354,9 @@ hipError_t launch_gw1(const float *x, const float *gy, float *gw, float *ws, con
     constexpr int UX = 4;
     const int nblk = g.cob * g.cib * g.ng;
     if (lds > 64 * 1024) {
-        static std::atomic<bool> raised{false};       // (the attribute is per function; setting it twice does no harm)
-        if (!raised.load(std::memory_order_relaxed)) {
-            const hipError_t e = hipFuncSetAttribute((const void *)conv_gw_tile_kernel<TB, WM, WN, UX, FAST>,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) return e;
-            raised.store(true, std::memory_order_relaxed);
-        }
+        static std::atomic<uint64_t> raised{0};
+        const hipError_t e = raise_lds((const void *)conv_gw_tile_kernel<TB, WM, WN, UX, FAST>, 160 * 1024, raised);
+        if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((conv_gw_tile_kernel<TB, WM, WN, UX, FAST>), dim3((unsigned)xcd_grid((int64_t)g.nsplit * nblk)), dim3(kThreads), lds,
                        s, x, gy, ws, g);

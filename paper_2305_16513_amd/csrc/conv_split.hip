@@ -518,12 +518,9 @@ hipError_t launch_steps(const float *x, const v4u *ws, float *y, const SplitGeom
     constexpr Cfg c = kCfg[I];
     auto k = conv_split_kernel<c.mb, c.nb, c.wm, c.wn, c.wk, c.u, c.nph, c.wpe, S>;
     if (lds > 64 * 1024) {
-        static std::atomic<bool> raised{false};       // (the attribute is per function; setting it twice does no harm)
-        if (!raised.load(std::memory_order_relaxed)) {
-            const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) return e;
-            raised.store(true, std::memory_order_relaxed);
-        }
+        static std::atomic<uint64_t> raised{0};
+        const hipError_t e = raise_lds((const void *)k, 160 * 1024, raised);
+        if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * c.wm * c.wn * c.wk), lds, s, x, ws, y, g);
     return hipGetLastError();

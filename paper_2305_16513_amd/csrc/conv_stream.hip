@@ -589,12 +589,10 @@ template <int CIN, int KH, int KW, bool MODE_B, int CGS, bool WADJ, bool X3 = fa
 hipError_t launch_stream1(const float *x, const float *wgt, float *y, const StreamGeom &g, size_t lds, int grid,
                          hipStream_t s)
 {
-    static bool raised = false;                       // (set once per process; the attribute is per function)
-    if (!raised && lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void *)conv_stream_kernel<CIN, KH, KW, MODE_B, CGS, WADJ, X3>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (lds > 64 * 1024) {
+        static std::atomic<uint64_t> raised{0};
+        const hipError_t e = raise_lds((const void *)conv_stream_kernel<CIN, KH, KW, MODE_B, CGS, WADJ, X3>, 160 * 1024, raised);
         if (e != hipSuccess) return e;
-        raised = true;
     }
     hipLaunchKernelGGL((conv_stream_kernel<CIN, KH, KW, MODE_B, CGS, WADJ, X3>), dim3((unsigned)grid), dim3(kThreads), lds, s, x,
                        wgt, y, g);

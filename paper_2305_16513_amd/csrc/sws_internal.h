@@ -127,6 +127,19 @@ inline int max_origin_shift(int64_t lo, int line)
     return line - b;
 }
 
+// A kernel's limit of dynamic LDS raised to `bytes`, once per device (`done`: the caller's, one bit a device; raising it twice does no harm).
+inline hipError_t raise_lds(const void *kernel, int bytes, std::atomic<uint64_t> &done)
+{
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev < 64 ? 1ull << dev : 0;
+    if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+    const hipError_t a = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (a == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+    return a;
+}
+
 // Device memory a caller lends a dense convolution for the duration of the call (stream-ordered); empty: none.
 struct Workspace {
     void *p = nullptr;
