@@ -172,8 +172,14 @@ def _scratch(n, like, stream):
         return None, None, 0
     try:
         if stream is None:
+            if _device is not None and like.get_device() != _device():       # another device's allocator does not know this stream
+                return None, None, 0
             t = like.new_empty(n // 4)
         else:
+            if not isinstance(stream, torch.cuda.Stream):                    # anything with the handle of a stream
+                stream = torch.cuda.ExternalStream(stream.cuda_stream, device=like.device)
+            if stream.device != like.device:
+                return None, None, 0
             with torch.cuda.stream(stream):
                 t = like.new_empty(n // 4)
     except torch.cuda.OutOfMemoryError:

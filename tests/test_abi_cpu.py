@@ -313,7 +313,7 @@ def test_grad_weight_runs_fill_whole_rounds_and_one_row_layers_go_to_the_faster_
     assert conv1(32, 256, 3136, 250, 3, 1, 1, 1, 1) > 0                      # (channels that kernel does not take)
 
 
-def test_no_memory_for_a_workspace_is_no_error():
+def test_no_memory_for_a_workspace_is_no_error(monkeypatch):
     import torch
     from paper_2305_16513_amd import binding as B
 
@@ -321,8 +321,27 @@ def test_no_memory_for_a_workspace_is_no_error():
         def new_empty(self, n):
             raise torch.cuda.OutOfMemoryError("no %d floats" % n)
 
+        def get_device(self):
+            return 0
+
+    monkeypatch.setattr(B, "_device", lambda: 0)
     assert B._scratch(1 << 20, Full(), None) == (None, None, 0)
     assert B._scratch(0, Full(), None) == (None, None, 0)
+
+
+def test_a_tensor_of_another_device_gets_no_workspace(monkeypatch):
+    """Memory of device 1 would be given back on device 1's stream while the call still runs on device 0's."""
+    from paper_2305_16513_amd import binding as B
+
+    class Elsewhere:
+        def new_empty(self, n):
+            raise AssertionError("allocated")
+
+        def get_device(self):
+            return 1
+
+    monkeypatch.setattr(B, "_device", lambda: 0)
+    assert B._scratch(1 << 20, Elsewhere(), None) == (None, None, 0)
 
 
 def test_grad_weight_workspace_and_argument_checks(L):

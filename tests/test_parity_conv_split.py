@@ -222,6 +222,28 @@ def test_a_workspace_too_small_gives_the_bits_of_none(B, cin, cout, k, stride, a
     assert_bit_exact(got[2], got[0], "not on a 16-byte boundary")
 
 
+def test_any_object_with_a_stream_handle(B):
+    """`stream` may be a torch Stream or anything with its handle, the default stream's too; the workspace is the stream's."""
+    import types
+    import torch
+    x = to_gpu(workloads.integer_valued((4, 40, 13, 11), -3, 3, 8))
+    wgt = to_gpu(workloads.integer_valued((48, 40, 3, 3), -3, 3, 9))
+    g = to_gpu(workloads.integer_valued((4, 48, 13, 11), -3, 3, 10))
+
+    def all_three(**kw):
+        return (B.sws_conv2d(x, wgt, 1, 1, 1, 1, **kw), B.sws_conv2d_grad_input(g, wgt, 13, 11, 1, 1, 1, 1, **kw),
+                B.sws_conv2d_grad_weight(x, g, 3, 3, 1, 1, 1, 1, **kw))
+
+    want = all_three()
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for stream in (side, types.SimpleNamespace(cuda_stream=side.cuda_stream), types.SimpleNamespace(cuda_stream=0), torch.cuda.default_stream()):
+        got = all_three(stream=stream)
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
+
+
 def test_graph_replay(B):
     """Captured in a HIP graph (the workspace comes from the graph's pool) and replayed with eager work between."""
     import torch
