@@ -30,6 +30,26 @@ def automatic(B):
     B.sws_set_option("conv2d_variant", 0)
 
 
+@pytest.fixture
+def lent(B, monkeypatch):
+    """Every workspace that a test lends, filled with a value that no kernel leaves throughout: taken(t) tells whether one was used."""
+    given, scratch = [], B._scratch
+
+    def fill(n, like, stream):
+        t, at, size = scratch(n, like, stream)
+        if t is not None:
+            t.fill_(12345.0)
+            given.append(t)
+        return t, at, size
+
+    monkeypatch.setattr(B, "_scratch", fill)
+    return given
+
+
+def _taken(t):
+    return bool((t != 12345.0).any())
+
+
 def _guarded(shape):
     """A contiguous tensor between two bands of a value that no output takes."""
     import torch
@@ -101,26 +121,32 @@ def test_chosen_configuration(B, case):
 
 
 @pytest.mark.parametrize("cfg", FORWARD)
-def test_every_forward_configuration(B, cfg):
+def test_every_forward_configuration(B, cfg, lent):
     """(A configuration whose tile does not fit a shape leaves it to the kernels without a workspace.)"""
     B.sws_set_option("conv2d_variant", 100 + cfg)
     for i, case in enumerate(CASES):
         _check(B, case, 20 + i, i % 2 == 0, adjoint=case[7] == 1)
+    taken = [_taken(t) for t in lent]
+    assert sum(taken) >= 19, taken                    # of 27 calls (the smallest tiles do not hold the widest lines)
 
 
 @pytest.mark.parametrize("cfg", PHASES)
-def test_every_phase_configuration(B, cfg):
+def test_every_phase_configuration(B, cfg, lent):
     B.sws_set_option("conv2d_variant", 100 + cfg)
     for i, case in enumerate(CASES):
         if case[7] == 2:
             _check(B, case, 50 + i, i % 2 == 0, forward=False)
+    taken = [_taken(t) for t in lent]
+    assert sum(taken) >= 6, taken                     # of 7 calls
 
 
-def test_many_chunks_and_large_tiles(B):
+def test_many_chunks_and_large_tiles(B, lent):
     """Several chunks of input channels through both staging buffers, tiles of every configuration filled."""
     for cfg in FORWARD:
         B.sws_set_option("conv2d_variant", 100 + cfg)
         _check(B, (2, 150, 130, 17, 19, 3, 3, 1, 1), 70, True)
+    taken = [_taken(t) for t in lent]
+    assert len(taken) == 2 * len(FORWARD) and all(taken[:16]), taken  # (likewise 8 and 9)
     B.sws_set_option("conv2d_variant", 0)
     _check(B, (2, 100, 70, 21, 18, 3, 3, 2, 1), 71, True)
 
@@ -298,7 +324,7 @@ GW_CASES = CASES + [
 
 @pytest.mark.parametrize("integer", [True, False])
 @pytest.mark.parametrize("case", GW_CASES)
-def test_grad_weight_through_transposing_reads(B, case, integer):
+def test_grad_weight_through_transposing_reads(B, case, integer, lent):
     n, cin, cout, h, w, kh, kw, s, p = case
     ph, sh = (p, s) if h > 1 else (0, 1)
     rng = np.random.default_rng(41)
@@ -313,8 +339,9 @@ def test_grad_weight_through_transposing_reads(B, case, integer):
     if integer:
         assert_bit_exact(to_host(gw), ref, "gw %s" % (case,))
     else:
-        # sums of up to n*ho*wo = 18200 products: a rounding of the running sum per 16 products and run of tiles
+        # sums of up to n*ho*wo = 36400 products, by a few hundred positions per run: the bound above, 2^-21 dropped
         assert_within_tol(to_host(gw), ref, mag, "gw %s" % (case,), tol=SPLIT_TOL)
+    assert len(lent) == 1 and _taken(lent[0])
     assert (flat[:64] == 12345.0).all() and (flat[-64:] == 12345.0).all()
 
 
