@@ -22,10 +22,6 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ unsigned pack_hi(float lo, float hi)     // the upper halves of two floats: two bf16
-{
-    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-}
 __device__ __forceinline__ void split3(float v, float &p2, float &p3)   // v = upper(v) + upper(p2) + upper(p3) ...
 {
     p2 = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);

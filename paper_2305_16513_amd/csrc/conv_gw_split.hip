@@ -35,11 +35,6 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
-// the upper halves of two floats as one register of two bf16 (lo in the low half)
-__device__ __forceinline__ unsigned pack_hi(float lo, float hi)
-{
-    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-}
 // v = p1 + p2 + p3 with every piece's significant bits in the upper half of a float
 __device__ __forceinline__ void split3(float v, float &p2, float &p3)
 {

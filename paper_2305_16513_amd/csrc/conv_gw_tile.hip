@@ -69,20 +69,6 @@ struct GwTile {
     unsigned short tapoff[kMaxTaps];                  // tap -> staged positions from a position's base
 };
 
-__device__ __forceinline__ int fdiv(int x, float inv_d) { return (int)(((float)x + 0.5f) * inv_d); }    // 0 <= x < 2^20
-
-__device__ __forceinline__ unsigned pack_hi(float lo, float hi)
-{
-    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-}
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
-}
-
-constexpr unsigned kNowhere = 0x80000000u;            // beyond every descriptor: such loads return zero
-
 // a 16-byte unit: eight channels' values, split into three pieces, to dst, dst + step, dst + 2 step
 __device__ __forceinline__ void put_unit(char *dst, int step, const float (&v)[8])
 {

@@ -72,14 +72,6 @@ struct PrepGeom {
     unsigned short wtap[kMaxSteps];                   // tap -> element
 };
 
-__device__ __forceinline__ int fdiv(int x, float inv_d) { return (int)(((float)x + 0.5f) * inv_d); }    // 0 <= x < 2^20
-
-// the upper halves of two floats as one register of two bf16 (lo in the low half)
-__device__ __forceinline__ unsigned pack_hi(float lo, float hi)
-{
-    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-}
-
 // One wavefront per (32 output channels, 16 contraction channels, tap): lane (l32, half) writes W[co = l32][8 half + e].
 // Rounding to nearest in every piece: the pieces sum to the weight exactly and the dropped products are smallest.
 __global__ __launch_bounds__(256) void split_weights_kernel(const float *__restrict__ wgt, v4u *__restrict__ ws, PrepGeom g)
@@ -124,14 +116,6 @@ __global__ __launch_bounds__(256) void split_weights_kernel(const float *__restr
 #pragma unroll
     for (int q = 0; q < 3; ++q) ws[step * (kStepBytes / 16) + q * 64 + lane] = (v4u){p[q][0], p[q][1], p[q][2], p[q][3]};
 }
-
-// One buffer descriptor: loads beyond `bytes` return zero.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
-}
-
-constexpr unsigned kNowhere = 0x80000000u;            // beyond every descriptor
 
 // U: staged units (eight channels of one position) per thread.  S: steps per chunk and wavefront when that number is
 // compiled in (the chunk is then straight-line code: the next chunk's loads go out between the first products and

@@ -73,9 +73,6 @@ struct StreamGeom {
     long long T;                                      // position blocks in all: co_tiles * N * BPI
 };
 
-// x / d for 0 <= x < 2^20 and 1 <= d < 2^12, exact (the margin 0.5/d dwarfs the rounding of the product)
-__device__ __forceinline__ int fdiv(int x, float inv_d) { return (int)(((float)x + 0.5f) * inv_d); }
-
 // CGS = log2 of the 16-column groups per line, rounded up to a power of two (0 .. 2)
 // X3: the arithmetic runs on the bf16 matrix cores with operands split exactly (see the file header).
 template <int CIN, int KH, int KW, bool MODE_B, int CGS, bool WADJ, bool X3 = false>

@@ -25,8 +25,6 @@ struct PgLarge {
     float inv_P, inv_TC;
 };
 
-__device__ __forceinline__ int fdiv(int x, float inv_d) { return (int)(((float)x + 0.5f) * inv_d); }    // 0 <= x < 2^20
-
 constexpr unsigned kPosMask = (1u << 27) - 1;         // row << 12 | column inside the tile
 
 // NW wavefronts per tile; U runs of 64 keys in flight: four, but one where the staged tile is no more than four of them

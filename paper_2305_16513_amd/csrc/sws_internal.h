@@ -55,6 +55,22 @@ template <> struct Op<SWS_OP_MIN> {
     static __device__ __forceinline__ float f(float a, float b) { return __builtin_fminf(a, b); }
 };
 
+// x / d for 0 <= x < 2^20, inv_d = 1.0f / d, exact (the margin 0.5 / d is larger than the rounding of the product: x / d < 2^20)
+__device__ __forceinline__ int fdiv(int x, float inv_d) { return (int)(((float)x + 0.5f) * inv_d); }
+
+// the upper halves of two floats as one register of two bf16 (lo in the low half)
+__device__ __forceinline__ unsigned pack_hi(float lo, float hi)
+{
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+
+// One buffer descriptor: loads beyond `bytes` return zero; kNowhere lies beyond every descriptor.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+constexpr unsigned kNowhere = 0x80000000u;
+
 // N sliding windows of K consecutive elements at stride 1, out[j] = in[j] (+) ... (+) in[j + K - 1], from what they
 // share: the elements N - 1 .. K - 1 lie in all of them and are combined once; window j puts the rest of the head
 // in front (in[j] .. in[N - 2]) and the start of the tail behind (in[K] .. in[K + j - 1]) — Section 3's suffix /
