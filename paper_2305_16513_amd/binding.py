@@ -375,7 +375,9 @@ def sws_pool2d_padded(op, x, kh, kw, sh=1, sw=1, pads=(0, 0, 0, 0), mode=0, scal
 
 def sws_conv1d_padded(x, wgt, stride=1, pad_left=0, pad_right=0, dilation=1, groups=1, mode=0, y=None, stream=None):
     """x [B, Cin, L], wgt [Cout, Cin/groups, k] -> y [B, Cout, Lo]: rows extended at both ends by the boundary
-    rule `mode` (SWS_PAD_IDENTITY = zeros, SWS_PAD_MIRROR, SWS_PAD_PERIODIC, SWS_PAD_EDGE)."""
+    rule `mode` (SWS_PAD_IDENTITY = zeros, SWS_PAD_MIRROR, SWS_PAD_PERIODIC, SWS_PAD_EDGE).
+
+    Finite inputs only: most dense layers multiply exactly split operands, where an infinity gives NaN."""
     _dev(x, "x")
     _dev(wgt, "wgt")
     b, cin, length = x.shape
@@ -391,7 +393,9 @@ def sws_conv1d_padded(x, wgt, stride=1, pad_left=0, pad_right=0, dilation=1, gro
 
 
 def sws_conv1d(x, wgt, stride=1, pad=0, dilation=1, groups=1, y=None, stream=None):
-    """x [B, Cin, L], wgt [Cout, Cin/groups, k] -> y [B, Cout, Lo]."""
+    """x [B, Cin, L], wgt [Cout, Cin/groups, k] -> y [B, Cout, Lo].
+
+    Finite inputs only: most dense layers multiply exactly split operands, where an infinity gives NaN."""
     _dev(x, "x")
     _dev(wgt, "wgt")
     b, cin, length = x.shape
@@ -434,7 +438,9 @@ def sws_conv1d_16(x, wgt, stride=1, pad=0, dilation=1, groups=1, y=None, stream=
 
 
 def sws_conv1d_grad_input(gy, wgt, length, stride=1, pad=0, dilation=1, groups=1, gx=None, stream=None):
-    """gy [B, Cout, Lo], wgt [Cout, Cin/groups, k], length = L of the forward input -> gx [B, Cin, L]."""
+    """gy [B, Cout, Lo], wgt [Cout, Cin/groups, k], length = L of the forward input -> gx [B, Cin, L].
+
+    Finite inputs only: most dense layers multiply exactly split operands, where an infinity gives NaN."""
     _dev(gy, "gy")
     _dev(wgt, "wgt")
     b, cout, lo = gy.shape
@@ -450,7 +456,9 @@ def sws_conv1d_grad_input(gy, wgt, length, stride=1, pad=0, dilation=1, groups=1
 
 
 def sws_conv1d_grad_weight(x, gy, k, stride=1, pad=0, dilation=1, groups=1, gw=None, stream=None):
-    """x [B, Cin, L], gy [B, Cout, Lo] -> gw [Cout, Cin/groups, k]."""
+    """x [B, Cin, L], gy [B, Cout, Lo] -> gw [Cout, Cin/groups, k].
+
+    Finite inputs only: most dense layers multiply exactly split operands, where an infinity gives NaN."""
     _dev(x, "x")
     _dev(gy, "gy")
     b, cin, length = x.shape
@@ -466,7 +474,9 @@ def sws_conv1d_grad_weight(x, gy, k, stride=1, pad=0, dilation=1, groups=1, gw=N
 
 def sws_conv2d_padded(x, wgt, sh=1, sw=1, pads=(0, 0, 0, 0), mode=0, y=None, stream=None):
     """x [N, Cin, H, W], wgt [Cout, Cin, kh, kw], pads = (top, left, bottom, right) -> y [N, Cout, Ho, Wo]:
-    planes extended on four sides by the boundary rule `mode` (SWS_PAD_IDENTITY = zeros, MIRROR, PERIODIC, EDGE)."""
+    planes extended on four sides by the boundary rule `mode` (SWS_PAD_IDENTITY = zeros, MIRROR, PERIODIC, EDGE).
+
+    Finite inputs only: most dense layers multiply exactly split operands, where an infinity gives NaN."""
     _dev(x, "x")
     _dev(wgt, "wgt")
     n, cin, h, wd = x.shape
@@ -484,7 +494,9 @@ def sws_conv2d_padded(x, wgt, sh=1, sw=1, pads=(0, 0, 0, 0), mode=0, y=None, str
 
 
 def sws_conv2d(x, wgt, sh=1, sw=1, ph=0, pw=0, y=None, stream=None):
-    """x [N, Cin, H, W], wgt [Cout, Cin, kh, kw] -> y [N, Cout, Ho, Wo]."""
+    """x [N, Cin, H, W], wgt [Cout, Cin, kh, kw] -> y [N, Cout, Ho, Wo].
+
+    Finite inputs only: most dense layers multiply exactly split operands, where an infinity gives NaN."""
     _dev(x, "x")
     _dev(wgt, "wgt")
     n, cin, h, wd = x.shape
@@ -502,7 +514,9 @@ def sws_conv2d(x, wgt, sh=1, sw=1, ph=0, pw=0, y=None, stream=None):
 
 
 def sws_conv2d_grad_input(gy, wgt, h, wd, sh=1, sw=1, ph=0, pw=0, gx=None, stream=None):
-    """gy [N, Cout, Ho, Wo], wgt [Cout, Cin, kh, kw], (h, wd) = the forward input's plane -> gx [N, Cin, H, W]."""
+    """gy [N, Cout, Ho, Wo], wgt [Cout, Cin, kh, kw], (h, wd) = the forward input's plane -> gx [N, Cin, H, W].
+
+    Finite inputs only: most dense layers multiply exactly split operands, where an infinity gives NaN."""
     _dev(gy, "gy")
     _dev(wgt, "wgt")
     n, cout, ho, wo = gy.shape
@@ -517,7 +531,9 @@ def sws_conv2d_grad_input(gy, wgt, h, wd, sh=1, sw=1, ph=0, pw=0, gx=None, strea
 
 
 def sws_conv2d_grad_weight(x, gy, kh, kw, sh=1, sw=1, ph=0, pw=0, gw=None, stream=None):
-    """x [N, Cin, H, W], gy [N, Cout, Ho, Wo] -> gw [Cout, Cin, kh, kw]."""
+    """x [N, Cin, H, W], gy [N, Cout, Ho, Wo] -> gw [Cout, Cin, kh, kw].
+
+    Finite inputs only: most dense layers multiply exactly split operands, where an infinity gives NaN."""
     _dev(x, "x")
     _dev(gy, "gy")
     n, cin, h, wd = x.shape

@@ -31,9 +31,9 @@
 // cells of a row leave as one store.
 //
 // Measured, us, with the weights' pass, this kernel / the fp32 matrix kernels: [32,256,14,14] -> 256, 3 x 3 50 / 113, adjoint 49 / 133;
-// [32,128,56,56] -> 128, 3 x 3 stride 2 55 / 104, adjoint 60 / 205; [17,128,23,14] -> 104, 5 x 5 43 / 153; 100 layers 2.8 x on
-// average.  Parts switched off, [32,256,14,14]: products alone 45 us (1.0 PFLOP/s of bf16 products: under this load the matrix
-// cores do not hold their nominal clock, a large library product reaches 1.2), so what staging adds is 5 us.  Blocks of one
+// [32,128,56,56] -> 128, 3 x 3 stride 2 55 / 104, adjoint 67 / 205; [17,128,23,14] -> 104, 5 x 5 43 / 153; 100 layers 2.8 x on
+// average.  [32,256,14,14]: 41 us for this kernel by itself; 200 workgroups on 256 compute units, whose matrix cores are busy 62 % of the
+// cycles, waits take 25 % of the wavefronts' time (stride 2 58 and 17 %, its adjoint 37 and 27 %).  Blocks of one
 // wavefront at least two positions wide (NB = 2): with NB = 1 the weights alone saturate the vector cache's 64 bytes
 // per cycle.
 #include "sws_internal.h"
