@@ -43,9 +43,9 @@ __host__ __device__ constexpr int lds_pos(int q) { return q + 4 * (q >> 4); }
 // `pmode` (mirror, periodic, edge) instead of zeros; only the tiles at the ends of a row differ.
 // STREAM: the tiles' strips are loaded streamed (non-temporal) — inputs far beyond the caches.
 template <int KB4, bool RULE, bool STREAM = false>
-__global__ __launch_bounds__(kThreads, (KB4 <= 8 ? 5 : 4)) void conv1d_thin_kernel(
+__global__ __launch_bounds__(kThreads, (KB4 < 8 ? 5 : 4)) void conv1d_thin_kernel(
     const float *__restrict__ x, const float *__restrict__ wgt, float *__restrict__ y, int L, int Lo, int k,
-    int pad, int Cin, int Cout, int cog, int tiles_per_row, int group, int chunks_per_row, int64_t n_units,
+    int pad, int Cin, int Cout, int cog, int tiles_per_row, int group, int chunks_per_row, int n_units,
     int wflip, int p_hi, int pmode)
 {
     constexpr int K4 = 4 * KB4;                      // taps, zero-padded to a multiple of 4
@@ -54,21 +54,19 @@ __global__ __launch_bounds__(kThreads, (KB4 <= 8 ? 5 : 4)) void conv1d_thin_kern
     constexpr int REGION = (lds_pos(NI) + 63) / 64 * 64;
     __shared__ __attribute__((aligned(16))) float lds[kWavesPerWg * REGION];
 
-    const int64_t unit = xcd_unit(n_units);
+    const int unit = xcd_run_unit(n_units);
     if (unit < 0) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float *A = lds + wave * REGION;
-    const int64_t ro = unit / chunks_per_row;        // output row = b*Cout + co
-    const int chunk = (int)(unit - ro * chunks_per_row);
-    const int64_t b = ro / Cout;
-    const int co = (int)(ro - b * Cout);
-    const float *xr = x + (b * Cin + co / cog) * (int64_t)L;
+    const int ro = (unsigned)unit / (unsigned)chunks_per_row, chunk = unit - ro * chunks_per_row;     // output row = b*Cout + co
+    const int b = (unsigned)ro / (unsigned)Cout, co = ro - b * Cout;
+    const float *xr = x + ((int64_t)b * Cin + (unsigned)co / (unsigned)cog) * L;
     const float *wr = wgt + (int64_t)co * k;
-    float *yr = y + ro * (int64_t)Lo;
+    float *yr = y + (int64_t)ro * Lo;
     // Tile origins are pulled back by c so that (ro*Lo + t0) is a multiple of 16 floats: every
     // 1 KB strip store starts on a 64-byte line of y.  Outputs before the row start are dropped.
-    const int c = (int)((ro * Lo) & 15);
+    const int c = (ro & 15) * (Lo & 15) & 15;
 
     // Taps: one coalesced load (lane t holds tap t, zero beyond k), then broadcast into scalar registers.
     float f[K4];
@@ -83,21 +81,17 @@ __global__ __launch_bounds__(kThreads, (KB4 <= 8 ? 5 : 4)) void conv1d_thin_kern
     const int sbase = 4 * lane + 4 * (lane >> 2);    // my strip element: lds_pos(256j + 4*lane) = sbase + 320j
 
     // Strips of one tile (inputs [p0, p0 + NI)): 4 full strips plus the k-1 halo, zero outside the row.
+    const __amdgpu_buffer_rsrc_t xrs = rsrc(xr, 4u * (unsigned)L);
     auto load_tile = [&](int t, v4f (&g)[5]) {
         const int p0 = t * kTileOut - c - pad;
         if (p0 >= 0 && p0 <= L - NI) {
-            // (streamed loads on inputs far beyond the caches, as in the sliding-sum scan kernel; the halo strip, which
-            // the next tile reads again, stays a plain load)
-            // (A template parameter: two run-time branches that differ in nothing but the hint are merged by the
-            // compiler into plain loads.)
-            if constexpr (STREAM) {
+            // (one register of offsets for all strips.  Streamed loads on inputs far beyond the caches, as in the sliding-sum
+            // scan kernel; the halo strip, which the next tile reads again, stays a plain load.)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) g[j] = __builtin_nontemporal_load((const v4f_u *)(xr + p0 + j * 256 + 4 * lane));
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) g[j] = *(const v4f_u *)(xr + p0 + j * 256 + 4 * lane);
-            }
-            g[4] = (4 * lane < K4) ? *(const v4f_u *)(xr + p0 + kTileOut + 4 * lane) : (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+            for (int j = 0; j < 4; ++j)
+                g[j] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xrs, 16 * lane, 4 * p0 + 1024 * j, STREAM ? 2 : 0));
+            g[4] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+            if (4 * lane < K4) g[4] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xrs, 16 * lane, 4 * p0 + 4096, 0));
         } else {
             // a tile at an end of its row: strip by strip (wave-uniform tests) — whole strips inside
             // the row are still 128-bit loads, strips wholly outside are zero
@@ -120,10 +114,10 @@ __global__ __launch_bounds__(kThreads, (KB4 <= 8 ? 5 : 4)) void conv1d_thin_kern
                 } else if (s0 >= L || s0 + 256 <= 0) {
                     g[j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
                 } else {
-                    g[j].x = (p + 0 >= 0 && p + 0 < L) ? xr[p + 0] : 0.0f;
-                    g[j].y = (p + 1 >= 0 && p + 1 < L) ? xr[p + 1] : 0.0f;
-                    g[j].z = (p + 2 >= 0 && p + 2 < L) ? xr[p + 2] : 0.0f;
-                    g[j].w = (p + 3 >= 0 && p + 3 < L) ? xr[p + 3] : 0.0f;
+                    // (no loads under a lane's condition: the compiler would wait for them at once)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        g[j][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrs, p + u < 0 ? kNowhere : 4u * (unsigned)(p + u), 0, 0));
                 }
             }
         }
@@ -132,17 +126,21 @@ __global__ __launch_bounds__(kThreads, (KB4 <= 8 ? 5 : 4)) void conv1d_thin_kern
     int t_end = (chunk + 1) * group;
     if (t_end > tiles_per_row) t_end = tiles_per_row;
     int t = chunk * group + wave;
+    if (t >= t_end) return;                          // (no workgroup barrier below)
     v4f cur[5];
-    if (t < t_end) load_tile(t, cur);
-    for (; t < t_end; t += kWavesPerWg) {
-        const int t0 = t * kTileOut - c;             // first output of the tile (may be < 0 for t = 0)
-        // ---- the next tile's loads go out before this tile's arithmetic
-        v4f nxt[5];
-        if (t + kWavesPerWg < t_end) load_tile(t + kWavesPerWg, nxt);
-        // ---- stage: strips -> LDS
+    load_tile(t, cur);
+    // strips -> LDS
+    auto stage = [&]() {
 #pragma unroll
         for (int j = 0; j < 4; ++j) *(v4f *)(A + sbase + 320 * j) = cur[j];
         if (4 * lane < K4) *(v4f *)(A + sbase + 1280) = cur[4];
+    };
+    stage();
+    for (; t < t_end; t += kWavesPerWg) {
+        const int t0 = t * kTileOut - c;             // first output of the tile (may be < 0 for t = 0)
+        const bool more = t + kWavesPerWg < t_end;
+        // ---- the next tile's loads go out before this tile's arithmetic
+        if (more) load_tile(t + kWavesPerWg, cur);
         wave_lds_sync();
         // ---- my window: inputs 16*lane .. 16*lane + K4 + 15
         float xw[K4 + 16];
@@ -165,25 +163,33 @@ __global__ __launch_bounds__(kThreads, (KB4 <= 8 ? 5 : 4)) void conv1d_thin_kern
         for (int u = 0; u < 4; ++u)
             *(v4f *)(A + wbase + 4 * u) = (v4f){acc[4 * u], acc[4 * u + 1], acc[4 * u + 2], acc[4 * u + 3]};
         wave_lds_sync();
+        // (a strip of the next tile takes the place of the outputs that have just been read; stores of a whole tile come in
+        // one piece of code with it, so that the loads are not waited for behind all of them)
         const int lim = Lo - t0;
-        const int qlo = t0 < 0 ? -t0 : 0;
+        if (more && t0 >= 0 && lim >= kTileOut) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int q = j * 256 + 4 * lane;
-            if (q >= lim) continue;
-            const v4f o = *(const v4f *)(A + sbase + 320 * j);
-            if (q >= qlo && q + 4 <= lim) {
-                __builtin_nontemporal_store(o, (v4f_u *)(yr + t0 + q));
-            } else {
-                if (q + 0 >= qlo && q + 0 < lim) yr[t0 + q + 0] = o.x;
-                if (q + 1 >= qlo && q + 1 < lim) yr[t0 + q + 1] = o.y;
-                if (q + 2 >= qlo && q + 2 < lim) yr[t0 + q + 2] = o.z;
-                if (q + 3 >= qlo && q + 3 < lim) yr[t0 + q + 3] = o.w;
+            for (int j = 0; j < 4; ++j) {
+                const v4f o = *(const v4f *)(A + sbase + 320 * j);
+                *(v4f *)(A + sbase + 320 * j) = cur[j];
+                __builtin_nontemporal_store(o, (v4f_u *)(yr + t0 + j * 256 + 4 * lane));
             }
-        }
-        wave_lds_sync();
+            if (4 * lane < K4) *(v4f *)(A + sbase + 1280) = cur[4];
+        } else {
 #pragma unroll
-        for (int j = 0; j < 5; ++j) cur[j] = nxt[j];
+            for (int j = 0; j < 4; ++j) {
+                const v4f o = *(const v4f *)(A + sbase + 320 * j);
+                if (more) *(v4f *)(A + sbase + 320 * j) = cur[j];
+                const int q = j * 256 + 4 * lane;
+                if (t0 + q >= 0 && q + 4 <= lim) {
+                    __builtin_nontemporal_store(o, (v4f_u *)(yr + t0 + q));
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (t0 + q + e >= 0 && q + e < lim) yr[t0 + q + e] = o[e];
+                }
+            }
+            if (more && 4 * lane < K4) *(v4f *)(A + sbase + 1280) = cur[4];
+        }
     }
 }
 
@@ -194,6 +200,8 @@ hipError_t launch_thin(const float *x, const float *wgt, float *y, int64_t rows_
     const int tiles_per_row = (Lo + max_origin_shift(Lo, 16) + kTileOut - 1) / kTileOut;     // origins move back
     // Tiles per workgroup (measured): two per wavefront while HBM is the bound (the tiles in flight
     // stay a compact window of memory), many once the FMAs dominate (k > 32: fewer prologues).
+    // With the workgroups dealt to the XCDs in short runs and the next tile staged before a tile's stores, cold inputs, us
+    // before / now: [32,128,16384] k = 3 97 / 93, k = 25 102 / 95, [8,64,65536] k = 3 .. 31 57 / 48 (copies of these sizes 86 and 43).
     // (With streamed loads four per wavefront measured 2.5 % faster when the layer's launches follow each other, 0.833
     // against 0.855 ms on cfg 5's k = 31 layer, but 1 % slower between other kernels, 0.779 against 0.771: not taken.)
     const bool stream = !RULE && rows_out * (int64_t)L >= ((int64_t)1 << 27) && !(g_opt.slide_chunk & 256);
@@ -203,18 +211,18 @@ hipError_t launch_thin(const float *x, const float *wgt, float *y, int64_t rows_
     const int chunks_per_row = (int)((tiles_per_row + g - 1) / g);
     const int group = (tiles_per_row + chunks_per_row - 1) / chunks_per_row;     // even chunks
     const int64_t n_units = rows_out * chunks_per_row;
-    const int64_t grid = xcd_grid(n_units);
-    if (grid > 2147483647LL) return kNotTaken;
+    const int64_t grid = xcd_run_grid(n_units);
+    if (grid > 2147483647LL - 64 || L >= (1 << 29)) return kNotTaken;
     // inputs far beyond the caches are loaded streamed (slide_chunk bit 256: plain loads, as for the sliding sums)
     if constexpr (!RULE) {
         if (stream) {
             hipLaunchKernelGGL((conv1d_thin_kernel<KB4, false, true>), dim3((unsigned)grid), dim3(kThreads), 0, s, x, wgt, y, L,
-                               Lo, k, pad, Cin, Cout, cog, tiles_per_row, group, chunks_per_row, n_units, wflip, p_hi, pmode);
+                               Lo, k, pad, Cin, Cout, cog, tiles_per_row, group, chunks_per_row, (int)n_units, wflip, p_hi, pmode);
             return hipGetLastError();
         }
     }
     hipLaunchKernelGGL((conv1d_thin_kernel<KB4, RULE>), dim3((unsigned)grid), dim3(kThreads), 0, s, x, wgt, y, L, Lo, k,
-                       pad, Cin, Cout, cog, tiles_per_row, group, chunks_per_row, n_units, wflip, p_hi, pmode);
+                       pad, Cin, Cout, cog, tiles_per_row, group, chunks_per_row, (int)n_units, wflip, p_hi, pmode);
     return hipGetLastError();
 }
 
@@ -253,23 +261,21 @@ template <int KB4, bool MULTI, bool STRIDED>
 __global__ __launch_bounds__(kThreads) void conv1d_thin_dilated_kernel(
     const float *__restrict__ x, const float *__restrict__ wgt, float *__restrict__ y, int L, int Lo, int k,
     int pad, DilPlan pl, int Cin, int Cout, int cog, int cig, int tiles_per_row, int group, int chunks_per_row,
-    int64_t n_units)
+    int n_units)
 {
     constexpr int K4 = 4 * KB4;
     constexpr int NG = KB4 + 4;
     extern __shared__ __attribute__((aligned(16))) float lds_dyn[];
 
-    const int64_t unit = xcd_unit(n_units);
+    const int unit = xcd_run_unit(n_units);
     if (unit < 0) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int4 *tab = (int4 *)lds_dyn;                     // [tab_strips][64]: LDS offsets of a strip's 4 elements
     float *A = lds_dyn + pl.tab_strips * 256 + wave * pl.slice;
-    const int64_t ro = unit / chunks_per_row;
-    const int chunk = (int)(unit - ro * chunks_per_row);
-    const int64_t b = ro / Cout;
-    const int co = (int)(ro - b * Cout);
-    const float *xg = x + (b * Cin + (int64_t)(co / cog) * cig) * (int64_t)L;     // first input channel of my group
+    const int ro = (unsigned)unit / (unsigned)chunks_per_row, chunk = unit - ro * chunks_per_row;
+    const int b = (unsigned)ro / (unsigned)Cout, co = ro - b * Cout;
+    const float *xg = x + ((int64_t)b * Cin + (int64_t)(co / cog) * cig) * (int64_t)L;     // first input channel of my group
     // Plain view: wgt[co][ci][wofs + t].  Adjoint view (pl.wadj; this launch maps output gradients
     // back to the input): my output channel is the stored array's input channel a = co % cog of
     // group co / cog, my input channel ci its output channel, the taps run backwards:
@@ -279,7 +285,7 @@ __global__ __launch_bounds__(kThreads) void conv1d_thin_dilated_kernel(
                                      : (int64_t)co * cig * pl.wstride + pl.wofs);
     const int w_st = pl.wadj ? -1 : 1;
     float *yr = y + ro * (int64_t)Lo;
-    const int c = (int)((ro * Lo) & 15);             // 64-byte-aligned strip stores, as in the undilated kernel
+    const int c = (ro & 15) * (Lo & 15) & 15;        // 64-byte-aligned strip stores, as in the undilated kernel
     const int d = pl.d, MP = pl.MP, TO = pl.TO, NI = pl.NI;
 
     // ---- scatter table: element q of the tile -> its phase-major LDS offset; elements the tile does
@@ -515,13 +521,13 @@ hipError_t launch_thin_dilated(const float *x, const float *wgt, float *y, int64
     const int chunks_per_row = (int)((tiles_per_row + g - 1) / g);
     const int group = (tiles_per_row + chunks_per_row - 1) / chunks_per_row;     // even chunks
     const int64_t n_units = rows_out * chunks_per_row;
-    const int64_t grid = xcd_grid(n_units);
-    if (grid > 2147483647LL) return kNotTaken;
+    const int64_t grid = xcd_run_grid(n_units);
+    if (grid > 2147483647LL - 64) return kNotTaken;
     const size_t lds_bytes = ((size_t)pl.tab_strips * 256 + (size_t)kWavesPerWg * pl.slice) * sizeof(float);
 #define SWS_DIL_LAUNCH(MULTI, STRIDED)                                                                          \
     hipLaunchKernelGGL((conv1d_thin_dilated_kernel<KB4, MULTI, STRIDED>), dim3((unsigned)grid), dim3(kThreads),  \
                        lds_bytes, s, x, wgt, y, L, Lo, k, pad, pl, Cin, Cout, cog, cig, tiles_per_row, group,    \
-                       chunks_per_row, n_units)
+                       chunks_per_row, (int)n_units)
     if (strided) {
         if (cig > 1) SWS_DIL_LAUNCH(true, true);
         else SWS_DIL_LAUNCH(false, true);
