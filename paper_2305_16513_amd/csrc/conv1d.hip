@@ -11,6 +11,8 @@
 //    Global traffic is coalesced 128-bit strips; LDS turns strips into per-lane windows
 //    and the per-lane outputs back into strips.
 //
+//  * kernels of more than 32 taps, and rows of one tile with taps 4, 8 or 16 apart: on the matrix cores (conv1d_toep.hip).
+//
 //  * conv1d_thin_dilated_kernel: the same with taps spaced d > 1 apart.  A dilated
 //    correlation is d independent undilated ones on the phase subsequences x[p + d*m], so the
 //    tile is staged phase-major in LDS and a lane slides the taps over a register window of
@@ -81,17 +83,18 @@ __global__ __launch_bounds__(kThreads, (KB4 < 8 ? 5 : 4)) void conv1d_thin_kerne
     const int sbase = 4 * lane + 4 * (lane >> 2);    // my strip element: lds_pos(256j + 4*lane) = sbase + 320j
 
     // Strips of one tile (inputs [p0, p0 + NI)): 4 full strips plus the k-1 halo, zero outside the row.
-    const __amdgpu_buffer_rsrc_t xrs = rsrc(xr, 4u * (unsigned)L);
     auto load_tile = [&](int t, v4f (&g)[5]) {
-        const int p0 = t * kTileOut - c - pad;
+        const int p0 = t * kTileOut - c - pad, o = p0 > 0 ? p0 : 0;          // (descriptor from there on: rows of any length)
+        const int64_t left = 4 * ((int64_t)L - o);
+        const __amdgpu_buffer_rsrc_t xrs = rsrc(xr + o, left < 0 ? 0u : (left < 0x7fffffff ? (unsigned)left : 0x7fffffffu));
         if (p0 >= 0 && p0 <= L - NI) {
             // (one register of offsets for all strips.  Streamed loads on inputs far beyond the caches, as in the sliding-sum
             // scan kernel; the halo strip, which the next tile reads again, stays a plain load.)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                g[j] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xrs, 16 * lane, 4 * p0 + 1024 * j, STREAM ? 2 : 0));
+                g[j] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xrs, 16 * lane, 1024 * j, STREAM ? 2 : 0));
             g[4] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-            if (4 * lane < K4) g[4] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xrs, 16 * lane, 4 * p0 + 4096, 0));
+            if (4 * lane < K4) g[4] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xrs, 16 * lane, 4096, 0));
         } else {
             // a tile at an end of its row: strip by strip (wave-uniform tests) — whole strips inside
             // the row are still 128-bit loads, strips wholly outside are zero
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(kThreads, (KB4 < 8 ? 5 : 4)) void conv1d_thin_kerne
                     // (no loads under a lane's condition: the compiler would wait for them at once)
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
-                        g[j][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrs, p + u < 0 ? kNowhere : 4u * (unsigned)(p + u), 0, 0));
+                        g[j][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrs, p + u < 0 ? kNowhere : 4u * (unsigned)(p + u - o), 0, 0));
                 }
             }
         }
@@ -212,7 +215,7 @@ hipError_t launch_thin(const float *x, const float *wgt, float *y, int64_t rows_
     const int group = (tiles_per_row + chunks_per_row - 1) / chunks_per_row;     // even chunks
     const int64_t n_units = rows_out * chunks_per_row;
     const int64_t grid = xcd_run_grid(n_units);
-    if (grid > 2147483647LL - 64 || L >= (1 << 29)) return kNotTaken;
+    if (grid > 2147483647LL - 64) return kNotTaken;
     // inputs far beyond the caches are loaded streamed (slide_chunk bit 256: plain loads, as for the sliding sums)
     if constexpr (!RULE) {
         if (stream) {
@@ -600,13 +603,21 @@ hipError_t launch_conv1d(const float *x, const float *wgt, float *y, int64_t B, 
     if (variant == 3 && !dense_ok) variant = 0;
     if (variant == 6 && !few_ok) variant = 0;
     if (variant == 7 && !strided_ok) variant = 0;
+    const bool toep_ok = cig == 1 && stride == 1 && conv1d_toep_takes(k, dilation);
+    if (variant == 8 && !toep_ok) variant = 0;
     const bool split_ok = ws.p && k <= 64 && stride <= 2 && g_opt.conv1d_variant == 0 && g_opt.conv2d_variant == 0;
     const bool valu_ok = few_ok || (strided_ok && cig > 1);
     if (variant == 0) {
-        if (thin_ok) variant = 2;
+        if (toep_ok && conv1d_toep_wanted(Lo, k, dilation)) variant = 8;
+        else if (thin_ok) variant = 2;
         else if (thin_dil_ok) variant = 4;
         else if (dense_ok && !(valu_ok && prefer_few(Cin, Cout, k, stride > 1, split_ok))) variant = 3;
         else variant = few_ok ? 6 : (strided_ok ? 7 : 1);
+    }
+    if (variant == 8) {
+        const hipError_t e = launch_conv1d_toep(x, wgt, y, B, Cin, L, Cout, Lo, k, pad, dilation, groups, s, wadj);
+        if (e != kNotTaken) return e;
+        variant = thin_ok ? 2 : (thin_dil_ok ? 4 : 1);
     }
     if (variant == 3 && g_opt.conv1d_variant == 0) {
         bool taken_s = false;

@@ -498,3 +498,46 @@ def test_conv1d_dense_split_operands_carry_every_bit(B):
     ref, mag = oracle.conv1d(x, w, 1, 1, 1, 1)
     y = to_host(B.sws_conv1d(to_gpu(x), to_gpu(w), 1, 1, 1, 1))
     assert_within_tol(y, ref, mag, "low bits", tol=2e-7)
+
+
+# Thin layers on the matrix cores (conv1d_variant 8; more than 32 taps by themselves): one, two and three wavefronts per workgroup,
+# every number of slices of T, ends of tiles and rows, several rows per workgroup (the last).  Tolerance: 31 + k <= 96 products
+# of exact pieces in fp32, six of nine (the dropped ones below 2^-21 of a term): 96 * 2^-24 + 2^-21 = 6.2e-6 of sum |terms|.
+@pytest.mark.parametrize("b,c,length,k,d,pad", [
+    (2, 3, 1057, 33, 1, 0), (1, 2, 1058, 34, 1, 16), (2, 2, 2050, 49, 1, 24), (1, 3, 3071, 64, 1, 0), (3, 5, 5000, 50, 1, 7), (1, 1, 66, 66 - 2, 1, 0),
+    (2, 3, 700, 5, 4, 3), (1, 2, 1024 + 4 * 32, 33, 4, 0), (1, 3, 4096, 63, 4, 124), (2, 3, 900, 18, 8, 8), (2, 3, 2448 + 16, 51, 8, 200), (1, 2, 9001, 49, 8, 0),
+    (2, 2, 800, 2, 16, 0), (1, 3, 4396, 33, 16, 8), (1, 2, 3000, 64, 16, 500), (1, 2, 9000, 64, 32, 0), (2, 3, 1700, 33, 32, 512),
+    (64, 400, 70, 33, 1, 0)])
+def test_conv1d_thin_matrix(B, b, c, length, k, d, pad):
+    r = _rng(k * 1000 + length + d)
+    x = (r.random((b, c, length), dtype=np.float32) * 2 - 1).astype(np.float32)
+    w = (r.standard_normal((c, 1, k), dtype=np.float32) / np.sqrt(k)).astype(np.float32)
+    B.sws_set_option("conv1d_variant", 8)
+    try:
+        y = to_host(B.sws_conv1d(to_gpu(x), to_gpu(w), 1, pad, d, c))
+        gy = r.standard_normal(y.shape, dtype=np.float32)
+        gx = to_host(B.sws_conv1d_grad_input(to_gpu(gy), to_gpu(w), length, 1, pad, d, c))
+        xi = r.integers(-3, 4, x.shape).astype(np.float32)
+        wi = r.integers(-3, 4, w.shape).astype(np.float32)
+        yi = to_host(B.sws_conv1d(to_gpu(xi), to_gpu(wi), 1, pad, d, c))
+    finally:
+        B.sws_set_option("conv1d_variant", 0)
+    what = str((b, c, length, k, d, pad))
+    assert_within_tol(y, *oracle.conv1d(x, w, 1, pad, d, c), what, tol=6.2e-6)
+    assert_within_tol(gx, *oracle.conv1d_grad_input(gy, w, length, 1, pad, d, c), what + " gx", tol=6.2e-6)
+    assert np.array_equal(yi, oracle.conv1d(xi, wi, 1, pad, d, c)[0]), what + " whole numbers"
+
+
+@pytest.mark.parametrize("d", [1, 8])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_conv1d_thin_matrix_not_finite(B, d, bad):
+    """One element that is not finite reaches the outputs whose windows hold it, and no others."""
+    k, length = 40, 5000
+    x = np.ones((1, 2, length), dtype=np.float32)
+    x[0, 1, 3000] = bad
+    w = np.full((2, 1, k), 0.5, dtype=np.float32)
+    y = to_host(B.sws_conv1d(to_gpu(x), to_gpu(w), 1, 0, d, 2))
+    want = np.full(y.shape, 0.5 * k, dtype=np.float32)
+    hit = 3000 - np.arange(k) * d
+    want[0, 1, hit] = bad
+    assert np.array_equal(y, want, equal_nan=True)
