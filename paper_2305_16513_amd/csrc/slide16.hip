@@ -10,7 +10,10 @@
 // of the lane whose outputs need them.  17 KB of LDS traffic and 4 KB of LDS per 1024 elements; with inputs staged as
 // fp32 and both scans in LDS (26 and 8 KB) [900,30000] w = 64 took 28.9 us against 24.0, [186479,422] w = 39 192
 // against 151, [8192,16384] w = 64 129.1 against 127.9 (more wavefronts per SIMD than the four that 124 registers
-// leave: spills, 365 us).  The next tile is requested before the current one is worked on.
+// leave: spills, 365 us).  The next tile is requested before the current one is worked on and staged before its results
+// are stored, with no load under a lane's condition on the way: the compiler waited for those at once, and for the stores
+// of the tile before, so that nothing was in flight during a tile's arithmetic ([8192,16384] w = 64 128 us, now 93,
+// 5.8 TB/s; [186479,422] w = 39 151 / 90, [50000,1000] w = 100 104 / 61).
 // Windows up to 33 also have a kernel on shifted loads (eight outputs per lane straight from
 // 128-bit loads, no LDS); it serves the windows up to 9 everywhere, and the others on short rows
 // and small tensors, where 1024-element wave tiles fit badly.
@@ -98,7 +101,7 @@ __global__ __launch_bounds__(kThreads) void slide16_scan_kernel(const T *__restr
 
     const int64_t unit = remap ? xcd_unit(n_units) : (int64_t)blockIdx.x;
     if (unit < 0) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float *A = lds + wave * N;                       // staged 16-bit inputs, then Pre in fp32, then the 16-bit results
     typename IO::v8 *const A16 = (typename IO::v8 *)A;       // ... as units of eight 16-bit elements, unit u at lds_unit(u)
     int64_t gt = unit * group + wave;
@@ -141,59 +144,64 @@ __global__ __launch_bounds__(kThreads) void slide16_scan_kernel(const T *__restr
 #pragma unroll
     for (int u = 0; u < 5; ++u) pp[u] = 4 * lds_group((4 * lane + s4 + u) & 255);
 
-    // The strips of my next tile are requested before the current tile is worked on (raw 16-bit
-    // registers, widened when their turn comes): with 2 KB per tile a wavefront would otherwise
-    // have too few bytes in flight to cover the memory latency (measured on 2^29 elements, w = 16:
-    // 0.59 ms without, 0.43 ms with; requesting two tiles ahead gains nothing more).  Tiles at an
-    // end of their row are not requested ahead; they are staged strip by strip at their turn.
-    typename IO::v8 raw0[2];                         // my current tile, later my next tile
-    auto request = [&](int64_t rr, int tt, int64_t g_idx, typename IO::v8 (&dst)[2]) -> bool {
-        if (g_idx >= gt_end) return false;
-        const int t0n = tt * tout - (int)((rr * lo) & (kLine - 1));
-        if (t0n < 0 || t0n > len - N) return false;
-        const T *xn = x + rr * (int64_t)len + t0n;
+    // The strips of my next tile are requested before the current tile is worked on, and staged after its results have been
+    // read back and before they are stored: 2 KB per tile is too little in flight to wait for at once, or behind stores.
+    // A tile that reaches beyond its row is loaded whole too (the neighbouring rows are there), its outside elements are replaced
+    // by the identity; only at the ends of x it is loaded element by element.
+    const int64_t total = n_tiles / tiles_per_row * (int64_t)len;
+    auto origin = [&](int64_t rr, int tt) { return tt * tout - (int)((rr * lo) & (kLine - 1)); };
+    typename IO::v8 raw[2];
+    auto request = [&](int64_t rr, int tt) -> bool {
+        const int64_t e = rr * (int64_t)len + origin(rr, tt);
+        const bool whole = e >= 0 && e + N <= total;
+        if (whole) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) dst[j] = IO::load_raw(xn + 512 * j + 8 * lane);
-        return true;
+            for (int j = 0; j < 2; ++j) raw[j] = IO::load_raw(x + e + 512 * j + 8 * lane);
+        }
+        return whole;
     };
-    int t1 = t + kWavesPerWg;
-    int64_t r1 = r;
-    while (t1 >= tiles_per_row) { t1 -= tiles_per_row; ++r1; }
-    bool have0 = request(r, t, gt, raw0);
-    for (; gt < gt_end; gt += kWavesPerWg) {
-        const T *xr = x + r * (int64_t)len;
+    auto stage_element_wise = [&](int64_t rr, int tt) {
+        const int t0 = origin(rr, tt);
+        const T *xr = x + rr * (int64_t)len;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            typename IO::v8 g;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const int e = t0 + 512 * j + 8 * lane + c;
+                g[c] = (e >= 0 && e < len) ? xr[e] : (T)O::id();
+            }
+            A16[lds_unit(64 * j + lane)] = g;
+        }
+    };
+    auto outside = [&](int64_t rr, int tt) {         // raw: the identity outside the row
+        const int t0 = origin(rr, tt);
+        if (t0 >= 0 && t0 + N <= len) return;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                if ((unsigned)(t0 + 512 * j + 8 * lane + c) >= (unsigned)len) raw[j][c] = (T)O::id();
+    };
+    if (gt >= gt_end) return;                        // (no workgroup barrier below)
+    if (request(r, t)) {
+        outside(r, t);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) A16[lds_unit(64 * j + lane)] = raw[j];
+    } else {
+        stage_element_wise(r, t);
+    }
+    for (;;) {
         // tile origins pulled back so that (r*lo + t0) is a multiple of 32 elements: every strip
         // store starts on a 64-byte line of y; outputs before the row start are not stored
-        const int t0 = t * tout - (int)((r * lo) & (kLine - 1));
+        const int t0 = origin(r, t);
         const int qlo = t0 < 0 ? -t0 : 0;
-        const T *xt = xr + t0;
         T *yt = y + r * (int64_t)lo + t0;
-        // ---- stage: two strips of 512 elements -> LDS as they are
-        typename IO::v8 g8[2];
-        if (have0) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) g8[j] = raw0[j];
-        } else {
-            // a tile at an end of its row: whole strips inside the row are still 128-bit loads,
-            // strips wholly outside hold the identity (wave-uniform tests)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int s0 = t0 + 512 * j;
-                if (s0 >= 0 && s0 + 512 <= len) {
-                    g8[j] = IO::load_raw(xt + 512 * j + 8 * lane);
-                } else {
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) {
-                        const int e = s0 + 8 * lane + c;
-                        g8[j][c] = (e >= 0 && e < len) ? xr[e] : (T)O::id();
-                    }
-                }
-            }
-        }
-        // ---- my next tile: request it now
-        have0 = request(r1, t1, gt + kWavesPerWg, raw0);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) A16[lds_unit(64 * j + lane)] = g8[j];
+        gt += kWavesPerWg;
+        t += kWavesPerWg;
+        while (t >= tiles_per_row) { t -= tiles_per_row; ++r; }
+        const bool more = gt < gt_end;
+        const bool whole = more && request(r, t);
         wave_lds_sync();
         // ---- my chunk of C consecutive elements
         float v[C];
@@ -259,27 +267,33 @@ __global__ __launch_bounds__(kThreads) void slide16_scan_kernel(const T *__restr
             for (int u = 0; u < 2; ++u) A16[lds_unit(2 * lane + u)] = IO::narrow(o[u]);
         }
         wave_lds_sync();
-        // ---- out: strips of eight results, 128-bit stores
+        // ---- out: strips of eight results, 128-bit stores; the next tile's strips take their places first
+        typename IO::v8 o[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) o[j] = A16[lds_unit(64 * j + lane)];
+        wave_lds_sync();
+        if (whole) {
+            outside(r, t);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) A16[lds_unit(64 * j + lane)] = raw[j];
+        } else if (more) {
+            stage_element_wise(r, t);
+        }
         int lim = lo - t0;
         if (lim > tout) lim = tout;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int q = 512 * j + 8 * lane;
             if (q >= lim) continue;
-            const typename IO::v8 o = A16[lds_unit(64 * j + lane)];
             if (q >= qlo && q + 8 <= lim) {
-                IO::store_raw(yt + q, o);
+                IO::store_raw(yt + q, o[j]);
             } else {
 #pragma unroll
                 for (int c = 0; c < 8; ++c)
-                    if (q + c >= qlo && q + c < lim) yt[q + c] = o[c];
+                    if (q + c >= qlo && q + c < lim) yt[q + c] = o[j][c];
             }
         }
-        wave_lds_sync();                             // the next tile overwrites A
-        t = t1;
-        r = r1;
-        t1 += kWavesPerWg;
-        while (t1 >= tiles_per_row) { t1 -= tiles_per_row; ++r1; }
+        if (!more) break;
     }
 }
 
@@ -444,12 +458,12 @@ hipError_t launch_16(const T *x, T *y, int64_t rows, int len, int lo, int w, flo
         const int tout = (kN - S) & ~(kLine - 1);    // a multiple of 64 bytes of y (at least 64 outputs)
         const int tiles = (lo + max_origin_shift(lo, kLine) + tout - 1) / tout;
         const int64_t n_tiles = rows * tiles;
-        // sixteen tiles per wavefront (measured best: 8 to 32), the next one in flight while one is
-        // worked on; workgroups in launch order
-        int64_t g = 16 * kWavesPerWg;
+        // Four tiles per wavefront (measured, us, 2 / 4 / 8 / 16: [8192,16384] w = 64 101 / 93 / 103 / 113, w = 255 118 / 101 / 101 / 112,
+        // [64,1048576] w = 64 48 / 50 / 56 / 65), eight where a row is a tile or two ([186479,422] w = 39 115 / 98 / 90 / 91:
+        // the starts of a workgroup weigh more there); workgroups in launch order (dealt to the XCDs in runs: the same).
+        int64_t g = (tiles <= 2 ? 8 : 4) * kWavesPerWg;
         int remap = 0;
-        // ... halved while that leaves fewer than 2048 workgroups (measured on 64 rows of 2^20:
-        // 5.8 against 4.9 TB/s; a limit of 4096 loses again on 4096 x 4096)
+        // ... halved while that leaves fewer than 2048 workgroups ([3000,5003] w = 40: 17.8 us with 1125, 17.2 with 2250)
         while (g > kWavesPerWg && n_tiles / g < 2048) g /= 2;
         if (g_opt.slide_group > 0) g = (g_opt.slide_group + kWavesPerWg - 1) / kWavesPerWg * kWavesPerWg;
         if (g_opt.slide_chunk & 4) remap = 1;

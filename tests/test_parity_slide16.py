@@ -205,3 +205,26 @@ def test_windows_longer_than_a_tile_in_one_pass(B, kind, op, w, length):
                                         ((2, 2, 2, 2, 0, 0), (3, 11, 5, 5)), ((9, 9, 1, 1, 8, 8), (3, 3, 1, 1))])
 def test_pool2d_16_on_small_planes(B, kind, op, geom, shape):
     test_pool2d_16(B, kind, op, geom, shape)
+
+
+@pytest.mark.parametrize("kind", ["bf16", "f16"])
+@pytest.mark.parametrize("w", [18, 64, 300])
+@pytest.mark.parametrize("rows,length", [(9, 1100), (7, 2999), (40, 5003)])
+def test_tiles_beyond_a_row_see_nothing_of_its_neighbours(B, kind, w, rows, length):
+    """Tiles that reach beyond their row load the neighbouring rows' elements with it: every third row holds infinities, the
+    rows between them come out as if they were alone (add: bit for bit)."""
+    rng = np.random.Generator(np.random.PCG64(w + rows))
+    x = torch.from_numpy(rng.standard_normal((rows, length), dtype=np.float32)).to(TYPES[kind][0])
+    clean = x.clone()
+    x[1::3] = float("inf")
+    B.sws_set_option("slide_variant", 2)                         # the scan kernel at every window
+    try:
+        got = B.sws_slide1d_16(0, x.cuda(), w, 1.0).cpu()
+        alone = B.sws_slide1d_16(0, clean.cuda(), w, 1.0).cpu()
+    finally:
+        B.sws_set_option("slide_variant", 0)
+    keep = [i for i in range(rows) if i % 3 != 1]
+    assert torch.equal(got[keep], alone[keep])
+    ref, mag = oracle.slide1d(0, clean[keep].to(torch.float32).numpy(), w, 1.0)
+    err = np.abs(got[keep].double().numpy() - ref)
+    assert (err <= TOL * mag + (np.abs(ref) + TOL * mag) * TYPES[kind][2] + 2.0 ** -25).all()
