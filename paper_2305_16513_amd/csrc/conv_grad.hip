@@ -113,28 +113,41 @@ __global__ __launch_bounds__(kThreads) void conv1d_grad_weight_naive_kernel(
 // starts 20 floats after its neighbour's and the 128-bit reads of eight lanes hit eight bank quads.
 __host__ __device__ constexpr int gpos(int q) { return q + 4 * (q >> 4); }
 
-// Strips of 256 elements of row `src` (valid indices [0, n)) from index p0 on -> LDS, zero outside.
+// Strips of 256 elements of row `src` (valid indices [0, n)) from index p0 on, zero outside; of the last one the first
+// `tail` elements (a multiple of 4).  No load under a lane's condition that the compiler would wait for at once.
 template <int STRIPS>
-__device__ __forceinline__ void stage_row(float *dst, const float *__restrict__ src, int p0, int n, int lane)
+__device__ __forceinline__ void load_row(v4f (&g)[STRIPS], const float *__restrict__ src, int p0, int n, int tail, int lane)
 {
-    v4f g4[STRIPS];
+    const int o = p0 > 0 ? p0 : 0;                   // (descriptor from there on: rows of any length)
+    const int64_t left = 4 * ((int64_t)n - o);
+    const __amdgpu_buffer_rsrc_t rs = rsrc(src + o, left < 0 ? 0u : (left < 0x7fffffff ? (unsigned)left : 0x7fffffffu));
+    const unsigned at = 16 * lane, at_last = 4 * lane < tail ? at : kNowhere;
+    if (p0 >= 0 && p0 <= n - 256 * STRIPS) {
 #pragma unroll
-    for (int j = 0; j < STRIPS; ++j) {
-        const int s0 = p0 + 256 * j;                 // wave-uniform
-        const int q = s0 + 4 * lane;
-        if (s0 >= 0 && s0 + 256 <= n) {
-            g4[j] = *(const v4f_u *)(src + q);
-        } else if (s0 >= n || s0 + 256 <= 0) {
-            g4[j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-        } else {
-            float e4[4];
+        for (int j = 0; j < STRIPS; ++j)
+            g[j] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs, j + 1 < STRIPS ? at : at_last, 1024 * j, 0));
+    } else {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) e4[c] = (q + c >= 0 && q + c < n) ? src[q + c] : 0.0f;
-            g4[j] = (v4f){e4[0], e4[1], e4[2], e4[3]};
+        for (int j = 0; j < STRIPS; ++j) {
+            const int s0 = p0 + 256 * j, q = s0 + 4 * lane;      // (wave-uniform tests)
+            if (s0 >= 0 && s0 + 256 <= n) {
+                g[j] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rs, j + 1 < STRIPS ? at : at_last, 4 * (s0 - o), 0));
+                continue;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                g[j][c] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, q + c < 0 ? kNowhere : 4u * (unsigned)(q + c - o), 0, 0));
         }
     }
+}
+
+// Such strips -> LDS
+template <int STRIPS>
+__device__ __forceinline__ void put_row(float *dst, const v4f (&g)[STRIPS], int tail, int lane)
+{
 #pragma unroll
-    for (int j = 0; j < STRIPS; ++j) *(v4f *)(dst + gpos(256 * j + 4 * lane)) = g4[j];
+    for (int j = 0; j < STRIPS; ++j)
+        if (j + 1 < STRIPS || 4 * lane < tail) *(v4f *)(dst + gpos(256 * j + 4 * lane)) = g[j];
 }
 
 // The same for taps spaced d apart: element q at phase q % d, index q / d inside it, a phase PP floats long, so that a
@@ -178,11 +191,11 @@ constexpr int kSumTiles = 16 * kWavesPerWg;          // tiles of a workgroup bet
 template <int KB4, bool DIL>
 __global__ __launch_bounds__(kThreads) void conv1d_thin_grad_weight_kernel(
     const float *__restrict__ x, const float *__restrict__ gy, float *__restrict__ gw, int B, int Cin, int L,
-    int Cout, int Lo, int k, int pad, int cog, int tiles_per_row, int64_t per, int d, int PPX, int PPG)
+    int Cout, int Lo, int k, int pad, int cog, int tiles_per_row, unsigned per, int d, int PPX, int PPG)
 {
     constexpr int K4 = 4 * KB4;
     constexpr int XS = (kTileOut + K4 + 255) / 256;  // strips of x per tile
-    constexpr int XREG = (gpos(256 * XS) + 63) / 64 * 64;
+    constexpr int XREG = (gpos(kTileOut + K4) + 63) / 64 * 64;
     constexpr int GREG = (gpos(kTileOut) + 63) / 64 * 64;
     constexpr int NG = KB4 + 4;                      // 4-float groups in a lane's window of x
     extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -194,8 +207,8 @@ __global__ __launch_bounds__(kThreads) void conv1d_thin_grad_weight_kernel(
     float *X = lds + wave * (xreg + greg), *G = X + xreg;
     // consecutive workgroups take consecutive channels of the same images: adjacent rows of memory
     const int co = (int)(blockIdx.x % (unsigned)Cout);
-    const int64_t j0 = (int64_t)(blockIdx.x / (unsigned)Cout) * per, total = (int64_t)B * tiles_per_row;
-    const int64_t j1 = j0 + per < total ? j0 + per : total;
+    const unsigned j0 = blockIdx.x / (unsigned)Cout * per, total = (unsigned)B * (unsigned)tiles_per_row;       // (below 2^31)
+    const unsigned j1 = j0 + per < total ? j0 + per : total;
     const int ci = co / cog;
     const float inv_d = 1.0f / (float)d;
     const int blocks = DIL ? 64 / d : 64;            // runs of 16 indices per phase
@@ -205,24 +218,48 @@ __global__ __launch_bounds__(kThreads) void conv1d_thin_grad_weight_kernel(
     const float *Xw = X + (DIL && on ? ph * PPX + 20 * blk : 20 * (DIL ? 0 : lane));
     const float *Gw = G + (DIL && on ? ph * PPG + 20 * blk : 20 * (DIL ? 0 : lane));
 
+    // Rows of taps next to each other: the next tile's strips are in registers while this one's products run, and go to LDS
+    // behind them (loaded and waited for tile by tile, 32 x 128 rows of 16384, k = 31: 126 us, now
+    // 100, 5.4 TB/s; cold inputs 143 / 119).
+    v4f xs[XS], gs[kTileOut / 256];
+    auto rows = [&](unsigned j, const float *&xr, const float *&gr, int &t0) {
+        const unsigned b = j / (unsigned)tiles_per_row;
+        t0 = (int)(j - b * (unsigned)tiles_per_row) * TO;
+        xr = x + ((int64_t)b * Cin + ci) * L;
+        gr = gy + ((int64_t)b * Cout + co) * Lo;
+    };
+    auto load_tile = [&](unsigned j) {
+        const float *xr, *gr;
+        int t0;
+        rows(j, xr, gr, t0);
+        load_row<XS>(xs, xr, t0 - pad, L, K4, lane);
+        load_row<kTileOut / 256>(gs, gr, t0, Lo, 256, lane);
+    };
+    auto put_tile = [&]() {
+        put_row<XS>(X, xs, K4, lane);
+        put_row<kTileOut / 256>(G, gs, 256, lane);
+    };
+    if (!DIL && j0 + wave < j1) {
+        load_tile(j0 + wave);
+        put_tile();
+    }
     // Totals are taken every 16 tiles of a wavefront: a lane's sum is then at most 256 terms long however long the run (one sum over a run
     // of 342 tiles: twice the error on [1024,768,512], which goes with the root of the length; 16 tiles cost as much as 17).
-    for (int64_t js = j0; js < j1; js += kSumTiles) {
-        const int64_t je = js + kSumTiles < j1 ? js + kSumTiles : j1;
+    for (unsigned js = j0; js < j1; js += kSumTiles) {
+        const unsigned je = js + kSumTiles < j1 ? js + kSumTiles : j1;
         float acc[K4];
 #pragma unroll
         for (int t = 0; t < K4; ++t) acc[t] = 0.0f;
-        for (int64_t j = js + wave; j < je; j += kWavesPerWg) {
-            const int64_t b = j / tiles_per_row;
-            const int t0 = (int)(j - b * tiles_per_row) * TO;
-            const float *xr = x + (b * Cin + ci) * (int64_t)L;
-            const float *gr = gy + (b * Cout + co) * (int64_t)Lo;
+        for (unsigned j = js + wave; j < je; j += kWavesPerWg) {
+            const bool more = !DIL && j + kWavesPerWg < j1;
             if constexpr (DIL) {
+                const float *xr, *gr;
+                int t0;
+                rows(j, xr, gr, t0);
                 stage_row_phases(X, xr, t0 - pad, L, TO + (k - 1) * d, d, inv_d, PPX, lane);
                 stage_row_phases(G, gr, t0, Lo, TO, d, inv_d, PPG, lane);
-            } else {
-                stage_row<XS>(X, xr, t0 - pad, L, lane);
-                stage_row<kTileOut / 256>(G, gr, t0, Lo, lane);
+            } else if (more) {
+                load_tile(j + kWavesPerWg);
             }
             wave_lds_sync();
             float gv[16], xw[4 * NG];
@@ -246,6 +283,12 @@ __global__ __launch_bounds__(kThreads) void conv1d_thin_grad_weight_kernel(
                 for (int e = 0; e < 16; ++e) acc[t] = __builtin_fmaf(gv[e], xw[e + t], acc[t]);
             }
             wave_lds_sync();                             // the next tile overwrites X and G
+            if constexpr (!DIL) {
+                // (the products stay in front of the wait for the next tile)
+#pragma unroll
+                for (int t = 0; t < K4; ++t) asm volatile("" : "+v"(acc[t]) : : "memory");
+                if (more) put_tile();
+            }
         }
         // ---- one total per tap: across lanes, then across the workgroup's wavefronts, then to memory
 #pragma unroll
@@ -502,11 +545,11 @@ hipError_t launch_thin_gw1(const float *x, const float *gy, float *gw, int B, in
     const int64_t per = (total + parts - 1) / parts;
     parts = (total + per - 1) / per;
     if (Cout * parts > 2147483647LL) return kNotTaken;
-    constexpr int K4 = 4 * KB4, XS = (kTileOut + K4 + 255) / 256;
+    constexpr int K4 = 4 * KB4;
     // a phase's length: its indices in 16 + 4 layout, an odd number of 16-byte groups (eight lanes of eight phases then
     // read eight bank quads)
     const int PPX = (gpos(TO / d + K4 + 16) / 8 * 8) + 4, PPG = (gpos(TO / d + 16) / 8 * 8) + 4;
-    const size_t xreg = DIL ? (size_t)d * PPX : (gpos(256 * XS) + 63) / 64 * 64, greg = DIL ? (size_t)d * PPG : (gpos(kTileOut) + 63) / 64 * 64;
+    const size_t xreg = DIL ? (size_t)d * PPX : (gpos(kTileOut + K4) + 63) / 64 * 64, greg = DIL ? (size_t)d * PPG : (gpos(kTileOut) + 63) / 64 * 64;
     const size_t lds = kWavesPerWg * (xreg + greg) * sizeof(float);
     if (lds > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute((const void *)conv1d_thin_grad_weight_kernel<KB4, DIL>,
@@ -514,7 +557,7 @@ hipError_t launch_thin_gw1(const float *x, const float *gy, float *gw, int B, in
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((conv1d_thin_grad_weight_kernel<KB4, DIL>), dim3((unsigned)(Cout * parts)), dim3(kThreads), lds, s, x, gy, gw,
-                       B, Cin, L, Cout, Lo, k, pad, cog, tiles_per_row, per, d, PPX, PPG);
+                       B, Cin, L, Cout, Lo, k, pad, cog, tiles_per_row, (unsigned)per, d, PPX, PPG);
     return hipGetLastError();
 }
 

@@ -490,3 +490,17 @@ def test_grad_weight_of_thin_layers_sums_long_runs_in_parts(B, dil):
     gw = B.sws_conv1d_grad_weight(x, gy, 1, 1, 0, dil, 2048).double()
     want = 512 * 16 * (1.0 + 3 * 2.0 ** -16)
     assert ((gw - want).abs() <= 13 * 2.0 ** -24 * want).all(), ((gw - want).abs().max() / want).item()
+
+
+# b, channels, length, k, pad: rows one below, at and one beyond a tile, ends inside a strip of 256, the smallest and the largest kernels, rows
+# shorter than the padding's reach, more than 16 tiles per wavefront (a total in between) and wavefronts without a tile
+THIN_GW = [(3, 2, 1024, 31, 15), (1, 1, 1025, 1, 0), (2, 1, 2047, 64, 63), (5, 3, 3079, 33, 0), (1, 2, 70000, 4, 1), (2, 1, 40, 36, 30),
+           (1, 1, 257, 2, 1), (90, 1, 1030, 61, 30), (1, 2, 1311, 32, 400)]
+
+
+@pytest.mark.parametrize("integer", [True, False])
+@pytest.mark.parametrize("b,c,length,k,pad", THIN_GW)
+def test_grad_weight_one_channel_per_output_adjacent_taps(B, b, c, length, k, pad, integer):
+    """Tiles that wait in registers while the one before is multiplied: every way in which a tile or a run can end."""
+    for cog in (1, 2):
+        _check_gw(B, (b, c, length, c * cog, k, 1, pad, 1, c), 70 + k, integer)
