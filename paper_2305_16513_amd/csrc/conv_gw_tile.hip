@@ -30,11 +30,11 @@
 // instance spills, whose reloads wait for the loads in flight ([32,64,56,56] -> 64 93 us, now 75).
 //
 // Sums leave as partial blocks in the caller's workspace, lane after lane, and gw_reduce_kernel adds them in a fixed order:
-// the result does not depend on the order in which workgroups end (6 - 13 us; the atomic adds of conv_gw_split.hip, 36864 per
+// the result does not depend on the order in which workgroups end (5 - 10 us; the atomic adds of conv_gw_split.hip, 36864 per
 // workgroup, take 27 us on 64 x 64 channels, 3 x 3).
 //
 // Measured, us, this kernel with its second pass / the kernels without a workspace: [17,128,23,14] -> 104, 5 x 5 55 / 313,
-// [1,96,65,65] -> 484, 3 x 3 49 / 208, [32,256,14,14] -> 256, 3 x 3 70 / 87, [32,64,56,56] -> 64 69 / 74, [16,64,4096] -> 64, k = 3
+// [1,96,65,65] -> 484, 3 x 3 49 / 208, [32,256,14,14] -> 256, 3 x 3 65 / 87, [32,64,56,56] -> 64 69 / 74, [16,64,4096] -> 64, k = 3
 // 28 / 31.  Two LDS buffers with tiles of 64 positions, one wavefront of a SIMD splitting while the other multiplies, came out even at nine
 // taps and behind at one (174 against 127 us on [19,96,87,87] -> 256): not taken.
 #include "sws_internal.h"
@@ -301,43 +301,62 @@ void conv_gw_tile_kernel(const float *__restrict__ x, const float *__restrict__ 
     }
 }
 
-// gw from the partial blocks: a workgroup adds 64 lanes of one (block, tap, wavefront, register), its four wavefronts
-// every fourth run; register v of lane (l32, half) is output channel 8*(v/4) + 4*half + v%4, input channel l32 of the
-// block of 32.  An octet of channels that reached beyond the last one held the last eight (see the staging).
-__global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
+// gw from the partial blocks: a workgroup adds a quarter (registers 4 q .. 4 q + 3: eight output channels x 32 input channels)
+// of one (block, wavefront) for TG taps, S wavefronts per tap, every S-th run each; register v of lane (l32, half) is output
+// channel 8*(v/4) + 4*half + v%4, input channel l32 of the block of 32.  An octet of channels that reached beyond the last one
+// held the last eight (see the staging).
+// Bound by latency: 128-bit loads, eight of a wavefront's in flight at once; few runs leave room for all taps of a channel
+// in one workgroup, whose stores are then contiguous (one tap and 64 elements per workgroup: 13 us on
+// 256 x 256 channels, 3 x 3, eight runs, now 7.6; 14 / 10 with sixteen).
+constexpr int kReduceWaves = 9, kReduceSplit = 8;     // wavefronts of a workgroup at most; ones of a tap, and ones where several taps meet
+__global__ __launch_bounds__(64 * kReduceWaves) void gw_reduce_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB,
+                                                                      int WM, int WN, int TG, int S)
 {
-    __shared__ float part[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nblk = g.cob * g.cib * g.ng, BLK = WM * WN;
-    const int v = blockIdx.x & 15, rest = (int)(blockIdx.x >> 4), w = rest % BLK, t = rest / BLK % TB, blk = rest / (BLK * TB);
-    const int grp = blk % g.ng, cb = blk / g.ng, cob = cb / g.cib, cib = cb - cob * g.cib;
-    if (t >= g.gnt[grp]) return;
-    const int64_t step = (int64_t)nblk * (TB * BLK * 1024);
-    const float *p = ws + (int64_t)blk * (TB * BLK * 1024) + t * (BLK * 1024) + w * 1024 + v * 64 + lane;
-    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    int k = wave;
-    for (; k + 12 < g.nsplit; k += 16) {
+    __shared__ v4f part[kReduceWaves][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int BLK = WM * WN, ntg = (int)((unsigned)(TB + TG - 1) / (unsigned)TG);
+    const unsigned rest = blockIdx.x >> 2, rest2 = rest / (unsigned)BLK, blk = rest2 / (unsigned)ntg, cb = blk / (unsigned)g.ng;
+    const int qr = blockIdx.x & 3, w = (int)(rest - rest2 * BLK), ta = (int)(rest2 - blk * ntg) * TG, grp = (int)(blk - cb * g.ng);
+    const int cob = (int)(cb / (unsigned)g.cib), cib = (int)cb - cob * g.cib;
+    const int nt = g.gnt[grp] - ta < TG ? g.gnt[grp] - ta : TG;      // my taps
+    if (nt <= 0) return;
+    const int sl = (int)((unsigned)wave / (unsigned)TG), t = wave - sl * TG;
+    if (t < nt) {
+        const int64_t step = (int64_t)g.cob * g.cib * g.ng * (TB * BLK * 256);
+        const v4f *p = (const v4f *)ws + (int64_t)blk * (TB * BLK * 256) + (ta + t) * (BLK * 256) + w * 256 + qr * 64 + lane;
+        v4f s[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) s[u] += p[(k + 4 * u) * step];
+        for (int u = 0; u < 8; ++u) s[u] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k = sl; k < g.nsplit; k += 8 * S) {
+            v4f f[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) f[u] = p[(k + u * S < g.nsplit ? k + u * S : k) * step];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s[u] += k + u * S < g.nsplit ? f[u] : (v4f){0.0f, 0.0f, 0.0f, 0.0f};     // (beyond the last run: not counted)
+        }
+        part[wave][lane] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
     }
-    for (; k < g.nsplit; k += 4) s[0] += p[k * step];
-    part[wave][lane] = (s[0] + s[1]) + (s[2] + s[3]);
     __syncthreads();
-    if (wave != 0) return;
-    const float sum = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
     auto channel = [](int slot, int n) {              // the channel a slot holds; -1: none, or one that another slot holds
         const int o = slot & ~7, c0 = o < n - 8 ? o : (n > 8 ? n - 8 : 0), c = c0 + (slot & 7);
         return o < n && c >= o && c < n ? c : -1;
     };
-    const int co = channel(cob * (32 * WM) + w % WM * 32 + 8 * (v / 4) + 4 * (lane >> 5) + v % 4, g.Cout);
-    const int ci = channel(cib * (32 * WN) + w / WM * 32 + (lane & 31), g.Cin);
-    if (co >= 0 && ci >= 0) gw[((int64_t)co * g.Cin + ci) * g.KT + g.gt0[grp] + t] = sum;
+    // (consecutive threads: consecutive taps of an input channel, then the next one, then the next output channel)
+    const float inv_nt = 1.0f / (float)nt;
+    for (int i = threadIdx.x; i < 256 * nt; i += blockDim.x) {
+        const int e = fdiv(i, inv_nt), tt = i - e * nt, c8 = e >> 5, l32 = e & 31;
+        const int at = (c8 & 3) * 64 + (c8 >> 2) * 32 + l32;         // register 4 qr + c8 % 4, lane
+        float sum = ((const float *)part[tt])[at];
+        for (int q = 1; q < S; ++q) sum += ((const float *)part[q * TG + tt])[at];
+        const int co = channel(cob * (32 * WM) + w % WM * 32 + 8 * qr + c8, g.Cout);
+        const int ci = channel(cib * (32 * WN) + w / WM * 32 + l32, g.Cin);
+        if (co >= 0 && ci >= 0) gw[((int64_t)co * g.Cin + ci) * g.KT + g.gt0[grp] + ta + tt] = sum;
+    }
 }
 
-template <int TB, int WM, int WN, bool FAST>
+template <int TB, int WM, int WN, bool FAST, int UX = 4>
 hipError_t launch_gw1(const float *x, const float *gy, float *gw, float *ws, const GwTile &g, size_t lds, hipStream_t s)
 {
-    constexpr int UX = 4;
     const int nblk = g.cob * g.cib * g.ng;
     if (lds > 64 * 1024) {
         static std::atomic<uint64_t> raised{0};
@@ -348,7 +367,11 @@ hipError_t launch_gw1(const float *x, const float *gy, float *gw, float *ws, con
                        s, x, gy, ws, g);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(gw_reduce_kernel, dim3((unsigned)(nblk * TB * WM * WN * 16)), dim3(256), 0, s, ws, gw, g, TB, WM, WN);
+    int S = (g.nsplit + 7) / 8;
+    S = S < kReduceSplit ? S : kReduceSplit;
+    const int TG = S == 1 || TB < kReduceSplit / S ? TB : kReduceSplit / S;
+    hipLaunchKernelGGL(gw_reduce_kernel, dim3((unsigned)(nblk * ((TB + TG - 1) / TG) * WM * WN * 4)), dim3(64 * TG * S), 0, s, ws, gw, g, TB, WM,
+                       WN, TG, S);
     return hipGetLastError();
 }
 
@@ -356,6 +379,9 @@ template <int TB, bool FAST>
 hipError_t launch_gw2(const float *x, const float *gy, float *gw, float *ws, const GwTile &g, int WM, int WN, size_t lds, hipStream_t s)
 {
     if (WM == 2 && WN == 2) return launch_gw1<TB, 2, 2, FAST>(x, gy, gw, ws, g, lds, s);
+    if constexpr (TB == 9)
+        if (WN == 1 && 4 * g.PS > 4 * kThreads)
+            return WM == 2 ? launch_gw1<TB, 2, 1, FAST, 5>(x, gy, gw, ws, g, lds, s) : launch_gw1<TB, 1, 1, FAST, 5>(x, gy, gw, ws, g, lds, s);
     if (WM == 2) return launch_gw1<TB, 2, 1, FAST>(x, gy, gw, ws, g, lds, s);
     if (WN == 2) return launch_gw1<TB, 1, 2, FAST>(x, gy, gw, ws, g, lds, s);
     return launch_gw1<TB, 1, 1, FAST>(x, gy, gw, ws, g, lds, s);
@@ -414,7 +440,6 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
     g.ng = q.ng;
     // Channel blocks of a workgroup, strip width, rows per tile and runs: the smallest estimated time of the longest run (products
     // on two wavefronts per SIMD, staging per unit, a run's end), in cycles.
-    constexpr int kUX = 4;
     bool found = false;
     double cost = 0;
     for (int wmn = 0; wmn < 4; ++wmn) {
@@ -426,7 +451,10 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
             const int TW = (int)((unsigned)(Wo + ns - 1) / ns), nstrips = (int)((unsigned)(Wo + TW - 1) / TW);
             const int CW = TW + (int)((unsigned)(SW - 1) / sw), LW = SWc * CW;
             for (int rpt = kBN / TW < g.NR ? kBN / TW : g.NR; rpt >= 1; rpt = rpt > 4 ? rpt * 3 / 4 : rpt - 1) {
-                const int crossings = (int)((unsigned)(rpt - 1 + g.Ho - 1) / g.Ho);
+                // (tiles start at multiples of rpt, so at most this far down an image: where rpt divides Ho no tile meets two)
+                int start = rpt, mod = g.Ho;
+                while (mod) { const int r = (int)((unsigned)start % (unsigned)mod); start = mod; mod = r; }
+                const int crossings = (int)((unsigned)(g.Ho - start + rpt - 1) / (unsigned)g.Ho);
                 const int64_t lines = (int64_t)(rpt - 1) * g.ls + g.SH + crossings * (g.SH - g.ls);
                 if (lines * LW > 1024) continue;
                 const int64_t imgs = rpt / Ho + 2;    // a tile's images within 32-bit offsets
@@ -434,7 +462,7 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
                 const int PS = ((int)(lines * LW) + 3) / 16 * 16 + 12;
                 const size_t stage = (size_t)4 * 3 * 16 * (wn * PS + wm * kPG) + kBN * 4;
                 const size_t red = (size_t)(8 - wm * wn) * 4 * (q.tb < 3 ? q.tb : 3) * 1024;
-                if (4 * wn * PS > kUX * kThreads || stage > 158 * 1024) continue;
+                if (4 * wn * PS > (wn == 1 && q.tb == 9 && sh == 2 && sw == 2 ? 5 : 4) * kThreads || stage > 158 * 1024) continue;
                 const int tps = (int)((unsigned)(g.NR + rpt - 1) / rpt), ksteps = (rpt * TW + 15) / 16, steps = (ksteps + wk - 1) / wk;
                 if ((int64_t)tps * nstrips >= (1LL << 30)) continue;
                 const int tiles = tps * nstrips;
