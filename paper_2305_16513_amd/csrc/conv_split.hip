@@ -64,6 +64,9 @@ struct SplitGeom {
     int nt[4];                                        // phases: taps of each
     float inv_tw, inv_twl, inv_Ho, inv_LPI, inv_LW, inv_CW, inv_PS, inv_KT;
     unsigned short tapoff[kMaxSteps];                 // tap -> staged positions from a position's base
+
+    // a chunk is the phases of a 3 x 3 kernel at stride 2 that is padded by one (the usual one): straight-line code
+    bool phases9() const { return KT == 9 && nt[0] == 1 && nt[1] == 2 && nt[2] == 2 && nt[3] == 4; }
 };
 
 struct PrepGeom {
@@ -120,15 +123,19 @@ __global__ __launch_bounds__(256) void split_weights_kernel(const float *__restr
 // U: staged units (eight channels of one position) per thread.  S: steps per chunk and wavefront when that number is
 // compiled in (the chunk is then straight-line code: the next chunk's loads go out between the first products and
 // their splitting runs between the last ones; with a loop over the steps the wait counters have to assume
-// the worst order of the two kinds of loads), 0: any number.  R: steps of weights held, R - 1 of them in flight.
+// the worst order of the two kinds of loads), 0: any number.  Straight-line code / the loop, us with the weights' pass, three inputs in
+// turn: stride-2 adjoints, 3 x 3, [32,128,56,56] <- 128 67 / 77, [32,256,28,28] <- 256 60 / 89, [8,256,28,28] <- 512 44 / 62, [1,128,56,56] <- 128
+// 17 / 22; 5 x 5 [32,256,14,14] -> 256 114 / 120, [8,128,28,28] -> 128 41 / 45.  Five taps of a row at two channel groups came out even: in the loop.  R: steps of weights held, R - 1 of them in flight.
 // WPE: wavefronts per SIMD that the registers are meant for.
 template <int MB, int NB, int WM, int WN, int WK, int U, int NPH, int WPE, int S>
 __global__ __launch_bounds__(64 * WM * WN * WK) __attribute__((amdgpu_waves_per_eu(WPE)))
 void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, float *__restrict__ y, SplitGeom g)
 {
     constexpr int T = 64 * WM * WN * WK;
-    constexpr int R = S ? (S % 3 == 0 ? 3 : 4) : 2;
-    static_assert(S == 0 || (S % R == 0 && NPH == 1), "the ring of weights closes over a chunk");
+    constexpr int R = S ? (S % 3 == 0 ? 3 : S % 4 == 0 ? 4 : 5) : 2;
+    static_assert(S == 0 || (S % R == 0 && (NPH == 1 || S == 9)), "the ring of weights closes over a chunk");
+    constexpr int kPhase9[9] = {0, 1, 1, 2, 2, 3, 3, 3, 3};      // straight-line chunks with phases: a step's phase (see launch_cfg)
+    constexpr int NLO = S ? NPH : 1;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -277,25 +284,27 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[f][m][b][v] = 0.0f;
     // Products of the leading pieces go to one accumulator, the other five (at most 2^-8 of them) to another, added
-    // once at the end (phases: once per chunk): an output then takes one rounding of its own size per 16 channels and tap
+    // once at the end (phases in a loop over the steps: once per chunk): an output then takes one rounding of its own size per 16 channels and tap
     // instead of six.
-    v16f lo[MB][NB];
+    v16f lo[NLO][MB][NB];
     auto clear_lo = [&]() {
 #pragma unroll
-        for (int m = 0; m < MB; ++m)
+        for (int f = 0; f < NLO; ++f)
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+            for (int m = 0; m < MB; ++m)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) lo[m][b][v] = 0.0f;
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) lo[f][m][b][v] = 0.0f;
     };
-    auto fold_lo = [&](v16f (&c)[MB][NB]) {
+    auto fold_lo = [&](v16f (&c)[MB][NB], int f) {
 #pragma unroll
         for (int m = 0; m < MB; ++m)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) c[m][b] += lo[m][b];
+            for (int b = 0; b < NB; ++b) c[m][b] += lo[f][m][b];
     };
     clear_lo();
-    auto products = [&](v16f (&c)[MB][NB], const v4u (&a)[MB][3], const v4u (&b)[NB][3]) {
+    auto products = [&](v16f (&c)[MB][NB], v16f (&cl)[MB][NB], const v4u (&a)[MB][3], const v4u (&b)[NB][3]) {
         constexpr int PA[6] = {2, 0, 1, 0, 1, 0}, PB[6] = {0, 0, 1, 2, 0, 1};      // (the leading product second: the chains alternate)
 #pragma unroll
         for (int k = 0; k < 6; ++k)
@@ -303,7 +312,7 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
             for (int m = 0; m < MB; ++m)
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
-                    v16f &d = k == 1 ? c[m][j] : lo[m][j];
+                    v16f &d = k == 1 ? c[m][j] : cl[m][j];
                     d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a[m][PA[k]]),
                                                                 __builtin_bit_cast(v8bf, b[j][PB[k]]), d, 0, 0, 0);
                 }
@@ -338,7 +347,8 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
                     for (int i = 0; i < U; ++i)
                         if (S - U + i == s || (S < U && s == S - 1)) commit(i, nxt);
                 }
-                products(acc[0], A[s % R], Bq[s & 1]);
+                constexpr bool kPh = NPH > 1;
+                products(acc[kPh ? kPhase9[s % 9] : 0], lo[kPh ? kPhase9[s % 9] : 0], A[s % R], Bq[s & 1]);
                 __builtin_amdgcn_sched_barrier(0);
             }
             ks += S;
@@ -362,7 +372,7 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
                 aload(A[r ^ 1], ks + 1);
                 bload(Bq[r ^ 1], cur, s + 1 < g.S ? s + 1 : 0);
                 __builtin_amdgcn_sched_barrier(0);
-                products(c, A[r], Bq[r]);
+                products(c, lo[0], A[r], Bq[r]);
                 __builtin_amdgcn_sched_barrier(0);
                 ++ks;
             };
@@ -393,7 +403,7 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
                     if (g.nt[f] == 0) continue;
                     clear_lo();
                     run(acc[f], s, s + g.nt[f]);
-                    fold_lo(acc[f]);
+                    fold_lo(acc[f], 0);
                     s += g.nt[f];
                 }
             }
@@ -405,7 +415,10 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
             }
         }
     }
-    if constexpr (NPH == 1) fold_lo(acc[0]);
+    if constexpr (NPH == 1 || S != 0) {
+#pragma unroll
+        for (int f = 0; f < NLO; ++f) fold_lo(acc[f], f);
+    }
 
     // ---- the wavefronts that share a block add up through LDS
     if constexpr (WK > 1) {
@@ -519,8 +532,11 @@ hipError_t launch_cfg(const float *x, const v4u *ws, float *y, const SplitGeom &
         case 8: return launch_steps<I, 8>(x, ws, y, g, grid, lds, s);
         case 9: return launch_steps<I, 9>(x, ws, y, g, grid, lds, s);
         case 12: return launch_steps<I, 12>(x, ws, y, g, grid, lds, s);
+        case 25: return launch_steps<I, 25>(x, ws, y, g, grid, lds, s);
         default: break;
         }
+    } else if (g.phases9()) {
+        return launch_steps<I, 9>(x, ws, y, g, grid, lds, s);
     }
     return launch_steps<I, 0>(x, ws, y, g, grid, lds, s);
 }
@@ -608,6 +624,8 @@ bool plan(const SplitGeom &g, const Cfg &c, int Wo, int SW, int cus, Tiling *bes
             const int by_lds = 160 * 1024 / h.need;
             if (by_lds < res) res = by_lds;
             if (res < 1) res = 1;
+            // (fitted before layers of 25 taps and the usual phases became straight-line chunks: calling them that here chose worse, [32,512,14,14] -> 512
+            // 71 us for 65, 5 x 5 on [8,50,40,40] -> 30 21.5 for 19.9)
             const bool line = c.nph == 1 && (h.S == 6 || h.S == 8 || h.S == 9 || h.S == 12);      // straight-line chunks
             const double mfma = (double)h.KS * c.mb * c.nb * 6 * 32 * wpw * (c.nph == 1 ? 1.0 : 1.106);
             const double wld = (double)h.KS * (T / 64) * c.mb * 48;       // weights through the vector cache, 64 bytes per cycle

@@ -424,3 +424,15 @@ def test_grad_weight_is_as_exact_as_the_fp32_kernels(B, monkeypatch, case):
     monkeypatch.setattr(B, "_scratch", lambda *a: (None, None, 0))
     plain = error()
     assert tiled <= 1.1 * plain, (tiled, plain)
+
+
+# 3 x 3, stride 2, padded by one: a chunk's phases as straight-line code; one and several chunks, odd planes (a last row or column of one
+# phase only), ragged channels
+@pytest.mark.parametrize("integer", [True, False])
+@pytest.mark.parametrize("cfg", (0,) + tuple(PHASES))
+def test_phases_of_the_usual_strided_layer(B, cfg, integer, lent):
+    B.sws_set_option("conv2d_variant", 100 + cfg if cfg else 0)
+    for i, (n, cin, cout, h, w) in enumerate([(2, 40, 70, 15, 22), (3, 16, 16, 8, 8), (1, 33, 130, 31, 17), (5, 64, 48, 2, 3), (1, 20, 9, 2, 40)]):
+        _check(B, (n, cin, cout, h, w, 3, 3, 2, 1), 80 + i, integer, forward=False)
+    taken = [_taken(t) for t in lent]
+    assert len(taken) == 5 and sum(taken) >= 4, taken
