@@ -765,9 +765,8 @@ static GwLayer gw_layer(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Co
 }
 
 // Layers that run on the tiled kernel, given a workspace.  3 x 3 at stride 2 on channels in multiples of 32 and rows of whole
-// 16-byte groups also has a kernel that reads its operands straight from memory; with both passes [32,128,56,56] -> 128 takes 101 us there, 77 here,
-// [32,64,56,56] -> 64 65 / 33, [8,64,112,112] -> 128 69 / 51, but [32,512,16,16] -> 512 64 / 106 (short rows are mostly halo here, and there four
-// workgroups share a block of gw): the smaller estimate.  At stride 1 [32,256,14,14] -> 256 88 / 65, [3,128,10,97] -> 472 150 / 46.
+// 16-byte groups stays on the kernel that reads its operands straight from memory (its tile here would be four
+// fifths halo): [32,128,56,56] -> 128 93 us there, 97 here; at stride 1 [32,256,14,14] -> 256 88 / 75, [3,128,10,97] -> 472 150 / 46.
 // *exact: the kernel that the layer runs on without a workspace multiplies in fp32, and gw's error against 64 bits (1.7e-7 whatever
 // the size) is to be no larger here.  The other layers' split-operand kernels (conv_gw_split.hip) are further off than either form of this one.
 // *other_us: what the kernel would take that serves the layer otherwise.  Layers one row high of k = 1, 3 and 5 have one of their own, whose pipeline
@@ -779,9 +778,10 @@ static bool tile_wanted(const GwLayer &l, bool *exact, double *other_us)
     *exact = true;
     *other_us = 1e30;
     if (g_opt.conv2d_variant == 100) return true;
+    const bool direct = l.kh == 3 && l.kw == 3 && l.sh == 2 && l.sw == 2 && l.Cin % 32 == 0 && l.Cout % 32 == 0 && l.W % 4 == 0 && l.Wo % 4 == 0;
+    if (direct) return false;
     if (conv2d_gw_split_takes(l.Cin, l.W, l.Cout, l.kh, l.kw, l.sh, l.sw, l.pw)) {
         *exact = false;
-        if (l.sh == 2 && !(l.W & 3) && !(l.Wo & 3)) *other_us = conv2d_gw_split_us(l.N, l.Cin, l.Cout, l.Ho, l.Wo);
     } else if (l.H == 1 && l.kh == 1 && l.sw == 1 && l.dil == 1) {
         const double us = conv1d_gw_split_us(l.N, l.Cin, l.W, l.Cout, l.Wo, l.kw, l.pw);
         if (us > 0) {

@@ -725,44 +725,6 @@ bool conv2d_gw_split_takes(int64_t Cin, int64_t W, int64_t Cout, int32_t kh, int
     return (pw == 0 || pw == 1) && (sw == 1 || pw == 1) && W < (1 << 28) && Cin <= 32768 && Cout <= 32768;
 }
 
-namespace {
-
-struct GwTasks {
-    int S, nseg;                                      // rows per task, tasks per column of eight outputs
-    int64_t pairs, per;                               // pairs of tasks; of them per workgroup
-    double cost;                                      // rows of the longest workgroup
-};
-
-GwTasks gw_tasks(int64_t N, int64_t Ho, int g8, int64_t blocks)
-{
-    // Workgroups per block of gw: enough to fill the GPU once, no more — every workgroup ends with atomic adds
-    // of its whole block.  Rows per task S: the one whose rounds of whole tasks cost least, counting a step and a
-    // half for a task's start (three rows loaded and converted with nothing to hide behind).
-    int64_t wgs = (int64_t)device_cus() / blocks;
-    if (wgs < 1) wgs = 1;
-    if (g_opt.slide_group > 0) wgs = g_opt.slide_group;      // A/B: workgroups per block of gw
-    GwTasks q = {1, (int)Ho, 1, 1, 1e300};
-    for (int s1 = 1; s1 <= 32 && s1 <= Ho; ++s1) {
-        const int ns = (int)((Ho + s1 - 1) / s1);
-        const int64_t pr = (N * g8 * ns + 1) / 2;
-        const int64_t pw_ = (pr + wgs - 1) / wgs;
-        const double cost = (double)pw_ * (s1 + 1.5);
-        if (cost < q.cost) q = {s1, ns, pr, pw_, cost};
-    }
-    return q;
-}
-
-}  // namespace
-
-// Estimated time at stride 2 with the pass that clears gw, us (fitted to twelve layers, 17 - 119 us, deviation 20 %: the rows of the longest
-// workgroup, and every workgroup's atomic adds); the caller has asked conv2d_gw_split_takes.
-double conv2d_gw_split_us(int64_t N, int64_t Cin, int64_t Cout, int64_t Ho, int64_t Wo)
-{
-    const int64_t blocks = ((Cout + 63) / 64) * ((Cin + 63) / 64);
-    const GwTasks q = gw_tasks(N, Ho, (int)((Wo + 7) / 8), blocks);
-    return 14.0 + 1.08 * q.cost + 0.12 * (double)((q.pairs + q.per - 1) / q.per * blocks);
-}
-
 // *taken = false: not this kernel's case (nothing launched).  gw must hold zeros.
 hipError_t launch_conv2d_gw_split(const float *x, const float *gy, float *gw, int64_t N, int64_t Cin, int64_t H, int64_t W,
                                   int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh, int32_t sw,
@@ -774,9 +736,22 @@ hipError_t launch_conv2d_gw_split(const float *x, const float *gy, float *gw, in
     const int g8 = (int)((Wo + 7) / 8);
     const int co_blocks = (int)((Cout + 63) / 64), ci_blocks = (int)((Cin + 63) / 64);
     if ((int64_t)co_blocks * ci_blocks > 65535) return hipSuccess;
-    const GwTasks q = gw_tasks(N, Ho, g8, (int64_t)co_blocks * ci_blocks);
-    const int S = q.S, nseg = q.nseg;
-    const int64_t pairs = q.pairs, per = q.per;
+    // Workgroups per block of gw: enough to fill the GPU once, no more — every workgroup ends with atomic adds
+    // of its whole block.  Rows per task S: the one whose rounds of whole tasks cost least, counting a step and a
+    // half for a task's start (three rows loaded and converted with nothing to hide behind).
+    int64_t wgs = (int64_t)device_cus() / ((int64_t)co_blocks * ci_blocks);
+    if (wgs < 1) wgs = 1;
+    if (g_opt.slide_group > 0) wgs = g_opt.slide_group;      // A/B: workgroups per block of gw
+    int S = 1, nseg = (int)Ho;
+    int64_t pairs = 1, per = 1;
+    double best = 1e300;
+    for (int s1 = 1; s1 <= 32 && s1 <= Ho; ++s1) {
+        const int ns = (int)((Ho + s1 - 1) / s1);
+        const int64_t pr = (N * g8 * ns + 1) / 2;
+        const int64_t pw_ = (pr + wgs - 1) / wgs;
+        const double cost = (double)pw_ * (s1 + 1.5);
+        if (cost < best) { best = cost; S = s1; nseg = ns; pairs = pr; per = pw_; }
+    }
     const int64_t n_tasks = N * g8 * nseg;
     const int64_t grid = (pairs + per - 1) / per;
     if (grid > 2147483647LL) return hipSuccess;

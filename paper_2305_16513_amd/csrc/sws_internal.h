@@ -294,7 +294,6 @@ hipError_t launch_conv1d_gw_split(const float *x, const float *gy, float *gw, in
 
 // Matrix-core convolution (conv_mfma.hip); *taken = false: shape not covered, nothing launched.
 bool conv2d_gw_split_takes(int64_t Cin, int64_t W, int64_t Cout, int32_t kh, int32_t kw, int32_t sh, int32_t sw, int32_t pw);
-double conv2d_gw_split_us(int64_t N, int64_t Cin, int64_t Cout, int64_t Ho, int64_t Wo);
 double conv1d_gw_split_us(int64_t rows, int64_t Cin, int64_t L, int64_t Cout, int64_t Lo, int32_t k, int32_t pad);
 hipError_t launch_conv2d_mfma(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin, int64_t H,
                               int64_t W, int64_t Cout, int64_t Ho, int64_t Wo, int32_t kh, int32_t kw, int32_t sh,
