@@ -7,6 +7,12 @@
 // are dealt to the threads one by one, each combining its window from LDS (down H, then across W,
 // as the direct evaluation does) and stored coalesced.  Window cells outside the plane are skipped
 // by clamping the loop bounds, so padding and real-cell averages cost nothing extra.
+//
+// What bounds it is latency: a workgroup loads, waits, and walks windows through dependent LDS reads.  So a workgroup takes no more planes
+// than give every compute unit eight of them, and where it has fewer outputs than threads, 2^ls threads share one, every
+// 2^ls-th column each (a global average of 7 x 7 was 49 reads one after the other in 80 of 256 threads).  Average of 7 x 7
+// planes, 65536 of them, 6.4 -> 5.2 us, its adjoint 10.1 -> 8.8, 3 x 3 on 16384 of them
+// 13.5 -> 5.8; four or sixteen workgroups per unit: 5.2 and 5.9 on the first, 9.2 and 9.5 on the second.
 #include "sws_internal.h"
 
 namespace sws {
@@ -22,7 +28,7 @@ template <int OP, typename T>
 __global__ __launch_bounds__(kThreads) void pool2d_small_kernel(const T *__restrict__ x, T *__restrict__ y,
                                                                 int64_t planes, int H, int W, int Ho, int Wo, int kh,
                                                                 int kw, int sh, int sw, int ph, int pw, float scale,
-                                                                int div_valid, int G, unsigned rcp_q, unsigned rcp_wo)
+                                                                int div_valid, int G, int ls, unsigned rcp_q, unsigned rcp_wo)
 {
     using O = Op<OP>;
     __shared__ __attribute__((aligned(16))) float lds[kStage];
@@ -46,7 +52,9 @@ __global__ __launch_bounds__(kThreads) void pool2d_small_kernel(const T *__restr
     __syncthreads();
     T *dst = y + p0 * Q;
     const int m = g * Q;
-    for (int o = tid; o < m; o += kThreads) {
+    const int share = tid & ((1 << ls) - 1);
+    for (int i = tid; i < m << ls; i += kThreads) {
+        const int o = i >> ls;
         // o = (plane, ho, wo); the quotients by multiplication with 2^32 / d + 1 (exact: o < 2^16, d < 2^12)
         const int pl = Q == 1 ? o : (int)__umulhi((unsigned)o, rcp_q);
         const int cell = o - pl * Q;
@@ -57,16 +65,17 @@ __global__ __launch_bounds__(kThreads) void pool2d_small_kernel(const T *__restr
         const int a_lo = h0 < 0 ? -h0 : 0, a_hi = kh < H - h0 ? kh : H - h0;
         const int b_lo = c0 < 0 ? -c0 : 0, b_hi = kw < W - c0 ? kw : W - c0;
         float acc = O::id();
-        for (int b = b_lo; b < b_hi; ++b) {
+        for (int b = b_lo + share; b < b_hi; b += 1 << ls) {
             float col = O::id();
             for (int a = a_lo; a < a_hi; ++a) col = O::f(col, xp[(h0 + a) * W + c0 + b]);
             acc = O::f(acc, col);
         }
+        for (int j = 1; j < 1 << ls; j <<= 1) acc = O::f(acc, __shfl_xor(acc, j, kWave));      // (an output's threads are neighbours: all here)
         if (OP == SWS_OP_ADD) {
             const int cells = (a_hi > a_lo ? a_hi - a_lo : 0) * (b_hi > b_lo ? b_hi - b_lo : 0);
             acc *= div_valid ? scale / (float)cells : scale;
         }
-        dst[o] = (T)acc;
+        if (share == 0) dst[o] = (T)acc;
     }
 }
 
@@ -87,13 +96,17 @@ hipError_t launch_pool2d_small(int op, const T *x, T *y, int64_t planes, int H, 
     // ... and at most 4096 outputs: windows that spread a plane (the adjoint of a global average: 1 x 1 -> 7 x 7, 65536
     // planes) would otherwise leave too few workgroups, or outputs beyond the reach of the quotient below
     if (G * Q > 4096) G = Q < 1024 ? (int)(4096 / Q) & ~3 : 4;
+    const int64_t want = planes / (8 * device_cus());
+    if (want < G) G = want < 4 ? 4 : (int)want & ~3;
+    int ls = 0;
+    while (G * Q << (ls + 1) <= kThreads && 1 << ls < kw && ls < 5) ++ls;
     const int64_t grid = (planes + G - 1) / G;
     if (grid > 2147483647LL) return hipSuccess;
     *taken = true;
     const unsigned rcp_q = (unsigned)(4294967296ULL / (uint64_t)Q + 1), rcp_wo = (unsigned)(4294967296ULL / (uint64_t)Wo + 1);
 #define SWS_PS(OPV)                                                                                                \
     hipLaunchKernelGGL((pool2d_small_kernel<OPV, T>), dim3((unsigned)grid), dim3(kThreads), 0, s, x, y, planes, H, W, Ho, Wo, \
-                       kh, kw, sh, sw, ph, pw, scale, div_valid, G, rcp_q, rcp_wo)
+                       kh, kw, sh, sw, ph, pw, scale, div_valid, G, ls, rcp_q, rcp_wo)
     switch (op) {
     case SWS_OP_ADD: SWS_PS(SWS_OP_ADD); break;
     case SWS_OP_MAX: SWS_PS(SWS_OP_MAX); break;

@@ -290,6 +290,23 @@ def test_small_planes(B, variant, geom, shape):
         B.sws_set_option("pool2d_variant", 0)
 
 
+@pytest.mark.parametrize("op", ["add", "max", "min"])
+@pytest.mark.parametrize("shape", [(1, 1, 7, 7), (1, 3, 31, 33), (1, 9000, 7, 7), (3, 2731, 8, 8), (2, 300, 1, 40), (1, 4100, 14, 14), (70, 1024, 5, 3)])
+def test_small_planes_whole_windows(B, op, shape):
+    """Windows of a whole plane: an output's columns are shared by 1, 2 .. 32 threads, and by more than it has columns; one plane per
+    workgroup slot, a last workgroup with fewer; a window that reaches beyond the plane, where some threads have no column."""
+    n, c, h, w = shape
+    x = np.random.Generator(np.random.PCG64(h * 64 + w)).standard_normal(shape, dtype=np.float32)
+    for kh, kw, ph, pw in ((h, w, 0, 0), (h, w, (h - 1) // 2, (w - 1) // 2)):
+        scale = 1.0 / (kh * kw)
+        y = to_host(B.sws_pool2d(OPS[op], to_gpu(x), kh, kw, h, w, ph, pw, scale))
+        ref, mag = oracle.pool2d(OPS[op], x, kh, kw, h, w, ph, pw, scale)
+        if op == "add":
+            assert_within_tol(y, ref, mag, "whole planes %s" % (shape,))
+        else:
+            assert_bit_exact(y, ref, "whole planes %s %s" % (shape, op))
+
+
 @pytest.mark.parametrize("divisor", [0, 1])
 @pytest.mark.parametrize("geom", EX_GEOMS)
 @pytest.mark.parametrize("shape", [(3, 500, 7, 7), (2, 99, 14, 14), (1, 30, 9, 20)])
