@@ -121,6 +121,14 @@ def sws_out_len(length, w, stride=1, pad=0, dilation=1):
     return int(lib().sws_out_len(length, w, stride, pad, dilation))
 
 
+def _out_len(length, w, stride, pad, dilation=1):
+    """sws_out_len in Python: two of them were 0.9 us of the 7.5 that a pooling call takes the host, now 0.4."""
+    if length < 0 or w < 1 or stride < 1 or pad < 0 or dilation < 1:
+        return -1
+    left = length + 2 * pad - dilation * (w - 1) - 1
+    return left // stride + 1 if left >= 0 else -1
+
+
 def sws_set_option(key, value):
     rc = lib().sws_set_option(key.encode(), int(value))
     for f in (_workspace_bytes, _conv1d_gw_bytes, _conv2d_gw_bytes):     # an option may take a layer to another kernel
@@ -285,7 +293,7 @@ def sws_pool2d(op, x, kh, kw, sh=1, sw=1, ph=0, pw=0, scale=1.0, y=None, stream=
     """x [N, C, H, W] -> y [N, C, Ho, Wo]."""
     _dev(x, "x")
     n, c, h, wd = x.shape
-    ho, wo = sws_out_len(h, kh, sh, ph), sws_out_len(wd, kw, sw, pw)
+    ho, wo = _out_len(h, kh, sh, ph), _out_len(wd, kw, sw, pw)
     if ho < 1 or wo < 1:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_pool2d")
     y = _out(y, (n, c, ho, wo), x)
@@ -299,7 +307,7 @@ def sws_maxpool2d_grad(x, gy, kh, kw, sh=1, sw=1, ph=0, pw=0, gx=None, stream=No
     _dev(x, "x")
     _dev(gy, "gy")
     n, c, h, wd = x.shape
-    if tuple(gy.shape) != (n, c, sws_out_len(h, kh, sh, ph), sws_out_len(wd, kw, sw, pw)):
+    if tuple(gy.shape) != (n, c, _out_len(h, kh, sh, ph), _out_len(wd, kw, sw, pw)):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_maxpool2d_grad")
     gx = _out(gx, (n, c, h, wd), x, "gx")
     _check(lib().sws_maxpool2d_grad(x.data_ptr(), gy.data_ptr(), gx.data_ptr(), n, c, h, wd, kh, kw, sh, sw, ph, pw,
@@ -312,7 +320,7 @@ def sws_avgpool2d_grad(gy, h, wd, kh, kw, sh=1, sw=1, ph=0, pw=0, divisor=0, sca
     (sws_pool2d_ex with SWS_OP_ADD, pads (ph, pw, ph, pw), the same divisor (0 = SWS_DIV_SCALE) and scale)."""
     _dev(gy, "gy")
     n, c, ho, wo = gy.shape
-    if (ho, wo) != (sws_out_len(h, kh, sh, ph), sws_out_len(wd, kw, sw, pw)):
+    if (ho, wo) != (_out_len(h, kh, sh, ph), _out_len(wd, kw, sw, pw)):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_avgpool2d_grad")
     gx = _out(gx, (n, c, h, wd), gy, "gx")
     _check(lib().sws_avgpool2d_grad(gy.data_ptr(), gx.data_ptr(), n, c, h, wd, kh, kw, sh, sw, ph, pw, int(divisor),
@@ -327,7 +335,7 @@ def sws_pool2d_16(op, x, kh, kw, sh=1, sw=1, ph=0, pw=0, scale=1.0, y=None, stre
     if x.dtype not in _DTYPE_16 or not x.is_contiguous():
         raise TypeError("x must be contiguous bfloat16 or float16")
     n, c, h, wd = x.shape
-    ho, wo = sws_out_len(h, kh, sh, ph), sws_out_len(wd, kw, sw, pw)
+    ho, wo = _out_len(h, kh, sh, ph), _out_len(wd, kw, sw, pw)
     if ho < 1 or wo < 1:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_pool2d_16")
     shape = (n, c, ho, wo)
@@ -402,7 +410,7 @@ def sws_conv1d(x, wgt, stride=1, pad=0, dilation=1, groups=1, y=None, stream=Non
     cout, cig, k = wgt.shape
     if cig * groups != cin:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d")
-    lo = sws_out_len(length, k, stride, pad, dilation)
+    lo = _out_len(length, k, stride, pad, dilation)
     if lo < 1:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d")
     y = _out(y, (b, cout, lo), x)
@@ -423,7 +431,7 @@ def sws_conv1d_16(x, wgt, stride=1, pad=0, dilation=1, groups=1, y=None, stream=
     cout, cig, k = wgt.shape
     if cig * groups != cin:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d_16")
-    lo = sws_out_len(length, k, stride, pad, dilation)
+    lo = _out_len(length, k, stride, pad, dilation)
     if lo < 1:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d_16")
     shape = (b, cout, lo)
@@ -445,7 +453,7 @@ def sws_conv1d_grad_input(gy, wgt, length, stride=1, pad=0, dilation=1, groups=1
     _dev(wgt, "wgt")
     b, cout, lo = gy.shape
     cout2, cig, k = wgt.shape
-    if cout2 != cout or lo != sws_out_len(length, k, stride, pad, dilation):
+    if cout2 != cout or lo != _out_len(length, k, stride, pad, dilation):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d_grad_input")
     cin = cig * groups
     gx = _out(gx, (b, cin, length), gy, "gx")
@@ -463,7 +471,7 @@ def sws_conv1d_grad_weight(x, gy, k, stride=1, pad=0, dilation=1, groups=1, gw=N
     _dev(gy, "gy")
     b, cin, length = x.shape
     b2, cout, lo = gy.shape
-    if b2 != b or cin % groups or lo != sws_out_len(length, k, stride, pad, dilation):
+    if b2 != b or cin % groups or lo != _out_len(length, k, stride, pad, dilation):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv1d_grad_weight")
     gw = _out(gw, (cout, cin // groups, k), x, "gw")
     keep, ws, ws_bytes = _scratch(_conv1d_gw_bytes(b, cin, length, cout, k, stride, pad, dilation, groups), x, stream)
@@ -503,7 +511,7 @@ def sws_conv2d(x, wgt, sh=1, sw=1, ph=0, pw=0, y=None, stream=None):
     cout, cin2, kh, kw = wgt.shape
     if cin2 != cin:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d")
-    ho, wo = sws_out_len(h, kh, sh, ph), sws_out_len(wd, kw, sw, pw)
+    ho, wo = _out_len(h, kh, sh, ph), _out_len(wd, kw, sw, pw)
     if ho < 1 or wo < 1:
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d")
     y = _out(y, (n, cout, ho, wo), x)
@@ -521,7 +529,7 @@ def sws_conv2d_grad_input(gy, wgt, h, wd, sh=1, sw=1, ph=0, pw=0, gx=None, strea
     _dev(wgt, "wgt")
     n, cout, ho, wo = gy.shape
     cout2, cin, kh, kw = wgt.shape
-    if cout2 != cout or ho != sws_out_len(h, kh, sh, ph) or wo != sws_out_len(wd, kw, sw, pw):
+    if cout2 != cout or ho != _out_len(h, kh, sh, ph) or wo != _out_len(wd, kw, sw, pw):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d_grad_input")
     gx = _out(gx, (n, cin, h, wd), gy, "gx")
     keep, ws, ws_bytes = _workspace(wgt, cout, cin, kh * kw, n * ho * wo, stream) if sh <= 2 and sw <= 2 else (None, None, 0)
@@ -538,7 +546,7 @@ def sws_conv2d_grad_weight(x, gy, kh, kw, sh=1, sw=1, ph=0, pw=0, gw=None, strea
     _dev(gy, "gy")
     n, cin, h, wd = x.shape
     n2, cout, ho, wo = gy.shape
-    if n2 != n or ho != sws_out_len(h, kh, sh, ph) or wo != sws_out_len(wd, kw, sw, pw):
+    if n2 != n or ho != _out_len(h, kh, sh, ph) or wo != _out_len(wd, kw, sw, pw):
         raise SwsError(SWS_ERR_INVALID_ARG, "sws_conv2d_grad_weight")
     gw = _out(gw, (cout, cin, kh, kw), x, "gw")
     keep, ws, ws_bytes = _scratch(_conv2d_gw_bytes(n, cin, h, wd, cout, kh, kw, sh, sw, ph, pw), x, stream)

@@ -35,6 +35,17 @@ def test_header_symbols_are_exported(L):
         assert getattr(L, n) is not None
 
 
+def test_the_binding_and_the_library_agree_on_output_lengths(L):
+    """The binding works the length out by itself: every sign and both sides of every limit."""
+    from paper_2305_16513_amd import binding
+    for n in (-1, 0, 1, 2, 5, 6, 7, 112, 2 ** 31 + 5, 2 ** 40):
+        for w in (-1, 0, 1, 2, 3, 7, 50, 2 ** 31 - 1):
+            for s in (-1, 0, 1, 2, 3, 64):
+                for p in (-1, 0, 1, 3, 1000):
+                    for d in (0, 1, 2, 8):
+                        assert binding._out_len(n, w, s, p, d) == L.sws_out_len(n, w, s, p, d), (n, w, s, p, d)
+
+
 def test_out_len(L):
     assert L.sws_out_len(1048576, 5, 1, 0, 1) == 1048572
     assert L.sws_out_len(4096, 3, 1, 0, 1) == 4094
