@@ -346,8 +346,13 @@ __global__ __launch_bounds__(64 * kReduceWaves) void gw_reduce_kernel(const floa
     for (int i = threadIdx.x; i < 256 * nt; i += blockDim.x) {
         const int e = fdiv(i, inv_nt), tt = i - e * nt, c8 = e >> 5, l32 = e & 31;
         const int at = (c8 & 3) * 64 + (c8 >> 2) * 32 + l32;         // register 4 qr + c8 % 4, lane
-        float sum = ((const float *)part[tt])[at];
-        for (int q = 1; q < S; ++q) sum += ((const float *)part[q * TG + tt])[at];
+        float f[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int q = 0; q < S; q += 4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (q + u < S) f[u] += ((const float *)part[(q + u) * TG + tt])[at];
+        }
+        const float sum = (f[0] + f[1]) + (f[2] + f[3]);
         const int co = channel(cob * (32 * WM) + w % WM * 32 + 8 * qr + c8, g.Cout);
         const int ci = channel(cib * (32 * WN) + w / WM * 32 + l32, g.Cin);
         if (co >= 0 && ci >= 0) gw[((int64_t)co * g.Cin + ci) * g.KT + g.gt0[grp] + ta + tt] = sum;

@@ -345,6 +345,34 @@ def test_grad_weight_through_transposing_reads(B, case, integer, lent):
     assert (flat[:64] == 12345.0).all() and (flat[-64:] == 12345.0).all()
 
 
+# n, cin, cout, h, w, kh, kw, stride, pad: tiles that never meet two images (rows per tile divide a plane's), that just do and that always do; 3 x 3 at
+# stride 2, whose tiles may be five units a thread; 1, 8, 9 and many runs to add up, one or several taps each
+GW_RUNS = [(4, 32, 64, 56, 54, 3, 3, 2, 1), (3, 33, 32, 16, 16, 3, 3, 2, 1), (2, 40, 32, 112, 42, 3, 3, 2, 1), (2, 60, 30, 56, 56, 3, 3, 2, 1),
+           (5, 32, 32, 12, 28, 3, 3, 1, 1), (7, 40, 30, 6, 60, 3, 3, 1, 1), (3, 33, 64, 4, 30, 3, 3, 1, 1), (1, 16, 24, 9, 9, 3, 3, 1, 1),
+           (40, 64, 32, 28, 28, 3, 3, 1, 1), (12, 256, 256, 14, 14, 3, 3, 1, 1), (9, 40, 72, 20, 20, 5, 5, 1, 2), (24, 32, 40, 1, 1000, 1, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("integer", [True, False])
+@pytest.mark.parametrize("case", GW_RUNS)
+def test_grad_weight_runs_and_images(B, case, integer, lent):
+    """By the library's own choice of kernel: a workspace is lent and used."""
+    n, cin, cout, h, w, kh, kw, s, p = case
+    ph, sh = (p, s) if h > 1 else (0, 1)
+    rng = np.random.default_rng(51)
+    x = workloads.integer_valued((n, cin, h, w), -3, 3, 52) if integer else rng.standard_normal((n, cin, h, w)).astype(np.float32)
+    ho, wo = (h + 2 * ph - kh) // sh + 1, (w + 2 * p - kw) // s + 1
+    gy = workloads.integer_valued((n, cout, ho, wo), -3, 3, 53) if integer else rng.standard_normal((n, cout, ho, wo)).astype(np.float32)
+    ref, mag = oracle.conv2d_grad_weight(x, gy, kh, kw, sh, s, ph, p)
+    flat, gw = _guarded(ref.shape)
+    B.sws_conv2d_grad_weight(to_gpu(x), to_gpu(gy), kh, kw, sh, s, ph, p, gw=gw)
+    if integer:
+        assert_bit_exact(to_host(gw), ref, "gw %s" % (case,))
+    else:
+        assert_within_tol(to_host(gw), ref, mag, "gw %s" % (case,), tol=SPLIT_TOL)      # (at most 31360 products: the bound of the test above)
+    assert len(lent) == 1 and _taken(lent[0])
+    assert (flat[:64] == 12345.0).all() and (flat[-64:] == 12345.0).all()
+
+
 def test_grad_weight_is_reproducible(B):
     """Partial sums are added in a fixed order: two calls give the same bits."""
     rng = np.random.default_rng(7)
