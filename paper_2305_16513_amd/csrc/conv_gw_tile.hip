@@ -29,7 +29,7 @@
 // Operands of one tap at a time, a piece of the next read as soon as the last product with the present one is out: with two sets the nine-tap
 // instance spills, whose reloads wait for the loads in flight ([32,64,56,56] -> 64 93 us, now 75).
 //
-// Sums leave as partial blocks in the caller's workspace, lane after lane, and gw_reduce_kernel adds them in a fixed order:
+// Sums leave as partial blocks in the caller's workspace, lane after lane, and gw_reduce_kernel or gw_reduce_few_kernel adds them in a fixed order:
 // the result does not depend on the order in which workgroups end (5 - 10 us; the atomic adds of conv_gw_split.hip, 36864 per
 // workgroup, take 27 us on 64 x 64 channels, 3 x 3).
 //
@@ -301,61 +301,76 @@ void conv_gw_tile_kernel(const float *__restrict__ x, const float *__restrict__ 
     }
 }
 
-// gw from the partial blocks: a workgroup adds a quarter (registers 4 q .. 4 q + 3: eight output channels x 32 input channels)
-// of one (block, wavefront) for TG taps, S wavefronts per tap, every S-th run each; register v of lane (l32, half) is output
-// channel 8*(v/4) + 4*half + v%4, input channel l32 of the block of 32.  An octet of channels that reached beyond the last one
-// held the last eight (see the staging).
-// Bound by latency: 128-bit loads, eight of a wavefront's in flight at once; few runs leave room for all taps of a channel
-// in one workgroup, whose stores are then contiguous (one tap and 64 elements per workgroup: 13 us on
-// 256 x 256 channels, 3 x 3, eight runs, now 7.6; 14 / 10 with sixteen).
-constexpr int kReduceWaves = 9, kReduceSplit = 8;     // wavefronts of a workgroup at most; ones of a tap, and ones where several taps meet
-__global__ __launch_bounds__(64 * kReduceWaves) void gw_reduce_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB,
-                                                                      int WM, int WN, int TG, int S)
+// The channel that a slot of a block holds; -1: none, or one that another slot holds (an octet of channels that reached beyond the last
+// one held the last eight, see the staging).
+__device__ __forceinline__ int slot_channel(int slot, int n)
 {
-    __shared__ v4f part[kReduceWaves][64];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int BLK = WM * WN, ntg = (int)((unsigned)(TB + TG - 1) / (unsigned)TG);
-    const unsigned rest = blockIdx.x >> 2, rest2 = rest / (unsigned)BLK, blk = rest2 / (unsigned)ntg, cb = blk / (unsigned)g.ng;
-    const int qr = blockIdx.x & 3, w = (int)(rest - rest2 * BLK), ta = (int)(rest2 - blk * ntg) * TG, grp = (int)(blk - cb * g.ng);
+    const int o = slot & ~7, c0 = o < n - 8 ? o : (n > 8 ? n - 8 : 0), c = c0 + (slot & 7);
+    return o < n && c >= o && c < n ? c : -1;
+}
+
+// gw from the partial blocks: a workgroup adds 64 lanes of one (block, tap, wavefront, register), its four wavefronts
+// every fourth run; register v of lane (l32, half) is output channel 8*(v/4) + 4*half + v%4, input channel l32 of the
+// block of 32.
+__global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
+{
+    __shared__ float part[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nblk = g.cob * g.cib * g.ng, BLK = WM * WN;
+    const int v = blockIdx.x & 15, rest = (int)(blockIdx.x >> 4), w = rest % BLK, t = rest / BLK % TB, blk = rest / (BLK * TB);
+    const int grp = blk % g.ng, cb = blk / g.ng, cob = cb / g.cib, cib = cb - cob * g.cib;
+    if (t >= g.gnt[grp]) return;
+    const int64_t step = (int64_t)nblk * (TB * BLK * 1024);
+    const float *p = ws + (int64_t)blk * (TB * BLK * 1024) + t * (BLK * 1024) + w * 1024 + v * 64 + lane;
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    int k = wave;
+    for (; k + 12 < g.nsplit; k += 16) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s[u] += p[(k + 4 * u) * step];
+    }
+    for (; k < g.nsplit; k += 4) s[0] += p[k * step];
+    part[wave][lane] = (s[0] + s[1]) + (s[2] + s[3]);
+    __syncthreads();
+    if (wave != 0) return;
+    const float sum = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    const int co = slot_channel(cob * (32 * WM) + w % WM * 32 + 8 * (v / 4) + 4 * (lane >> 5) + v % 4, g.Cout);
+    const int ci = slot_channel(cib * (32 * WN) + w / WM * 32 + (lane & 31), g.Cin);
+    if (co >= 0 && ci >= 0) gw[((int64_t)co * g.Cin + ci) * g.KT + g.gt0[grp] + t] = sum;
+}
+
+// The same where few runs are to be added, at most kFewRuns: a workgroup takes a quarter (registers 4 q .. 4 q + 3, eight output channels x 32 input
+// channels) of one (block, wavefront) and all its taps, a wavefront each, so that what it stores is contiguous; 128-bit loads, all of a
+// wavefront's in flight at once.  A tap and 64 elements per workgroup, as above, left a channel's taps to nine workgroups of different XCDs: 256 x 256
+// channels, 3 x 3, 13 us there, 7.7 here; with 24, 116 and 256 runs 5.6, 6.2 and 6.9 there, 6.4, 7.2 and 6.6 here (eight wavefronts per tap).
+constexpr int kFewRuns = 8;
+__global__ __launch_bounds__(576) void gw_reduce_few_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
+{
+    __shared__ v4f part[9][64];
+    const int lane = threadIdx.x & 63, t = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int BLK = WM * WN;
+    const unsigned rest = blockIdx.x >> 2, blk = rest / (unsigned)BLK, cb = blk / (unsigned)g.ng;
+    const int qr = blockIdx.x & 3, w = (int)(rest - blk * BLK), grp = (int)(blk - cb * g.ng);
     const int cob = (int)(cb / (unsigned)g.cib), cib = (int)cb - cob * g.cib;
-    const int nt = g.gnt[grp] - ta < TG ? g.gnt[grp] - ta : TG;      // my taps
-    if (nt <= 0) return;
-    const int sl = (int)((unsigned)wave / (unsigned)TG), t = wave - sl * TG;
+    const int nt = g.gnt[grp];
     if (t < nt) {
         const int64_t step = (int64_t)g.cob * g.cib * g.ng * (TB * BLK * 256);
-        const v4f *p = (const v4f *)ws + (int64_t)blk * (TB * BLK * 256) + (ta + t) * (BLK * 256) + w * 256 + qr * 64 + lane;
-        v4f s[8];
+        const v4f *p = (const v4f *)ws + ((int64_t)blk * TB + t) * (BLK * 256) + w * 256 + qr * 64 + lane;
+        v4f f[kFewRuns];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s[u] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-        for (int k = sl; k < g.nsplit; k += 8 * S) {
-            v4f f[8];
+        for (int u = 0; u < kFewRuns; ++u) f[u] = p[(u < g.nsplit ? u : 0) * step];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) f[u] = p[(k + u * S < g.nsplit ? k + u * S : k) * step];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s[u] += k + u * S < g.nsplit ? f[u] : (v4f){0.0f, 0.0f, 0.0f, 0.0f};     // (beyond the last run: not counted)
-        }
-        part[wave][lane] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+        for (int u = 1; u < kFewRuns; ++u) f[u] = u < g.nsplit ? f[u] : (v4f){0.0f, 0.0f, 0.0f, 0.0f};       // (beyond the last run: not counted)
+        part[t][lane] = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
     }
     __syncthreads();
-    auto channel = [](int slot, int n) {              // the channel a slot holds; -1: none, or one that another slot holds
-        const int o = slot & ~7, c0 = o < n - 8 ? o : (n > 8 ? n - 8 : 0), c = c0 + (slot & 7);
-        return o < n && c >= o && c < n ? c : -1;
-    };
     // (consecutive threads: consecutive taps of an input channel, then the next one, then the next output channel)
     const float inv_nt = 1.0f / (float)nt;
     for (int i = threadIdx.x; i < 256 * nt; i += blockDim.x) {
         const int e = fdiv(i, inv_nt), tt = i - e * nt, c8 = e >> 5, l32 = e & 31;
-        const int at = (c8 & 3) * 64 + (c8 >> 2) * 32 + l32;         // register 4 qr + c8 % 4, lane
-        float f[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int q = 0; q < S; q += 4) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (q + u < S) f[u] += ((const float *)part[(q + u) * TG + tt])[at];
-        }
-        const float sum = (f[0] + f[1]) + (f[2] + f[3]);
-        const int co = channel(cob * (32 * WM) + w % WM * 32 + 8 * qr + c8, g.Cout);
-        const int ci = channel(cib * (32 * WN) + w / WM * 32 + l32, g.Cin);
-        if (co >= 0 && ci >= 0) gw[((int64_t)co * g.Cin + ci) * g.KT + g.gt0[grp] + ta + tt] = sum;
+        const float sum = ((const float *)part[tt])[(c8 & 3) * 64 + (c8 >> 2) * 32 + l32];        // register 4 qr + c8 % 4, lane
+        const int co = slot_channel(cob * (32 * WM) + w % WM * 32 + 8 * qr + c8, g.Cout);
+        const int ci = slot_channel(cib * (32 * WN) + w / WM * 32 + l32, g.Cin);
+        if (co >= 0 && ci >= 0) gw[((int64_t)co * g.Cin + ci) * g.KT + g.gt0[grp] + tt] = sum;
     }
 }
 
@@ -372,11 +387,10 @@ hipError_t launch_gw1(const float *x, const float *gy, float *gw, float *ws, con
                        s, x, gy, ws, g);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    int S = (g.nsplit + 7) / 8;
-    S = S < kReduceSplit ? S : kReduceSplit;
-    const int TG = S == 1 || TB < kReduceSplit / S ? TB : kReduceSplit / S;
-    hipLaunchKernelGGL(gw_reduce_kernel, dim3((unsigned)(nblk * ((TB + TG - 1) / TG) * WM * WN * 4)), dim3(64 * TG * S), 0, s, ws, gw, g, TB, WM,
-                       WN, TG, S);
+    if (g.nsplit <= kFewRuns)
+        hipLaunchKernelGGL(gw_reduce_few_kernel, dim3((unsigned)(nblk * WM * WN * 4)), dim3(64 * TB), 0, s, ws, gw, g, TB, WM, WN);
+    else
+        hipLaunchKernelGGL(gw_reduce_kernel, dim3((unsigned)(nblk * TB * WM * WN * 16)), dim3(256), 0, s, ws, gw, g, TB, WM, WN);
     return hipGetLastError();
 }
 
@@ -467,6 +481,8 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
                 const int PS = ((int)(lines * LW) + 3) / 16 * 16 + 12;
                 const size_t stage = (size_t)4 * 3 * 16 * (wn * PS + wm * kPG) + kBN * 4;
                 const size_t red = (size_t)(8 - wm * wn) * 4 * (q.tb < 3 ? q.tb : 3) * 1024;
+                // (3 x 3 at stride 2 on one block of input channels: a fifth unit a thread lets a tile hold 112 positions instead of 84, whose four
+                // wavefronts per block then take seven groups of 16 in the time of six: [32,64,56,56] -> 64, taken here for comparison, 34 us -> 26)
                 if (4 * wn * PS > (wn == 1 && q.tb == 9 && sh == 2 && sw == 2 ? 5 : 4) * kThreads || stage > 158 * 1024) continue;
                 const int tps = (int)((unsigned)(g.NR + rpt - 1) / rpt), ksteps = (rpt * TW + 15) / 16, steps = (ksteps + wk - 1) / wk;
                 if ((int64_t)tps * nstrips >= (1LL << 30)) continue;
