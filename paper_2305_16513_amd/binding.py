@@ -121,12 +121,17 @@ def sws_out_len(length, w, stride=1, pad=0, dilation=1):
     return int(lib().sws_out_len(length, w, stride, pad, dilation))
 
 
+_I32_MAX = 2 ** 31 - 1
+
+
 def _out_len(length, w, stride, pad, dilation=1):
-    """sws_out_len in Python: two of them were 0.9 us of the 7.5 that a pooling call takes the host, now 0.4."""
-    if length < 0 or w < 1 or stride < 1 or pad < 0 or dilation < 1:
-        return -1
-    left = length + 2 * pad - dilation * (w - 1) - 1
-    return left // stride + 1 if left >= 0 else -1
+    """sws_out_len in Python for plain ints of the library's range.  Anything else is the library's to answer: numpy's
+    fixed-width numbers wrap in these sums, and numbers beyond 32 bits lose their upper half on the way into every call."""
+    if (type(length) is type(w) is type(stride) is type(pad) is type(dilation) is int and 0 <= length <= 2 ** 62 and
+            0 < w <= _I32_MAX and 0 < stride <= _I32_MAX and 0 <= pad <= _I32_MAX and 0 < dilation <= _I32_MAX):
+        left = length + 2 * pad - dilation * (w - 1) - 1
+        return left // stride + 1 if left >= 0 else -1
+    return sws_out_len(length, w, stride, pad, dilation)
 
 
 def sws_set_option(key, value):

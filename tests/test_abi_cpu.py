@@ -4,6 +4,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -44,6 +45,17 @@ def test_the_binding_and_the_library_agree_on_output_lengths(L):
                 for p in (-1, 0, 1, 3, 1000):
                     for d in (0, 1, 2, 8):
                         assert binding._out_len(n, w, s, p, d) == L.sws_out_len(n, w, s, p, d), (n, w, s, p, d)
+
+
+def test_output_lengths_of_numbers_that_are_not_plain_ints(L):
+    """numpy's fixed-width numbers and numbers beyond 32 bits: an output is as long as the library will write, whatever the
+    call's numbers become on their way in (a shorter one would be written behind its end)."""
+    from paper_2305_16513_amd import binding
+    for a in [(100, 3, 1, np.uint8(200), 1), (np.int8(100), 3, 1, 20, 1), (np.int16(30000), 3, 1, 1000, 1), (100, np.uint8(1), 1, 0, 1),
+              (2 ** 31, np.int32(5000), 1, 0, np.int32(2 ** 20)), (100, 3, np.int64(2), np.int8(100), 1), (100, 3, 2 ** 32 + 2, 0, 1),
+              (100, 2 ** 32 + 3, 1, 0, 1), (100, 3, 1, 2 ** 32 + 1, 1), (100, 3, 1, 0, 2 ** 32 + 1), (100, 1 - 2 ** 32, 1, 0, 1),
+              (100, 3, 1, -2 ** 32, 1), (2 ** 64 + 100, 3, 1, 0, 1), (100, 3, True, False, True)]:
+        assert binding._out_len(*a) == L.sws_out_len(*a), a
 
 
 def test_out_len(L):
