@@ -541,3 +541,40 @@ def test_conv1d_thin_matrix_not_finite(B, d, bad):
     hit = 3000 - np.arange(k) * d
     want[0, 1, hit] = bad
     assert np.array_equal(y, want, equal_nan=True)
+
+
+@pytest.mark.parametrize("b,c,length,k,d,pad", [(1, 2, 5000, 40, 1, 20), (2, 3, 3100, 51, 8, 200), (3, 2, 800, 3, 4, 5), (1, 2, 9001, 49, 32, 0), (2, 2, 66, 64, 1, 40)])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_conv1d_thin_matrix_not_finite_near_ends(B, bad, b, c, length, k, d, pad):
+    """Infinities and NaN in inputs at both ends, around a tile's end and in the taps: cells outside the row are no terms, whatever their tap."""
+    r = _rng(length + k)
+    x = r.uniform(0.5, 1, (b, c, length)).astype(np.float32)
+    w = r.uniform(0.5, 1, (c, 1, k)).astype(np.float32)
+    x[0, 0, [0, length - 1]] = bad
+    x[-1, -1, min(1023, length // 2)] = bad
+    B.sws_set_option("conv1d_variant", 8)
+    try:
+        for tap in (None, 0, k - 1):
+            wt = w.copy()
+            if tap is not None:
+                wt[-1, 0, tap] = bad
+            y = to_host(B.sws_conv1d(to_gpu(x), to_gpu(wt), 1, pad, d, c))
+            ref, mag = oracle.conv1d(x, wt, 1, pad, d, c)
+            fine = np.isfinite(ref)
+            assert np.array_equal(y[~fine], ref[~fine].astype(np.float32), equal_nan=True)
+            assert_within_tol(y[fine], ref[fine], mag[fine], str(tap), tol=6.2e-6)
+    finally:
+        B.sws_set_option("conv1d_variant", 0)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_conv1d_thin_matrix_taps_not_finite(B, bad):
+    """A tap that is not finite reaches all outputs of its channel, and no other channel's."""
+    k, length = 40, 3000
+    x = np.ones((1, 3, length), dtype=np.float32)
+    w = np.full((3, 1, k), 0.5, dtype=np.float32)
+    w[1, 0, 7] = bad
+    y = to_host(B.sws_conv1d(to_gpu(x), to_gpu(w), 1, 0, 1, 3))
+    want = np.full(y.shape, 0.5 * k, dtype=np.float32)
+    want[0, 1] = bad
+    assert np.array_equal(y, want, equal_nan=True)
