@@ -22,8 +22,12 @@
 // copy of that size 86; matrix cores 41 % busy), 49 taps 32 apart, which no other kernel but the direct one takes,
 // [8,64,65536] 1260 / 85.  Error against 64 bits 4.3e-8 (vector ALU 1.3e-7).
 //
-// An input that is not finite makes every output of its run NaN (zeros of T meet it); a tile with a result that is not finite
-// is therefore evaluated again, tap by tap from memory.
+// bf16 reaches down to 2^-133: three pieces hold every bit of a number from 2^-110 on.  Inputs are multiplied by 2^40 before they are
+// split, so that this is all of them, and taps by 2^-40; a channel with a tap below 2^-70 has its taps multiplied by 2^40
+// too, and its results by 2^-80.
+//
+// An input that is not finite makes every output of its run NaN (zeros of T meet it), and one beyond 2^87 is not finite when multiplied; a
+// tile with a result that is not finite is therefore evaluated again, tap by tap from memory.
 #include "sws_internal.h"
 
 namespace sws {
@@ -37,6 +41,7 @@ typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef short v4s __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 1024;                           // outputs per wavefront
+constexpr float kUp = 0x1p40f;
 
 // A workgroup takes `rows` rows of one channel (images apart) and `group` tiles of NW * 1024 outputs of each.
 struct ToepGeom {
@@ -81,11 +86,16 @@ void conv1d_toep_kernel(const float *__restrict__ x, const float *__restrict__ w
     const int b_end = b + g.rows < g.B ? b + g.rows : g.B;
     const int t_first = chunk * g.group, t_end = t_first + g.group < g.tiles ? t_first + g.group : g.tiles;
 
+    // (every lane of every wavefront comes here; k <= 64)
+    const float tap = __builtin_fabsf(wr[lane < g.k ? lane : 0]);
+    const bool tiny = __builtin_amdgcn_ballot_w64(tap > 0.0f && tap < 0x1p-70f) != 0;
+    const float tap_scale = tiny ? kUp : 1.0f / kUp;
+
     // ---- T: slot p of copy X holds tap p - 32 - X (zero outside [0, k)), so that a lane's eight taps, from tap
     // 16 c + 8 half - j on, start on a dword of copy j & 1
     for (int i = tid; i < 2 * TLEN; i += T) {
         const int X = i >= TLEN, p = i - X * TLEN, t = p - 32 - X;
-        const float f = t >= 0 && t < g.k ? wr[g.wflip ? g.k - 1 - t : t] : 0.0f;
+        const float f = t >= 0 && t < g.k ? tap_scale * wr[g.wflip ? g.k - 1 - t : t] : 0.0f;
         const __bf16 f1 = (__bf16)(__builtin_fabsf(f) < 0x1.ffp127f ? f : __uint_as_float(__float_as_uint(f) & 0xffff0000u));
         const float r1 = f - (float)f1;
         const __bf16 f2 = (__bf16)r1;
@@ -120,14 +130,15 @@ void conv1d_toep_kernel(const float *__restrict__ x, const float *__restrict__ w
         for (int i = 0; i < U; ++i) {
             const int q = 4 * (tid + i * T);
             if ((i + 1) * 4 * T > NI && q >= NI) continue;
-            float r1[4], r2[4];
+            float f[4], r1[4], r2[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                r1[e] = in[i][e] - __uint_as_float(__float_as_uint(in[i][e]) & 0xffff0000u);
+                f[e] = kUp * in[i][e];
+                r1[e] = f[e] - __uint_as_float(__float_as_uint(f[e]) & 0xffff0000u);
                 r2[e] = r1[e] - __uint_as_float(__float_as_uint(r1[e]) & 0xffff0000u);
             }
             unsigned short *d = plane + at(q);
-            *(v2u *)d = (v2u){pack_hi(in[i][0], in[i][1]), pack_hi(in[i][2], in[i][3])};
+            *(v2u *)d = (v2u){pack_hi(f[0], f[1]), pack_hi(f[2], f[3])};
             *(v2u *)(d + PLANE) = (v2u){pack_hi(r1[0], r1[1]), pack_hi(r1[2], r1[3])};
             *(v2u *)(d + 2 * PLANE) = (v2u){pack_hi(r2[0], r2[1]), pack_hi(r2[2], r2[3])};
         }
@@ -208,6 +219,10 @@ void conv1d_toep_kernel(const float *__restrict__ x, const float *__restrict__ w
         // ---- out: register v is run 8 (v / 4) + 4 half + v % 4, position l32
         if (!mine) continue;
         float *yr = y + ((int64_t)b_now * g.Cout + co) * g.Lo;
+        if (tiny) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) hi[v] *= 1.0f / (kUp * kUp);
+        }
         float s = 0.0f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) s += hi[v];

@@ -578,3 +578,31 @@ def test_conv1d_thin_matrix_taps_not_finite(B, bad):
     want = np.full(y.shape, 0.5 * k, dtype=np.float32)
     want[0, 1] = bad
     assert np.array_equal(y, want, equal_nan=True)
+
+# Thin layers on the matrix cores, operands of every size: a piece of 16 bits must not lose what a small number has below 2^-133, the smallest
+# step of bf16.  Inputs and taps are 2^x and 2^t times numbers of ordinary size; some of each only in every second or in the outer taps (a
+# Gaussian's tails).  Tolerance as above, plus one step of 2^-149 per term for terms that are subnormal themselves.
+@pytest.mark.parametrize("d,k,length", [(1, 40, 2500), (8, 40, 2500), (4, 3, 500)])
+@pytest.mark.parametrize("x_exp,w_exp,tails", [
+    (-109, 0, 0), (-112, 0, 0), (-117, 20, 0), (-126, 0, 0), (-126, 30, 0), (-140, 60, 0), (-148, 60, 0),
+    (0, -69, 0), (0, -72, 0), (0, -112, 0), (10, -126, 0), (60, -140, 0), (-30, -75, 0), (-60, -60, 0), (-117, -5, -100), (-120, 0, -80),
+    (0, 0, -100), (0, 0, -140), (-126, 0, -20), (86, 0, 0), (90, 0, 0), (125, -60, 0), (125, -140, 0), (-126, 120, 0), (-149, 125, 0), (60, 50, -120)])
+def test_conv1d_thin_matrix_small_and_large(B, d, k, length, x_exp, w_exp, tails):
+    r = _rng(1000 + 10 * abs(x_exp) + abs(w_exp) + d)
+    x = np.ldexp(r.uniform(1, 2, (2, 3, length)) * r.choice([-1.0, 1.0], (2, 3, length)), x_exp).astype(np.float32)
+    w = np.ldexp(r.uniform(0.5, 1, (3, 1, k)), w_exp)
+    w[..., : k // 3] = np.ldexp(w[..., : k // 3], tails)
+    w[..., k - k // 3:] = np.ldexp(w[..., k - k // 3:], tails)
+    w = w.astype(np.float32)
+    x[0, 0] = 0.0
+    x[0, 1, ::2] = 0.0
+    B.sws_set_option("conv1d_variant", 8)
+    try:
+        y = to_host(B.sws_conv1d(to_gpu(x), to_gpu(w), 1, 2, d, 3))
+        gx = to_host(B.sws_conv1d_grad_input(to_gpu(x), to_gpu(w), length + d * (k - 1), 1, 0, d, 3))
+    finally:
+        B.sws_set_option("conv1d_variant", 0)
+    for got, (ref, mag) in ((y, oracle.conv1d(x, w, 1, 2, d, 3)), (gx, oracle.conv1d_grad_input(x, w, length + d * (k - 1), 1, 0, d, 3))):
+        assert np.isfinite(got).all()
+        err = np.abs(got.astype(np.float64) - ref) - (6.2e-6 * mag + k * 2.0 ** -149)
+        assert (err <= 0).all(), (err.max(), np.abs(ref).max())
