@@ -11,7 +11,8 @@
 //    Global traffic is coalesced 128-bit strips; LDS turns strips into per-lane windows
 //    and the per-lane outputs back into strips.
 //
-//  * kernels of more than 32 taps, and rows of one tile with taps 4, 8 or 16 apart: on the matrix cores (conv1d_toep.hip).
+//  * one input channel per output channel without a boundary rule, 33 - 64 taps at distance 1, 4, 8, 16 or 32, and any number up to 64 at
+//    distance 4, 8 or 16 on rows of one tile: on the matrix cores (conv1d_toep.hip).
 //
 //  * conv1d_thin_dilated_kernel: the same with taps spaced d > 1 apart.  A dilated
 //    correlation is d independent undilated ones on the phase subsequences x[p + d*m], so the
@@ -202,7 +203,7 @@ hipError_t launch_thin(const float *x, const float *wgt, float *y, int64_t rows_
 {
     const int tiles_per_row = (Lo + max_origin_shift(Lo, 16) + kTileOut - 1) / kTileOut;     // origins move back
     // Tiles per workgroup (measured): two per wavefront while HBM is the bound (the tiles in flight
-    // stay a compact window of memory), many once the FMAs dominate (k > 32: fewer prologues).
+    // stay a compact window of memory), many once the FMAs dominate (boundary rules with more than 32 taps: fewer prologues).
     // With the workgroups dealt to the XCDs in short runs and the next tile staged before a tile's stores, cold inputs, us
     // before / now: [32,128,16384] k = 3 97 / 93, k = 25 102 / 95, [8,64,65536] k = 3 .. 31 57 / 48 (copies of these sizes 86 and 43).
     // (With streamed loads four per wavefront measured 2.5 % faster when the layer's launches follow each other, 0.833
@@ -543,6 +544,7 @@ hipError_t launch_thin_dilated(const float *x, const float *wgt, float *y, int64
 }
 
 constexpr int kThinMaxK = 64;
+constexpr int kThinPlainK = 32;                      // adjacent taps without a boundary rule; more of them: conv1d_toep.hip
 
 // Dense channels: the vector-ALU kernel against the matrix-core kernel.  Measured on
 // x[64, C, 16384], C -> C channels (TFLOP/s, vector ALU / matrix cores): k = 51: 52 / 11 (C = 8),
@@ -583,7 +585,7 @@ hipError_t launch_conv1d(const float *x, const float *wgt, float *y, int64_t B, 
     if (taken) *taken = true;
     int variant = g_opt.conv1d_variant;
     const int cig = (int)(Cin / groups);
-    const bool thin_ok = cig == 1 && stride == 1 && dilation == 1 && k <= kThinMaxK;
+    const bool thin_ok = cig == 1 && stride == 1 && dilation == 1 && k <= kThinPlainK;
     const bool dense_ok = groups == 1 && Cin >= 2;
     // The phase-major kernel: taps spaced apart, several input channels per output channel, and — as
     // a chain of launches over chunks of at most 64 taps, each adding to y — kernels of any length.
@@ -663,8 +665,6 @@ hipError_t launch_conv1d(const float *x, const float *wgt, float *y, int64_t B, 
         return launch_thin<KB>(x, wgt, y, B * Cout, (int)L, (int)Lo, k, pad, (int)Cin, (int)Cout, cog, s, wadj)
         switch ((k + 3) / 4) {
             SWS_THIN(1); SWS_THIN(2); SWS_THIN(3); SWS_THIN(4); SWS_THIN(5); SWS_THIN(6); SWS_THIN(7); SWS_THIN(8);
-            SWS_THIN(9); SWS_THIN(10); SWS_THIN(11); SWS_THIN(12); SWS_THIN(13); SWS_THIN(14); SWS_THIN(15);
-            SWS_THIN(16);
         default: break;
         }
 #undef SWS_THIN

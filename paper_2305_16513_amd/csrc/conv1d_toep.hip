@@ -313,14 +313,16 @@ hipError_t launch_waves(const float *x, const float *wgt, float *y, const ToepGe
 {
     const int n = (g.Lo + max_origin_shift(g.Lo, 16) + kTile - 1) / kTile;
     if constexpr (NCH < 4) {                          // (few taps: only rows of one tile come here, see conv1d_toep_wanted)
-        if constexpr (LD >= 2 && LD <= 4) return n == 1 ? launch<NCH, LD, 1>(x, wgt, y, g, s) : kNotTaken;
+        if constexpr (LD >= 2 && LD <= 4)
+            if (n == 1) return launch<NCH, LD, 1>(x, wgt, y, g, s);
         return kNotTaken;
-    }
-    if constexpr (LD < 5) {
+    } else if constexpr (LD < 5) {
         if (n == 1) return launch<NCH, LD, 1>(x, wgt, y, g, s);
         if ((n + 2) / 3 * 3 < (n + 1) / 2 * 2) return launch<NCH, LD, 3>(x, wgt, y, g, s);
+        return launch<NCH, LD, 2>(x, wgt, y, g, s);
+    } else {
+        return launch<NCH, LD, 2>(x, wgt, y, g, s);
     }
-    return launch<NCH, LD, 2>(x, wgt, y, g, s);
 }
 
 template <int LD>
