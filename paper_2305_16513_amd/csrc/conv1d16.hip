@@ -214,10 +214,6 @@ hipError_t launch_thin16(const T *x, const float *wgt, T *y, int64_t rows_out, i
     return hipGetLastError();
 }
 
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef v4u v4u_u __attribute__((aligned(2)));
 
 template <typename T> struct Bits;

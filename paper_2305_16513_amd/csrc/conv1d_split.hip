@@ -18,9 +18,6 @@ namespace sws {
 namespace {
 
 constexpr int kThreads = 512;                        // eight wavefronts share one set of split weights
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void split3(float v, float &p2, float &p3)   // v = upper(v) + upper(p2) + upper(p3) ...
 {

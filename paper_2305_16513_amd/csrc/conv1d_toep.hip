@@ -34,12 +34,6 @@ namespace sws {
 
 namespace {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
-typedef short v4s __attribute__((ext_vector_type(4)));
-
 constexpr int kTile = 1024;                           // outputs per wavefront
 constexpr float kUp = 0x1p40f;
 
@@ -49,15 +43,6 @@ struct ToepGeom {
     int tiles, group, chunks, rows;                   // tiles of a row, of a workgroup's row; workgroups per row; rows per workgroup
     int wflip, units;
 };
-
-// eight consecutive s of one run: two transposing reads of four
-__device__ __forceinline__ v8bf tr8(const char *p0, const char *p1)
-{
-    typedef __attribute__((address_space(3))) v4s lds_v4s;
-    const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)p0);
-    const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)p1);
-    return __builtin_bit_cast(v8bf, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
-}
 
 // NCH: slices of 16 s, 31 + k <= 16 NCH.  LD: log2 of the taps' distance (0, 2 .. 5).  NW: wavefronts.
 template <int NCH, int LD, int NW>
@@ -96,12 +81,11 @@ void conv1d_toep_kernel(const float *__restrict__ x, const float *__restrict__ w
     for (int i = tid; i < 2 * TLEN; i += T) {
         const int X = i >= TLEN, p = i - X * TLEN, t = p - 32 - X;
         const float f = t >= 0 && t < g.k ? tap_scale * wr[g.wflip ? g.k - 1 - t : t] : 0.0f;
-        const __bf16 f1 = (__bf16)(__builtin_fabsf(f) < 0x1.ffp127f ? f : __uint_as_float(__float_as_uint(f) & 0xffff0000u));
-        const float r1 = f - (float)f1;
-        const __bf16 f2 = (__bf16)r1;
+        __bf16 f1, f2, f3;
+        split_nearest(f, f1, f2, f3);
         taps[0][X][p] = __builtin_bit_cast(unsigned short, f1);
         taps[1][X][p] = __builtin_bit_cast(unsigned short, f2);
-        taps[2][X][p] = __builtin_bit_cast(unsigned short, (__bf16)(r1 - (float)f2));
+        taps[2][X][p] = __builtin_bit_cast(unsigned short, f3);
     }
 
     v4f in[U];

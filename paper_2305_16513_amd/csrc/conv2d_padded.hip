@@ -69,7 +69,6 @@ __device__ __forceinline__ bool frame_cell(const Frame &f, int Wo, int q, int *h
 constexpr int kSlots = 4;                            // taps gathered together
 constexpr int kCc = 16;                              // input channels per chunk
 constexpr int kWp = kCoPer + 1;                      // pitch of a weight row in LDS (bank spread for the transposing writes)
-typedef float v16f __attribute__((ext_vector_type(16)));
 
 __global__ __launch_bounds__(kThreads) void conv2d_border_kernel(const float *__restrict__ x, const float *__restrict__ wgt,
                                                                  float *__restrict__ y, int Cin, int H, int W, int Cout,

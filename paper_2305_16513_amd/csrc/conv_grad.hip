@@ -31,8 +31,6 @@ constexpr int kThreads = 256;
 constexpr int kWavesPerWg = kThreads / kWave;
 constexpr int kTileOut = 1024;
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-
 __device__ __forceinline__ void wave_lds_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

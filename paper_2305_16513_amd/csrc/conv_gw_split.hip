@@ -31,9 +31,6 @@ namespace sws {
 namespace {
 
 constexpr int kThreads = 256;
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 // v = p1 + p2 + p3 with every piece's significant bits in the upper half of a float
 __device__ __forceinline__ void split3(float v, float &p2, float &p3)

@@ -43,10 +43,6 @@ namespace sws {
 
 namespace {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 
 constexpr int kThreads = 512;
@@ -87,15 +83,6 @@ __device__ __forceinline__ void put_unit(char *dst, int step, const float (&v)[8
     }
 #pragma unroll
     for (int q = 0; q < 3; ++q) *(v4u *)(dst + q * step) = (v4u){p[q][0], p[q][1], p[q][2], p[q][3]};
-}
-
-// eight positions of this lane's channel: two transposing reads of four
-__device__ __forceinline__ v8bf tr8(const char *p0, const char *p1)
-{
-    typedef __attribute__((address_space(3))) v4s lds_v4s;
-    const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)p0);
-    const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)p1);
-    return __builtin_bit_cast(v8bf, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // TB: taps per group at most (a shorter last group computes its last tap again); WM x WN blocks of 32 x 32 channels, WK

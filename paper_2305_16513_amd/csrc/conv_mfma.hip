@@ -33,8 +33,6 @@ namespace {
 
 constexpr int kCoTile = 64;                           // output channels per workgroup
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-
 struct ConvGeom {
     int Cin, H, W, Cout, Ho, Wo, kh, kw, ph, pw;
     int sh, sw;                                       // strides (the channel-fastest kernel only)

@@ -44,9 +44,6 @@ namespace sws {
 
 namespace {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef v2f v2f_u __attribute__((aligned(4)));
 
 constexpr int kMaxSteps = 64;                         // contraction steps per chunk and wavefront (one lane holds one)
@@ -101,12 +98,8 @@ __global__ __launch_bounds__(256) void split_weights_kernel(const float *__restr
         unsigned short h[3][2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const float v = f[e + u];
-            // (to nearest, but cut where that would be infinity)
-            const __bf16 f1 = (__bf16)(__builtin_fabsf(v) < 0x1.ffp127f ? v : __uint_as_float(__float_as_uint(v) & 0xffff0000u));
-            const float r1 = v - (float)f1;
-            const __bf16 f2 = (__bf16)r1;
-            const __bf16 f3 = (__bf16)(r1 - (float)f2);
+            __bf16 f1, f2, f3;
+            split_nearest(f[e + u], f1, f2, f3);
             h[0][u] = __builtin_bit_cast(unsigned short, f1);
             h[1][u] = __builtin_bit_cast(unsigned short, f2);
             h[2][u] = __builtin_bit_cast(unsigned short, f3);

@@ -51,10 +51,6 @@ namespace sws {
 
 namespace {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-
 constexpr int kThreads = 512;
 constexpr int kPad = 4;                               // floats of padding per staged position
 constexpr int kScratchFloats = 2 * 2 * 4 * 3 * 64 * 4;  // [buffer][wm][owner quarter][source][lane][4]
@@ -283,13 +279,11 @@ __global__ __launch_bounds__(kThreads) void conv_stream_kernel(const float *__re
 #pragma unroll
                 for (int t = 0; t < KT; ++t) {
                     const float f = rd[WADJ ? KT - 1 - t : t];
-                    // (to nearest, but cut where that would be infinity)
-                    const __bf16 f1 = (__bf16)(__builtin_fabsf(f) < 0x1.ffp127f ? f : __uint_as_float(__float_as_uint(f) & 0xffff0000u));
-                    const float r1 = f - (float)f1;
-                    const __bf16 f2 = (__bf16)r1;
+                    __bf16 f1, f2, f3;
+                    split_nearest(f, f1, f2, f3);
                     w3[t][0][e] = f1;
                     w3[t][1][e] = f2;
-                    w3[t][2][e] = (__bf16)(r1 - (float)f2);
+                    w3[t][2][e] = f3;
                 }
                 __builtin_amdgcn_sched_barrier(0);            // (one channel's reads in flight at a time: registers)
             }

@@ -38,6 +38,11 @@ constexpr int kXcd = 8;      // XCDs (separate L2s) on MI355X
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef v4f v4f_u __attribute__((aligned(4)));     // 16-byte access at 4-byte alignment
 typedef float v2f __attribute__((ext_vector_type(2)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef short v4s __attribute__((ext_vector_type(4)));
 
 // The operator (+) of the sliding window sum, with its identity element.  `a` is always
 // the older (left) operand so the kernels stay valid for non-commutative operators.
@@ -62,6 +67,25 @@ __device__ __forceinline__ int fdiv(int x, float inv_d) { return (int)(((float)x
 __device__ __forceinline__ unsigned pack_hi(float lo, float hi)
 {
     return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+
+// f as three bf16 numbers whose sum it is, each rounded to nearest (but cut where that would be infinity): the products of pieces
+// that are left out are then smallest.
+__device__ __forceinline__ void split_nearest(float f, __bf16 &f1, __bf16 &f2, __bf16 &f3)
+{
+    f1 = (__bf16)(__builtin_fabsf(f) < 0x1.ffp127f ? f : __uint_as_float(__float_as_uint(f) & 0xffff0000u));
+    const float r1 = f - (float)f1;
+    f2 = (__bf16)r1;
+    f3 = (__bf16)(r1 - (float)f2);
+}
+
+// Eight 16-bit elements of a lane by two transposing LDS reads of four.
+__device__ __forceinline__ v8bf tr8(const char *p0, const char *p1)
+{
+    typedef __attribute__((address_space(3))) v4s lds_v4s;
+    const v4s a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)p0);
+    const v4s b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)p1);
+    return __builtin_bit_cast(v8bf, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // One buffer descriptor: loads beyond `bytes` return zero; kNowhere lies beyond every descriptor.
