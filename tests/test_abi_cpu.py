@@ -324,6 +324,15 @@ def test_grad_weight_workspace_goes_with_the_work(L):
     assert conv2(0, 64, 30, 30, 64, 3, 3, 1, 1, 0, 0) == 0
 
 
+def test_grad_weight_plans_that_the_gpu_tests_count_on(L):
+    """The layers of test_grad_weight_runs_and_images have as many blocks of partial sums as its comments say: as many runs, and tiles as large."""
+    from tests.test_parity_conv_split import GW_RUNS
+    for (n, cin, cout, h, w, kh, kw, s, p), blocks in GW_RUNS.items():
+        ph, sh = (p, s) if h > 1 else (0, 1)
+        taps = 5 if (kh, kw) == (5, 5) else kh * kw                          # (of a workgroup)
+        assert L.sws_conv2d_grad_weight_workspace(n, cin, h, w, cout, kh, kw, sh, s, ph, p) == 4096 * taps * blocks, (n, cin, cout, h, w, kh, kw, s, p)
+
+
 def test_grad_weight_runs_fill_whole_rounds_and_one_row_layers_go_to_the_faster_kernel(L):
     """A workgroup of the tiled kernel fills a compute unit: a few more workgroups than there are units would be a second round.  (Counted from
     the partial sums: 64 x 64 channels x 9 taps each.)"""

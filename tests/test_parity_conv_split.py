@@ -345,11 +345,23 @@ def test_grad_weight_through_transposing_reads(B, case, integer, lent):
     assert (flat[:64] == 12345.0).all() and (flat[-64:] == 12345.0).all()
 
 
-# n, cin, cout, h, w, kh, kw, stride, pad: tiles that never meet two images (rows per tile divide a plane's), that just do and that always do; 3 x 3 at
-# stride 2, whose tiles may be five units a thread; 1, 8, 9 and many runs to add up, one or several taps each
-GW_RUNS = [(4, 32, 64, 56, 54, 3, 3, 2, 1), (3, 33, 32, 16, 16, 3, 3, 2, 1), (2, 40, 32, 112, 42, 3, 3, 2, 1), (2, 60, 30, 56, 56, 3, 3, 2, 1),
-           (5, 32, 32, 12, 28, 3, 3, 1, 1), (7, 40, 30, 6, 60, 3, 3, 1, 1), (3, 33, 64, 4, 30, 3, 3, 1, 1), (1, 16, 24, 9, 9, 3, 3, 1, 1),
-           (40, 64, 32, 28, 28, 3, 3, 1, 1), (12, 256, 256, 14, 14, 3, 3, 1, 1), (9, 40, 72, 20, 20, 5, 5, 1, 2), (24, 32, 40, 1, 1000, 1, 3, 1, 1)]
+# n, cin, cout, h, w, kh, kw, stride, pad: blocks of partial sums (32 x 32 channels x the taps of a workgroup x runs; test_abi_cpu.py holds the planner
+# to them).  Tiles that never meet two images (rows per tile divide a plane's), that just do and that always do; 3 x 3 at stride 2
+# with tiles of five units a thread (the four behind the comment: 185 tiles of 5 x 25 positions hold 11 x 52 inputs, more than the 512 of four units;
+# 188 of 11 x 11, 11 and 10 of 24 x 4), both widths of a block and both ways to multiply; few runs added in one pass (at most 8, 1 to 9 taps), 9 and many
+GW_RUNS = {(4, 32, 64, 56, 54, 3, 3, 2, 1): 138, (3, 33, 32, 16, 16, 3, 3, 2, 1): 24, (2, 40, 32, 112, 42, 3, 3, 2, 1): 224, (2, 60, 30, 56, 56, 3, 3, 2, 1): 168,
+           (5, 32, 32, 12, 28, 3, 3, 1, 1): 28, (7, 40, 30, 6, 60, 3, 3, 1, 1): 84, (3, 33, 64, 4, 30, 3, 3, 1, 1): 24, (1, 16, 24, 9, 9, 3, 3, 1, 1): 1,
+           (40, 64, 32, 28, 28, 3, 3, 1, 1): 500, (12, 256, 256, 14, 14, 3, 3, 1, 1): 13 * 64, (9, 40, 72, 20, 20, 5, 5, 1, 2): 15 * 30,
+           (24, 32, 40, 1, 1000, 1, 3, 1, 1): 216 * 2,
+           # five units a thread
+           (37, 10, 8, 50, 50, 3, 3, 2, 1): 185, (47, 10, 37, 43, 43, 3, 3, 2, 1): 188 * 2, (62, 224, 96, 7, 7, 3, 3, 2, 1): 11 * 21,
+           (55, 320, 96, 7, 7, 3, 3, 2, 1): 10 * 40,
+           # few runs, and one more than that
+           (2, 20, 24, 10, 13, 3, 3, 1, 1): 5, (4, 20, 24, 9, 20, 3, 3, 1, 0): 8, (3, 20, 24, 9, 20, 3, 3, 1, 1): 9, (4, 256, 250, 14, 14, 3, 3, 1, 1): 7 * 64,
+           (12, 300, 290, 9, 9, 3, 3, 1, 1): 8 * 100,
+           (5, 20, 24, 10, 13, 1, 1, 1, 0): 8, (3, 20, 24, 12, 30, 1, 1, 1, 0): 9, (5, 9, 32, 9, 20, 1, 2, 1, 0): 8, (2, 20, 24, 30, 14, 1, 3, 1, 0): 8,
+           (2, 20, 24, 17, 23, 2, 2, 1, 0): 8, (5, 9, 32, 9, 20, 1, 5, 1, 0): 8, (2, 20, 24, 17, 23, 2, 3, 1, 0): 8, (2, 20, 24, 12, 30, 1, 7, 1, 0): 8,
+           (2, 9, 32, 17, 23, 2, 4, 1, 0): 8}
 
 
 @pytest.mark.parametrize("integer", [True, False])
