@@ -11,7 +11,7 @@
 //    Global traffic is coalesced 128-bit strips; LDS turns strips into per-lane windows
 //    and the per-lane outputs back into strips.
 //
-//  * one input channel per output channel without a boundary rule, 33 - 64 taps at distance 1, 4, 8, 16 or 32, and any number up to 64 at
+//  * one input channel per output channel without a boundary rule, 33 - 64 taps at distance 1, 4, 8, 16 or 32, and 5 - 64 at
 //    distance 4, 8 or 16 on rows of one tile: on the matrix cores (conv1d_toep.hip).
 //
 //  * conv1d_thin_dilated_kernel: the same with taps spaced d > 1 apart.  A dilated

@@ -5,7 +5,8 @@
 //     out[m + j] = sum over s of  X[m + s] * T[s][j],   T[s][j] = f[s - j] (0 <= s - j < k, else 0),
 // and 32 such runs together are the product of a 32 x S by an S x 32 matrix, S = 31 + k rounded up to 16.  Both operands
 // are exact sums of three bf16 numbers; six of the nine products of pieces are accumulated in fp32 (the other three are
-// below 2^-21 of their term), the leading one and the rest in accumulators of their own.  A tile of 1024 outputs takes
+// below 2^-21 of their term) in one accumulator: the five lesser ones of all slices first, at most 2^-6 of the terms, then the
+// leading ones on top, so that a result takes S / 16 <= 6 roundings of its own size.  A tile of 1024 outputs takes
 // 6 S / 16 instructions of 32 cycles (k = 51: 1152 cycles) where one fused multiply-add per tap and output takes
 // 64 k (3264).
 //
@@ -313,7 +314,6 @@ template <int LD>
 hipError_t launch_taps(const float *x, const float *wgt, float *y, const ToepGeom &g, hipStream_t s)
 {
     switch ((31 + g.k + 15) / 16) {
-    case 2: return launch_waves<2, LD>(x, wgt, y, g, s);
     case 3: return launch_waves<3, LD>(x, wgt, y, g, s);
     case 4: return launch_waves<4, LD>(x, wgt, y, g, s);
     case 5: return launch_waves<5, LD>(x, wgt, y, g, s);
@@ -324,16 +324,20 @@ hipError_t launch_taps(const float *x, const float *wgt, float *y, const ToepGeo
 
 }  // namespace
 
+// One to four taps keep their fp32 kernels: so few terms round less than what six of nine products leave out.  Error against 64 bits, 2-norm
+// and largest, of normal numbers (multiply-adds / here, 1e-8): k = 1 2.5, 6.0 / 3.9, 17, k = 2 3.1, 11 / 3.9, 21, k = 3 3.6, 15 / 3.9, 20,
+// k = 4 4.1, 17 / 3.9, 17, k = 5 4.3, 19 / 3.7, 16, k = 9 5.7, 23 / 3.7, 13.
 bool conv1d_toep_takes(int32_t k, int32_t dilation)
 {
-    return k <= 64 && (dilation == 1 || dilation == 4 || dilation == 8 || dilation == 16 || dilation == 32);
+    return k >= 5 && k <= 64 && (dilation == 1 || dilation == 4 || dilation == 8 || dilation == 16 || dilation == 32);
 }
 
 // More than 32 taps: the vector-ALU kernels are bound by their multiply-adds.  Measured (them / here, us, cold inputs):
 // dilation 1, [1,512,65536] k = 33 57 / 58, 37 65 / 57, 49 85 / 56, [40,128,3000] k = 33 36.5 / 36.6, 49 43 / 38; dilation 8,
 // [1,512,65536] k = 25 61 / 59, 33 68 / 59, 49 90 / 61, [16,128,2095] k = 25 15.6 / 17.6, 33 16.9 / 16.8, 49 22 / 17.5;
 // dilation 32, [1,512,65536] k = 17 62 / 79, 33 95 / 80.  Rows of one tile with taps 4, 8 or 16 apart (their scatter table is built for one tile):
-// [64,45,900], dilation 4, k = 3 13.3 / 10.9, 25 16.8 / 11.1, dilation 16, k = 3 14.1 / 13.5.
+// [64,45,900], dilation 4, k = 5 13.3 / 10.8, 25 15.9 / 10.9, dilation 8, k = 5 13.1 / 12.5, dilation 16, k = 5 14.1 / 13.5; 16 apart rows that
+// fill a tile are even where there are few of them and ahead where there are many: [32,64,1000], k = 5 10.2 / 11.0, [400,100,1000] 178 / 137.
 bool conv1d_toep_wanted(int64_t Lo, int32_t k, int32_t dilation)
 {
     return k > 32 || (dilation >= 4 && dilation <= 16 && Lo + max_origin_shift(Lo, 16) <= kTile);

@@ -501,11 +501,12 @@ def test_conv1d_dense_split_operands_carry_every_bit(B):
 
 
 # Thin layers on the matrix cores (conv1d_variant 8; more than 32 taps by themselves): one, two and three wavefronts per workgroup,
-# every number of slices of T, ends of tiles and rows, several rows per workgroup (the last).  Tolerance: 31 + k <= 96 products
+# every number of slices of T at every distance that has it, ends of tiles and rows, several rows per workgroup (the last).  Tolerance: 31 + k <= 96 products
 # of exact pieces in fp32, six of nine (the dropped ones below 2^-21 of a term): 96 * 2^-24 + 2^-21 = 6.2e-6 of sum |terms|.
 @pytest.mark.parametrize("b,c,length,k,d,pad", [
     (2, 3, 1057, 33, 1, 0), (1, 2, 1058, 34, 1, 16), (2, 2, 2050, 49, 1, 24), (1, 3, 3071, 64, 1, 0), (3, 5, 5000, 50, 1, 7), (1, 1, 66, 66 - 2, 1, 0),
     (2, 3, 700, 5, 4, 3), (1, 2, 1024 + 4 * 32, 33, 4, 0), (1, 3, 4096, 63, 4, 124), (2, 3, 900, 18, 8, 8), (2, 3, 2448 + 16, 51, 8, 200), (1, 2, 9001, 49, 8, 0),
+    (2, 3, 900, 1, 4, 0), (2, 3, 1024, 4, 8, 0), (3, 2, 100, 5, 16, 2), (2, 3, 900, 5, 8, 30), (2, 3, 500, 17, 8, 0), (2, 3, 600, 17, 4, 0),
     (2, 2, 800, 2, 16, 0), (1, 3, 4396, 33, 16, 8), (1, 2, 3000, 64, 16, 500), (1, 2, 9000, 64, 32, 0), (2, 3, 1700, 33, 32, 512),
     (64, 400, 70, 33, 1, 0)])
 def test_conv1d_thin_matrix(B, b, c, length, k, d, pad):
@@ -520,6 +521,11 @@ def test_conv1d_thin_matrix(B, b, c, length, k, d, pad):
         xi = r.integers(-3, 4, x.shape).astype(np.float32)
         wi = r.integers(-3, 4, w.shape).astype(np.float32)
         yi = to_host(B.sws_conv1d(to_gpu(xi), to_gpu(wi), 1, pad, d, c))
+        # the matrix kernel ran, from five taps on: fp32 multiply-adds round otherwise (8 falls back to 2, 4 and 1)
+        for other in (1, 4) if d in (4, 8, 16) else (1,):
+            B.sws_set_option("conv1d_variant", other)
+            same = np.array_equal(to_host(B.sws_conv1d(to_gpu(x), to_gpu(w), 1, pad, d, c)), y)
+            assert not same if k >= 5 else same or other == 1, "variant %d" % other
     finally:
         B.sws_set_option("conv1d_variant", 0)
     what = str((b, c, length, k, d, pad))
@@ -543,7 +549,7 @@ def test_conv1d_thin_matrix_not_finite(B, d, bad):
     assert np.array_equal(y, want, equal_nan=True)
 
 
-@pytest.mark.parametrize("b,c,length,k,d,pad", [(1, 2, 5000, 40, 1, 20), (2, 3, 3100, 51, 8, 200), (3, 2, 800, 3, 4, 5), (1, 2, 9001, 49, 32, 0), (2, 2, 66, 64, 1, 40)])
+@pytest.mark.parametrize("b,c,length,k,d,pad", [(1, 2, 5000, 40, 1, 20), (2, 3, 3100, 51, 8, 200), (3, 2, 800, 5, 4, 5), (1, 2, 9001, 49, 32, 0), (2, 2, 66, 64, 1, 40)])
 @pytest.mark.parametrize("bad", [np.inf, np.nan])
 def test_conv1d_thin_matrix_not_finite_near_ends(B, bad, b, c, length, k, d, pad):
     """Infinities and NaN in inputs at both ends, around a tile's end and in the taps: cells outside the row are no terms, whatever their tap."""
@@ -582,7 +588,7 @@ def test_conv1d_thin_matrix_taps_not_finite(B, bad):
 # Thin layers on the matrix cores, operands of every size: a piece of 16 bits must not lose what a small number has below 2^-133, the smallest
 # step of bf16.  Inputs and taps are 2^x and 2^t times numbers of ordinary size; some of each only in every second or in the outer taps (a
 # Gaussian's tails).  Tolerance as above, plus one step of 2^-149 per term for terms that are subnormal themselves.
-@pytest.mark.parametrize("d,k,length", [(1, 40, 2500), (8, 40, 2500), (4, 3, 500)])
+@pytest.mark.parametrize("d,k,length", [(1, 40, 2500), (8, 40, 2500), (4, 5, 500)])
 @pytest.mark.parametrize("x_exp,w_exp,tails", [
     (-109, 0, 0), (-112, 0, 0), (-117, 20, 0), (-126, 0, 0), (-126, 30, 0), (-140, 60, 0), (-148, 60, 0),
     (0, -69, 0), (0, -72, 0), (0, -112, 0), (10, -126, 0), (60, -140, 0), (-30, -75, 0), (-60, -60, 0), (-117, -5, -100), (-120, 0, -80),
@@ -606,3 +612,22 @@ def test_conv1d_thin_matrix_small_and_large(B, d, k, length, x_exp, w_exp, tails
         assert np.isfinite(got).all()
         err = np.abs(got.astype(np.float64) - ref) - (6.2e-6 * mag + k * 2.0 ** -149)
         assert (err <= 0).all(), (err.max(), np.abs(ref).max())
+
+
+@pytest.mark.parametrize("positive", [False, True])
+@pytest.mark.parametrize("d", [4, 8, 16])
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 9, 17, 33, 64])
+def test_conv1d_thin_layers_are_as_exact_as_the_fp32_kernels(B, k, d, positive):
+    """The automatic choice on rows of one tile: error against 64 bits (2-norm, half a million outputs) as with fp32 multiply-adds."""
+    r = _rng(100 * k + d)
+    draw = (lambda s: r.uniform(0, 1, s)) if positive else r.standard_normal
+    x, w = draw((20, 30, 900 + d * (k - 1))).astype(np.float32), draw((30, 1, k)).astype(np.float32)
+    ref, _ = oracle.conv1d(x, w, 1, 0, d, 30)
+    error = []
+    for variant in (0, 4):
+        B.sws_set_option("conv1d_variant", variant)
+        try:
+            error.append(np.linalg.norm(to_host(B.sws_conv1d(to_gpu(x), to_gpu(w), 1, 0, d, 30)).astype(np.float64) - ref))
+        finally:
+            B.sws_set_option("conv1d_variant", 0)
+    assert error[0] <= 1.02 * error[1], error[0] / error[1]
