@@ -71,15 +71,6 @@ __global__ __launch_bounds__(kThreads, (KB4 < 8 ? 5 : 4)) void conv1d_thin_kerne
     // 1 KB strip store starts on a 64-byte line of y.  Outputs before the row start are dropped.
     const int c = (ro & 15) * (Lo & 15) & 15;
 
-    // Taps: one coalesced load (lane t holds tap t, zero beyond k), then broadcast into scalar registers.
-    float f[K4];
-    {
-        float tv = wr[lane < k ? (wflip ? k - 1 - lane : lane) : 0];   // wflip: the adjoint's taps, last first
-        tv = lane < k ? tv : 0.0f;
-#pragma unroll
-        for (int t = 0; t < K4; ++t) f[t] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tv), t));
-    }
-
     const int wbase = 20 * lane;                     // my window: lds_pos(16*lane + 4u) = wbase + 4u + 4*(u >> 2)
     const int sbase = 4 * lane + 4 * (lane >> 2);    // my strip element: lds_pos(256j + 4*lane) = sbase + 320j
 
@@ -105,6 +96,8 @@ __global__ __launch_bounds__(kThreads, (KB4 < 8 ? 5 : 4)) void conv1d_thin_kerne
                 const int p = s0 + 4 * lane;
                 if (s0 >= 0 && s0 + 256 <= L) {
                     g[j] = *(const v4f_u *)(xr + p);
+                } else if (RULE ? s0 >= p_hi || s0 + 256 <= -pad : s0 >= L || s0 + 256 <= 0) {
+                    g[j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
                 } else if (RULE) {
                     // virtual elements stand for the row element the rule names; beyond the extended row: zero
                     float e4[4];
@@ -115,8 +108,6 @@ __global__ __launch_bounds__(kThreads, (KB4 < 8 ? 5 : 4)) void conv1d_thin_kerne
                         e4[u] = src >= 0 ? xr[src] : 0.0f;
                     }
                     g[j] = (v4f){e4[0], e4[1], e4[2], e4[3]};
-                } else if (s0 >= L || s0 + 256 <= 0) {
-                    g[j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
                 } else {
                     // (no loads under a lane's condition: the compiler would wait for them at once)
 #pragma unroll
@@ -131,8 +122,16 @@ __global__ __launch_bounds__(kThreads, (KB4 < 8 ? 5 : 4)) void conv1d_thin_kerne
     if (t_end > tiles_per_row) t_end = tiles_per_row;
     int t = chunk * group + wave;
     if (t >= t_end) return;                          // (no workgroup barrier below)
+    // Taps: one coalesced load (lane t holds tap t, zero beyond k), broadcast into scalar registers when the first tile's loads are out
+    // (waited for before them it cost rows of one tile a second latency: [512,64,130], 3 taps, 47.6 us, now 38.4).
+    float tv = wr[lane < k ? (wflip ? k - 1 - lane : lane) : 0];       // wflip: the adjoint's taps, last first
     v4f cur[5];
     load_tile(t, cur);
+    __builtin_amdgcn_sched_barrier(0);
+    float f[K4];
+    tv = lane < k ? tv : 0.0f;
+#pragma unroll
+    for (int u = 0; u < K4; ++u) f[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tv), u));
     // strips -> LDS
     auto stage = [&]() {
 #pragma unroll
@@ -183,6 +182,7 @@ __global__ __launch_bounds__(kThreads, (KB4 < 8 ? 5 : 4)) void conv1d_thin_kerne
             for (int j = 0; j < 4; ++j) {
                 const v4f o = *(const v4f *)(A + sbase + 320 * j);
                 if (more) *(v4f *)(A + sbase + 320 * j) = cur[j];
+                if (j * 256 >= lim) continue;
                 const int q = j * 256 + 4 * lane;
                 if (t0 + q >= 0 && q + 4 <= lim) {
                     __builtin_nontemporal_store(o, (v4f_u *)(yr + t0 + q));
