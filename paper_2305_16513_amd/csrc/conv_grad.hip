@@ -221,7 +221,8 @@ __global__ __launch_bounds__(kThreads) void conv1d_thin_grad_weight_kernel(
 
     // Rows of taps next to each other: the next tile's strips are in registers while this one's products run, and go to LDS
     // behind them (loaded and waited for tile by tile, 32 x 128 rows of 16384, k = 31: 126 us, now
-    // 100, 5.4 TB/s; cold inputs 143 / 119).
+    // 100, 5.4 TB/s; cold inputs 143 / 119).  More than 40 taps: a tile's addresses are worked out anew (opaque), which leaves the registers of
+    // three wavefronts per SIMD ([32,128,16384], 63 taps 179 us with two, 151 with three).
     v4f xs[XS], gs[kTileOut / 256];
     auto rows = [&](unsigned j, const float *&xr, const float *&gr, int &t0) {
         const unsigned b = j / (unsigned)tiles_per_row;
@@ -233,12 +234,16 @@ __global__ __launch_bounds__(kThreads) void conv1d_thin_grad_weight_kernel(
         const float *xr, *gr;
         int t0;
         rows(j, xr, gr, t0);
-        load_row<XS>(xs, xr, t0 - pad, L, K4, lane);
-        load_row<kTileOut / 256>(gs, gr, t0, Lo, 256, lane);
+        int me = lane;
+        if (KB4 > 10) asm volatile("" : "+v"(me));
+        load_row<XS>(xs, xr, t0 - pad, L, K4, me);
+        load_row<kTileOut / 256>(gs, gr, t0, Lo, 256, me);
     };
     auto put_tile = [&]() {
-        put_row<XS>(X, xs, K4, lane);
-        put_row<kTileOut / 256>(G, gs, 256, lane);
+        int me = lane;
+        if (KB4 > 10) asm volatile("" : "+v"(me));
+        put_row<XS>(X, xs, K4, me);
+        put_row<kTileOut / 256>(G, gs, 256, me);
     };
     if (!DIL && j0 + wave < j1) {
         load_tile(j0 + wave);
