@@ -208,8 +208,8 @@ hipError_t launch_thin(const float *x, const float *wgt, float *y, int64_t rows_
     // before / now: [32,128,16384] k = 3 97 / 93, k = 25 102 / 95, [8,64,65536] k = 3 .. 31 57 / 48 (copies of these sizes 86 and 43).
     // (With streamed loads four per wavefront measured 2.5 % faster when the layer's launches follow each other, 0.833
     // against 0.855 ms on cfg 5's k = 31 layer, but 1 % slower between other kernels, 0.779 against 0.771: not taken.)
-    const bool stream = !RULE && rows_out * (int64_t)L >= ((int64_t)1 << 27) && !(g_opt.slide_chunk & 256);
-    int64_t g = (KB4 <= 8 ? 2 : 16) * kWavesPerWg;
+    const bool stream = !RULE && KB4 <= 8 && rows_out * (int64_t)L >= ((int64_t)1 << 27) && !(g_opt.slide_chunk & 256);
+    int64_t g = (KB4 <= 8 || (KB4 == 9 && !RULE) ? 2 : 16) * kWavesPerWg;
     if (g_opt.slide_group > 0) g = g_opt.slide_group;
     if (g > tiles_per_row) g = tiles_per_row;
     const int chunks_per_row = (int)((tiles_per_row + g - 1) / g);
@@ -218,7 +218,7 @@ hipError_t launch_thin(const float *x, const float *wgt, float *y, int64_t rows_
     const int64_t grid = xcd_run_grid(n_units);
     if (grid > 2147483647LL - 64) return kNotTaken;
     // inputs far beyond the caches are loaded streamed (slide_chunk bit 256: plain loads, as for the sliding sums)
-    if constexpr (!RULE) {
+    if constexpr (!RULE && KB4 <= 8) {
         if (stream) {
             hipLaunchKernelGGL((conv1d_thin_kernel<KB4, false, true>), dim3((unsigned)grid), dim3(kThreads), 0, s, x, wgt, y, L,
                                Lo, k, pad, Cin, Cout, cog, tiles_per_row, group, chunks_per_row, (int)n_units, wflip, p_hi, pmode);
@@ -544,7 +544,7 @@ hipError_t launch_thin_dilated(const float *x, const float *wgt, float *y, int64
 }
 
 constexpr int kThinMaxK = 64;
-constexpr int kThinPlainK = 32;                      // adjacent taps without a boundary rule; more of them: conv1d_toep.hip
+constexpr int kThinPlainK = 36;                      // adjacent taps without a boundary rule; more of them: conv1d_toep.hip
 
 // Dense channels: the vector-ALU kernel against the matrix-core kernel.  Measured on
 // x[64, C, 16384], C -> C channels (TFLOP/s, vector ALU / matrix cores): k = 51: 52 / 11 (C = 8),
@@ -665,6 +665,7 @@ hipError_t launch_conv1d(const float *x, const float *wgt, float *y, int64_t B, 
         return launch_thin<KB>(x, wgt, y, B * Cout, (int)L, (int)Lo, k, pad, (int)Cin, (int)Cout, cog, s, wadj)
         switch ((k + 3) / 4) {
             SWS_THIN(1); SWS_THIN(2); SWS_THIN(3); SWS_THIN(4); SWS_THIN(5); SWS_THIN(6); SWS_THIN(7); SWS_THIN(8);
+            SWS_THIN(9);
         default: break;
         }
 #undef SWS_THIN

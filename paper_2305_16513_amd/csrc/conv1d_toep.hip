@@ -274,17 +274,24 @@ hipError_t launch(const float *x, const float *wgt, float *y, ToepGeom g, hipStr
 {
     constexpr int TO = kTile * NW;
     g.tiles = (g.Lo + max_origin_shift(g.Lo, 16) + TO - 1) / TO;
-    // Tiles per workgroup: T is built once for them, but there should be a few workgroups for every place on the device.
-    const int64_t places = 4 * 3072 / NW;
-    int64_t per = 4;
-    if (g_opt.slide_group > 0) per = g_opt.slide_group;
-    const int64_t row_tiles = per < g.tiles ? per : g.tiles;
-    g.chunks = (int)((g.tiles + row_tiles - 1) / row_tiles);
-    while (row_tiles > 1 && g.chunks < g.tiles && (int64_t)g.B * g.Cout * g.chunks < places) ++g.chunks;
+    // Tiles of a row per workgroup, one to four: T is built once for them, in about a tile's time, and a compute unit holds twelve wavefronts.
+    // The fewest rounds of workgroups times tiles; with one tile each wherever that fills the device ([16,64,4000], 33 taps, 1.3
+    // rounds) 12.2 us, now 9.9.
+    const int64_t places = 12 * (int64_t)device_cus() / NW, rows_out = (int64_t)g.B * g.Cout;
+    const int per = g_opt.slide_group > 0 ? (int)g_opt.slide_group : 4;
+    int64_t best = 0;
+    for (int t = g_opt.slide_group > 0 && per < g.tiles ? per : 1; t <= per && t <= g.tiles; ++t) {
+        const int chunks = (g.tiles + t - 1) / t;
+        const int64_t cost = (rows_out * chunks + places - 1) / places * (t + 1);
+        if (best == 0 || cost <= best) {
+            best = cost;
+            g.chunks = chunks;
+        }
+    }
     g.group = (g.tiles + g.chunks - 1) / g.chunks;
     g.chunks = (g.tiles + g.group - 1) / g.group;
     g.rows = 1;
-    while (g.chunks == 1 && (g.rows + 1) * g.tiles <= per && (int64_t)((g.B + g.rows) / (g.rows + 1)) * g.Cout >= places) ++g.rows;
+    while (g.chunks == 1 && (g.rows + 1) * g.tiles <= per && (int64_t)((g.B + g.rows) / (g.rows + 1)) * g.Cout >= 4 * places) ++g.rows;
     const int64_t units = (int64_t)((g.B + g.rows - 1) / g.rows) * g.Cout * g.chunks, grid = xcd_run_grid(units);
     if (grid > 2147483647LL - 64) return kNotTaken;
     g.units = (int)units;
@@ -292,7 +299,8 @@ hipError_t launch(const float *x, const float *wgt, float *y, ToepGeom g, hipStr
     return hipGetLastError();
 }
 
-// Two wavefronts per workgroup, or one or three where that leaves fewer of them without outputs.
+// Two wavefronts per workgroup, or three where that leaves fewer of them without outputs; one for rows of a few tiles, if a tile's halo is short
+// ([40,128,3000], 41 taps 32.5 us with three, 30 with one; [32,64,4000], 33 taps 4 apart 18.7 with two, 17.4).
 template <int NCH, int LD>
 hipError_t launch_waves(const float *x, const float *wgt, float *y, const ToepGeom &g, hipStream_t s)
 {
@@ -302,7 +310,7 @@ hipError_t launch_waves(const float *x, const float *wgt, float *y, const ToepGe
             if (n == 1) return launch<NCH, LD, 1>(x, wgt, y, g, s);
         return kNotTaken;
     } else if constexpr (LD < 5) {
-        if (n == 1) return launch<NCH, LD, 1>(x, wgt, y, g, s);
+        if (n == 1 || (n <= 4 && LD <= 2)) return launch<NCH, LD, 1>(x, wgt, y, g, s);
         if ((n + 2) / 3 * 3 < (n + 1) / 2 * 2) return launch<NCH, LD, 3>(x, wgt, y, g, s);
         return launch<NCH, LD, 2>(x, wgt, y, g, s);
     } else {
@@ -338,9 +346,15 @@ bool conv1d_toep_takes(int32_t k, int32_t dilation)
 // dilation 32, [1,512,65536] k = 17 62 / 79, 33 95 / 80.  Rows of one tile with taps 4, 8 or 16 apart (their scatter table is built for one tile):
 // [64,45,900], dilation 4, k = 5 13.3 / 10.8, 25 15.9 / 10.9, dilation 8, k = 5 13.1 / 12.5, dilation 16, k = 5 14.1 / 13.5; 16 apart rows that
 // fill a tile are even where there are few of them and ahead where there are many: [32,64,1000], k = 5 10.2 / 11.0, [400,100,1000] 178 / 137.
+//
+// 33 - 36 adjacent taps on rows of two to eight tiles stay on the vector ALU: it spares their many starts (conv1d_thin_kernel / here, us; rows x
+// length): 1024 x 2000 6.5 / 8.0, 4096 x 3000 23.6 / 27.6, 3276 x 4100 28.7 / 31.3, 1755 x 7000 21.5 / 25, but 4096 x 1000 13.9 / 13.8,
+// 12288 x 1000 33.6 / 30.1, 1445 x 16384 43.5 / 42.8.
 bool conv1d_toep_wanted(int64_t Lo, int32_t k, int32_t dilation)
 {
-    return k > 32 || (dilation >= 4 && dilation <= 16 && Lo + max_origin_shift(Lo, 16) <= kTile);
+    const int64_t tiles = (Lo + max_origin_shift(Lo, 16) + kTile - 1) / kTile;
+    if (dilation == 1 && k <= 36 && tiles >= 2 && tiles <= 8) return false;
+    return k > 32 || (dilation >= 4 && dilation <= 16 && tiles == 1);
 }
 
 hipError_t launch_conv1d_toep(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Lo,
