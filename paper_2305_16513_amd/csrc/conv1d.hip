@@ -11,7 +11,7 @@
 //    Global traffic is coalesced 128-bit strips; LDS turns strips into per-lane windows
 //    and the per-lane outputs back into strips.
 //
-//  * one input channel per output channel without a boundary rule, 33 - 64 taps at distance 1, 4, 8, 16 or 32, and 5 - 64 at
+//  * one input channel per output channel without a boundary rule, 33 - 64 taps at distance 1, 4, 8, 16 or 32, and 3 - 64 at
 //    distance 4, 8 or 16 on rows of one tile: on the matrix cores (conv1d_toep.hip).
 //
 //  * conv1d_thin_dilated_kernel: the same with taps spaced d > 1 apart.  A dilated
@@ -583,6 +583,7 @@ hipError_t launch_conv1d(const float *x, const float *wgt, float *y, int64_t B, 
     // evaluates (x holds output gradients); the kernels read it transposed inside each group, taps
     // last first.  The direct-evaluation fallback does not know that view: *taken = false then.
     if (taken) *taken = true;
+    if (k == 1) dilation = 1;                        // (one tap has no distance to another)
     int variant = g_opt.conv1d_variant;
     const int cig = (int)(Cin / groups);
     const bool thin_ok = cig == 1 && stride == 1 && dilation == 1 && k <= kThinPlainK;

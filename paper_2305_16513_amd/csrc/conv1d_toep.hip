@@ -5,7 +5,7 @@
 //     out[m + j] = sum over s of  X[m + s] * T[s][j],   T[s][j] = f[s - j] (0 <= s - j < k, else 0),
 // and 32 such runs together are the product of a 32 x S by an S x 32 matrix, S = 31 + k rounded up to 16.  Both operands
 // are exact sums of three bf16 numbers; six of the nine products of pieces are accumulated in fp32 (the other three are
-// below 2^-21 of their term) in one accumulator: the five lesser ones of all slices first, at most 2^-6 of the terms, then the
+// below 2^-21 of their term; up to 17 taps, whose sums round so little that this would show, eight) in one accumulator: the five lesser ones of all slices first, at most 2^-6 of the terms, then the
 // leading ones on top, so that a result takes S / 16 <= 6 roundings of its own size.  A tile of 1024 outputs takes
 // 6 S / 16 instructions of 32 cycles (k = 51: 1152 cycles) where one fused multiply-add per tap and output takes
 // 64 k (3264).
@@ -181,6 +181,10 @@ void conv1d_toep_kernel(const float *__restrict__ x, const float *__restrict__ w
             for (int c = 0; c < NCH; ++c) {
                 const v8bf x2 = operand(base, 2, c), x1 = operand(base, 1, c);
                 x0[c] = operand(base, 0, c);
+                if constexpr (NCH < 4) {              // (eight products: see conv1d_toep_takes)
+                    hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x2, F[1][c], hi, 0, 0, 0);
+                    hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, F[2][c], hi, 0, 0, 0);
+                }
                 hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x2, F[0][c], hi, 0, 0, 0);
                 hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, F[1][c], hi, 0, 0, 0);
                 hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0[c], F[2][c], hi, 0, 0, 0);
@@ -332,12 +336,12 @@ hipError_t launch_taps(const float *x, const float *wgt, float *y, const ToepGeo
 
 }  // namespace
 
-// One to four taps keep their fp32 kernels: so few terms round less than what six of nine products leave out.  Error against 64 bits, 2-norm
-// and largest, of normal numbers (multiply-adds / here, 1e-8): k = 1 2.5, 6.0 / 3.9, 17, k = 2 3.1, 11 / 3.9, 21, k = 3 3.6, 15 / 3.9, 20,
-// k = 4 4.1, 17 / 3.9, 17, k = 5 4.3, 19 / 3.7, 16, k = 9 5.7, 23 / 3.7, 13.
+// One and two taps keep their fp32 kernels, whose few roundings are less than the matrix cores'.  Error against 64 bits, 2-norm of normal
+// numbers and of numbers in 0 .. 1 (multiply-adds / here, 1e-8): k = 1 2.5, 2.5 / 3.4, 3.3, k = 2 3.1, 3.0 / 3.3, 3.0, k = 3 3.6, 3.3 / 3.2, 2.8,
+// k = 5 4.1, 3.9 / 3.2, 2.8, k = 17 7.5, 6.4 / 3.4, 3.1, k = 33 10, 8.5 / 4.2, 3.4.
 bool conv1d_toep_takes(int32_t k, int32_t dilation)
 {
-    return k >= 5 && k <= 64 && (dilation == 1 || dilation == 4 || dilation == 8 || dilation == 16 || dilation == 32);
+    return k >= 3 && k <= 64 && (dilation == 1 || dilation == 4 || dilation == 8 || dilation == 16 || dilation == 32);
 }
 
 // More than 32 taps: the vector-ALU kernels are bound by their multiply-adds.  Measured (them / here, us, cold inputs):
