@@ -611,7 +611,7 @@ hipError_t launch_conv1d(const float *x, const float *wgt, float *y, int64_t B, 
     const bool split_ok = ws.p && k <= 64 && stride <= 2 && g_opt.conv1d_variant == 0 && g_opt.conv2d_variant == 0;
     const bool valu_ok = few_ok || (strided_ok && cig > 1);
     if (variant == 0) {
-        if (toep_ok && conv1d_toep_wanted(Lo, k, dilation)) variant = 8;
+        if (toep_ok && conv1d_toep_wanted(B * Cout, Lo, k, dilation)) variant = 8;
         else if (thin_ok) variant = 2;
         else if (thin_dil_ok) variant = 4;
         else if (dense_ok && !(valu_ok && prefer_few(Cin, Cout, k, stride > 1, split_ok))) variant = 3;

@@ -72,23 +72,6 @@ void conv1d_toep_kernel(const float *__restrict__ x, const float *__restrict__ w
     const int b_end = b + g.rows < g.B ? b + g.rows : g.B;
     const int t_first = chunk * g.group, t_end = t_first + g.group < g.tiles ? t_first + g.group : g.tiles;
 
-    // (every lane of every wavefront comes here; k <= 64)
-    const float tap = __builtin_fabsf(wr[lane < g.k ? lane : 0]);
-    const bool tiny = __builtin_amdgcn_ballot_w64(tap > 0.0f && tap < 0x1p-70f) != 0;
-    const float tap_scale = tiny ? kUp : 1.0f / kUp;
-
-    // ---- T: slot p of copy X holds tap p - 32 - X (zero outside [0, k)), so that a lane's eight taps, from tap
-    // 16 c + 8 half - j on, start on a dword of copy j & 1
-    for (int i = tid; i < 2 * TLEN; i += T) {
-        const int X = i >= TLEN, p = i - X * TLEN, t = p - 32 - X;
-        const float f = t >= 0 && t < g.k ? tap_scale * wr[g.wflip ? g.k - 1 - t : t] : 0.0f;
-        __bf16 f1, f2, f3;
-        split_nearest(f, f1, f2, f3);
-        taps[0][X][p] = __builtin_bit_cast(unsigned short, f1);
-        taps[1][X][p] = __builtin_bit_cast(unsigned short, f2);
-        taps[2][X][p] = __builtin_bit_cast(unsigned short, f3);
-    }
-
     v4f in[U];
     // tile origins are pulled back: groups of stores start on 64-byte lines of y
     auto shift = [&](int b) { return ((b * g.Cout + co) & 15) * (g.Lo & 15) & 15; };
@@ -130,8 +113,28 @@ void conv1d_toep_kernel(const float *__restrict__ x, const float *__restrict__ w
     };
     auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
+    // (lane t of every wavefront holds tap t, k <= 64: one load, and all lanes take part; the first tile's loads go out before it is waited for)
+    const float tap = lane < g.k ? wr[g.wflip ? g.k - 1 - lane : lane] : 0.0f;
     int t = t_first;
     load(b, t);
+    __builtin_amdgcn_sched_barrier(0);
+    const bool tiny = __builtin_amdgcn_ballot_w64(tap != 0.0f && __builtin_fabsf(tap) < 0x1p-70f) != 0;
+    const float scaled = tap * (tiny ? kUp : 1.0f / kUp);
+
+    // ---- T: slot p of copy X holds tap p - 32 - X (zero outside [0, k)), so that a lane's eight taps, from tap
+    // 16 c + 8 half - j on, start on a dword of copy j & 1
+#pragma unroll
+    for (int i0 = 0; i0 < 2 * TLEN; i0 += T) {
+        const int i = i0 + tid, X = i >= TLEN, p = i - X * TLEN, t = p - 32 - X;
+        const float f = __shfl(scaled, t & 63, kWave);
+        __bf16 f1, f2, f3;
+        split_nearest(t >= 0 && t < g.k ? f : 0.0f, f1, f2, f3);
+        if (i < 2 * TLEN) {
+            taps[0][X][p] = __builtin_bit_cast(unsigned short, f1);
+            taps[1][X][p] = __builtin_bit_cast(unsigned short, f2);
+            taps[2][X][p] = __builtin_bit_cast(unsigned short, f3);
+        }
+    }
     barrier();
     v8bf F[3][NCH];
 #pragma unroll
@@ -351,13 +354,13 @@ bool conv1d_toep_takes(int32_t k, int32_t dilation)
 // [64,45,900], dilation 4, k = 5 13.3 / 10.8, 25 15.9 / 10.9, dilation 8, k = 5 13.1 / 12.5, dilation 16, k = 5 14.1 / 13.5; 16 apart rows that
 // fill a tile are even where there are few of them and ahead where there are many: [32,64,1000], k = 5 10.2 / 11.0, [400,100,1000] 178 / 137.
 //
-// 33 - 36 adjacent taps on rows of two to eight tiles stay on the vector ALU: it spares their many starts (conv1d_thin_kernel / here, us; rows x
-// length): 1024 x 2000 6.5 / 8.0, 4096 x 3000 23.6 / 27.6, 3276 x 4100 28.7 / 31.3, 1755 x 7000 21.5 / 25, but 4096 x 1000 13.9 / 13.8,
-// 12288 x 1000 33.6 / 30.1, 1445 x 16384 43.5 / 42.8.
-bool conv1d_toep_wanted(int64_t Lo, int32_t k, int32_t dilation)
+// 33 - 36 adjacent taps on up to 8192 tiles, two to eight in a row, stay on the vector ALU: it spares their many starts (conv1d_thin_kernel /
+// here, us, 36 taps; rows x length): 1024 x 2000 6.6 / 8.3, 2048 x 3000 13.0 / 14.4, 819 x 4100 10.5 / 13.5, 877 x 7000 12.5 / 14.7, but 4096 x 1000
+// 13.9 / 12.7, 6144 x 2000 26.4 / 24.7, 8192 x 3000 51.4 / 45.0, 10922 x 5200 107 / 105, 1445 x 16384 42.3 / 40.4.
+bool conv1d_toep_wanted(int64_t rows, int64_t Lo, int32_t k, int32_t dilation)
 {
     const int64_t tiles = (Lo + max_origin_shift(Lo, 16) + kTile - 1) / kTile;
-    if (dilation == 1 && k <= 36 && tiles >= 2 && tiles <= 8) return false;
+    if (dilation == 1 && k <= 36 && tiles >= 2 && tiles <= 8 && rows * tiles <= 8192) return false;
     return k > 32 || (dilation >= 4 && dilation <= 16 && tiles == 1);
 }
 

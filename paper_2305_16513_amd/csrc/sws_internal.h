@@ -272,7 +272,7 @@ hipError_t launch_conv1d_padded(const float *x, const float *wgt, float *y, int6
 // Thin layers (one input channel per output channel) on the bf16 matrix cores (conv1d_toep.hip); wadj: the taps run
 // backwards.  toep_wanted: the layers that run there by themselves; kNotTaken: not its case, nothing launched.
 bool conv1d_toep_takes(int32_t k, int32_t dilation);
-bool conv1d_toep_wanted(int64_t Lo, int32_t k, int32_t dilation);
+bool conv1d_toep_wanted(int64_t rows, int64_t Lo, int32_t k, int32_t dilation);
 hipError_t launch_conv1d_toep(const float *x, const float *wgt, float *y, int64_t B, int64_t Cin, int64_t L, int64_t Cout, int64_t Lo,
                               int32_t k, int32_t pad, int32_t dilation, int32_t groups, hipStream_t s, int wadj);
 // Dense 1-D layers of 32 / 64 input channels on the bf16 matrix cores with split fp32 operands (conv1d_split.hip);
