@@ -45,6 +45,8 @@ def test_the_binding_and_the_library_agree_on_output_lengths(L):
                 for p in (-1, 0, 1, 3, 1000):
                     for d in (0, 1, 2, 8):
                         assert binding._out_len(n, w, s, p, d) == L.sws_out_len(n, w, s, p, d), (n, w, s, p, d)
+                    want = L.sws_out_len(n, w, s, p, 1)
+                    assert binding._out_hw(n, 50, w, 3, s, 2, p, 1) == (want, 25) and binding._out_hw(50, n, 3, w, 2, s, 1, p) == (25, want)
 
 
 def test_output_lengths_of_numbers_that_are_not_plain_ints(L):
@@ -56,6 +58,10 @@ def test_output_lengths_of_numbers_that_are_not_plain_ints(L):
               (100, 2 ** 32 + 3, 1, 0, 1), (100, 3, 1, 2 ** 32 + 1, 1), (100, 3, 1, 0, 2 ** 32 + 1), (100, 1 - 2 ** 32, 1, 0, 1),
               (100, 3, 1, -2 ** 32, 1), (2 ** 64 + 100, 3, 1, 0, 1), (100, 3, True, False, True)]:
         assert binding._out_len(*a) == L.sws_out_len(*a), a
+        if a[4] == 1:
+            n, w, st, p, _ = a
+            want = L.sws_out_len(n, w, st, p, 1)
+            assert binding._out_hw(n, 50, w, 3, st, 2, p, 1) == (want, 25) and binding._out_hw(50, n, 3, w, 2, st, 1, p) == (25, want), a
 
 
 def test_out_len(L):
