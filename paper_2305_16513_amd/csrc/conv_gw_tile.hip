@@ -327,8 +327,9 @@ __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict_
 
 // The same where few runs are to be added, at most kFewRuns: a workgroup takes a quarter (registers 4 q .. 4 q + 3, eight output channels x 32 input
 // channels) of one (block, wavefront) and all its taps, a wavefront each, so that what it stores is contiguous; 128-bit loads, all of a
-// wavefront's in flight at once.  A tap and 64 elements per workgroup, as above, left a channel's taps to nine workgroups of different XCDs: 256 x 256
-// channels, 3 x 3, 13 us there, 7.7 here; with 24, 116 and 256 runs 5.6, 6.2 and 6.9 there, 6.4, 7.2 and 6.6 here (eight wavefronts per tap).
+// wavefront's in flight at once, which is what limits the runs.  A tap and 64 elements per workgroup, as above, leave a channel's taps to as many workgroups
+// of different XCDs.  Durations, us, above / here: 256 x 256 channels, 3 x 3, 8 runs 13.0 / 6.6, 3 runs 12.3 / 5.3; 512 x 480, 2 runs, 1 x 1 6.5 / 4.9 (512 x 512),
+// 1 x 3 15.7 / 5.8, 2 x 2 19.8 / 6.9, 1 x 5 24.2 / 7.3, 3 x 3, 4 runs 40.8 / 13.8; one block of one run 2.9 / 4.1.
 constexpr int kFewRuns = 8;
 __global__ __launch_bounds__(576) void gw_reduce_few_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
 {
@@ -445,7 +446,8 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
     const int SW = (q.taps - 1) * dil + 1, SWc = SW < sw ? SW : sw, cus = device_cus();
     g.ng = q.ng;
     // Channel blocks of a workgroup, strip width, rows per tile and runs: the smallest estimated time of the longest run (products
-    // on two wavefronts per SIMD, staging per unit, a run's end), in cycles.
+    // on two wavefronts per SIMD, staging per unit, a run's end), in cycles.  (The second pass is in `end` as it was before
+    // there were two of them: it weighs channel blocks against runs, and takes 3 - 14 us either way.)
     bool found = false;
     double cost = 0;
     for (int wmn = 0; wmn < 4; ++wmn) {
