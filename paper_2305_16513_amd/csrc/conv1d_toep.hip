@@ -4,10 +4,10 @@
 // The taps at distance d act on each of the d phases of a row by themselves.  32 consecutive outputs of one phase are
 //     out[m + j] = sum over s of  X[m + s] * T[s][j],   T[s][j] = f[s - j] (0 <= s - j < k, else 0),
 // and 32 such runs together are the product of a 32 x S by an S x 32 matrix, S = 31 + k rounded up to 16.  Both operands
-// are exact sums of three bf16 numbers; six of the nine products of pieces are accumulated in fp32 (the other three are
-// below 2^-21 of their term; up to 17 taps, whose sums round so little that this would show, eight) in one accumulator: the five lesser ones of all slices first, at most 2^-6 of the terms, then the
-// leading ones on top, so that a result takes S / 16 <= 6 roundings of its own size.  A tile of 1024 outputs takes
-// 6 S / 16 instructions of 32 cycles (k = 51: 1152 cycles) where one fused multiply-add per tap and output takes
+// are exact sums of three bf16 numbers; six of the nine products of pieces are accumulated in fp32 (the other three are below 2^-21 of
+// their term; up to 17 taps, whose sums round so little that this would show, eight) in one accumulator: the lesser ones of all slices first,
+// at most 2^-6 of the terms, then the leading ones on top, so that a result takes S / 16 <= 6 roundings of its own size.  A
+// tile of 1024 outputs takes 6 S / 16 instructions of 32 cycles (k = 51: 1152 cycles) where one fused multiply-add per tap and output takes
 // 64 k (3264).
 //
 // A workgroup stages the inputs of its NW tiles (one per wavefront) once, split, as three planes of 16-bit numbers in LDS, in the order
@@ -18,10 +18,10 @@
 // lane holds four phases of one position: d >= 4 stores whole 16-byte groups, 64 bytes and more side by side; d = 1: 128 bytes.
 //
 // Loads of the next tile are in flight during a tile's products, and it is split into LDS before the tile's stores, which its loads would
-// otherwise be waited for behind.  Bound by HBM up to its workgroups' starts and barriers (three wavefronts per SIMD: T takes 72
-// registers at 51 taps).  Measured, cold inputs, us, the vector-ALU kernels / this one: [1,1024,65536], 51 taps 8 apart 178 / 104 (a
-// copy of that size 86; matrix cores 41 % busy), 49 taps 32 apart, which no other kernel but the direct one takes,
-// [8,64,65536] 1260 / 85.  Error against 64 bits 4.3e-8 (vector ALU 1.3e-7).
+// otherwise be waited for behind; the first tile's go out before T is built.  Bound by HBM up to its workgroups' starts and barriers (three wavefronts
+// per SIMD: T takes 72 registers at 51 taps).  Measured, cold inputs, us, the vector-ALU kernels / this one: [1,1024,65536], 51 taps 8 apart
+// 168 / 104 (a copy of that size 86; matrix cores 41 % busy), 49 taps 32 apart, which no other kernel but the direct one takes,
+// [8,64,65536] 1256 / 82.  Error against 64 bits 4.5e-8 (vector ALU 1.3e-7).
 //
 // bf16 reaches down to 2^-133: three pieces hold every bit of a number from 2^-110 on.  Inputs are multiplied by 2^40 before they are
 // split, so that this is all of them, and taps by 2^-40; a channel with a tap below 2^-70 has its taps multiplied by 2^40
@@ -347,12 +347,12 @@ bool conv1d_toep_takes(int32_t k, int32_t dilation)
     return k >= 3 && k <= 64 && (dilation == 1 || dilation == 4 || dilation == 8 || dilation == 16 || dilation == 32);
 }
 
-// More than 32 taps: the vector-ALU kernels are bound by their multiply-adds.  Measured (them / here, us, cold inputs):
-// dilation 1, [1,512,65536] k = 33 57 / 58, 37 65 / 57, 49 85 / 56, [40,128,3000] k = 33 36.5 / 36.6, 49 43 / 38; dilation 8,
-// [1,512,65536] k = 25 61 / 59, 33 68 / 59, 49 90 / 61, [16,128,2095] k = 25 15.6 / 17.6, 33 16.9 / 16.8, 49 22 / 17.5;
-// dilation 32, [1,512,65536] k = 17 62 / 79, 33 95 / 80.  Rows of one tile with taps 4, 8 or 16 apart (their scatter table is built for one tile):
-// [64,45,900], dilation 4, k = 5 13.3 / 10.8, 25 15.9 / 10.9, dilation 8, k = 5 13.1 / 12.5, dilation 16, k = 5 14.1 / 13.5; 16 apart rows that
-// fill a tile are even where there are few of them and ahead where there are many: [32,64,1000], k = 5 10.2 / 11.0, [400,100,1000] 178 / 137.
+// More than 32 taps: the vector-ALU kernels are bound by their multiply-adds.  Measured (them / here, us, cold inputs): dilation 1, [1,512,65536]
+// k = 25 48 / 56, 33 53 / 54, 37 63 / 55, 49 73 / 56, [40,128,3000] 49 39 / 28; dilation 8, [1,512,65536] k = 25 61 / 55, 33 67 / 57,
+// 49 90 / 57, [16,128,2095] k = 25 14.7 / 17.4, 33 16.5 / 17.1, 49 21 / 16.5; dilation 32, [1,512,65536] k = 17 61 / 61, 33
+// 96 / 74.  Rows of one tile with taps 4, 8 or 16 apart (their scatter table is built for one tile): [64,45,900], dilation 4, k = 5 13.4 / 9.7, dilation
+// 16, k = 5 14.1 / 12.6; 16 apart rows that fill a tile are behind where there are few of them and ahead where there are many: [32,64,1000], k = 5
+// 9.9 / 10.9, [400,100,1000] 178 / 135.
 //
 // 33 - 36 adjacent taps on up to 8192 tiles, two to eight in a row, stay on the vector ALU: it spares their many starts (conv1d_thin_kernel /
 // here, us, 36 taps; rows x length): 1024 x 2000 6.6 / 8.3, 2048 x 3000 13.0 / 14.4, 819 x 4100 10.5 / 13.5, 877 x 7000 12.5 / 14.7, but 4096 x 1000

@@ -96,13 +96,14 @@ hipError_t launch_pool2d_small(int op, const T *x, T *y, int64_t planes, int H, 
     // ... and at most 4096 outputs: windows that spread a plane (the adjoint of a global average: 1 x 1 -> 7 x 7, 65536
     // planes) would otherwise leave too few workgroups, or outputs beyond the reach of the quotient below
     if (G * Q > 4096) G = Q < 1024 ? (int)(4096 / Q) & ~3 : 4;
-    // ... and no more than leave every compute unit eight workgroups (rounded up: one workgroup over would be a round of its own), but then as
-    // many as fill its last pass over the threads (300000 planes, 3 x 3, stride 2: 4 x 4, 576 outputs in three passes 9.6 us, 768 8.4; 5 x 5 16.2 / 14)
+    // ... and no more than leave every compute unit eight workgroups (rounded up: one workgroup over would be a round of its own), but then, where there
+    // are only a few passes over the threads, as many as fill the last one (300000 planes, 3 x 3, stride 2: 4 x 4, 576 outputs in three passes
+    // 9.5 us, 768 8.4; 5 x 5 16.0 / 14.4)
     const int64_t want = (planes + 8 * device_cus() - 1) / (8 * device_cus());
     if (want < G) {
         const int g = ((int)want + 3) & ~3;
         const int whole = (int)((g * Q + kThreads - 1) / kThreads * kThreads / Q) & ~3;
-        const int to = g * Q > kThreads && whole > g ? whole : g;
+        const int to = g * Q > kThreads && g * Q <= 6 * kThreads && whole > g ? whole : g;
         if (to < G) G = to;
     }
     int ls = 0;
