@@ -232,6 +232,11 @@ sws_status sws_avgpool2d_grad(const float *gy, float *gx, int64_t N, int64_t C, 
  *
  *   x : device [B,Cin,L]    wgt : device [Cout,Cin/groups,k]    y : device [B,Cout,Lo]
  * groups = 1 is the dense-channel contraction; groups = Cin = Cout is depthwise.
+ * Accumulation is fp32 and the summation order is unspecified; every output is within 1e-5 * sum|terms| of the exact
+ * sum.  On layers with one input channel per output channel at stride 1 a product x * w is evaluated as six (up to 17 taps: eight)
+ * exact products of bf16 pieces of the fp32 operands, which drops less than 2^-21 (2^-31) of it, where there are 33 to 64
+ * taps at distance 1, 4, 8, 16 or 32, or 3 to 64 taps at distance 4, 8 or 16 on rows of up to 1024 outputs: operands of any
+ * finite size, subnormal ones too, and infinities and NaN as in the sum itself.  Dense layers: see sws_conv2d.
  * Errors: INVALID_ARG for sizes < 0, Cin/Cout/k/stride/dilation/groups < 1, pad < 0,
  * Cin or Cout not divisible by groups, kernel span above the padded length, NULL pointer
  * with output, L above the int32 limit. */
@@ -279,7 +284,8 @@ sws_status sws_conv1d_16(sws_dtype dtype, const void *x, const float *wgt, void 
  *                                                                              (d loss / d wgt)
  *
  * All sizes are those of the forward call (L is the length of x, Lo = sws_out_len(...) that of
- * gy).  gx and gw are overwritten, not accumulated into.  gw is summed with atomic adds whose
+ * gy).  gx and gw are overwritten, not accumulated into.  gx is evaluated like the forward call, thin layers' products in pieces where
+ * it says so (the length that counts is then L).  gw is summed with atomic adds whose
  * order is not fixed: its last bits may differ between runs.  On dense layers (groups = 1, stride and
  * dilation 1, k = 1, 3 or 5, channel counts in multiples of 32) a product of gw is evaluated as six
  * exact products of bf16 pieces of its fp32 operands, which drops less than 2^-21 of it, on average 2^-25 (inputs
@@ -302,8 +308,9 @@ sws_status sws_conv1d_grad_weight(const float *x, const float *gy, float *gw, in
  * Accumulation is fp32 and the summation order is unspecified; every output is within
  * 1e-5 * sum|terms| of the exact sum.  On some layers (64 input channels, 3 x 3, stride 1) a product
  * x * w is evaluated as six exact products of bf16 pieces of the fp32 operands, which drops less than
- * 2^-21 of it, on average 2^-25; products of integers below 2^8 stay exact.  (The same holds for sws_conv1d on dense
- * layers of 32 / 64 input channels.)
+ * 2^-21 of it, on average 2^-25; products of integers below 2^8 stay exact.  With a workspace (sws_conv2d_ws) most dense layers are
+ * evaluated so, and sws_conv1d's dense layers of 32 / 64 input channels without one.  There an operand below 2^-110 in magnitude
+ * keeps no bit below 2^-133, and inputs must be finite (an infinite operand splits into inf and NaN).
  * Errors: as sws_conv1d. */
 sws_status sws_conv2d(const float *x, const float *wgt, float *y, int64_t N, int64_t Cin,
                       int64_t H, int64_t W, int64_t Cout, int32_t kh, int32_t kw,

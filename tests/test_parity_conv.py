@@ -500,7 +500,7 @@ def test_conv1d_dense_split_operands_carry_every_bit(B):
     assert_within_tol(y, ref, mag, "low bits", tol=2e-7)
 
 
-# Thin layers on the matrix cores (conv1d_variant 8; more than 32 taps by themselves): one, two and three wavefronts per workgroup,
+# Thin layers on the matrix cores (conv1d_variant 8; by themselves see conv1d_toep_wanted): one, two and three wavefronts per workgroup,
 # every number of slices of T at every distance that has it, ends of tiles and rows, several rows per workgroup (the last).  Tolerance: 31 + k <= 96 products
 # of exact pieces in fp32, six of nine (the dropped ones below 2^-21 of a term): 96 * 2^-24 + 2^-21 = 6.2e-6 of sum |terms|.
 @pytest.mark.parametrize("b,c,length,k,d,pad", [
@@ -631,3 +631,22 @@ def test_conv1d_thin_layers_are_as_exact_as_the_fp32_kernels(B, k, d, positive):
         finally:
             B.sws_set_option("conv1d_variant", 0)
     assert error[0] <= 1.02 * error[1], error[0] / error[1]
+
+
+# 33 - 36 adjacent taps: the vector ALU (variant 2) on rows of two to eight tiles of 1024 and up to 8192 tiles, the matrix cores (8) beyond on each side
+@pytest.mark.parametrize("rows,length,k,route", [
+    (6, 1056, 33, 8), (6, 1090, 33, 2), (3, 2100, 34, 2), (2, 8192 + 35, 36, 2), (1, 8192 + 16 + 35, 36, 8), (4096, 1100, 35, 2), (4097, 1100, 35, 8), (2, 1500, 37, 8)])
+def test_conv1d_thin_routes_of_33_to_36_taps(B, rows, length, k, route):
+    r = _rng(rows + length)
+    x = r.standard_normal((1, rows, length), dtype=np.float32)
+    w = (r.standard_normal((rows, 1, k), dtype=np.float32) / np.sqrt(k)).astype(np.float32)
+    y = to_host(B.sws_conv1d(to_gpu(x), to_gpu(w), 1, 0, 1, rows))
+    B.sws_set_option("conv1d_variant", route)
+    try:
+        assert np.array_equal(y, to_host(B.sws_conv1d(to_gpu(x), to_gpu(w), 1, 0, 1, rows)))
+        B.sws_set_option("conv1d_variant", 10 - route)
+        other = to_host(B.sws_conv1d(to_gpu(x), to_gpu(w), 1, 0, 1, rows))
+    finally:
+        B.sws_set_option("conv1d_variant", 0)
+    assert np.array_equal(y, other) == (k > 36)          # (more than 36 taps: the one kernel either way)
+    assert_within_tol(y, *oracle.conv1d(x, w, 1, 0, 1, rows), "rows %d length %d k %d" % (rows, length, k), tol=6.2e-6)

@@ -307,6 +307,19 @@ def test_small_planes_whole_windows(B, op, shape):
             assert_bit_exact(y, ref, "whole planes %s %s" % (shape, op))
 
 
+@pytest.mark.parametrize("op", ["add", "max"])
+@pytest.mark.parametrize("planes,h,w,k,s,p", [(150000, 4, 4, 3, 2, 1), (150001, 3, 3, 3, 1, 1), (99999, 5, 5, 3, 2, 1), (40003, 7, 7, 3, 1, 1), (300007, 2, 2, 2, 1, 1)])
+def test_small_planes_by_whole_passes(B, op, planes, h, w, k, s, p):
+    """Thousands of planes dealt to eight workgroups per compute unit: one pass over the threads, a few that are filled up, and many."""
+    x = np.random.Generator(np.random.PCG64(planes)).standard_normal((1, planes, h, w), dtype=np.float32)
+    y = to_host(B.sws_pool2d(OPS[op], to_gpu(x), k, k, s, s, p, p, 0.25))
+    ref, mag = oracle.pool2d(OPS[op], x, k, k, s, s, p, p, 0.25)
+    if op == "add":
+        assert_within_tol(y, ref, mag, "%d planes" % planes)
+    else:
+        assert_bit_exact(y, ref, "%d planes" % planes)
+
+
 @pytest.mark.parametrize("divisor", [0, 1])
 @pytest.mark.parametrize("geom", EX_GEOMS)
 @pytest.mark.parametrize("shape", [(3, 500, 7, 7), (2, 99, 14, 14), (1, 30, 9, 20)])
