@@ -650,3 +650,16 @@ def test_conv1d_thin_routes_of_33_to_36_taps(B, rows, length, k, route):
         B.sws_set_option("conv1d_variant", 0)
     assert np.array_equal(y, other) == (k > 36)          # (more than 36 taps: the one kernel either way)
     assert_within_tol(y, *oracle.conv1d(x, w, 1, 0, 1, rows), "rows %d length %d k %d" % (rows, length, k), tol=6.2e-6)
+
+
+@pytest.mark.parametrize("cin,cout,groups", [(3, 3, 3), (2, 6, 2), (6, 4, 2), (1, 5, 1), (32, 64, 1), (5, 7, 1)])
+@pytest.mark.parametrize("stride,pad,d", [(1, 0, 8), (1, 3, 100), (2, 1, 5), (3, 0, 70), (70, 2, 3)])
+def test_conv1d_one_tap_has_no_distance(B, cin, cout, groups, stride, pad, d):
+    r = _rng(cin * 100 + stride + d)
+    x = r.standard_normal((2, cin, 700), dtype=np.float32)
+    w = r.standard_normal((cout, cin // groups, 1), dtype=np.float32)
+    _c1(B, x, w, stride=stride, pad=pad, dilation=d, groups=groups, what="one tap s%d p%d d%d" % (stride, pad, d))
+    if stride == 1:
+        gy = r.standard_normal((2, cout, 700 + 2 * pad), dtype=np.float32)
+        gx = to_host(B.sws_conv1d_grad_input(to_gpu(gy), to_gpu(w), 700, 1, pad, d, groups))
+        assert_within_tol(gx, *oracle.conv1d_grad_input(gy, w, 700, 1, pad, d, groups), "gx")
