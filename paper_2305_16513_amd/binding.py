@@ -17,6 +17,9 @@ SWS_OK, SWS_ERR_INVALID_ARG, SWS_ERR_UNSUPPORTED, SWS_ERR_HIP = 0, 1, 2, 3
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsws.so")
 _lib = None
+# Native code for the small calls (csrc/calls.cpp), loaded with the library; None: not built for this torch, or not loaded yet.  It answers None
+# where a call is out of the ordinary, and the Python code below it then does the same call.
+_calls = None
 
 _i64, _i32, _f32, _vp = ctypes.c_int64, ctypes.c_int32, ctypes.c_float, ctypes.c_void_p
 
@@ -106,7 +109,22 @@ def lib():
         L.sws_set_option.argtypes = [ctypes.c_char_p, _i64]
         L.sws_version.restype = ctypes.c_char_p
         _lib = L
+        _load_calls()
     return _lib
+
+
+def _load_calls():
+    """The native calls, beside the library that they are linked to.  They hold torch's C++ interface of the version that they were
+    built with; where they do not load, the Python code serves every call."""
+    global _calls
+    if not os.path.samefile(os.path.dirname(LIB_PATH), _HERE):
+        return
+    try:
+        from . import _calls as native
+    except ImportError:
+        return
+    native.set_error(SwsError)
+    _calls = native
 
 
 def status_string(status):
@@ -233,6 +251,10 @@ def _check(rc, what):
 
 def sws_slide1d(op, x, w, scale=1.0, y=None, stream=None):
     """x [..., len] -> y [..., len-w+1]; all leading dimensions are independent rows."""
+    if y is None and stream is None and _calls is not None:
+        r = _calls.slide1d(op, x, w, scale)
+        if r is not None:
+            return r
     _dev(x, "x")
     length = x.shape[-1]
     rows = x.numel() // length if length else 0
@@ -251,6 +273,10 @@ _DTYPE_16 = {torch.bfloat16: SWS_DTYPE_BF16, torch.float16: SWS_DTYPE_F16}
 
 def sws_slide1d_16(op, x, w, scale=1.0, y=None, stream=None):
     """x [..., len] of bfloat16 or float16 -> y [..., len-w+1] of the same type (fp32 arithmetic)."""
+    if y is None and stream is None and _calls is not None:
+        r = _calls.slide1d_16(op, x, w, scale)
+        if r is not None:
+            return r
     if not isinstance(x, torch.Tensor) or not x.is_cuda:
         raise TypeError("x must be a GPU tensor")
     if x.dtype not in _DTYPE_16 or not x.is_contiguous():
@@ -276,6 +302,10 @@ SWS_PAD_IDENTITY, SWS_PAD_MIRROR, SWS_PAD_PERIODIC, SWS_PAD_EDGE, SWS_PAD_SHRINK
 
 def sws_slide1d_padded(op, x, w, pad_left, pad_right, mode, scale=1.0, y=None, stream=None):
     """x [..., len] -> y [..., len+pad_left+pad_right-w+1]: the rows are extended by the boundary rule `mode`."""
+    if y is None and stream is None and _calls is not None:
+        r = _calls.slide1d_padded(op, x, w, pad_left, pad_right, mode, scale)
+        if r is not None:
+            return r
     _dev(x, "x")
     length = x.shape[-1]
     rows = x.numel() // length if length else 0
@@ -308,6 +338,10 @@ def sws_slide1d_pair(u, v, w, yu=None, yv=None, stream=None):
 
 def sws_pool2d(op, x, kh, kw, sh=1, sw=1, ph=0, pw=0, scale=1.0, y=None, stream=None):
     """x [N, C, H, W] -> y [N, C, Ho, Wo]."""
+    if y is None and stream is None and _calls is not None:
+        r = _calls.pool2d(op, x, kh, kw, sh, sw, ph, pw, scale)
+        if r is not None:
+            return r
     _dev(x, "x")
     n, c, h, wd = x.shape
     ho, wo = _out_hw(h, wd, kh, kw, sh, sw, ph, pw)
@@ -321,6 +355,10 @@ def sws_pool2d(op, x, kh, kw, sh=1, sw=1, ph=0, pw=0, scale=1.0, y=None, stream=
 
 def sws_maxpool2d_grad(x, gy, kh, kw, sh=1, sw=1, ph=0, pw=0, gx=None, stream=None):
     """x [N, C, H, W], gy [N, C, Ho, Wo] -> gx [N, C, H, W]: gradients routed to the windows' maxima."""
+    if gx is None and stream is None and _calls is not None:
+        r = _calls.maxpool2d_grad(x, gy, kh, kw, sh, sw, ph, pw)
+        if r is not None:
+            return r
     _dev(x, "x")
     _dev(gy, "gy")
     n, c, h, wd = x.shape
@@ -335,6 +373,10 @@ def sws_maxpool2d_grad(x, gy, kh, kw, sh=1, sw=1, ph=0, pw=0, gx=None, stream=No
 def sws_avgpool2d_grad(gy, h, wd, kh, kw, sh=1, sw=1, ph=0, pw=0, divisor=0, scale=1.0, gx=None, stream=None):
     """gy [N, C, Ho, Wo], (h, wd) = the pooled plane -> gx [N, C, H, W]: the adjoint of average pooling
     (sws_pool2d_ex with SWS_OP_ADD, pads (ph, pw, ph, pw), the same divisor (0 = SWS_DIV_SCALE) and scale)."""
+    if gx is None and stream is None and _calls is not None:
+        r = _calls.avgpool2d_grad(gy, h, wd, kh, kw, sh, sw, ph, pw, divisor, scale)
+        if r is not None:
+            return r
     _dev(gy, "gy")
     n, c, ho, wo = gy.shape
     if (ho, wo) != _out_hw(h, wd, kh, kw, sh, sw, ph, pw):
@@ -347,6 +389,10 @@ def sws_avgpool2d_grad(gy, h, wd, kh, kw, sh=1, sw=1, ph=0, pw=0, divisor=0, sca
 
 def sws_pool2d_16(op, x, kh, kw, sh=1, sw=1, ph=0, pw=0, scale=1.0, y=None, stream=None):
     """x [N, C, H, W] of bfloat16 or float16 -> y [N, C, Ho, Wo] of the same type (fp32 arithmetic)."""
+    if y is None and stream is None and _calls is not None:
+        r = _calls.pool2d_16(op, x, kh, kw, sh, sw, ph, pw, scale)
+        if r is not None:
+            return r
     if not isinstance(x, torch.Tensor) or not x.is_cuda:
         raise TypeError("x must be a GPU tensor")
     if x.dtype not in _DTYPE_16 or not x.is_contiguous():
@@ -421,6 +467,10 @@ def sws_conv1d(x, wgt, stride=1, pad=0, dilation=1, groups=1, y=None, stream=Non
     """x [B, Cin, L], wgt [Cout, Cin/groups, k] -> y [B, Cout, Lo].
 
     Finite inputs only: most dense layers multiply exactly split operands, where an infinity gives NaN."""
+    if groups != 1 and y is None and stream is None and _calls is not None:
+        r = _calls.conv1d(x, wgt, stride, pad, dilation, groups)
+        if r is not None:
+            return r
     _dev(x, "x")
     _dev(wgt, "wgt")
     b, cin, length = x.shape
@@ -439,6 +489,10 @@ def sws_conv1d(x, wgt, stride=1, pad=0, dilation=1, groups=1, y=None, stream=Non
 
 def sws_conv1d_16(x, wgt, stride=1, pad=0, dilation=1, groups=1, y=None, stream=None):
     """x [B, Cin, L] of bfloat16 or float16, wgt [Cout, Cin/groups, k] fp32 -> y [B, Cout, Lo] of x's type."""
+    if y is None and stream is None and _calls is not None:
+        r = _calls.conv1d_16(x, wgt, stride, pad, dilation, groups)
+        if r is not None:
+            return r
     if not isinstance(x, torch.Tensor) or not x.is_cuda:
         raise TypeError("x must be a GPU tensor")
     if x.dtype not in _DTYPE_16 or not x.is_contiguous() or x.dim() != 3:
@@ -466,6 +520,10 @@ def sws_conv1d_grad_input(gy, wgt, length, stride=1, pad=0, dilation=1, groups=1
     """gy [B, Cout, Lo], wgt [Cout, Cin/groups, k], length = L of the forward input -> gx [B, Cin, L].
 
     Finite inputs only: most dense layers multiply exactly split operands, where an infinity gives NaN."""
+    if groups != 1 and gx is None and stream is None and _calls is not None:
+        r = _calls.conv1d_grad_input(gy, wgt, length, stride, pad, dilation, groups)
+        if r is not None:
+            return r
     _dev(gy, "gy")
     _dev(wgt, "wgt")
     b, cout, lo = gy.shape
@@ -484,6 +542,10 @@ def sws_conv1d_grad_weight(x, gy, k, stride=1, pad=0, dilation=1, groups=1, gw=N
     """x [B, Cin, L], gy [B, Cout, Lo] -> gw [Cout, Cin/groups, k].
 
     Finite inputs only: most dense layers multiply exactly split operands, where an infinity gives NaN."""
+    if groups != 1 and gw is None and stream is None and _calls is not None:
+        r = _calls.conv1d_grad_weight(x, gy, k, stride, pad, dilation, groups)
+        if r is not None:
+            return r
     _dev(x, "x")
     _dev(gy, "gy")
     b, cin, length = x.shape

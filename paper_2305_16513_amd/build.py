@@ -53,7 +53,26 @@ def build(verbose=False):
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    _build_calls()
     return LIB
+
+
+def _build_calls():
+    """The binding's small calls in native code: host code against torch's headers, beside the library and linked to it."""
+    import sysconfig
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", os.path.join(ROOT, "include"),
+           "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "calls.cpp"), "-o", os.path.join(HERE, "_calls.so"),
+           "-L", HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN", "-L", lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for calls.cpp:\n" + r.stderr)
+    if r.stderr.strip():
+        print(r.stderr, file=sys.stderr)
 
 
 if __name__ == "__main__":

@@ -1,0 +1,103 @@
+"""The binding's native calls (csrc/calls.cpp) against its Python code: the same bits, and None for whatever is out of the ordinary."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2305_16513_amd import binding as B
+
+
+@pytest.fixture(scope="module")
+def native():
+    B.lib()
+    if B._calls is None:
+        pytest.skip("not built")
+    return B._calls
+
+
+ODD = {"slide1d": (0, None, 3, 1.0), "slide1d_16": (0, None, 3, 1.0), "slide1d_padded": (0, None, 3, 1, 1, 0, 1.0), "pool2d": (0, None, 3, 3, 1, 1, 1, 1, 1.0),
+       "pool2d_16": (0, None, 3, 3, 1, 1, 1, 1, 1.0), "maxpool2d_grad": (None, None, 3, 3, 1, 1, 1, 1), "avgpool2d_grad": (None, 4, 4, 3, 3, 1, 1, 1, 1, 0, 1.0),
+       "conv1d": (None, None, 1, 0, 1, 2), "conv1d_16": (None, None, 1, 0, 1, 2), "conv1d_grad_input": (None, None, 9, 1, 0, 1, 2),
+       "conv1d_grad_weight": (None, None, 3, 1, 0, 1, 2)}
+
+
+@pytest.mark.parametrize("name", ODD)
+def test_calls_out_of_the_ordinary_are_left_to_python(native, name):
+    f, args = getattr(native, name), ODD[name]
+    for x in (None, 3, "x", torch.zeros(2, 2, 9), torch.zeros(2, 2, 4, 4), np.zeros((2, 9), np.float32)):
+        assert f(*[x if a is None else a for a in args]) is None
+    assert f() is None and f(*args, 1) is None
+
+
+def _all(train=True):
+    g = torch.Generator(device="cuda").manual_seed(5)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda")
+    x, p, w, gy = r(3, 4, 1001), r(2, 5, 9, 11), r(4, 1, 7), r(3, 4, 1001)
+    h, ph = x.bfloat16(), p.half()
+    yield "slide1d", lambda **k: B.sws_slide1d(B.OP_ADD, x, 5, 0.2, **k)
+    yield "slide1d int scale", lambda **k: B.sws_slide1d(B.OP_MAX, x, 5, 2, **k)
+    yield "slide1d_16", lambda **k: B.sws_slide1d_16(B.OP_ADD, h, 64, 1 / 64, **k)
+    yield "slide1d_padded", lambda **k: B.sws_slide1d_padded(B.OP_MIN, x, 6, 2, 3, B.SWS_PAD_MIRROR, **k)
+    yield "pool2d", lambda **k: B.sws_pool2d(B.OP_ADD, p, 3, 2, 2, 1, 1, 0, 1 / 6, **k)
+    yield "pool2d_16", lambda **k: B.sws_pool2d_16(B.OP_MAX, ph, 3, 3, 2, 2, 1, 1, **k)
+    yield "conv1d", lambda **k: B.sws_conv1d(x, w, 1, 3, 1, 4, **k)
+    yield "conv1d_16", lambda **k: B.sws_conv1d_16(h, w, 1, 3, 1, 4, **k)
+    yield "conv1d strided", lambda **k: B.sws_conv1d(x, w, 2, 3, 2, 4, **k)
+    if train:
+        yield "maxpool2d_grad", lambda **k: B.sws_maxpool2d_grad(p, r(2, 5, 5, 6) * 0 + 1, 3, 3, 2, 2, 1, 1, **k)
+        yield "avgpool2d_grad", lambda **k: B.sws_avgpool2d_grad(p, 9, 11, 3, 3, 1, 1, 1, 1, B.SWS_DIV_REAL_CELLS, 1.0, **k)
+        yield "conv1d_grad_input", lambda **k: B.sws_conv1d_grad_input(gy, w, 1001, 1, 3, 1, 4, **k)
+        yield "conv1d_grad_weight", lambda **k: B.sws_conv1d_grad_weight(x, gy, 7, 1, 3, 1, 4, **k)
+
+
+@pytest.mark.gpu
+def test_native_calls_give_the_bits_of_the_python_code(native, monkeypatch):
+    side = torch.cuda.Stream()
+    for name, f in _all():
+        got = f()
+        monkeypatch.setattr(B, "_calls", None)
+        want = f()
+        monkeypatch.setattr(B, "_calls", native)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            other = f()
+        side.synchronize()
+        for y in (got, other):
+            assert type(y) is torch.Tensor and y.shape == want.shape and y.dtype == want.dtype and y.is_contiguous() and not y.requires_grad
+            if name == "conv1d_grad_weight":                                 # (atomic adds: no fixed order)
+                assert torch.allclose(y, want, rtol=1e-5, atol=1e-4)
+            else:
+                assert torch.equal(y, want), name
+        for k in ("y", "gx", "gw"):                                          # an output of the caller's, a stream handed over: the Python code
+            try:
+                out = torch.empty_like(want)
+                assert f(**{k: out}) is out
+            except TypeError:
+                continue
+
+
+@pytest.mark.gpu
+def test_native_calls_refuse_what_python_refuses(native):
+    x = torch.randn(2, 4, 64, device="cuda")
+    w = torch.randn(4, 1, 7, device="cuda")
+    for bad, err in ((lambda: B.sws_slide1d(0, x, 65), B.SwsError), (lambda: B.sws_slide1d(0, x, 0), B.SwsError), (lambda: B.sws_slide1d(7, x, 3), B.SwsError),
+                     (lambda: B.sws_slide1d(0, x.double(), 3), TypeError), (lambda: B.sws_slide1d(0, x[:, :, ::2], 3), TypeError),
+                     (lambda: B.sws_slide1d(0, x.cpu(), 3), TypeError), (lambda: B.sws_conv1d(x, w, 1, 0, 1, 2), B.SwsError),
+                     (lambda: B.sws_conv1d(x, w, 0, 0, 1, 4), B.SwsError), (lambda: B.sws_conv1d(x, w, 1, 0, 11, 4), B.SwsError),
+                     (lambda: B.sws_slide1d_padded(0, x, 3, -1, 1, 0), B.SwsError), (lambda: B.sws_slide1d_padded(0, x, 3, 70, 70, 1), B.SwsError)):
+        with pytest.raises(err):
+            bad()
+    y = B.sws_slide1d(0, x, np.int64(5), np.float32(0.5))                    # numbers of other types: as before
+    assert torch.equal(y, B.sws_slide1d(0, x, 5, 0.5))
+    with torch.inference_mode():
+        assert B.sws_slide1d(0, x, 5).is_inference()
+    graph = torch.cuda.CUDAGraph()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=s):
+        y = B.sws_slide1d(0, x, 9, 1.0)
+    for _ in range(3):
+        x.normal_()
+        want = B.sws_slide1d(0, x, 9, 1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
