@@ -92,6 +92,7 @@ template <int TB, int WM, int WN, int UX, bool FAST>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void conv_gw_tile_kernel(const float *__restrict__ x, const float *__restrict__ gy, float *__restrict__ ws, GwTile g)
 {
+    fetch_arguments<24 + sizeof(GwTile)>();
     constexpr int WK = 8 / (WM * WN), OG = 4 * WM, OX = 4 * WN;      // octets of channels
     extern __shared__ __attribute__((aligned(16))) char lds[];
     char *const G = lds, *const X = lds + OG * kOctG;
@@ -301,6 +302,7 @@ __device__ __forceinline__ int slot_channel(int slot, int n)
 // block of 32.
 __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
 {
+    fetch_arguments<28 + sizeof(GwTile)>();
     __shared__ float part[4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nblk = g.cob * g.cib * g.ng, BLK = WM * WN;
@@ -333,6 +335,7 @@ __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict_
 constexpr int kFewRuns = 8;
 __global__ __launch_bounds__(576) void gw_reduce_few_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
 {
+    fetch_arguments<28 + sizeof(GwTile)>();
     __shared__ v4f part[9][64];
     const int lane = threadIdx.x & 63, t = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int BLK = WM * WN;
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(576) void gw_reduce_few_kernel(const float *__restr
     __syncthreads();
     // (consecutive threads: consecutive taps of an input channel, then the next one, then the next output channel)
     const float inv_nt = 1.0f / (float)nt;
-    for (int i = threadIdx.x; i < 256 * nt; i += blockDim.x) {
+    for (int i = threadIdx.x; i < 256 * nt; i += 64 * TB) {
         const int e = fdiv(i, inv_nt), tt = i - e * nt, c8 = e >> 5, l32 = e & 31;
         const float sum = ((const float *)part[tt])[(c8 & 3) * 64 + (c8 >> 2) * 32 + l32];        // register 4 qr + c8 % 4, lane
         const int co = slot_channel(cob * (32 * WM) + w % WM * 32 + 8 * qr + c8, g.Cout);

@@ -280,6 +280,7 @@ __global__ __launch_bounds__(WAVES * 64, (2 * WAVES + 3) / 4) void conv2d_mfma_c
                                                                        float *__restrict__ y, ConvGeom g,
                                                                        SegPlan sp)
 {
+    fetch_arguments<24 + sizeof(ConvGeom) + sizeof(SegPlan)>();
     // NB blocks of 8 input channels are staged per barrier pair (NB > 1 for few taps, where one
     // block is too little matrix work between two barriers).
     constexpr int CIB = 8, XP = 12;

@@ -76,6 +76,7 @@ struct PrepGeom {
 // Rounding to nearest in every piece: the pieces sum to the weight exactly and the dropped products are smallest.
 __global__ __launch_bounds__(256) void split_weights_kernel(const float *__restrict__ wgt, v4u *__restrict__ ws, PrepGeom g)
 {
+    fetch_arguments<16 + sizeof(PrepGeom)>();
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
     const int t = blockIdx.z * 4 + (int)(threadIdx.x >> 6);
     if (t >= g.KT) return;
@@ -124,6 +125,7 @@ template <int MB, int NB, int WM, int WN, int WK, int U, int NPH, int WPE, int S
 __global__ __launch_bounds__(64 * WM * WN * WK) __attribute__((amdgpu_waves_per_eu(WPE)))
 void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, float *__restrict__ y, SplitGeom g)
 {
+    fetch_arguments<24 + sizeof(SplitGeom)>();
     constexpr int T = 64 * WM * WN * WK;
     constexpr int R = S ? (S % 3 == 0 ? 3 : S % 4 == 0 ? 4 : 5) : 2;
     static_assert(S == 0 || (S % R == 0 && (NPH == 1 || S == 9)), "the ring of weights closes over a chunk");

@@ -76,6 +76,7 @@ __global__ __launch_bounds__(kThreads) void conv_stream_kernel(const float *__re
                                                                const float *__restrict__ wgt,
                                                                float *__restrict__ y, StreamGeom g)
 {
+    fetch_arguments<24 + sizeof(StreamGeom)>();
     constexpr int KT = KH * KW;
     constexpr int PITCH = CIN + kPad;
     constexpr int PB = X3 ? kPitch3 : PITCH * 4;      // bytes per staged position

@@ -88,6 +88,30 @@ __device__ __forceinline__ v8bf tr8(const char *p0, const char *p1)
     return __builtin_bit_cast(v8bf, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// The lines of a kernel's arguments (BYTES of them) fetched side by side, as the first thing that it does.  A launch's arguments are cold: a 64-byte line takes a wavefront
+// 700 cycles, from the scalar cache 84, and the compiler reads the fields of a large structure one after the other, where they are used.
+// (Waited for in here: the registers hold nothing that anybody reads.)
+template <int BYTES>
+__device__ __forceinline__ void fetch_arguments()
+{
+    constexpr int n = (BYTES + 63) / 64, last = (BYTES - 4) / 4 * 4;
+    static_assert(n <= 12, "more lines than loads below");
+    const auto *p = __builtin_amdgcn_kernarg_segment_ptr();
+    unsigned t0, t1, t2, t3, t4, t5, t6, t7, t8, t9, t10, t11;
+#define SWS_LINE(I) "i"(64 * I < last ? 64 * I : last)
+    if constexpr (n <= 4)
+        asm volatile("s_load_dword %0, %4, %5\n\ts_load_dword %1, %4, %6\n\ts_load_dword %2, %4, %7\n\ts_load_dword %3, %4, %8\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3) : "s"(p), SWS_LINE(0), SWS_LINE(1), SWS_LINE(2), SWS_LINE(3));
+    else
+        asm volatile("s_load_dword %0, %12, %13\n\ts_load_dword %1, %12, %14\n\ts_load_dword %2, %12, %15\n\ts_load_dword %3, %12, %16\n\t"
+                     "s_load_dword %4, %12, %17\n\ts_load_dword %5, %12, %18\n\ts_load_dword %6, %12, %19\n\ts_load_dword %7, %12, %20\n\t"
+                     "s_load_dword %8, %12, %21\n\ts_load_dword %9, %12, %22\n\ts_load_dword %10, %12, %23\n\ts_load_dword %11, %12, %24\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4), "=&s"(t5), "=&s"(t6), "=&s"(t7), "=&s"(t8), "=&s"(t9), "=&s"(t10), "=&s"(t11)
+                     : "s"(p), SWS_LINE(0), SWS_LINE(1), SWS_LINE(2), SWS_LINE(3), SWS_LINE(4), SWS_LINE(5), SWS_LINE(6), SWS_LINE(7), SWS_LINE(8),
+                       SWS_LINE(9), SWS_LINE(10), SWS_LINE(11));
+#undef SWS_LINE
+}
+
 // One buffer descriptor: loads beyond `bytes` return zero; kNowhere lies beyond every descriptor.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, unsigned bytes)
 {
