@@ -30,10 +30,11 @@
 // the same staged gradients; every tap belongs to one phase, so the work is that of the forward pass, and the two
 // cells of a row leave as one store.
 //
-// Measured, us, with the weights' pass, this kernel / the fp32 matrix kernels: [32,256,14,14] -> 256, 3 x 3 50 / 113, adjoint 49 / 133;
-// [32,128,56,56] -> 128, 3 x 3 stride 2 55 / 104, adjoint 67 / 205; [17,128,23,14] -> 104, 5 x 5 43 / 153; 100 layers 2.8 x on
-// average.  [32,256,14,14]: 41 us for this kernel by itself; 200 workgroups on 256 compute units, whose matrix cores are busy 62 % of the
-// cycles, waits take 25 % of the wavefronts' time (stride 2 58 and 17 %, its adjoint 37 and 27 %).  Blocks of one
+// Measured, us, with the weights' pass, this kernel / the fp32 matrix kernels: [32,256,14,14] -> 256, 3 x 3 48 / 113, adjoint 47 / 133;
+// [32,128,56,56] -> 128, 3 x 3 stride 2 51 / 104, adjoint 62 / 205; [17,128,23,14] -> 104, 5 x 5 43 / 153.
+// Staging wavefronts (P), here / without them: [32,256,14,14] 47.8 / 50.2, [32,128,56,56] 51 / 55, [8,256,28,28] -> 512 at stride 2 45 / 56,
+// [32,192,19,19] -> 64 at stride 2 32 / 40, [1,416,84,84] -> 232 75 / 83.  What is left of [32,256,14,14], in cycles of a workgroup's 80 k: 7 k until the first
+// products, eight chunks of 8.0 k (6.9 k of products), 7 k for the sum over two wavefronts and the stores; 200 workgroups on 256 compute units.  Blocks of one
 // wavefront at least two positions wide (NB = 2): with NB = 1 the weights alone saturate the vector cache's 64 bytes
 // per cycle.
 #include "sws_internal.h"
@@ -121,19 +122,22 @@ __global__ __launch_bounds__(256) void split_weights_kernel(const float *__restr
 // turn: stride-2 adjoints, 3 x 3, [32,128,56,56] <- 128 67 / 77, [32,256,28,28] <- 256 60 / 89, [8,256,28,28] <- 512 44 / 62, [1,128,56,56] <- 128
 // 17 / 22; 5 x 5 [32,256,14,14] -> 256 114 / 120, [8,128,28,28] -> 128 41 / 45.  Five taps of a row at two channel groups came out even: in the loop.  R: steps of weights held, R - 1 of them in flight.
 // WPE: wavefronts per SIMD that the registers are meant for.
-template <int MB, int NB, int WM, int WN, int WK, int U, int NPH, int WPE, int S>
-__global__ __launch_bounds__(64 * WM * WN * WK) __attribute__((amdgpu_waves_per_eu(WPE)))
+// P: wavefronts that only stage: they load the input, split it and write it to LDS, the others multiply.  0: every wavefront does both.
+template <int MB, int NB, int WM, int WN, int WK, int U, int NPH, int WPE, int P, int S>
+__global__ __launch_bounds__(64 * (WM * WN * WK + P)) __attribute__((amdgpu_waves_per_eu(WPE)))
 void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, float *__restrict__ y, SplitGeom g)
 {
     fetch_arguments<24 + sizeof(SplitGeom)>();
-    constexpr int T = 64 * WM * WN * WK;
-    constexpr int R = S ? (S % 3 == 0 ? 3 : S % 4 == 0 ? 4 : 5) : 2;
+    constexpr int T = P ? 64 * P : 64 * WM * WN * WK; // threads that stage
+    constexpr int R = S ? (S % 3 == 0 ? 3 : P ? 2 : S % 4 == 0 ? 4 : 5) : 2;
     static_assert(S == 0 || (S % R == 0 && (NPH == 1 || S == 9)), "the ring of weights closes over a chunk");
     constexpr int kPhase9[9] = {0, 1, 1, 2, 2, 3, 3, 3, 3};      // straight-line chunks with phases: a step's phase (see launch_cfg)
     constexpr int NLO = S ? NPH : 1;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool stages = P == 0 || wave >= WM * WN * WK;
+    const int tid = P ? (int)threadIdx.x - 64 * WM * WN * WK : (int)threadIdx.x;      // (of those that stage)
     const int wk = wave / (WM * WN), wmn = wave - wk * (WM * WN), wn = wmn / WM, wm = wmn - wn * WM;
 
     // XCD-aware: workgroup b runs on XCD b mod 8; each XCD takes a contiguous run of tiles, the channel tiles of one
@@ -152,15 +156,19 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
     const int n0 = R0 / g.Ho, oh0 = R0 - n0 * g.Ho;
     const int colbase = strip * g.TW;
 
+    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
     // ---- where my output positions start in the staged tile
     auto place = [&](int b, int &Rr, int &c, int &dn, int &oh) {
-        const int jj = c_0 + (wn * NB + b) * 32 + l32;
+        int me = l32;
+        if constexpr (P > 0) asm volatile("" : "+v"(me));      // (worked out twice: kept over the products the places would be spilled)
+        const int jj = c_0 + (wn * NB + b) * 32 + me;
         Rr = fdiv(jj, inv_tw);
         c = jj - Rr * tw;
         const int tt = oh0 + Rr;
         dn = fdiv(tt, g.inv_Ho);
         oh = tt - dn * g.Ho;
-        return (wn * NB + b) * 32 + l32 < bnp && R0 + Rr < g.NR;
+        return (wn * NB + b) * 32 + me < bnp && R0 + Rr < g.NR;
     };
     int posb[NB];
 #pragma unroll
@@ -180,9 +188,8 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
     const int nlines = dl * g.LPI + (tl - dl * g.Ho) * g.ls - oh0 * g.ls + g.SH;
     unsigned voff[U];                                 // bytes from image n0 to the position, channel 0; cells that do not exist: kNowhere
     int dst[U], c8[U];                                // place in the staged tile; first channel inside the chunk
-#pragma unroll
-    for (int i = 0; i < U; ++i) {
-        const int u = tid + i * T;
+    // unit i of the thread: first + i * step
+    auto unit = [&](int i, int u) {
         const int oct = fdiv(u, g.inv_PS), pos = u - oct * g.PS;
         const int lr = fdiv(pos, g.inv_LW), cc = pos - lr * g.LW;
         const int cph = fdiv(cc, g.inv_CW), cq = cc - cph * g.CW;
@@ -194,7 +201,11 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
         voff[i] = ok ? 4u * (unsigned)(dn * g.Cin * g.HW + row * g.W + col) : kNowhere;
         c8[i] = oct * 8;
         dst[i] = in ? (oct * 3 * g.PS + pos) * 16 : -1;
-    }
+    };
+    // (P: the first chunk is staged by everybody, U0 units each)
+    constexpr int T0 = P ? T + 64 * WM * WN * WK : T, U0 = P ? (U * T + T0 - 1) / T0 : U;
+#pragma unroll
+    for (int i = 0; i < U0; ++i) unit(i, (int)threadIdx.x + i * T0);
     const int units = noct * g.PS;
     const int64_t x_left = 4 * (int64_t)(g.N - n0) * g.Cin * g.HW;
     const __amdgpu_buffer_rsrc_t xrs = rsrc(x + (int64_t)n0 * g.Cin * g.HW, x_left < 0x7fffffff ? (unsigned)x_left : 0x7fffffffu);
@@ -211,7 +222,6 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
         }
     };
     auto commit = [&](int i, char *buf) {
-        if (i * T >= units) return;
         unsigned p[3][4];
 #pragma unroll
         for (int e = 0; e < 8; e += 2) {
@@ -231,7 +241,37 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
             for (int q = 0; q < 3; ++q) *(v4u *)(buf + dst[i] + q * (g.PS * 16)) = (v4u){p[q][0], p[q][1], p[q][2], p[q][3]};
         }
     };
-    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    if constexpr (P > 0) {
+#pragma unroll
+        for (int i = 0; i < U0; ++i) issue(i, 0);
+        if (stages) {
+#pragma unroll
+            for (int i = 0; i < U0; ++i)
+                if (i * T0 < units) commit(i, lds);
+            barrier();
+            // from here on the chunk that is multiplied is one behind the one written, two behind the one asked for
+            if (g.nchunk > 1) {
+#pragma unroll
+                for (int i = 0; i < U; ++i) unit(i, tid + i * T);
+#pragma unroll
+                for (int i = 0; i < U; ++i) issue(i, 1);
+            }
+            char *cur = lds;
+            for (int ch = 1; ch < g.nchunk; ++ch) {
+                cur = cur == lds ? lds + g.bufs : lds;
+#pragma unroll
+                for (int i = 0; i < U; ++i)
+                    if (i * T < units) commit(i, cur);
+                if (ch + 1 < g.nchunk) {
+#pragma unroll
+                    for (int i = 0; i < U; ++i) issue(i, ch + 1);
+                }
+                barrier();                            // chunk ch is there; chunk ch - 1 has been multiplied
+            }
+            for (int k = 0; k < 2 * (WK - 1); ++k) barrier();
+            return;
+        }
+    }
 
     // ---- my steps' places in the staged tile, one per lane (relative to my wavefront's first channel group)
     int steptab;
@@ -260,7 +300,13 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
             for (int q = 0; q < 3; ++q)
                 a[m][q] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(ars[m], lane * 16 + q * 1024, ks * kStepBytes, 0));
     };
-    v4u Bq[2][NB][3];
+    v4u Bq[P ? 1 : 2][NB][3];
+    // one piece of a step's inputs
+    auto bread = [&](const char *buf, int s, int q) {
+        const int off = __builtin_amdgcn_readlane(steptab, s) + bbase;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) Bq[0][j][q] = *(const v4u *)(buf + (off + posb[j]) + q * bpiece);
+    };
     auto bload = [&](v4u (&b)[NB][3], const char *buf, int s) {
         const int off = __builtin_amdgcn_readlane(steptab, s) + bbase;
 #pragma unroll
@@ -313,16 +359,60 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
                 }
     };
 
+    if constexpr (P == 0) {
 #pragma unroll
-    for (int i = 0; i < U; ++i) issue(i, 0);
+        for (int i = 0; i < U; ++i) issue(i, 0);
+    }
+    // (P: one set of inputs, whose pieces are read again as soon as their last product is out: three wavefronts' registers hold no second one)
+    auto products_of = [&](v16f (&c)[MB][NB], v16f (&cl)[MB][NB], const v4u (&a)[MB][3], int qa, int qb) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                v16f &d = qa + qb == 0 ? c[m][j] : cl[m][j];
+                d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a[m][qa]), __builtin_bit_cast(v8bf, Bq[0][j][qb]), d, 0, 0, 0);
+            }
+    };
+
 #pragma unroll
     for (int r = 0; r < R - 1; ++r) aload(A[r], r);
 #pragma unroll
-    for (int i = 0; i < U; ++i) commit(i, lds);
+    for (int i = 0; i < U0; ++i)
+        if (i * T0 < units) commit(i, lds);
     barrier();
     int ks = 0;                                       // my step
     char *cur = lds;
-    if constexpr (S != 0) {
+    if constexpr (P > 0) {
+        for (int ch = 0; ch < g.nchunk; ++ch) {
+#pragma unroll
+            for (int q = 2; q >= 0; --q) bread(cur, 0, q);
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                aload(A[(s + R - 1) % R], ks + s + R - 1);
+                __builtin_amdgcn_sched_barrier(0);
+                products_of(acc[0], lo[0], A[s % R], 0, 2);
+                __builtin_amdgcn_sched_barrier(0);
+                if (s + 1 < S) bread(cur, s + 1, 2);
+                __builtin_amdgcn_sched_barrier(0);
+                products_of(acc[0], lo[0], A[s % R], 1, 1);
+                products_of(acc[0], lo[0], A[s % R], 0, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                if (s + 1 < S) bread(cur, s + 1, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                products_of(acc[0], lo[0], A[s % R], 2, 0);
+                products_of(acc[0], lo[0], A[s % R], 1, 0);
+                products_of(acc[0], lo[0], A[s % R], 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (s + 1 < S) bread(cur, s + 1, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            ks += S;
+            if (ch + 1 < g.nchunk) {
+                cur = cur == lds ? lds + g.bufs : lds;
+                barrier();
+            }
+        }
+    } else if constexpr (S != 0) {
         // a chunk: on entry the weights of its first R - 1 steps are in slots 0 .. R - 2, on exit those of the next
         auto chunk = [&](auto more, int ch) {
             char *nxt = cur == lds ? lds + g.bufs : lds;
@@ -331,16 +421,17 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
             for (int s = 0; s < S; ++s) {
                 aload(A[(s + R - 1) % R], ks + s + R - 1);
                 if (s + 1 < S) bload(Bq[(s + 1) & 1], cur, s + 1);
-                if constexpr (more.value) {
+                if constexpr (more.value && P == 0) {
 #pragma unroll
                     for (int i = 0; i < U; ++i)
                         if (i * (S / 2) / U == s) issue(i, ch + 1);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                if constexpr (more.value) {
+                if constexpr (more.value && P == 0) {
 #pragma unroll
                     for (int i = 0; i < U; ++i)
-                        if (S - U + i == s || (S < U && s == S - 1)) commit(i, nxt);
+                        if (S - U + i == s || (S < U && s == S - 1))
+                            if (i * T < units) commit(i, nxt);
                 }
                 constexpr bool kPh = NPH > 1;
                 products(acc[kPh ? kPhase9[s % 9] : 0], lo[kPh ? kPhase9[s % 9] : 0], A[s % R], Bq[s & 1]);
@@ -357,7 +448,7 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
     } else {
         for (int ch = 0; ch < g.nchunk; ++ch) {
             const bool more = ch + 1 < g.nchunk;
-            if (more) {
+            if (more && P == 0) {
 #pragma unroll
                 for (int i = 0; i < U; ++i) issue(i, ch + 1);
             }
@@ -404,8 +495,11 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
             }
             if (more) {
                 cur = cur == lds ? lds + g.bufs : lds;
+                if constexpr (P == 0) {
 #pragma unroll
-                for (int i = 0; i < U; ++i) commit(i, cur);
+                    for (int i = 0; i < U; ++i)
+                        if (i * T < units) commit(i, cur);
+                }
                 barrier();
             }
         }
@@ -484,7 +578,14 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
     }
 }
 
-struct Cfg { int mb, nb, wm, wn, wk, u, nph, wpe; };
+struct Cfg {
+    int mb, nb, wm, wn, wk, u, nph, wpe;
+    // Wavefronts that only stage: one per SIMD beside two that multiply (in chunks of straight-line code).  Loads come back in order, so a
+    // wavefront that does both waits at a weight for the input that it asked for before, and its splitting stands between its products: a chunk of
+    // [32,256,14,14] -> 256 takes 9.7 k cycles without them and 8.0 k with them (6.9 k of products).  Workgroups of four multiplying wavefronts have none: with
+    // six wavefronts only one workgroup finds room on a compute unit ([32,128,56,56] -> 128 at stride 2 60 us for 56).
+    constexpr int stagers(int S) const { return nph == 1 && wm * wn * wk == 8 && (S == 6 || S == 8 || S == 9 || S == 12) ? 4 : 0; }
+};
 // wavefront block x wavefronts x K split; staged units per thread; phases; wavefronts per SIMD
 constexpr Cfg kCfg[] = {
     {2, 2, 2, 2, 1, 3, 1, 1},     // 0: 128 x 128
@@ -501,20 +602,25 @@ constexpr Cfg kCfg[] = {
     {1, 1, 2, 2, 1, 4, 4, 2},     // 11:  64 x 64 x 4
     {1, 1, 2, 2, 2, 3, 4, 2},     // 12:  64 x 64 x 4, two
     {1, 1, 1, 2, 2, 4, 4, 2},     // 13:  32 x 64 x 4, two wavefronts per block
+    {1, 2, 4, 2, 1, 3, 1, 2},     // 14: 128 x 128, eight wavefronts
+    {1, 2, 2, 4, 1, 3, 1, 2},     // 15:  64 x 256, eight
+    {1, 2, 4, 1, 2, 3, 1, 2},     // 16: 128 x 64, two wavefronts per block
 };
+constexpr int kLargeCfg = 14;
 constexpr int kNumCfg = sizeof(kCfg) / sizeof(kCfg[0]);
 
 template <int I, int S>
 hipError_t launch_steps(const float *x, const v4u *ws, float *y, const SplitGeom &g, int grid, size_t lds, hipStream_t s)
 {
     constexpr Cfg c = kCfg[I];
-    auto k = conv_split_kernel<c.mb, c.nb, c.wm, c.wn, c.wk, c.u, c.nph, c.wpe, S>;
+    constexpr int P = c.stagers(S), U = P ? c.u * c.wm * c.wn * c.wk / P : c.u;
+    auto k = conv_split_kernel<c.mb, c.nb, c.wm, c.wn, c.wk, U, c.nph, P ? 3 : c.wpe, P, S>;
     if (lds > 64 * 1024) {
         static std::atomic<uint64_t> raised{0};
         const hipError_t e = raise_lds((const void *)k, 160 * 1024, raised);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * c.wm * c.wn * c.wk), lds, s, x, ws, y, g);
+    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * (c.wm * c.wn * c.wk + P)), lds, s, x, ws, y, g);
     return hipGetLastError();
 }
 
@@ -629,6 +735,17 @@ bool plan(const SplitGeom &g, const Cfg &c, int Wo, int SW, int cus, Tiling *bes
             const double shared = (m > l ? m : l) + 0.625 * stage;
             const double alone = 0.958 * mfma + 0.516 * wld + stage + 6979 + (c.wk > 1 ? 466 * c.mb * c.nb * c.nph : 0);
             const double n = (double)tiles * h.cot / cus;
+            if (c.stagers(h.S)) {
+                // one workgroup per compute unit; a chunk takes its products or its staging (1350 cycles per unit of a staging thread), whichever is longer
+                const double prod = 1.157 * mfma / h.nchunk, put = 1350.0 * ((2 * nc * h.PS + 255) / 256);
+                const double t = 10000 + __builtin_ceil(n) * (h.nchunk * (prod > put ? prod : put) + 16000 + (c.wk > 1 ? 466 * c.mb * c.nb : 0));
+                if (!found || t < best->cost) {
+                    found = true;
+                    h.cost = t;
+                    *best = h;
+                }
+                continue;
+            }
             const double full = __builtin_floor(n / res), rem = n - full * res;
             double t = full * (res * shared > alone ? res * shared : alone);
             if (rem > 0) t += __builtin_ceil(rem) * shared > alone ? __builtin_ceil(rem) * shared : alone;
@@ -707,6 +824,8 @@ hipError_t launch_conv_split(const float *x, const float *wgt, float *y, int64_t
     const int force = forced ? g_opt.conv2d_variant - 100 : -1;       // A/B and tests: this configuration
     for (int i = 0; i < kNumCfg; ++i) {
         if ((kCfg[i].nph > 1) != (ph != nullptr) || (force >= 0 && force < kNumCfg && force != i)) continue;
+        // (a tile each for a third of the compute units: below that the largest tiles never win, and planning them is host time of every call)
+        if (i >= kLargeCfg && force < 0 && 3.0 * N * Ho * Wo * Cout < (double)cus * (1024 * kCfg[i].mb * kCfg[i].nb * kCfg[i].wm * kCfg[i].wn)) continue;
         Tiling h;
         if (!plan(g, kCfg[i], (int)Wo, SW, cus, &h)) continue;
         // a tile's images, and a wavefront's weights, within 32-bit offsets
@@ -740,8 +859,8 @@ hipError_t launch_conv_split(const float *x, const float *wgt, float *y, int64_t
 #define SWS_CFG(I) case I: return launch_cfg<I>(x, (const v4u *)ws.p, y, g, grid, (size_t)b.need, s)
     switch (bi) {
         SWS_CFG(0); SWS_CFG(1); SWS_CFG(2); SWS_CFG(3); SWS_CFG(4); SWS_CFG(5); SWS_CFG(6); SWS_CFG(7); SWS_CFG(8); SWS_CFG(9);
-        SWS_CFG(10); SWS_CFG(11); SWS_CFG(12);
-    default: return launch_cfg<13>(x, (const v4u *)ws.p, y, g, grid, (size_t)b.need, s);
+        SWS_CFG(10); SWS_CFG(11); SWS_CFG(12); SWS_CFG(13); SWS_CFG(14); SWS_CFG(15);
+    default: return launch_cfg<16>(x, (const v4u *)ws.p, y, g, grid, (size_t)b.need, s);
     }
 #undef SWS_CFG
 }
