@@ -23,7 +23,7 @@
 // is cut by the large ones every time (a bias: 6.8e-7 on [32,64,56,56] -> 64, 3 x 3).  So the leading products and the
 // other five go to accumulators of their own.  Up to three taps: per tile from zero, added to the run's sum at its end.  Four to eight: per 16 positions
 // from zero.  Nine: the leading ones on the run's sum, the others per 16 positions (registers).  Layers whose kernel without a workspace is a
-// split-operand one too (FAST, five and nine taps): all six on the run's sum, still more exact than that kernel.  Error of gw against
+// split-operand one too (FAST, five and nine taps): all six on the run's sum, still more exact than that kernel (but not in conv_gw_staged_kernel).  Error of gw against
 // 64 bits, fp32 kernels / all six on the run's sum / now: [1,168,84,84] -> 200, 5 x 5 1.6e-7 / 3.3e-7 / 1.6e-7, [16,500,28,28] -> 500,
 // 3 x 3 1.7e-7 / 6.1e-7 / 1.4e-7, [32,61,14,14] -> 32 1.45e-7 / 2.1e-7 / 1.1e-7, [16,24,5574] -> 32, k = 1 3.7e-7 / 6.2e-7 / 1.2e-7.
 // Operands of one tap at a time, a piece of the next read as soon as the last product with the present one is out: with two sets the nine-tap
@@ -34,10 +34,12 @@
 // workgroup, take 27 us on 64 x 64 channels, 3 x 3).
 //
 // Measured, us, this kernel with its second pass / the kernels without a workspace: [17,128,23,14] -> 104, 5 x 5 55 / 313,
-// [1,96,65,65] -> 484, 3 x 3 49 / 208, [32,256,14,14] -> 256, 3 x 3 65 / 87, [32,64,56,56] -> 64 69 / 74, [16,64,4096] -> 64, k = 3
+// [1,96,65,65] -> 484, 3 x 3 49 / 208, [32,256,14,14] -> 256, 3 x 3 56 / 87, [32,64,56,56] -> 64 53 / 74, [16,64,4096] -> 64, k = 3
 // 28 / 31.  Two LDS buffers with tiles of 64 positions, one wavefront of a SIMD splitting while the other multiplies, came out even at nine
 // taps and behind at one (174 against 127 us on [19,96,87,87] -> 256): not taken.
 #include "sws_internal.h"
+
+#include <type_traits>
 
 namespace sws {
 
@@ -59,7 +61,8 @@ struct GwTile {
     int PS;                                           // positions per staged plane of x, = 12 mod 16: the octets' planes
                                                       // then start 16 banks apart, and a transposing read of four of them meets each bank twice
     int ksteps, per, nsplit, cob, cib, ng;            // groups of 16 positions per tile; tiles per workgroup, runs; channel blocks, tap groups
-    float inv_TW, inv_Ho, inv_LPI, inv_LW, inv_CW, inv_PS;
+    int lines, nq, group, rows;                             // conv_gw_staged_kernel: lines of x per tile, groups of four columns of a line, rows of a group, of a run (0: not its)
+    float inv_TW, inv_Ho, inv_LPI, inv_LW, inv_CW, inv_PS, inv_nq, inv_lines;
     short gdh[kMaxGroups], gdw[kMaxGroups];           // tap group: row and column of its first tap, relative to the position
     unsigned char gt0[kMaxGroups], gnt[kMaxGroups];   // first tap, taps
     unsigned short tapoff[kMaxTaps];                  // tap -> staged positions from a position's base
@@ -257,9 +260,9 @@ void conv_gw_tile_kernel(const float *__restrict__ x, const float *__restrict__ 
     }
 
     // ---- the wavefronts of a block add up through LDS, three taps at a time; then to the workspace:
-    //      ws[split][block][tap][wm, wn][register][lane]
+    //      ws[split][block][tap][wm, wn][register / 4][lane][register % 4]
     constexpr int BLK = WM * WN, ROWS = TB < 3 ? TB : 3;
-    float *const out = ws + ((int64_t)split * nblk + blk) * (TB * BLK * 1024) + (wave % BLK) * 1024 + lane;
+    v4f *const out = (v4f *)ws + ((int64_t)split * nblk + blk) * (TB * BLK * 256) + (wave % BLK) * 256 + lane;
     v4f *const red = (v4f *)lds + lane;
 #pragma unroll
     for (int q = 0; q < TB; q += 3) {
@@ -279,14 +282,293 @@ void conv_gw_tile_kernel(const float *__restrict__ x, const float *__restrict__ 
                 for (int v = 0; v < 4; ++v) {
                     v4f r = {acc[t][4 * v], acc[t][4 * v + 1], acc[t][4 * v + 2], acc[t][4 * v + 3]};
                     for (int k = 0; k < WK - 1; ++k) r += red[((k * BLK + wave) * (4 * ROWS) + (t - q) * 4 + v) * 64];
-                    if (t < nt) {
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) out[t * (BLK * 1024) + (4 * v + u) * 64] = r[u];
-                    }
+                    if (t < nt) out[t * (BLK * 256) + v * 64] = r;
                 }
         }
         barrier();
     }
+}
+
+// The same for 3 x 3 at stride 1 (nine taps, 32 WM x 32 channels, whole blocks) with wavefronts that only stage: four of them (one per SIMD) load,
+// split and write tiles, eight multiply.  A multiplying wavefront holds one block of 32 x 32 channels, five or four of the taps (two wavefronts of a SIMD:
+// one of each) and every WK-th group of 16 positions: 80 accumulators instead of 144, so that three wavefronts per SIMD find registers.  x has two
+// buffers; gy has one, which is free as soon as everybody has read its last group's operand, and is written while that group is multiplied.
+//   What bounds the kernel above is that all its wavefronts stage at once (4.5 k cycles of a tile's 14 k in addresses and loads, 3 k in splitting and writing, 6.9 k
+// of products) while none multiplies.  One-dword loads alone would keep the staging wavefronts longer than the products take: a load occupies the address unit
+// for 16 cycles whatever its width.  So a thread stages eight channels of four consecutive columns (x) or two consecutive positions (gy) by eight 16- or 8-byte loads.
+//   Runs are rows, not whole tiles, so that the runs of a round end together (seven tiles where 6.2 are due, before), and go through the strips of a group of
+// images before the next one: strips share cache lines, and runs side by side an XCD's cache (without it [32,64,56,56] -> 64 165 us for a
+// training step, with it 156).
+//   Second pass included, us, kernel above / here: [32,256,14,14] -> 256 65.0 / 56.4, [32,64,56,56] -> 64 65.6 / 52.6, [32,128,28,28] -> 128 60.6 / 51.3,
+// [64,160,12,12] -> 160 50.0 / 41.4, [4,256,56,56] -> 128 64.5 / 54.0.  The bound is now the products, 2.1 k cycles per 16 positions and SIMD of which 1.7 k are theirs,
+// and what a run has besides: its first tile's staging and the sums at its end, a fifth of these layers.
+// Sums: the leading products on the run's sum, the other five per 16 positions from zero (as the kernel above without FAST): error of
+// gw against 64 bits on the two layers of 56 x 56 and 14 x 14 3.4e-7 and 2.4e-7 above, 1.9e-7 here.
+template <int WM>
+__global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3)))
+void conv_gw_staged_kernel(const float *__restrict__ x, const float *__restrict__ gy, float *__restrict__ ws, GwTile g)
+{
+    fetch_arguments<24 + sizeof(GwTile)>();
+    constexpr int WK = 4 / WM, OG = 4 * WM, OX = 4, T = 256, TB = 9, TW = 5;      // octets of channels; staging threads; TW: taps of a wavefront
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int pieceX = g.PS * 16, octX = 3 * pieceX, bufX = OX * octX;
+    char *const G = lds, *const X = lds + OG * kOctG;
+    int *const tab = (int *)(X + 2 * bufX);           // position -> byte offset of its base in a plane of x; two of them
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wm = wave % WM, wk = wave / WM % WK, th = wave >> 2;
+
+    const int Gx = (int)gridDim.x;                    // a multiple of 8: each XCD takes a contiguous run
+    const int id = (int)(blockIdx.x & 7) * (Gx >> 3) + (int)(blockIdx.x >> 3);
+    const int nblk = g.cob * g.cib * g.ng;
+    if (id >= g.nsplit * nblk) return;
+    const int split = id / nblk, blk = id - split * nblk;
+    const int grp = blk % g.ng, cb = blk / g.ng, cob = cb / g.cib, cib = cb - cob * g.cib;
+    const int nt = g.gnt[grp], t0 = g.gt0[grp], dh = g.gdh[grp], dw = g.gdw[grp];
+    const int co0 = cob * (32 * WM), ci0 = cib * 32;
+    // A run is g.rows rows in the order (group of whole images, strip, row); its tiles have rpt of them, the last one of a run and of a group what is left.
+    struct Place { int at, R, gs, ge, strip; };       // rows before it; its row; first row and last + 1 of its group; its strip
+    const int begin = split * g.rows, all = g.nstrips * g.NR, end = begin + g.rows < all ? begin + g.rows : all;
+    Place now;
+    {
+        const int full = g.nstrips * g.group, grp0 = begin / full, gs = grp0 * g.group, ge = gs + g.group < g.NR ? gs + g.group : g.NR;
+        const int rest = begin - grp0 * full, strip = rest / (ge - gs);
+        now = {begin, gs + rest - strip * (ge - gs), gs, ge, strip};
+    }
+    auto rows_of = [&](const Place &p) {
+        const int r = end - p.at < g.rpt ? end - p.at : g.rpt;
+        return r < p.ge - p.R ? r : p.ge - p.R;
+    };
+    auto after_of = [&](Place p) {
+        const int rows = rows_of(p);
+        p.at += rows;
+        p.R += rows;
+        if (p.R == p.ge) {
+            p.R = p.gs;
+            if (++p.strip == g.nstrips) {
+                p.R = p.gs = p.ge;
+                p.ge = p.ge + g.group < g.NR ? p.ge + g.group : g.NR;
+                p.strip = 0;
+            }
+        }
+        return p;
+    };
+    auto barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    if (wave >= 8) {
+        const int tid = (int)threadIdx.x - 512;
+        struct Tile { int n0, oh0, cb0, rows; };      // its first row's image and row there, first column, rows
+        auto tile_of = [&](const Place &p) {
+            const int n0 = p.R / g.Ho;
+            return Tile{n0, p.R - n0 * g.Ho, p.strip * g.TW, rows_of(p)};
+        };
+        struct Cols { int clo, lo, hi; };             // first staged column of x; first and last + 1 that exist
+        auto cols = [&](const Tile &t) {
+            Cols c;
+            c.clo = t.cb0 + dw;
+            c.lo = c.clo > 0 ? c.clo : 0;
+            c.hi = c.clo + g.LW < g.W ? c.clo + g.LW : g.W;
+            if (c.hi <= c.lo) c.lo = c.hi = c.clo;    // (all of them padding)
+            return c;
+        };
+        // my unit of x: four columns of a line; of gy: pairs of positions 2 (tid % 64), octets tid / 64 and four further
+        const int xrow = fdiv(tid, g.inv_nq), q4 = 4 * (tid - xrow * g.nq), xoct = fdiv(xrow, g.inv_lines), ln = xrow - xoct * g.lines;
+        const int xat = (ci0 + 8 * xoct) * g.HW + q4, xdst = xoct * octX + (ln * g.LW + q4) * 16;
+        const int gpos = 2 * (tid & 63), goct = tid >> 6, gR = fdiv(gpos, g.inv_TW), gc = gpos - gR * g.TW;
+        v4f xr[8];
+        v2f gr[WM][8];
+        auto issue_x = [&](const Tile &t) {
+            const int64_t xl_ = 4 * (int64_t)(g.N - t.n0) * g.Cin * g.HW;
+            const __amdgpu_buffer_rsrc_t xs = rsrc(x + (int64_t)t.n0 * g.Cin * g.HW, xl_ < 0x7fffffff ? (unsigned)xl_ : 0x7fffffffu);
+            const Cols k = cols(t);
+            const int l = t.oh0 + ln, dn = fdiv(l, g.inv_LPI), row = l - dn * g.LPI + dh;
+            const bool ok = xoct < OX && t.n0 + dn < g.N && (unsigned)row < (unsigned)g.H;
+            const unsigned at = ok ? 4u * (unsigned)(dn * g.Cin * g.HW + row * g.W + k.lo + xat) : kNowhere;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) xr[e] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(xs, at, 4 * e * g.HW, 0));
+        };
+        auto issue_g = [&](const Tile &t) {
+            const int64_t gl_ = 4 * (int64_t)(g.N - t.n0) * g.Cout * g.HoWo;
+            const __amdgpu_buffer_rsrc_t gs = rsrc(gy + (int64_t)t.n0 * g.Cout * g.HoWo, gl_ < 0x7fffffff ? (unsigned)gl_ : 0x7fffffffu);
+            const int r = t.oh0 + gR, dn = fdiv(r, g.inv_Ho), oh = r - dn * g.Ho;
+            const bool ok = gR < t.rows && t.cb0 + gc < g.Wo;      // (even columns of rows of even length: both positions or none)
+#pragma unroll
+            for (int i = 0; i < WM; ++i) {
+                const unsigned at = ok ? 4u * (unsigned)((dn * g.Cout + co0 + 8 * (goct + 4 * i)) * g.HoWo + oh * g.Wo + t.cb0 + gc) : kNowhere;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) gr[i][e] = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(gs, at, 4 * e * g.HoWo, 0));
+            }
+        };
+        // (the columns that a row lacks on either side are zeros)
+        auto commit_x = [&](const Tile &t, char *Xb) {
+            const Cols k = cols(t);
+            const int left = xoct < OX ? k.hi - k.lo - q4 : 0, front = k.lo - k.clo;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float v[8] = {xr[0][c], xr[1][c], xr[2][c], xr[3][c], xr[4][c], xr[5][c], xr[6][c], xr[7][c]};
+                if (c < left) put_unit(Xb + xdst + (front + c) * 16, pieceX, v);
+            }
+            const int pads = g.LW - (k.hi - k.lo);
+            if (pads > 0) {
+                const float inv = 1.0f / (float)pads;
+                for (int u = tid; u < pads * OX * g.lines; u += T) {
+                    const int r = fdiv(u, inv), j = u - r * pads, o = fdiv(r, g.inv_lines);
+                    char *const d = Xb + o * octX + ((r - o * g.lines) * g.LW + (j < front ? j : j + k.hi - k.lo)) * 16;
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) *(v4u *)(d + p * pieceX) = (v4u){0, 0, 0, 0};
+                }
+            }
+        };
+        auto commit_g = [&](const Tile &t, int *tb) {
+            if (tid < kBN) {
+                const int R = fdiv(tid, g.inv_TW), c = tid - R * g.TW, r = t.oh0 + R, dn = fdiv(r, g.inv_Ho), oh = r - dn * g.Ho;
+                tb[tid] = R < g.rpt ? ((dn * g.LPI + oh - t.oh0) * g.LW + c) * 16 : 0;
+            }
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const float v[8] = {gr[i][0][c], gr[i][1][c], gr[i][2][c], gr[i][3][c], gr[i][4][c], gr[i][5][c], gr[i][6][c], gr[i][7][c]};
+                    put_unit(G + (goct + 4 * i) * kOctG + (gpos + c) * 16, kPG * 16, v);
+                }
+        };
+        // Between two tiles stands only the splitting of gy; its loads go out behind the barrier, those of x a tile further ahead
+        Tile tile = tile_of(now);
+        issue_x(tile);
+        issue_g(tile);
+        commit_x(tile, X);
+        commit_g(tile, tab);
+        Place next = after_of(now);
+        if (next.at < end) issue_x(tile = tile_of(next));
+        barrier();                                    // the first tile is there
+        int cur = 0;
+        for (bool more = next.at < end;; ) {
+            cur ^= 1;
+            Tile ahead = tile;
+            if (more) {
+                issue_g(tile);
+                commit_x(tile, X + cur * bufX);
+                next = after_of(next);
+                if (next.at < end) issue_x(ahead = tile_of(next));
+            }
+            barrier();                                // the tile's operands of gy have been read
+            if (!more) break;
+            commit_g(tile, tab + cur * kBN);
+            barrier();                                // the next tile is there, this one has been multiplied
+            tile = ahead;
+            more = next.at < end;
+        }
+        barrier();
+        barrier();
+        return;
+    }
+
+    // ---- operand reads: lane 16 b + m points at octet 2 (b & 1) + (m & 3) / 2, half (m & 1), position 8 (b >> 1) + m / 4
+    const int b = lane >> 4, m = lane & 15;
+    const int oct = 2 * (b & 1) + ((m & 3) >> 1), pj = 8 * (b >> 1) + (m >> 2);
+    const char *const Ga = G + (4 * wm + oct) * kOctG + (m & 1) * 8 + pj * 16;
+    const char *const Xa = X + oct * octX + (m & 1) * 8;
+    int off[TW];                                      // my taps' offsets (the fifth of the second wavefront: its fourth again, not stored)
+#pragma unroll
+    for (int j = 0; j < TW; ++j) {
+        const int t = TW * th + j, tt = t < nt && t < TB ? t : nt - 1;
+        off[j] = __builtin_amdgcn_readfirstlane((int)g.tapoff[t0 + tt]) * 16;
+    }
+    v16f acc[TW];
+#pragma unroll
+    for (int t = 0; t < TW; ++t) acc[t] = (v16f){0.0f};
+
+    auto run = [&](auto mine) {
+        constexpr int NT = mine.value;                // taps
+        barrier();                                    // the first tile is there
+        int cur = 0;
+        Place p = now;
+        while (p.at < end) {
+            const int ksteps = (rows_of(p) * g.TW + 15) >> 4;
+            p = after_of(p);
+            const char *const Xc = Xa + cur * bufX;
+            const int *const tc = tab + cur * kBN;
+            auto xread = [&](int p0, int p1, int t, int q) { return tr8(Xc + p0 + off[t] + q * pieceX, Xc + p1 + off[t] + q * pieceX); };
+            auto gread = [&](v8bf (&a)[3], int s) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) a[q] = tr8(Ga + s * 256 + q * (kPG * 16), Ga + s * 256 + 64 + q * (kPG * 16));
+            };
+            v8bf a[3], an[3], b2, b1, b0;
+            int p0 = 0, p1 = 0;
+            if (wk < ksteps) {
+                gread(an, wk);
+                p0 = tc[16 * wk + pj];
+                p1 = tc[16 * wk + pj + 4];
+                b2 = xread(p0, p1, 0, 2);
+                b1 = xread(p0, p1, 0, 1);
+                b0 = xread(p0, p1, 0, 0);
+            } else {
+                barrier();
+            }
+            for (int s = wk; s < ksteps; s += WK) { // sixteen positions
+                const bool last = s + WK >= ksteps;
+                const int c0 = p0, c1 = p1, sn = last ? s : s + WK;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) a[q] = an[q];
+                if (last) barrier();                  // everybody has its last operands of gy
+                else gread(an, sn);
+                p0 = tc[16 * sn + pj];
+                p1 = tc[16 * sn + pj + 4];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    // (a piece of the next tap is read as soon as this tap's last product of it is out)
+                    const int n0 = t + 1 < NT ? c0 : p0, n1 = t + 1 < NT ? c1 : p1, tn = t + 1 < NT ? t + 1 : 0;
+                    v16f l = {0.0f};
+                    __builtin_amdgcn_sched_barrier(0);
+                    l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b2, l, 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    b2 = xread(n0, n1, tn, 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                    l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b1, l, 0, 0, 0);
+                    l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b1, l, 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    b1 = xread(n0, n1, tn, 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b0, acc[t], 0, 0, 0);
+                    l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b0, l, 0, 0, 0);
+                    l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b0, l, 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    b0 = xread(n0, n1, tn, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[t] += l;
+                }
+            }
+            cur ^= 1;
+            if (p.at < end) barrier();           // the next tile is there, this one has been multiplied
+        }
+    };
+    if (th == 0) run(std::integral_constant<int, TW>{});
+    else run(std::integral_constant<int, TB - TW>{});
+
+    // ---- the WK wavefronts of a block's taps add up through LDS, 4 / WK of four groups of registers each; then to the workspace, as above
+    v4f *const red = (v4f *)lds + lane;
+    barrier();
+#pragma unroll
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (v % WK != wk) red[(wave * (4 * TW) + t * 4 + v) * 64] = (v4f){acc[t][4 * v], acc[t][4 * v + 1], acc[t][4 * v + 2], acc[t][4 * v + 3]};
+    barrier();
+    v4f *const out = (v4f *)ws + ((int64_t)split * nblk + blk) * (TB * WM * 256) + wm * 256 + lane;
+#pragma unroll
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (v % WK != wk) continue;
+            v4f r = {acc[t][4 * v], acc[t][4 * v + 1], acc[t][4 * v + 2], acc[t][4 * v + 3]};
+#pragma unroll
+            for (int k = 1; k < WK; ++k) {
+                const int other = 4 * th + wm + WM * ((wk + k) % WK);
+                r += red[(other * (4 * TW) + t * 4 + v) * 64];
+            }
+            const int tt = TW * th + t;
+            if (tt < nt && (th == 0 || t < TB - TW)) out[tt * (WM * 256) + v * 64] = r;
+        }
 }
 
 // The channel that a slot of a block holds; -1: none, or one that another slot holds (an octet of channels that reached beyond the last
@@ -297,9 +579,8 @@ __device__ __forceinline__ int slot_channel(int slot, int n)
     return o < n && c >= o && c < n ? c : -1;
 }
 
-// gw from the partial blocks: a workgroup adds 64 lanes of one (block, tap, wavefront, register), its four wavefronts
-// every fourth run; register v of lane (l32, half) is output channel 8*(v/4) + 4*half + v%4, input channel l32 of the
-// block of 32.
+// gw from the partial blocks: a workgroup adds 64 elements of one (block, tap, wavefront), its four wavefronts
+// every fourth run; element 256 q + 4 (32 half + l32) + r of a block of 32 x 32 is output channel 8 q + 4 half + r, input channel l32.
 __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
 {
     fetch_arguments<28 + sizeof(GwTile)>();
@@ -322,8 +603,9 @@ __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict_
     __syncthreads();
     if (wave != 0) return;
     const float sum = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
-    const int co = slot_channel(cob * (32 * WM) + w % WM * 32 + 8 * (v / 4) + 4 * (lane >> 5) + v % 4, g.Cout);
-    const int ci = slot_channel(cib * (32 * WN) + w / WM * 32 + (lane & 31), g.Cin);
+    const int from = 16 * (v & 3) + (lane >> 2);      // the lane that summed it
+    const int co = slot_channel(cob * (32 * WM) + w % WM * 32 + 8 * (v >> 2) + 4 * (from >> 5) + (lane & 3), g.Cout);
+    const int ci = slot_channel(cib * (32 * WN) + w / WM * 32 + (from & 31), g.Cin);
     if (co >= 0 && ci >= 0) gw[((int64_t)co * g.Cin + ci) * g.KT + g.gt0[grp] + t] = sum;
 }
 
@@ -358,25 +640,47 @@ __global__ __launch_bounds__(576) void gw_reduce_few_kernel(const float *__restr
     const float inv_nt = 1.0f / (float)nt;
     for (int i = threadIdx.x; i < 256 * nt; i += 64 * TB) {
         const int e = fdiv(i, inv_nt), tt = i - e * nt, c8 = e >> 5, l32 = e & 31;
-        const float sum = ((const float *)part[tt])[(c8 & 3) * 64 + (c8 >> 2) * 32 + l32];        // register 4 qr + c8 % 4, lane
+        const float sum = ((const float *)part[tt])[((c8 >> 2) * 32 + l32) * 4 + (c8 & 3)];
         const int co = slot_channel(cob * (32 * WM) + w % WM * 32 + 8 * qr + c8, g.Cout);
         const int ci = slot_channel(cib * (32 * WN) + w / WM * 32 + l32, g.Cin);
         if (co >= 0 && ci >= 0) gw[((int64_t)co * g.Cin + ci) * g.KT + g.gt0[grp] + tt] = sum;
     }
 }
 
-template <int TB, int WM, int WN, bool FAST, int UX = 4>
-hipError_t launch_gw1(const float *x, const float *gy, float *gw, float *ws, const GwTile &g, size_t lds, hipStream_t s)
+template <int WM>
+hipError_t launch_staged(const float *x, const float *gy, float *ws, const GwTile &g, size_t lds, hipStream_t s)
 {
-    const int nblk = g.cob * g.cib * g.ng;
+    if (lds > 64 * 1024) {
+        static std::atomic<uint64_t> raised{0};
+        const hipError_t e = raise_lds((const void *)conv_gw_staged_kernel<WM>, 160 * 1024, raised);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(conv_gw_staged_kernel<WM>, dim3((unsigned)xcd_grid((int64_t)g.nsplit * g.cob * g.cib * g.ng)), dim3(768), lds, s, x, gy, ws, g);
+    return hipGetLastError();
+}
+
+template <int TB, int WM, int WN, bool FAST, int UX>
+hipError_t launch_all(const float *x, const float *gy, float *ws, const GwTile &g, size_t lds, hipStream_t s)
+{
     if (lds > 64 * 1024) {
         static std::atomic<uint64_t> raised{0};
         const hipError_t e = raise_lds((const void *)conv_gw_tile_kernel<TB, WM, WN, UX, FAST>, 160 * 1024, raised);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((conv_gw_tile_kernel<TB, WM, WN, UX, FAST>), dim3((unsigned)xcd_grid((int64_t)g.nsplit * nblk)), dim3(kThreads), lds,
+    hipLaunchKernelGGL((conv_gw_tile_kernel<TB, WM, WN, UX, FAST>), dim3((unsigned)xcd_grid((int64_t)g.nsplit * g.cob * g.cib * g.ng)), dim3(kThreads), lds,
                        s, x, gy, ws, g);
-    const hipError_t e = hipGetLastError();
+    return hipGetLastError();
+}
+
+template <int TB, int WM, int WN, bool FAST, int UX = 4>
+hipError_t launch_gw1(const float *x, const float *gy, float *gw, float *ws, const GwTile &g, size_t lds, hipStream_t s)
+{
+    const int nblk = g.cob * g.cib * g.ng;
+    hipError_t e;
+    if constexpr (TB == 9 && WN == 1 && UX == 4 && FAST)
+        e = g.rows ? launch_staged<WM>(x, gy, ws, g, lds, s) : launch_all<TB, WM, WN, FAST, UX>(x, gy, ws, g, lds, s);
+    else
+        e = launch_all<TB, WM, WN, FAST, UX>(x, gy, ws, g, lds, s);
     if (e != hipSuccess) return e;
     if (g.nsplit <= kFewRuns)
         hipLaunchKernelGGL(gw_reduce_few_kernel, dim3((unsigned)(nblk * WM * WN * 4)), dim3(64 * TB), 0, s, ws, gw, g, TB, WM, WN);
@@ -448,6 +752,9 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
     g.LPI = (int)(Ho - 1) * g.ls + g.SH;
     const int SW = (q.taps - 1) * dil + 1, SWc = SW < sw ? SW : sw, cus = device_cus();
     g.ng = q.ng;
+    // Layers of conv_gw_staged_kernel: 3 x 3 at stride 1, channels in whole blocks, rows and strips of even length (pairs of positions lie side by side), one
+    // unit of x per staging thread.
+    const bool whole_blocks = kh == 3 && kw == 3 && sh == 1 && sw == 1 && Cin % 32 == 0 && Cout % 32 == 0 && Wo % 2 == 0;
     // Channel blocks of a workgroup, strip width, rows per tile and runs: the smallest estimated time of the longest run (products
     // on two wavefronts per SIMD, staging per unit, a run's end), in cycles.  (The second pass is in `end` as it was before
     // there were two of them: it weighs channel blocks against runs, and takes 3 - 14 us either way.)
@@ -465,7 +772,7 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
                 // (tiles start at multiples of rpt, so at most this far down an image: where rpt divides Ho no tile meets two)
                 int start = rpt, mod = g.Ho;
                 while (mod) { const int r = (int)((unsigned)start % (unsigned)mod); start = mod; mod = r; }
-                const int crossings = (int)((unsigned)(g.Ho - start + rpt - 1) / (unsigned)g.Ho);
+                const int crossings = (int)((unsigned)(g.Ho - start + rpt - 1) / (unsigned)g.Ho), period = start;
                 const int64_t lines = (int64_t)(rpt - 1) * g.ls + g.SH + crossings * (g.SH - g.ls);
                 if (lines * LW > 1024) continue;
                 const int64_t imgs = rpt / Ho + 2;    // a tile's images within 32-bit offsets
@@ -480,7 +787,10 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
                 if ((int64_t)tps * nstrips >= (1LL << 30)) continue;
                 const int tiles = tps * nstrips;
                 const int units = (4 * wn * PS + kThreads - 1) / kThreads + wm;
-                const double tile = steps * (double)q.tb * 6 * 32 * 2 * 1.2 + 1200 + 500.0 * units;
+                const int nq = ((LW < g.W ? LW : g.W) + 3) / 4;
+                const size_t two = (size_t)4 * 3 * 16 * (2 * PS + wm * kPG) + 2 * kBN * 4, sums = (size_t)8 * 4 * 5 * 1024;
+                const bool both = !exact && wn == 1 && whole_blocks && TW % 2 == 0 && 4 * lines * nq <= 256 && two <= 160 * 1024 &&
+                                    (int64_t)g.NR * nstrips < (1LL << 30);
                 // Runs per block of gw: a workgroup fills a compute unit (LDS), so as many as there are units, or twice as many,
                 // and never a few more: those would be a round of their own ([4,288,4658] -> 448, k = 1, 18 runs of 15 blocks: 132 us,
                 // 17 runs: 66).
@@ -495,21 +805,34 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
                     int64_t n = whole * cus / nblk;
                     if (n < least) n = least;
                     if (n > tiles) n = tiles;
-                    const int per = (int)((unsigned)(tiles + n - 1) / (unsigned)n), nsplit = (int)((unsigned)(tiles + per - 1) / per);
-                    const int64_t bytes = nblk * nsplit * q.tb * wm * wn * 4096;
-                    if (bytes > limit || nblk * nsplit >= (1LL << 30)) continue;
-                    const double rounds = (double)((nblk * nsplit + cus - 1) / cus);
-                    const double end = q.tb * wm * wn * (double)(nblk * nsplit);
-                    const double c = rounds * (per * tile + 4000 + 6.0 * end / 64);
-                    if (!found || c < cost) {
-                        found = true;
-                        cost = c;
-                        best->WM = wm; best->WN = wn;
-                        best->lds = stage > red ? stage : red;
-                        best->bytes = bytes;
-                        best->us = 6.9 + rounds * (per * (0.269 * steps * q.tb + 1.67 + 0.09 * units) + 0.75) + 0.0026 * end;
-                        g.TW = TW; g.nstrips = nstrips; g.CW = CW; g.LW = LW; g.rpt = rpt; g.PS = PS; g.tps = tps; g.tiles = tiles;
-                        g.ksteps = ksteps; g.per = per; g.nsplit = nsplit; g.cob = (int)cob; g.cib = (int)cib;
+                    const int per = (int)((unsigned)(tiles + n - 1) / (unsigned)n), few = (int)((unsigned)(tiles + per - 1) / per);
+                    // (A staged run costs its first tile's staging by half as many wavefronts and 160 KB of sums at its end, and saves the staging of every further
+                    // tile.  8000 cycles is on the safe side, long runs only: with 3500 [8,96,30,30] -> 160, four tiles a run, would come here too, 33 us -> 26.)
+                    for (int staged = 0; staged <= (int)both; ++staged) {
+                        // (a staged run is rows: the runs of a round end together)
+                        const int64_t all = (int64_t)g.NR * nstrips, rows = staged ? ((all + n - 1) / n + period - 1) / period * period : 0;
+                        const int nsplit = staged ? (int)((all + rows - 1) / rows) : few;
+                        // (runs of one image's strips side by side, i.e. in the same XCD's cache: a row's strips share cache lines)
+                        const int64_t group = nstrips == 1 || rows >= g.NR ? g.NR : rows < g.Ho ? g.Ho : (rows + g.Ho / 2) / g.Ho * g.Ho;
+                        const int64_t bytes = nblk * nsplit * q.tb * wm * wn * 4096;
+                        if (bytes > limit || nblk * nsplit >= (1LL << 30)) continue;
+                        const double rounds = (double)((nblk * nsplit + cus - 1) / cus);
+                        const double end = q.tb * wm * wn * (double)(nblk * nsplit);
+                        auto tile = [&](int rows) { return ((rows * TW + 15) / 16 + wk / 2 - 1) / (wk / 2) * (9 * 6 * 32 * 1.25) + 1500; };
+                        const double run = staged ? (double)(rows / rpt) * tile(rpt) + (rows % rpt ? tile((int)(rows % rpt)) : 0) + (group % rows ? 3000 : 0) + 8000
+                                                  : per * (steps * (double)q.tb * 6 * 32 * 2 * 1.2 + 1200 + 500.0 * units);
+                        const double c = rounds * (run + 4000 + 6.0 * end / 64);
+                        if (!found || c < cost) {
+                            found = true;
+                            cost = c;
+                            best->WM = wm; best->WN = wn;
+                            best->lds = staged ? (two > sums ? two : sums) : stage > red ? stage : red;
+                            best->bytes = bytes;
+                            best->us = 6.9 + rounds * (per * (0.269 * steps * q.tb + 1.67 + 0.09 * units) + 0.75) + 0.0026 * end;
+                            g.TW = TW; g.nstrips = nstrips; g.CW = CW; g.LW = LW; g.rpt = rpt; g.PS = PS; g.tps = tps; g.tiles = tiles;
+                            g.ksteps = ksteps; g.lines = (int)lines; g.nq = nq; g.rows = (int)rows; g.group = (int)group;
+                            g.per = per; g.nsplit = nsplit; g.cob = (int)cob; g.cib = (int)cib;
+                        }
                     }
                 }
             }
@@ -569,6 +892,7 @@ hipError_t launch_conv_gw_tile(const float *x, const float *gy, float *gw, const
     for (int t = g.KT; t < kMaxTaps; ++t) g.tapoff[t] = 0;
     g.inv_TW = 1.0f / g.TW; g.inv_Ho = 1.0f / g.Ho; g.inv_LPI = 1.0f / g.LPI; g.inv_LW = 1.0f / g.LW; g.inv_CW = 1.0f / g.CW;
     g.inv_PS = 1.0f / g.PS;
+    g.inv_nq = 1.0f / g.nq; g.inv_lines = 1.0f / g.lines;
     float *w = (float *)ws.p;
     *taken = true;
 #define SWS_GW_TB(T) case T: return launch_gw<T>(x, gy, gw, w, g, exact, WM, WN, lds, s)
