@@ -581,6 +581,8 @@ __device__ __forceinline__ int slot_channel(int slot, int n)
 
 // gw from the partial blocks: a workgroup adds 64 elements of one (block, tap, wavefront), its four wavefronts
 // every fourth run; element 256 q + 4 (32 half + l32) + r of a block of 32 x 32 is output channel 8 q + 4 half + r, input channel l32.
+// Bound by the way to memory and back, not by bytes: sixteen runs in flight a wavefront, 64 x 64 channels, 3 taps, 256 runs 5.0 us, four in flight 6.8;
+// 9 taps, 128 runs 6.4 either way.  Two elements a lane and eight wavefronts: 6.2 and 7.6.
 __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
 {
     fetch_arguments<28 + sizeof(GwTile)>();
@@ -592,14 +594,23 @@ __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict_
     if (t >= g.gnt[grp]) return;
     const int64_t step = (int64_t)nblk * (TB * BLK * 1024);
     const float *p = ws + (int64_t)blk * (TB * BLK * 1024) + t * (BLK * 1024) + w * 1024 + v * 64 + lane;
-    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    int k = wave;
-    for (; k + 12 < g.nsplit; k += 16) {
+    float s[16];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) s[u] += p[(k + 4 * u) * step];
+    for (int u = 0; u < 16; ++u) s[u] = 0.0f;
+    int k = wave;
+    for (; k + 60 < g.nsplit; k += 64) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) s[u] += p[(k + 4 * u) * step];
     }
-    for (; k < g.nsplit; k += 4) s[0] += p[k * step];
-    part[wave][lane] = (s[0] + s[1]) + (s[2] + s[3]);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        if (k + 4 * u < g.nsplit) s[u] += p[(k + 4 * u) * step];
+    }
+#pragma unroll
+    for (int m = 8; m >= 1; m >>= 1)
+#pragma unroll
+        for (int u = 0; u < m; ++u) s[u] += s[u + m];
+    part[wave][lane] = s[0];
     __syncthreads();
     if (wave != 0) return;
     const float sum = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
