@@ -581,13 +581,14 @@ __device__ __forceinline__ int slot_channel(int slot, int n)
 
 // gw from the partial blocks: a workgroup adds 64 elements of one (block, tap, wavefront), its four wavefronts
 // every fourth run; element 256 q + 4 (32 half + l32) + r of a block of 32 x 32 is output channel 8 q + 4 half + r, input channel l32.
-// Bound by the way to memory and back, not by bytes: sixteen runs in flight a wavefront, 64 x 64 channels, 3 taps, 256 runs 5.0 us, four in flight 6.8;
-// 9 taps, 128 runs 6.4 either way.  Two elements a lane and eight wavefronts: 6.2 and 7.6.
+// Bound by the way to memory and back: sixteen runs in flight a wavefront.  us, four in flight / sixteen: 64 x 64 channels, 3 taps, 256 runs 6.8 / 4.9,
+// 24 x 18, 3 taps 6.8 / 4.5, 256 x 32, 3 taps, 52 runs 4.2 / 4.1; 72 x 40, 5 x 5 (2400 workgroups) 6.8 / 5.8; 64 x 64, 9 taps, 128 runs 6.9 either
+// way.  Two elements a lane and eight wavefronts: 6.2 on the first.
 __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
 {
     fetch_arguments<28 + sizeof(GwTile)>();
     __shared__ float part[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int nblk = g.cob * g.cib * g.ng, BLK = WM * WN;
     const int v = blockIdx.x & 15, rest = (int)(blockIdx.x >> 4), w = rest % BLK, t = rest / BLK % TB, blk = rest / (BLK * TB);
     const int grp = blk % g.ng, cb = blk / g.ng, cob = cb / g.cib, cib = cb - cob * g.cib;
@@ -598,19 +599,25 @@ __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict_
 #pragma unroll
     for (int u = 0; u < 16; ++u) s[u] = 0.0f;
     int k = wave;
-    for (; k + 60 < g.nsplit; k += 64) {
+    auto batch = [&](auto many) {
+        constexpr int n = many.value;
 #pragma unroll
-        for (int u = 0; u < 16; ++u) s[u] += p[(k + 4 * u) * step];
+        for (int u = 0; u < n; ++u) s[u] += p[(k + 4 * u) * step];
+        k += 4 * n;
+    };
+    while (k + 60 < g.nsplit) batch(std::integral_constant<int, 16>{});
+    if (k + 28 < g.nsplit) batch(std::integral_constant<int, 8>{});
+    if (k + 12 < g.nsplit) batch(std::integral_constant<int, 4>{});
+    if (k < g.nsplit) {
+        float f[3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) f[u] = p[(k + 4 * u < g.nsplit ? k + 4 * u : k) * step];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) s[u] += k + 4 * u < g.nsplit ? f[u] : 0.0f;       // (beyond the last run: not counted)
     }
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        if (k + 4 * u < g.nsplit) s[u] += p[(k + 4 * u) * step];
-    }
-#pragma unroll
-    for (int m = 8; m >= 1; m >>= 1)
-#pragma unroll
-        for (int u = 0; u < m; ++u) s[u] += s[u + m];
-    part[wave][lane] = s[0];
+    for (int u = 4; u < 16; ++u) s[u & 3] += s[u];
+    part[wave][lane] = (s[0] + s[1]) + (s[2] + s[3]);
     __syncthreads();
     if (wave != 0) return;
     const float sum = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
