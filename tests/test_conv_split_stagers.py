@@ -1,7 +1,7 @@
 """Configurations of the split-operand convolution whose workgroups hold wavefronts that only stage (csrc/conv_split.hip)."""
 import pytest
 
-from tests.test_parity_conv_split import B, CASES, _check, _taken, lent  # noqa: F401
+from tests.test_parity_conv_split import B, CASES, _check, _taken, automatic, lent  # noqa: F401
 
 # 64 x 128 with a split contraction, and the three largest tiles
 STAGED = (3, 14, 15, 16)

@@ -6,7 +6,7 @@ import pytest
 import oracle
 from paper_2305_16513_amd import workloads
 from tests.parity_util import assert_bit_exact, assert_within_tol, to_gpu, to_host
-from tests.test_parity_conv_split import SPLIT_TOL, B, _guarded, _taken, lent  # noqa: F401
+from tests.test_parity_conv_split import SPLIT_TOL, B, _guarded, _taken, automatic, lent  # noqa: F401
 
 # n, cin, cout, h, w, pad: runs of rows as the planner cuts them (of 32 x 32 channels: the blocks of partial sums beside them)
 RUNS = {(3, 320, 128, 18, 60, 1): 12 * 40,            # two strips, runs of half an image
