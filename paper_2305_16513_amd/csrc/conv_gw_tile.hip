@@ -581,23 +581,27 @@ __device__ __forceinline__ int slot_channel(int slot, int n)
 
 // gw from the partial blocks: a workgroup adds 64 elements of one (block, tap, wavefront), its four wavefronts
 // every fourth run; element 256 q + 4 (32 half + l32) + r of a block of 32 x 32 is output channel 8 q + 4 half + r, input channel l32.
-// Bound by the way to memory and back: sixteen runs in flight a wavefront.  us, four in flight / sixteen: 64 x 64 channels, 3 taps, 256 runs 6.8 / 4.9,
-// 24 x 18, 3 taps 6.8 / 4.5, 256 x 32, 3 taps, 52 runs 4.2 / 4.1; 72 x 40, 5 x 5 (2400 workgroups) 6.8 / 5.8; 64 x 64, 9 taps, 128 runs 6.9 either
-// way.  Two elements a lane and eight wavefronts: 6.2 on the first.
+// DEEP: sixteen runs in flight a wavefront.  A second pass of few workgroups or of little to add waits for memory and back; a larger one is bound by bytes, and
+// four runs in flight with nothing in front of them get more of those.  (wave: not made uniform.  With a scalar loop the last runs wait for the others:
+// 128 x 416 channels, 9 taps, 18 runs 12.6 us / 16.3, and DEEP 14.7.)  us, four in flight / DEEP, both measured: 64 x 64, 3 taps, 256 runs 6.8 / 4.9, 24 x 18, 3 taps 6.8 / 4.5;
+// 192 x 57, 9 taps, 80 runs 7.4 / 8.2, 320 x 288, 3 taps, 9 runs 8.2 / 8.9, 241 x 352, 9 taps, 9 runs 18.7 / 21.5.  Two elements a lane and eight wavefronts:
+// 6.2 on the first.
+template <bool DEEP>
 __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
 {
-    fetch_arguments<28 + sizeof(GwTile)>();
+    if constexpr (DEEP) fetch_arguments<28 + sizeof(GwTile)>();
     __shared__ float part[4][64];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nblk = g.cob * g.cib * g.ng, BLK = WM * WN;
     const int v = blockIdx.x & 15, rest = (int)(blockIdx.x >> 4), w = rest % BLK, t = rest / BLK % TB, blk = rest / (BLK * TB);
     const int grp = blk % g.ng, cb = blk / g.ng, cob = cb / g.cib, cib = cb - cob * g.cib;
     if (t >= g.gnt[grp]) return;
     const int64_t step = (int64_t)nblk * (TB * BLK * 1024);
     const float *p = ws + (int64_t)blk * (TB * BLK * 1024) + t * (BLK * 1024) + w * 1024 + v * 64 + lane;
-    float s[16];
+    constexpr int M = DEEP ? 16 : 4;
+    float s[M];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) s[u] = 0.0f;
+    for (int u = 0; u < M; ++u) s[u] = 0.0f;
     int k = wave;
     auto batch = [&](auto many) {
         constexpr int n = many.value;
@@ -605,18 +609,23 @@ __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict_
         for (int u = 0; u < n; ++u) s[u] += p[(k + 4 * u) * step];
         k += 4 * n;
     };
-    while (k + 60 < g.nsplit) batch(std::integral_constant<int, 16>{});
-    if (k + 28 < g.nsplit) batch(std::integral_constant<int, 8>{});
-    if (k + 12 < g.nsplit) batch(std::integral_constant<int, 4>{});
-    if (k < g.nsplit) {
-        float f[3];
+    if constexpr (DEEP) {
+        while (k + 60 < g.nsplit) batch(std::integral_constant<int, 16>{});
+        if (k + 28 < g.nsplit) batch(std::integral_constant<int, 8>{});
+        if (k + 12 < g.nsplit) batch(std::integral_constant<int, 4>{});
+        if (k < g.nsplit) {
+            float f[3];
 #pragma unroll
-        for (int u = 0; u < 3; ++u) f[u] = p[(k + 4 * u < g.nsplit ? k + 4 * u : k) * step];
+            for (int u = 0; u < 3; ++u) f[u] = p[(k + 4 * u < g.nsplit ? k + 4 * u : k) * step];
 #pragma unroll
-        for (int u = 0; u < 3; ++u) s[u] += k + 4 * u < g.nsplit ? f[u] : 0.0f;       // (beyond the last run: not counted)
+            for (int u = 0; u < 3; ++u) s[u] += k + 4 * u < g.nsplit ? f[u] : 0.0f;       // (beyond the last run: not counted)
+        }
+#pragma unroll
+        for (int u = 4; u < M; ++u) s[u & 3] += s[u];
+    } else {
+        while (k + 12 < g.nsplit) batch(std::integral_constant<int, 4>{});
+        for (; k < g.nsplit; k += 4) s[0] += p[k * step];
     }
-#pragma unroll
-    for (int u = 4; u < 16; ++u) s[u & 3] += s[u];
     part[wave][lane] = (s[0] + s[1]) + (s[2] + s[3]);
     __syncthreads();
     if (wave != 0) return;
@@ -630,7 +639,7 @@ __global__ __launch_bounds__(256) void gw_reduce_kernel(const float *__restrict_
 // The same where few runs are to be added, at most kFewRuns: a workgroup takes a quarter (registers 4 q .. 4 q + 3, eight output channels x 32 input
 // channels) of one (block, wavefront) and all its taps, a wavefront each, so that what it stores is contiguous; 128-bit loads, all of a
 // wavefront's in flight at once, which is what limits the runs.  A tap and 64 elements per workgroup, as above, leave a channel's taps to as many workgroups
-// of different XCDs.  Durations, us, above / here: 256 x 256 channels, 3 x 3, 8 runs 13.0 / 6.6, 3 runs 12.3 / 5.3; 512 x 480, 2 runs, 1 x 1 6.5 / 4.9 (512 x 512),
+// of different XCDs.  Durations, us, gw_reduce_kernel<false> / here: 256 x 256 channels, 3 x 3, 8 runs 13.0 / 6.6, 3 runs 12.3 / 5.3; 512 x 480, 2 runs, 1 x 1 6.5 / 4.9 (512 x 512),
 // 1 x 3 15.7 / 5.8, 2 x 2 19.8 / 6.9, 1 x 5 24.2 / 7.3, 3 x 3, 4 runs 40.8 / 13.8; one block of one run 2.9 / 4.1.
 constexpr int kFewRuns = 8;
 __global__ __launch_bounds__(576) void gw_reduce_few_kernel(const float *__restrict__ ws, float *__restrict__ gw, GwTile g, int TB, int WM, int WN)
@@ -702,8 +711,13 @@ hipError_t launch_gw1(const float *x, const float *gy, float *gw, float *ws, con
     if (e != hipSuccess) return e;
     if (g.nsplit <= kFewRuns)
         hipLaunchKernelGGL(gw_reduce_few_kernel, dim3((unsigned)(nblk * WM * WN * 4)), dim3(64 * TB), 0, s, ws, gw, g, TB, WM, WN);
-    else
-        hipLaunchKernelGGL(gw_reduce_kernel, dim3((unsigned)(nblk * TB * WM * WN * 16)), dim3(256), 0, s, ws, gw, g, TB, WM, WN);
+    else {
+        // (300 layers: with DEEP everywhere up to 3 us longer, with it nowhere up to 3.3; above this line it takes 0.3 - 2 us more on most, below it 0.3 - 3.3 less)
+        const int64_t wgs = (int64_t)nblk * TB * WM * WN * 16;
+        const int cus = device_cus();
+        auto k = wgs <= 2 * cus || wgs * g.nsplit <= 96 * cus ? gw_reduce_kernel<true> : gw_reduce_kernel<false>;
+        hipLaunchKernelGGL(k, dim3((unsigned)wgs), dim3(256), 0, s, ws, gw, g, TB, WM, WN);
+    }
     return hipGetLastError();
 }
 
