@@ -718,8 +718,9 @@ bool plan(const SplitGeom &g, const Cfg &c, int Wo, int SW, int cus, Tiling *bes
             if (h.need < red) h.need = red;
             if (h.need > 156 * 1024) continue;
             // Estimated time, in cycles: a workgroup alone takes `alone`, res of them share a compute unit at one per
-            // `shared`.  The constants are fitted to 1900 measured launches (104 layers, both directions, all
-            // configurations): the choice they give is on average 1 % slower than the best configuration of each layer.
+            // `shared`.  The constants are fitted to 1900 measured launches (104 layers, both directions, configurations
+            // 0 - 13): the choice they give is on average 1 % slower than the best configuration of each layer.  Layers that
+            // 14, 15 and 16 take by them (and keep_smaller) against those before: with staging wavefronts 9, 14 and 15 % faster on average, without 11, 8 and 8 % (834 layers).
             const double wpw = T / 256.0;             // wavefronts per SIMD and workgroup
             double res = c.wpe / wpw;                 // workgroups per compute unit: registers, 160 KB of LDS
             const int by_lds = 160 * 1024 / h.need;
@@ -735,7 +736,13 @@ bool plan(const SplitGeom &g, const Cfg &c, int Wo, int SW, int cus, Tiling *bes
             const double shared = (m > l ? m : l) + 0.625 * stage;
             const double alone = 0.958 * mfma + 0.516 * wld + stage + 6979 + (c.wk > 1 ? 466 * c.mb * c.nb * c.nph : 0);
             const double n = (double)tiles * h.cot / cus;
-            if (c.stagers(h.S)) {
+            // Where the staged form's estimate does not hold: 128 channels a tile of which half or more do not exist, in more than one round of one workgroup per unit (3 x 3 at
+            // stride 2: [64,200,41,41] -> 32 82 us / 96 with it, [51,224,67,67] -> 32 156 / 167), is left to the others.  The tile of 64 x 128, which was there before that form, is
+            // then estimated as it was, also at half a tile of channels ([4,384,90,90] -> 32 70 / 75, [1,200,99,99] -> 495 123 / 126).
+            const bool rounds = (int64_t)tiles * h.cot > cus, half = 2 * g.Cout <= BM;
+            const bool staged = c.stagers(h.S) > 0;
+            if (staged && c.wm == 4 && rounds && half) continue;
+            if (staged && !(c.wm == 2 && c.wn == 2 && (rounds || half))) {
                 // one workgroup per compute unit; a chunk takes its products or its staging (1350 cycles per unit of a staging thread), whichever is longer
                 const double prod = 1.157 * mfma / h.nchunk, put = 1350.0 * ((2 * nc * h.PS + 255) / 256);
                 const double t = 10000 + __builtin_ceil(n) * (h.nchunk * (prod > put ? prod : put) + 16000 + (c.wk > 1 ? 466 * c.mb * c.nb : 0));
@@ -757,6 +764,20 @@ bool plan(const SplitGeom &g, const Cfg &c, int Wo, int SW, int cus, Tiling *bes
         }
     }
     return found;
+}
+
+// The largest configurations against the one that the estimate puts just behind: not the estimate but measurements of 1800 layers.  h: the tiling of i, b: that
+// of bi.  true: bi stays.
+bool keep_smaller(int i, const Tiling &h, int bi, const Tiling &b, int64_t Cout, int cus)
+{
+    const bool staged = kCfg[i].stagers(h.S) > 0, rounds = (int64_t)h.tiles * h.cot > cus;
+    // With staging wavefronts 14 is up to 5 % slower than 6 where a tenth or more of its channels do not exist and 3 - 12 % faster where they do; 15 is 1 - 5 % slower than 6 on
+    // nine taps where it fills more than four fifths of the compute units and 3 - 11 % faster below.
+    if (bi == 6 && staged) return (i == 14 && 10 * Cout <= 9 * 128 * h.cot) || (i == 15 && h.S == 9 && 5LL * h.tiles * h.cot > 4 * cus);
+    // Without them 16 is 0 - 15 % slower than 3, 3 % on average, and, in more than one round, 0 - 4 % slower than 5 (in one 3 - 18 % faster); 14 in more than one round, where
+    // the estimates differ by less than 1 %, up to 3 % slower than 5.
+    if (i == 16 && !staged) return bi == 3 || (bi == 5 && rounds);
+    return i == 14 && !staged && bi == 5 && rounds && h.cost > 0.99 * b.cost;
 }
 
 }  // namespace
@@ -822,12 +843,17 @@ hipError_t launch_conv_split(const float *x, const float *wgt, float *y, int64_t
     int bi = -1;
     Tiling b;
     const int force = forced ? g_opt.conv2d_variant - 100 : -1;       // A/B and tests: this configuration
+    bool kept = false;
     for (int i = 0; i < kNumCfg; ++i) {
         if ((kCfg[i].nph > 1) != (ph != nullptr) || (force >= 0 && force < kNumCfg && force != i)) continue;
         // (a tile each for a third of the compute units: below that the largest tiles never win, and planning them is host time of every call)
         if (i >= kLargeCfg && force < 0 && 3.0 * N * Ho * Wo * Cout < (double)cus * (1024 * kCfg[i].mb * kCfg[i].nb * kCfg[i].wm * kCfg[i].wn)) continue;
         Tiling h;
         if (!plan(g, kCfg[i], (int)Wo, SW, cus, &h)) continue;
+        if (force < 0 && i >= kLargeCfg && bi >= 0 && (kept || keep_smaller(i, h, bi, b, Cout, cus))) {
+            kept = kept || bi == 6;                   // (16 is not faster either where 14 or 15 is not)
+            continue;
+        }
         // a tile's images, and a wavefront's weights, within 32-bit offsets
         const int64_t imgs = (int64_t)(h.bnp > h.bnpl ? h.bnp : h.bnpl) / (h.TWl * Ho) + 2;
         if (imgs * Cin * H * W >= (1LL << 29) || (int64_t)h.KS * kStepBytes >= (1LL << 31)) continue;

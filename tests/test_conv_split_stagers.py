@@ -21,3 +21,23 @@ def test_staging_wavefronts(B, cfg, integer, lent):  # noqa: F811
         _check(B, case, 80 + i, integer, adjoint=case[7] == 1)
     taken = [_taken(t) for t in lent]
     assert sum(taken) >= 30, taken                    # (a tile that does not fit leaves a shape to the kernels without a workspace)
+
+
+# n, cin, cout, h, w, k, stride: the configuration that is faster, the one that the estimate alone would take.  Times of the two, us: 82 / 96, 88 / 93, 70 / 75, 134 / 139
+FASTER = {(64, 200, 32, 41, 41, 3, 2): (5, 16), (1, 288, 320, 95, 95, 3, 1): (6, 15), (4, 384, 32, 90, 90, 3, 1): (9, 3), (1, 96, 432, 97, 97, 5, 1): (5, 16)}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", FASTER)
+def test_the_faster_configuration_is_taken(B, case):  # noqa: F811
+    """Told apart by the bits of the sums: the two split the contraction over different numbers of wavefronts."""
+    import torch
+    n, cin, cout, h, w, k, s = case
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x, wgt = torch.randn(n, cin, h, w, generator=g, device="cuda"), torch.randn(cout, cin, k, k, generator=g, device="cuda")
+    y = {}
+    for cfg in (None, *FASTER[case]):
+        B.sws_set_option("conv2d_variant", 0 if cfg is None else 100 + cfg)
+        y[cfg] = B.sws_conv2d(x, wgt, s, s, k // 2, k // 2)
+    faster, other = (y[c] for c in FASTER[case])
+    assert not torch.equal(faster, other) and torch.equal(y[None], faster)
