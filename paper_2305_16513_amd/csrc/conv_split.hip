@@ -766,18 +766,19 @@ bool plan(const SplitGeom &g, const Cfg &c, int Wo, int SW, int cus, Tiling *bes
     return found;
 }
 
-// The largest configurations against the one that the estimate puts just behind: not the estimate but measurements of 1800 layers.  h: the tiling of i, b: that
+// The largest configurations against the one that the estimate puts just behind: not the estimate but measurements of 5000 layers.  h: the tiling of i, b: that
 // of bi.  true: bi stays.
 bool keep_smaller(int i, const Tiling &h, int bi, const Tiling &b, int64_t Cout, int cus)
 {
     const bool staged = kCfg[i].stagers(h.S) > 0, rounds = (int64_t)h.tiles * h.cot > cus;
-    // With staging wavefronts 14 is up to 5 % slower than 6 where a tenth or more of its channels do not exist and 3 - 12 % faster where they do; 15 is 1 - 5 % slower than 6 on
-    // nine taps where it fills more than four fifths of the compute units and 3 - 11 % faster below.
-    if (bi == 6 && staged) return (i == 14 && 10 * Cout <= 9 * 128 * h.cot) || (i == 15 && h.S == 9 && 5LL * h.tiles * h.cot > 4 * cus);
+    // With staging wavefronts 14 is up to 5 % slower than 6 where a tenth or more of its channels do not exist and 3 - 12 % faster where they do; 15 and 16 are 1 - 13 % slower than 6
+    // on nine taps where they fill more than four fifths of the compute units, and 3 - 14 % faster below.
+    if (bi == 6 && staged) return i == 14 ? 10 * Cout <= 9 * 128 * h.cot : h.S == 9 && 5LL * h.tiles * h.cot > 4 * cus;
     // Without them 16 is 0 - 15 % slower than 3, 3 % on average, and, in more than one round, 0 - 4 % slower than 5 (in one 3 - 18 % faster); 14 in more than one round, where
-    // the estimates differ by less than 1 %, up to 3 % slower than 5.
-    if (i == 16 && !staged) return bi == 3 || (bi == 5 && rounds);
-    return i == 14 && !staged && bi == 5 && rounds && h.cost > 0.99 * b.cost;
+    // the estimates differ by less than 1 %, up to 3 % slower than 5; beside 6 it is 1 % faster to 5 % slower.
+    if (staged) return false;
+    if (i == 16) return bi == 3 || (bi == 5 && rounds);
+    return i == 14 && (bi == 6 || (bi == 5 && rounds && h.cost > 0.99 * b.cost));
 }
 
 }  // namespace
@@ -850,9 +851,11 @@ hipError_t launch_conv_split(const float *x, const float *wgt, float *y, int64_t
         if (i >= kLargeCfg && force < 0 && 3.0 * N * Ho * Wo * Cout < (double)cus * (1024 * kCfg[i].mb * kCfg[i].nb * kCfg[i].wm * kCfg[i].wn)) continue;
         Tiling h;
         if (!plan(g, kCfg[i], (int)Wo, SW, cus, &h)) continue;
-        if (force < 0 && i >= kLargeCfg && bi >= 0 && (kept || keep_smaller(i, h, bi, b, Cout, cus))) {
-            kept = kept || bi == 6;                   // (16 is not faster either where 14 or 15 is not)
-            continue;
+        if (force < 0 && i >= kLargeCfg && bi >= 0 && h.cost < b.cost) {
+            if (i == 16 && kept) continue;            // (2 - 12 % slower than 6 where 14 or 15 is slower)
+            const bool keep = keep_smaller(i, h, bi, b, Cout, cus);
+            kept |= keep && bi == 6;
+            if (keep) continue;
         }
         // a tile's images, and a wavefront's weights, within 32-bit offsets
         const int64_t imgs = (int64_t)(h.bnp > h.bnpl ? h.bnp : h.bnpl) / (h.TWl * Ho) + 2;
