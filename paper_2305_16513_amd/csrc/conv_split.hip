@@ -131,6 +131,7 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
     constexpr int T = P ? 64 * P : 64 * WM * WN * WK; // threads that stage
     constexpr int R = S ? (S % 3 == 0 ? 3 : P ? 2 : S % 4 == 0 ? 4 : 5) : 2;
     static_assert(S == 0 || (S % R == 0 && (NPH == 1 || S == 9)), "the ring of weights closes over a chunk");
+    static_assert(P == 0 || (S != 0 && NPH == 1), "with wavefronts that only stage: straight-line chunks of one phase");
     constexpr int kPhase9[9] = {0, 1, 1, 2, 2, 3, 3, 3, 3};      // straight-line chunks with phases: a step's phase (see launch_cfg)
     constexpr int NLO = S ? NPH : 1;
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -421,13 +422,13 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
             for (int s = 0; s < S; ++s) {
                 aload(A[(s + R - 1) % R], ks + s + R - 1);
                 if (s + 1 < S) bload(Bq[(s + 1) & 1], cur, s + 1);
-                if constexpr (more.value && P == 0) {
+                if constexpr (more.value) {
 #pragma unroll
                     for (int i = 0; i < U; ++i)
                         if (i * (S / 2) / U == s) issue(i, ch + 1);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                if constexpr (more.value && P == 0) {
+                if constexpr (more.value) {
 #pragma unroll
                     for (int i = 0; i < U; ++i)
                         if (S - U + i == s || (S < U && s == S - 1))
@@ -448,7 +449,7 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
     } else {
         for (int ch = 0; ch < g.nchunk; ++ch) {
             const bool more = ch + 1 < g.nchunk;
-            if (more && P == 0) {
+            if (more) {
 #pragma unroll
                 for (int i = 0; i < U; ++i) issue(i, ch + 1);
             }
@@ -495,11 +496,9 @@ void conv_split_kernel(const float *__restrict__ x, const v4u *__restrict__ ws, 
             }
             if (more) {
                 cur = cur == lds ? lds + g.bufs : lds;
-                if constexpr (P == 0) {
 #pragma unroll
-                    for (int i = 0; i < U; ++i)
-                        if (i * T < units) commit(i, cur);
-                }
+                for (int i = 0; i < U; ++i)
+                    if (i * T < units) commit(i, cur);
                 barrier();
             }
         }
