@@ -641,31 +641,35 @@ hipError_t launch_cfg(const float *x, const v4u *ws, float *y, const SplitGeom &
     return launch_steps<I, 0>(x, ws, y, g, grid, lds, s);
 }
 
+// A tile's positions; the same for all configurations of as many.
+struct Shape {
+    int nstrips, TW, TWl, CW, LW, bnp, bnpl, tpf, tiles, PS;
+};
+constexpr int kMaxShapes = 10;                        // (up to five numbers of strips, each with tiles of whole rows and without)
+
 // A tile geometry for one configuration; cost: estimated cycles of the launch.
-struct Tiling {
-    int nstrips, TW, TWl, CW, LW, bnp, bnpl, tpf, tiles, cot, PS, NC, nchunk, S, KS, bufs, need;
+struct Tiling : Shape {
+    int cot, NC, nchunk, S, KS, bufs, need;
     double cost;
 };
 
-// The cheapest tiling of configuration c; false: none fits.  (32-bit divisions: this runs on every call.)
-bool plan(const SplitGeom &g, const Cfg &c, int Wo, int SW, int cus, Tiling *best)
+// The shapes of tiles of BN positions.  (32-bit divisions: this runs on every call.)
+int shapes_of(const SplitGeom &g, int BN, int Wo, int SW, Shape *out)
 {
-    const int BN = 32 * c.nb * c.wn, BM = 32 * c.mb * c.wm, T = 64 * c.wm * c.wn * c.wk;
     const int SWc = SW < g.sw ? SW : g.sw;            // column residues that are read
-    const unsigned groups = (unsigned)(g.Cin + 15) / 16;
-    bool found = false;
-    Tiling h;
-    h.cot = (int)((unsigned)(g.Cout + BM - 1) / BM);
     const int whole = (int)((unsigned)(Wo + BN - 1) / BN);      // strips of at most BN columns
+    const int more = (int)((unsigned)(SW - 1) / g.sw);
+    int count = 0;
     for (int ns = 1; ns <= Wo; ns = ns < 4 ? ns + 1 : (ns < whole ? whole : Wo + 1)) {
         for (int aligned = 0; aligned < 2; ++aligned) {
+            Shape &h = out[count];
             int tw = (int)((unsigned)(Wo + ns - 1) / ns);
             if (ns >= 4 && aligned && tw < BN) tw = BN < Wo ? BN : Wo;
             if (tw > 16384) continue;
             h.nstrips = (int)((unsigned)(Wo + tw - 1) / tw);
             h.TW = tw;
             h.TWl = Wo - (h.nstrips - 1) * tw;
-            h.CW = tw + (int)((unsigned)(SW - 1) / g.sw);
+            h.CW = tw + more;
             h.LW = SWc * h.CW;
             int lines = 0;
             unsigned tl[2];
@@ -693,73 +697,109 @@ bool plan(const SplitGeom &g, const Cfg &c, int Wo, int SW, int cus, Tiling *bes
             if (h.nstrips == 1) { h.bnp = h.bnpl; tl[0] = tl[1]; }
             h.PS = lines * h.LW;
             const int64_t tiles = (int64_t)tl[0] * (h.nstrips - 1) + tl[1];
-            if (tiles * h.cot > (1 << 30)) continue;
+            if (tiles > (1 << 30)) continue;
             h.tpf = (int)tl[0];
             h.tiles = (int)tiles;
-            // channel groups per chunk: enough steps to pass a chunk's loads behind (kernels of few taps), whole rounds of the K split
-            int nc = c.wk, per = 1;                   // per = nc / wk
-            if (c.nph == 1)
-                while (per * g.KT < 8 && (unsigned)(2 * nc) <= (groups + c.wk - 1) / c.wk * c.wk && 2 * per * g.KT <= kMaxSteps &&
-                       4 * nc * h.PS <= c.u * T) {
-                    nc *= 2;
-                    per *= 2;
-                }
-            if (2 * nc * h.PS > c.u * T) continue;
-            h.NC = nc;
-            h.nchunk = (int)((groups + nc - 1) / nc);
-            h.S = per * g.KT;
-            if (h.S > kMaxSteps) continue;
-            h.KS = h.nchunk * h.S;
-            const int buf = 2 * nc * 3 * h.PS * 16;
-            h.bufs = h.nchunk > 1 ? buf : 0;
-            h.need = buf + h.bufs;
-            const int red = c.wk > 1 ? c.nph * c.mb * c.nb * 4 * 64 * 16 * c.wm * c.wn : 0;
-            if (h.need < red) h.need = red;
-            if (h.need > 156 * 1024) continue;
-            // Estimated time, in cycles: a workgroup alone takes `alone`, res of them share a compute unit at one per
-            // `shared`.  The constants are fitted to 1900 measured launches (104 layers, both directions, configurations
-            // 0 - 13): the choice they give is on average 1 % slower than the best configuration of each layer.  Layers that
-            // 14, 15 and 16 take by them (and keep_smaller) against those before: with staging wavefronts 9, 14 and 15 % faster on average, without 11, 8 and 8 % (834 layers).
-            const double wpw = T / 256.0;             // wavefronts per SIMD and workgroup
-            double res = c.wpe / wpw;                 // workgroups per compute unit: registers, 160 KB of LDS
-            const int by_lds = 160 * 1024 / h.need;
-            if (by_lds < res) res = by_lds;
-            if (res < 1) res = 1;
-            // (fitted before layers of 25 taps and the usual phases became straight-line chunks: calling them that here chose worse, [32,512,14,14] -> 512
-            // 71 us for 65, 5 x 5 on [8,50,40,40] -> 30 21.5 for 19.9)
-            const bool line = c.nph == 1 && (h.S == 6 || h.S == 8 || h.S == 9 || h.S == 12);      // straight-line chunks
-            const double mfma = (double)h.KS * c.mb * c.nb * 6 * 32 * wpw * (c.nph == 1 ? 1.0 : 1.106);
-            const double wld = (double)h.KS * (T / 64) * c.mb * 48;       // weights through the vector cache, 64 bytes per cycle
-            const double stage = h.nchunk * (890 + 375 * wpw * ((2 * nc * h.PS + T - 1) / T)) * (line ? 1.0 : 1.105);
-            const double m = 1.419 * mfma, l = 0.157 * wld;
-            const double shared = (m > l ? m : l) + 0.625 * stage;
-            const double alone = 0.958 * mfma + 0.516 * wld + stage + 6979 + (c.wk > 1 ? 466 * c.mb * c.nb * c.nph : 0);
-            const double n = (double)tiles * h.cot / cus;
-            // Where the staged form's estimate does not hold: 128 channels a tile of which half or more do not exist, in more than one round of one workgroup per unit (3 x 3 at
-            // stride 2: [64,200,41,41] -> 32 82 us / 96 with it, [51,224,67,67] -> 32 156 / 167), is left to the others.  The tile of 64 x 128, which was there before that form, is
-            // then estimated as it was, also at half a tile of channels ([4,384,90,90] -> 32 70 / 75, [1,200,99,99] -> 495 123 / 126).
-            const bool rounds = (int64_t)tiles * h.cot > cus, half = 2 * g.Cout <= BM;
-            const bool staged = c.stagers(h.S) > 0;
-            if (staged && c.wm == 4 && rounds && half) continue;
-            if (staged && !(c.wm == 2 && c.wn == 2 && (rounds || half))) {
-                // one workgroup per compute unit; a chunk takes its products or its staging (1350 cycles per unit of a staging thread), whichever is longer
-                const double prod = 1.157 * mfma / h.nchunk, put = 1350.0 * ((2 * nc * h.PS + 255) / 256);
-                const double t = 10000 + __builtin_ceil(n) * (h.nchunk * (prod > put ? prod : put) + 16000 + (c.wk > 1 ? 466 * c.mb * c.nb : 0));
-                if (!found || t < best->cost) {
-                    found = true;
-                    h.cost = t;
-                    *best = h;
-                }
-                continue;
+            ++count;
+        }
+    }
+    return count;
+}
+
+// What a launch of n workgroups per compute unit takes at least by plan's formulas: its products and weights (mfma, wld as there).
+double plan_least(const Cfg &c, double mfma, double wld, double n)
+{
+    const double alone = 0.958 * mfma + 0.516 * wld + 6979, all = 1.419 * mfma * n;
+    double t = all > alone ? all : alone;
+    if (c.nph == 1 && c.wm * c.wn * c.wk == 8) {
+        const double staged = 10000 + __builtin_ceil(n) * (1.157 * mfma + 16000);
+        t = staged < t ? staged : t;
+    }
+    return t * (1 - 1e-9);                            // (rounding)
+}
+
+// The cheapest tiling of configuration c, of those that cost less than `limit`; false: there is none.  (Nothing is worked out
+// for tilings whose products alone take longer than the best so far.)
+bool plan(const SplitGeom &g, const Cfg &c, const Shape *shapes, int count, int Wo, int cus, double limit, Tiling *best)
+{
+    const int BN = 32 * c.nb * c.wn, BM = 32 * c.mb * c.wm, T = 64 * c.wm * c.wn * c.wk;
+    const unsigned groups = (unsigned)(g.Cin + 15) / 16;
+    bool found = false;
+    Tiling h;
+    h.cot = (int)((unsigned)(g.Cout + BM - 1) / BM);
+    // the fewest steps that the contraction can have (whole rounds of the K split), and the fewest tiles
+    const unsigned turns = (groups + c.wk - 1) / (unsigned)c.wk;
+    const double steps = (double)(g.KT * (int)turns);
+    const double mfma_least = steps * (c.mb * c.nb * 6 * 32) * (T / 256.0) * (c.nph == 1 ? 1.0 : 1.106), wld_least = steps * (T / 64 * c.mb * 48);
+    const double per_cu = (double)h.cot / cus;
+    if (plan_least(c, mfma_least, wld_least, (double)g.NR * Wo / BN * per_cu) >= limit) return false;
+    for (int at = 0; at < count; ++at) {
+        static_cast<Shape &>(h) = shapes[at];
+        const int64_t tiles = h.tiles;
+        if (tiles * h.cot > (1 << 30) || plan_least(c, mfma_least, wld_least, (double)tiles * per_cu) >= limit) continue;
+        // channel groups per chunk: enough steps to pass a chunk's loads behind (kernels of few taps), whole rounds of the K split
+        int nc = c.wk, per = 1;                   // per = nc / wk
+        if (c.nph == 1)
+            while (per * g.KT < 8 && (unsigned)(2 * nc) <= turns * c.wk && 2 * per * g.KT <= kMaxSteps &&
+                   4 * nc * h.PS <= c.u * T) {
+                nc *= 2;
+                per *= 2;
             }
-            const double full = __builtin_floor(n / res), rem = n - full * res;
-            double t = full * (res * shared > alone ? res * shared : alone);
-            if (rem > 0) t += __builtin_ceil(rem) * shared > alone ? __builtin_ceil(rem) * shared : alone;
-            if (!found || t < best->cost) {
+        if (2 * nc * h.PS > c.u * T) continue;
+        h.NC = nc;
+        h.nchunk = (int)((groups + nc - 1) / nc);
+        h.S = per * g.KT;
+        if (h.S > kMaxSteps) continue;
+        h.KS = h.nchunk * h.S;
+        const int buf = 2 * nc * 3 * h.PS * 16;
+        h.bufs = h.nchunk > 1 ? buf : 0;
+        h.need = buf + h.bufs;
+        const int red = c.wk > 1 ? c.nph * c.mb * c.nb * 4 * 64 * 16 * c.wm * c.wn : 0;
+        if (h.need < red) h.need = red;
+        if (h.need > 156 * 1024) continue;
+        // Estimated time, in cycles: a workgroup alone takes `alone`, res of them share a compute unit at one per
+        // `shared`.  The constants are fitted to 1900 measured launches (104 layers, both directions, configurations
+        // 0 - 13): the choice they give is on average 1 % slower than the best configuration of each layer.  Layers that
+        // 14, 15 and 16 take by them (and keep_smaller) against those before: with staging wavefronts 9, 14 and 15 % faster on average, without 11, 8 and 8 % (834 layers).
+        const double wpw = T / 256.0;             // wavefronts per SIMD and workgroup
+        double res = c.wpe / wpw;                 // workgroups per compute unit: registers, 160 KB of LDS
+        const int by_lds = 160 * 1024 / h.need;
+        if (by_lds < res) res = by_lds;
+        if (res < 1) res = 1;
+        // (fitted before layers of 25 taps and the usual phases became straight-line chunks: calling them that here chose worse, [32,512,14,14] -> 512
+        // 71 us for 65, 5 x 5 on [8,50,40,40] -> 30 21.5 for 19.9)
+        const bool line = c.nph == 1 && (h.S == 6 || h.S == 8 || h.S == 9 || h.S == 12);      // straight-line chunks
+        const double mfma = (double)h.KS * c.mb * c.nb * 6 * 32 * wpw * (c.nph == 1 ? 1.0 : 1.106);
+        const double wld = (double)h.KS * (T / 64) * c.mb * 48;       // weights through the vector cache, 64 bytes per cycle
+        const double stage = h.nchunk * (890 + 375 * wpw * ((2 * nc * h.PS + T - 1) / T)) * (line ? 1.0 : 1.105);
+        const double m = 1.419 * mfma, l = 0.157 * wld;
+        const double shared = (m > l ? m : l) + 0.625 * stage;
+        const double alone = 0.958 * mfma + 0.516 * wld + stage + 6979 + (c.wk > 1 ? 466 * c.mb * c.nb * c.nph : 0);
+        const double n = (double)tiles * h.cot / cus;
+        // Where the staged form's estimate does not hold: 128 channels a tile of which half or more do not exist, in more than one round of one workgroup per unit (3 x 3 at
+        // stride 2: [64,200,41,41] -> 32 82 us / 96 with it, [51,224,67,67] -> 32 156 / 167), is left to the others.  The tile of 64 x 128, which was there before that form, is
+        // then estimated as it was, also at half a tile of channels ([4,384,90,90] -> 32 70 / 75, [1,200,99,99] -> 495 123 / 126).
+        const bool rounds = (int64_t)tiles * h.cot > cus, half = 2 * g.Cout <= BM;
+        const bool staged = c.stagers(h.S) > 0;
+        if (staged && c.wm == 4 && rounds && half) continue;
+        if (staged && !(c.wm == 2 && c.wn == 2 && (rounds || half))) {
+            // one workgroup per compute unit; a chunk takes its products or its staging (1350 cycles per unit of a staging thread), whichever is longer
+            const double prod = 1.157 * mfma / h.nchunk, put = 1350.0 * ((2 * nc * h.PS + 255) / 256);
+            const double t = 10000 + __builtin_ceil(n) * (h.nchunk * (prod > put ? prod : put) + 16000 + (c.wk > 1 ? 466 * c.mb * c.nb : 0));
+            if (t < limit) {
                 found = true;
-                h.cost = t;
+                h.cost = limit = t;
                 *best = h;
             }
+            continue;
+        }
+        const double full = __builtin_floor(n / res), rem = n - full * res;
+        double t = full * (res * shared > alone ? res * shared : alone);
+        if (rem > 0) t += __builtin_ceil(rem) * shared > alone ? __builtin_ceil(rem) * shared : alone;
+        if (t < limit) {
+            found = true;
+            h.cost = limit = t;
+            *best = h;
         }
     }
     return found;
@@ -844,13 +884,17 @@ hipError_t launch_conv_split(const float *x, const float *wgt, float *y, int64_t
     Tiling b;
     const int force = forced ? g_opt.conv2d_variant - 100 : -1;       // A/B and tests: this configuration
     bool kept = false;
+    Shape shapes[4][kMaxShapes];
+    int counts[4] = {-1, -1, -1, -1};
     for (int i = 0; i < kNumCfg; ++i) {
         if ((kCfg[i].nph > 1) != (ph != nullptr) || (force >= 0 && force < kNumCfg && force != i)) continue;
         // (a tile each for a third of the compute units: below that the largest tiles never win, and planning them is host time of every call)
         if (i >= kLargeCfg && force < 0 && 3.0 * N * Ho * Wo * Cout < (double)cus * (1024 * kCfg[i].mb * kCfg[i].nb * kCfg[i].wm * kCfg[i].wn)) continue;
         Tiling h;
-        if (!plan(g, kCfg[i], (int)Wo, SW, cus, &h)) continue;
-        if (force < 0 && i >= kLargeCfg && bi >= 0 && h.cost < b.cost) {
+        const int nbwn = kCfg[i].nb * kCfg[i].wn, of = nbwn >= 8 ? 3 : nbwn >> 1;      // (1, 2, 4 or 8 blocks of 32 positions)
+        if (counts[of] < 0) counts[of] = shapes_of(g, 32 * nbwn, (int)Wo, SW, shapes[of]);
+        if (!plan(g, kCfg[i], shapes[of], counts[of], (int)Wo, cus, bi < 0 ? 1e300 : b.cost, &h)) continue;
+        if (force < 0 && i >= kLargeCfg && bi >= 0) {
             if (i == 16 && kept) continue;            // (2 - 12 % slower than 6 where 14 or 15 is slower)
             const bool keep = keep_smaller(i, h, bi, b, Cout, cus);
             kept |= keep && bi == 6;
@@ -859,7 +903,8 @@ hipError_t launch_conv_split(const float *x, const float *wgt, float *y, int64_t
         // a tile's images, and a wavefront's weights, within 32-bit offsets
         const int64_t imgs = (int64_t)(h.bnp > h.bnpl ? h.bnp : h.bnpl) / (h.TWl * Ho) + 2;
         if (imgs * Cin * H * W >= (1LL << 29) || (int64_t)h.KS * kStepBytes >= (1LL << 31)) continue;
-        if (bi < 0 || h.cost < b.cost) { bi = i; b = h; }
+        bi = i;
+        b = h;
     }
     if (bi < 0) return hipSuccess;
     const Cfg &c = kCfg[bi];
