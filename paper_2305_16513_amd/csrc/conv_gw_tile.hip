@@ -787,84 +787,115 @@ bool plan_gw(const GwLayer &l, bool exact, int64_t limit, GwPlan *best)
     // Layers of conv_gw_staged_kernel: 3 x 3 at stride 1, channels in whole blocks, rows and strips of even length (pairs of positions lie side by side), one
     // unit of x per staging thread.
     const bool whole_blocks = kh == 3 && kw == 3 && sh == 1 && sw == 1 && Cin % 32 == 0 && Cout % 32 == 0 && Wo % 2 == 0;
-    // Channel blocks of a workgroup, strip width, rows per tile and runs: the smallest estimated time of the longest run (products
+    // The shapes of tiles: strip width and rows.  They are the same whatever the channel blocks.
+    struct Shape { int TW, nstrips, CW, LW, rpt, period, lines, PS, tps, tiles, ksteps, nq; };
+    Shape shapes[4 * 16];                             // (rows: 128, 96, 72 ... 4, 3, 2, 1 at most)
+    int count = 0;
+    for (int ns = (int)((Wo + kBN - 1) / kBN), last = ns + 3; ns <= last && ns <= Wo; ++ns) {
+        Shape h;
+        h.TW = (int)((unsigned)(Wo + ns - 1) / ns); h.nstrips = (int)((unsigned)(Wo + h.TW - 1) / h.TW);
+        h.CW = h.TW + (int)((unsigned)(SW - 1) / sw); h.LW = SWc * h.CW;
+        h.nq = ((h.LW < g.W ? h.LW : g.W) + 3) / 4;
+        for (int rpt = kBN / h.TW < g.NR ? kBN / h.TW : g.NR; rpt >= 1; rpt = rpt > 4 ? rpt * 3 / 4 : rpt - 1) {
+            // (tiles start at multiples of rpt, so at most this far down an image: where rpt divides Ho no tile meets two)
+            int start = rpt, mod = g.Ho;
+            while (mod) { const int r = (int)((unsigned)start % (unsigned)mod); start = mod; mod = r; }
+            const int crossings = (int)((unsigned)(g.Ho - start + rpt - 1) / (unsigned)g.Ho);
+            const int64_t lines = (int64_t)(rpt - 1) * g.ls + g.SH + crossings * (g.SH - g.ls);
+            if (lines * h.LW > 1024) continue;
+            const int64_t imgs = (unsigned)rpt / (unsigned)g.Ho + 2;      // a tile's images within 32-bit offsets
+            if (imgs * Cin * H * W >= (1LL << 29) || imgs * Cout * Ho * Wo >= (1LL << 29)) continue;
+            h.rpt = rpt; h.period = start; h.lines = (int)lines;
+            h.PS = ((int)(lines * h.LW) + 3) / 16 * 16 + 12;
+            h.tps = (int)((unsigned)(g.NR + rpt - 1) / rpt); h.ksteps = (rpt * h.TW + 15) / 16;
+            if ((int64_t)h.tps * h.nstrips >= (1LL << 30)) continue;
+            h.tiles = h.tps * h.nstrips;
+            shapes[count++] = h;
+        }
+    }
+    // Channel blocks of a workgroup, tile and runs: the smallest estimated time of the longest run (products
     // on two wavefronts per SIMD, staging per unit, a run's end), in cycles.  (The second pass is in `end` as it was before
-    // there were two of them: it weighs channel blocks against runs, and takes 3 - 14 us either way.)
+    // there were two of them: it weighs channel blocks against runs, and takes 3 - 14 us either way.  This runs on every call: a form whose tiles alone, dealt to all compute units
+    // evenly, take longer than the best so far is left at that.)
     bool found = false;
-    double cost = 0;
+    double cost = 1e300;
     for (int wmn = 0; wmn < 4; ++wmn) {
         const int wm = 1 + (wmn & 1), wn = 1 + (wmn >> 1), wk = 8 / (wm * wn);
         if ((wm == 2 && Cout <= 32) || (wn == 2 && Cin <= 32)) continue;
         const int64_t cob = (Cout + 32 * wm - 1) / (32 * wm), cib = (Cin + 32 * wn - 1) / (32 * wn), nblk = cob * cib * g.ng;
         if (nblk * 16 * wm * wn * q.tb >= (1LL << 30)) continue;
-        for (int ns = (int)((Wo + kBN - 1) / kBN), last = ns + 3; ns <= last && ns <= Wo; ++ns) {
-            const int TW = (int)((unsigned)(Wo + ns - 1) / ns), nstrips = (int)((unsigned)(Wo + TW - 1) / TW);
-            const int CW = TW + (int)((unsigned)(SW - 1) / sw), LW = SWc * CW;
-            for (int rpt = kBN / TW < g.NR ? kBN / TW : g.NR; rpt >= 1; rpt = rpt > 4 ? rpt * 3 / 4 : rpt - 1) {
-                // (tiles start at multiples of rpt, so at most this far down an image: where rpt divides Ho no tile meets two)
-                int start = rpt, mod = g.Ho;
-                while (mod) { const int r = (int)((unsigned)start % (unsigned)mod); start = mod; mod = r; }
-                const int crossings = (int)((unsigned)(g.Ho - start + rpt - 1) / (unsigned)g.Ho), period = start;
-                const int64_t lines = (int64_t)(rpt - 1) * g.ls + g.SH + crossings * (g.SH - g.ls);
-                if (lines * LW > 1024) continue;
-                const int64_t imgs = rpt / Ho + 2;    // a tile's images within 32-bit offsets
-                if (imgs * Cin * H * W >= (1LL << 29) || imgs * Cout * Ho * Wo >= (1LL << 29)) continue;
-                const int PS = ((int)(lines * LW) + 3) / 16 * 16 + 12;
-                const size_t stage = (size_t)4 * 3 * 16 * (wn * PS + wm * kPG) + kBN * 4;
-                const size_t red = (size_t)(8 - wm * wn) * 4 * (q.tb < 3 ? q.tb : 3) * 1024;
-                // (3 x 3 at stride 2 on one block of input channels: a fifth unit a thread lets a tile hold 112 positions instead of 84, whose four
-                // wavefronts per block then take seven groups of 16 in the time of six: [32,64,56,56] -> 64, taken here for comparison, 34 us -> 26)
-                if (4 * wn * PS > (wn == 1 && q.tb == 9 && sh == 2 && sw == 2 ? 5 : 4) * kThreads || stage > 158 * 1024) continue;
-                const int tps = (int)((unsigned)(g.NR + rpt - 1) / rpt), ksteps = (rpt * TW + 15) / 16, steps = (ksteps + wk - 1) / wk;
-                if ((int64_t)tps * nstrips >= (1LL << 30)) continue;
-                const int tiles = tps * nstrips;
-                const int units = (4 * wn * PS + kThreads - 1) / kThreads + wm;
-                const int nq = ((LW < g.W ? LW : g.W) + 3) / 4;
-                const size_t two = (size_t)4 * 3 * 16 * (2 * PS + wm * kPG) + 2 * kBN * 4, sums = (size_t)8 * 4 * 5 * 1024;
-                const bool both = !exact && wn == 1 && whole_blocks && TW % 2 == 0 && 4 * lines * nq <= 256 && two <= 160 * 1024 &&
-                                    (int64_t)g.NR * nstrips < (1LL << 30);
-                // Runs per block of gw: a workgroup fills a compute unit (LDS), so as many as there are units, or twice as many,
-                // and never a few more: those would be a round of their own ([4,288,4658] -> 448, k = 1, 18 runs of 15 blocks: 132 us,
-                // 17 runs: 66).
-                for (int r = 1; r <= 2; ++r) {
-                    int64_t least = 1;
-                    if (exact) {
-                        const int adds = q.tb <= 3 ? 1 : steps * (q.tb < 9 ? 1 : 3), most = kMaxAdds / adds > 1 ? kMaxAdds / adds : 1;
-                        least = (tiles + most - 1) / most;
+        const double once = (4000 + 6.0 / 64 * q.tb * wm * wn * (double)nblk) * (1 - 1e-9), each = (double)nblk / cus * (1 - 1e-9);      // (rounding)
+        for (int at = 0; at < count; ++at) {
+            const Shape &h = shapes[at];
+            const int TW = h.TW, rpt = h.rpt, tiles = h.tiles;
+            const size_t stage = (size_t)4 * 3 * 16 * (wn * h.PS + wm * kPG) + kBN * 4;
+            const size_t red = (size_t)(8 - wm * wn) * 4 * (q.tb < 3 ? q.tb : 3) * 1024;
+            // (3 x 3 at stride 2 on one block of input channels: a fifth unit a thread lets a tile hold 112 positions instead of 84, whose four
+            // wavefronts per block then take seven groups of 16 in the time of six: [32,64,56,56] -> 64, taken here for comparison, 34 us -> 26)
+            if (4 * wn * h.PS > (wn == 1 && q.tb == 9 && sh == 2 && sw == 2 ? 5 : 4) * kThreads || stage > 158 * 1024) continue;
+            const int steps = (h.ksteps + wk - 1) / wk, units = (4 * wn * h.PS + kThreads - 1) / kThreads + wm;
+            const double tile = steps * (double)q.tb * 6 * 32 * 2 * 1.2 + 1200 + 500.0 * units;
+            const size_t two = (size_t)4 * 3 * 16 * (2 * h.PS + wm * kPG) + 2 * kBN * 4, sums = (size_t)8 * 4 * 5 * 1024;
+            const int64_t all = (int64_t)g.NR * h.nstrips;
+            // conv_gw_staged_kernel: a multiplying wavefront's 16 positions and what a tile takes besides
+            constexpr double kStep = 9 * 6 * 32 * 1.25, kTile = 1500;
+            const bool one = once + each * tiles * tile < cost;
+            const bool both = !exact && wn == 1 && whole_blocks && TW % 2 == 0 && 4 * h.lines * h.nq <= 256 && two <= 160 * 1024 && all < (1LL << 30) &&
+                              once + 8000 + each * (double)all * TW / (8 * wk) * kStep < cost;
+            if (!one && !both) continue;
+            // Runs per block of gw: a workgroup fills a compute unit (LDS), so as many as there are units, or twice as many,
+            // and never a few more: those would be a round of their own ([4,288,4658] -> 448, k = 1, 18 runs of 15 blocks: 132 us,
+            // 17 runs: 66).
+            for (int r = 1; r <= 2; ++r) {
+                int64_t least = 1, whole = r;         // rounds
+                if (exact) {
+                    const int adds = q.tb <= 3 ? 1 : steps * (q.tb < 9 ? 1 : 3), most = kMaxAdds / adds > 1 ? kMaxAdds / adds : 1;
+                    least = (int)((unsigned)(tiles + most - 1) / (unsigned)most);
+                    const int64_t needs = (least * nblk + cus - 1) / cus;
+                    if (whole < needs) whole = needs;
+                }
+                int64_t n = whole * cus / nblk;
+                if (n < least) n = least;
+                if (n > tiles) n = tiles;
+                auto better = [&](double run, int nsplit, double rounds, double end) {
+                    const double c = rounds * (run + 4000 + 6.0 * end / 64);
+                    if (!(c < cost)) return false;
+                    found = true;
+                    cost = c;
+                    best->WM = wm; best->WN = wn;
+                    best->bytes = nblk * nsplit * q.tb * wm * wn * 4096;
+                    g.TW = TW; g.nstrips = h.nstrips; g.CW = h.CW; g.LW = h.LW; g.rpt = rpt; g.PS = h.PS; g.tps = h.tps; g.tiles = tiles;
+                    g.ksteps = h.ksteps; g.lines = h.lines; g.nq = h.nq; g.nsplit = nsplit; g.cob = (int)cob; g.cib = (int)cib;
+                    return true;
+                };
+                auto fits = [&](int nsplit) { return nblk * nsplit * q.tb * wm * wn * 4096 <= limit && nblk * nsplit < (1LL << 30); };
+                const int per = (int)((unsigned)(tiles + n - 1) / (unsigned)n), few = (int)((unsigned)(tiles + per - 1) / per);
+                const double full = 0.269 * steps * q.tb + 1.67 + 0.09 * units;
+                if (one && fits(few)) {
+                    const double rounds = (double)(int)((unsigned)(nblk * few + cus - 1) / (unsigned)cus), end = q.tb * wm * wn * (double)(nblk * few);
+                    if (better(per * tile, few, rounds, end)) {
+                        best->lds = stage > red ? stage : red;
+                        best->us = 6.9 + rounds * (per * full + 0.75) + 0.0026 * end;
+                        g.per = per; g.rows = g.group = 0;
                     }
-                    int64_t whole = (least * nblk + cus - 1) / cus;      // rounds
-                    if (whole < r) whole = r;
-                    int64_t n = whole * cus / nblk;
-                    if (n < least) n = least;
-                    if (n > tiles) n = tiles;
-                    const int per = (int)((unsigned)(tiles + n - 1) / (unsigned)n), few = (int)((unsigned)(tiles + per - 1) / per);
-                    // (A staged run costs its first tile's staging by half as many wavefronts and 160 KB of sums at its end, and saves the staging of every further
-                    // tile.  8000 cycles is on the safe side, long runs only: with 3500 [8,96,30,30] -> 160, four tiles a run, would come here too, 33 us -> 26.)
-                    for (int staged = 0; staged <= (int)both; ++staged) {
-                        // (a staged run is rows: the runs of a round end together)
-                        const int64_t all = (int64_t)g.NR * nstrips, rows = staged ? ((all + n - 1) / n + period - 1) / period * period : 0;
-                        const int nsplit = staged ? (int)((all + rows - 1) / rows) : few;
-                        // (runs of one image's strips side by side, i.e. in the same XCD's cache: a row's strips share cache lines)
-                        const int64_t group = nstrips == 1 || rows >= g.NR ? g.NR : rows < g.Ho ? g.Ho : (rows + g.Ho / 2) / g.Ho * g.Ho;
-                        const int64_t bytes = nblk * nsplit * q.tb * wm * wn * 4096;
-                        if (bytes > limit || nblk * nsplit >= (1LL << 30)) continue;
-                        const double rounds = (double)((nblk * nsplit + cus - 1) / cus);
-                        const double end = q.tb * wm * wn * (double)(nblk * nsplit);
-                        auto tile = [&](int rows) { return ((rows * TW + 15) / 16 + wk / 2 - 1) / (wk / 2) * (9 * 6 * 32 * 1.25) + 1500; };
-                        const double run = staged ? (double)(rows / rpt) * tile(rpt) + (rows % rpt ? tile((int)(rows % rpt)) : 0) + (group % rows ? 3000 : 0) + 8000
-                                                  : per * (steps * (double)q.tb * 6 * 32 * 2 * 1.2 + 1200 + 500.0 * units);
-                        const double c = rounds * (run + 4000 + 6.0 * end / 64);
-                        if (!found || c < cost) {
-                            found = true;
-                            cost = c;
-                            best->WM = wm; best->WN = wn;
-                            best->lds = staged ? (two > sums ? two : sums) : stage > red ? stage : red;
-                            best->bytes = bytes;
-                            best->us = 6.9 + rounds * (per * (0.269 * steps * q.tb + 1.67 + 0.09 * units) + 0.75) + 0.0026 * end;
-                            g.TW = TW; g.nstrips = nstrips; g.CW = CW; g.LW = LW; g.rpt = rpt; g.PS = PS; g.tps = tps; g.tiles = tiles;
-                            g.ksteps = ksteps; g.lines = (int)lines; g.nq = nq; g.rows = (int)rows; g.group = (int)group;
-                            g.per = per; g.nsplit = nsplit; g.cob = (int)cob; g.cib = (int)cib;
-                        }
+                }
+                // A staged run costs its first tile's staging by half as many wavefronts and 160 KB of sums at its end, and saves the staging of every further
+                // tile.  8000 cycles is on the safe side, long runs only: with 3500 [8,96,30,30] -> 160, four tiles a run, would come here too, 33 us -> 26.
+                if (both) {
+                    // (a staged run is rows: the runs of a round end together)
+                    const int rows = (int)((unsigned)((all + n - 1) / n + h.period - 1) / (unsigned)h.period) * h.period;
+                    const int nsplit = (int)((unsigned)(all + rows - 1) / (unsigned)rows);
+                    if (!fits(nsplit)) continue;
+                    // (runs of one image's strips side by side, i.e. in the same XCD's cache: a row's strips share cache lines)
+                    const int group = h.nstrips == 1 || rows >= g.NR ? g.NR : rows < g.Ho ? g.Ho : (int)((unsigned)(rows + g.Ho / 2) / (unsigned)g.Ho) * g.Ho;
+                    const double rounds = (double)(int)((unsigned)(nblk * nsplit + cus - 1) / (unsigned)cus), end = q.tb * wm * wn * (double)(nblk * nsplit);
+                    auto part = [&](int of) { return ((of * TW + 15) / 16 + wk / 2 - 1) / (wk / 2) * kStep + kTile; };
+                    const int whole_tiles = (int)((unsigned)rows / (unsigned)rpt), rest = rows - whole_tiles * rpt;
+                    const double run = whole_tiles * part(rpt) + (rest ? part(rest) : 0) + ((unsigned)group % (unsigned)rows ? 3000 : 0) + 8000;
+                    if (better(run, nsplit, rounds, end)) {
+                        best->lds = two > sums ? two : sums;
+                        best->us = 6.9 + rounds * (per * full + 0.75) + 0.0026 * end;
+                        g.per = per; g.rows = rows; g.group = group;
                     }
                 }
             }
