@@ -21,90 +21,79 @@ namespace {
 
 PyObject *g_error = nullptr;                          // binding.SwsError
 
-struct Odd {};                                        // not for here
-
-// an exact int of 31 bits
-int32_t num(PyObject *o)
-{
-    if (!PyLong_CheckExact(o)) throw Odd();
-    int over = 0;
-    const long long v = PyLong_AsLongLongAndOverflow(o, &over);
-    if (over || v < 0 || v > 0x7fffffff) throw Odd();
-    return (int32_t)v;
-}
-
-float real(PyObject *o)
-{
-    if (PyFloat_CheckExact(o)) return (float)PyFloat_AS_DOUBLE(o);
-    return (float)num(o);
-}
-
-// a contiguous tensor with memory of the current device, and nothing that wraps or watches it
-const at::Tensor &tensor(PyObject *o, int device)
-{
-    if (!THPVariable_CheckExact(o)) throw Odd();
-    const at::Tensor &t = THPVariable_Unpack(o);
-    if (!t.defined() || !t.is_cuda() || t.device().index() != device || t.layout() != c10::kStrided || !t.has_storage() || !t.is_contiguous() ||
-        t.key_set().has_any(c10::DispatchKeySet({c10::DispatchKey::Python, c10::DispatchKey::Functionalize})))
-        throw Odd();
-    return t;
-}
-const at::Tensor &f32(PyObject *o, int device)
-{
-    const at::Tensor &t = tensor(o, device);
-    if (t.scalar_type() != at::kFloat) throw Odd();
-    return t;
-}
-const at::Tensor &half(PyObject *o, int device, int *dtype)
-{
-    const at::Tensor &t = tensor(o, device);
-    if (t.scalar_type() == at::kBFloat16) *dtype = SWS_DTYPE_BF16;
-    else if (t.scalar_type() == at::kHalf) *dtype = SWS_DTYPE_F16;
-    else throw Odd();
-    return t;
-}
-
-// sws_out_len for numbers of 31 bits; nothing below 1 goes on here
-int64_t out_len(int64_t n, int64_t w, int64_t stride, int64_t pad, int64_t dilation = 1)
-{
-    if (w < 1 || stride < 1 || dilation < 1) throw Odd();
-    const int64_t left = n + 2 * pad - dilation * (w - 1) - 1;
-    if (left < 0) throw Odd();
-    return left / stride + 1;
-}
-void same(bool ok) { if (!ok) throw Odd(); }
-
-// F(device, stream) -> the output; F allocates, then calls the library through `go`
+// One call.  Its functions note what is not for here in `odd`, so that a refusal costs a tenth of a microsecond (a C++ exception: 2.9).
 struct Call {
-    const char *name;
-    int device;
-    hipStream_t stream;
+    PyObject *const *a;
+    bool odd = false;
+    int device = -1;                                  // the current one, asked for when a tensor of any is met
     at::Tensor out;
     int rc = SWS_OK;
-    template <class... P, class... A> void go_on(sws_status (*entry)(P...), A... a)
+
+    // an int of 31 bits
+    int32_t num(int i)
     {
-        PyThreadState *save = PyEval_SaveThread();
-        rc = entry(static_cast<P>(a)...);
-        PyEval_RestoreThread(save);
+        long long v = -1;
+        int over = 0;
+        if (PyLong_Check(a[i])) v = PyLong_AsLongLongAndOverflow(a[i], &over);
+        odd |= over != 0 || v < 0 || v > 0x7fffffff;
+        return (int32_t)v;
     }
-    template <class E, class... A> void go(E entry, A... a) { go_on(entry, a..., stream); }
-    template <class S> void *alloc(const S &sizes, const at::Tensor &like)
+    float real(int i)
     {
-        out = at::empty(sizes, like.options());
-        return out.data_ptr();
+        if (PyFloat_Check(a[i])) return (float)PyFloat_AS_DOUBLE(a[i]);
+        long long v = 0;
+        int over = 1;
+        if (PyLong_Check(a[i])) v = PyLong_AsLongLongAndOverflow(a[i], &over);
+        odd |= over != 0;
+        return (float)(double)v;
+    }
+    // a contiguous tensor with memory of the current device, and nothing that wraps or watches it; not looked at where the call is odd
+    const at::Tensor &tensor(int i, bool half = false)
+    {
+        static const at::Tensor none;
+        if (!THPVariable_CheckExact(a[i])) { odd = true; return none; }
+        const at::Tensor &t = THPVariable_Unpack(a[i]);
+        if (!t.defined() || !t.is_cuda() || t.layout() != c10::kStrided || !t.has_storage() || !t.is_contiguous() ||
+            t.key_set().has_any(c10::DispatchKeySet({c10::DispatchKey::Python, c10::DispatchKey::Functionalize})) ||
+            (half ? t.scalar_type() != at::kBFloat16 && t.scalar_type() != at::kHalf : t.scalar_type() != at::kFloat)) {
+            odd = true;
+            return none;
+        }
+        if (device < 0) device = c10::hip::current_device();
+        odd |= t.device().index() != device;
+        return t;
+    }
+    static int dtype(const at::Tensor &t) { return t.scalar_type() == at::kHalf ? SWS_DTYPE_F16 : SWS_DTYPE_BF16; }
+
+    // The output, of x's type, and the library's call on it: f(address, stream)
+    template <class F> bool run(at::IntArrayRef sizes, const at::Tensor &x, F f)
+    {
+        const hipStream_t stream = c10::hip::getCurrentHIPStream((c10::DeviceIndex)device).stream();
+        out = at::empty(sizes, x.options());
+        void *const y = out.data_ptr();
+        PyThreadState *const save = PyEval_SaveThread();
+        rc = f(y, stream);
+        PyEval_RestoreThread(save);
+        return true;
     }
 };
 
-template <class F>
-PyObject *call(const char *name, Py_ssize_t want, Py_ssize_t n, F f)
+// sws_out_len for numbers of 31 bits; 0: not for here
+int64_t out_len(int64_t n, int64_t w, int64_t stride, int64_t pad, int64_t dilation = 1)
 {
+    if (w < 1 || stride < 1 || dilation < 1) return 0;
+    const int64_t left = n + 2 * pad - dilation * (w - 1) - 1;
+    return left < 0 ? 0 : left / stride + 1;
+}
+
+// f(call): false where the call is not for here
+template <class F>
+PyObject *call(const char *name, PyObject *const *a, Py_ssize_t want, Py_ssize_t n, F f)
+{
+    if (n != want || c10::impl::TorchDispatchModeTLS::any_modes_set() || at::impl::torch_function_mode_enabled()) Py_RETURN_NONE;
     try {
-        if (n != want || c10::impl::TorchDispatchModeTLS::any_modes_set() || at::impl::torch_function_mode_enabled()) throw Odd();
-        Call c;
-        c.name = name;
-        c.device = c10::hip::current_device();
-        c.stream = c10::hip::getCurrentHIPStream((c10::DeviceIndex)c.device).stream();
-        f(c);
+        Call c{a};
+        if (!f(c)) Py_RETURN_NONE;
         if (c.rc == SWS_OK) return THPVariable_Wrap(std::move(c.out));
         PyObject *e = PyObject_CallFunction(g_error, "is", c.rc, name);
         if (e) {
@@ -112,121 +101,154 @@ PyObject *call(const char *name, Py_ssize_t want, Py_ssize_t n, F f)
             Py_DECREF(e);
         }
         return nullptr;
-    } catch (...) {                                   // (what torch throws too: the Python code meets it again)
+    } catch (...) {                                   // (what torch throws, no memory for one: the Python code meets it again)
         PyErr_Clear();
         Py_RETURN_NONE;
     }
 }
 
 typedef const float *fp;
-#define SWS_CALL(NAME, N) PyObject *NAME(PyObject *, PyObject *const *a, Py_ssize_t n) { return call("sws_" #NAME, N, n, [&](Call &c)
+#define SWS_CALL(NAME, N) PyObject *NAME(PyObject *, PyObject *const *a, Py_ssize_t n) { return call("sws_" #NAME, a, N, n, [](Call &c) -> bool
 #define SWS_END ); }
 
-c10::SmallVector<int64_t, 6> with_last(const at::Tensor &t, int64_t last)
-{
-    same(t.dim() >= 1);
-    c10::SmallVector<int64_t, 6> s(t.sizes().begin(), t.sizes().end());
-    s.back() = last;
-    return s;
-}
 int64_t rows(const at::Tensor &t) { return t.numel() / t.size(-1); }
 
+// the sliding sums: rows of x shortened to lo
+template <class F>
+bool along_rows(Call &c, const at::Tensor &x, int64_t lo, F f)
+{
+    if (lo < 1) return false;
+    c10::SmallVector<int64_t, 6> shape(x.sizes().begin(), x.sizes().end());
+    shape.back() = lo;
+    const void *const p = x.data_ptr();
+    const int64_t many = rows(x), length = x.size(-1);
+    return c.run(shape, x, [&](void *y, hipStream_t s) { return f(p, y, many, length, s); });
+}
+
 SWS_CALL(slide1d, 4) {
-    const int op = num(a[0]), w = num(a[2]);
-    const at::Tensor &x = f32(a[1], c.device);
-    const auto shape = with_last(x, out_len(x.dim() ? x.size(-1) : 0, w, 1, 0));
-    float *y = (float *)c.alloc(shape, x);
-    c.go(sws_slide1d, op, (fp)x.data_ptr(), y, rows(x), x.size(-1), w, real(a[3]));
+    const int op = c.num(0), w = c.num(2);
+    const float scale = c.real(3);
+    const at::Tensor &x = c.tensor(1);
+    if (c.odd || x.dim() < 1) return false;
+    return along_rows(c, x, out_len(x.size(-1), w, 1, 0), [=](const void *p, void *y, int64_t many, int64_t length, hipStream_t s) {
+        return sws_slide1d((sws_op)op, (fp)p, (float *)y, many, length, w, scale, s);
+    });
 } SWS_END
 
 SWS_CALL(slide1d_16, 4) {
-    int dt = 0;
-    const int op = num(a[0]), w = num(a[2]);
-    const at::Tensor &x = half(a[1], c.device, &dt);
-    const auto shape = with_last(x, out_len(x.dim() ? x.size(-1) : 0, w, 1, 0));
-    void *y = c.alloc(shape, x);
-    c.go(sws_slide1d_16, op, dt, (const void *)x.data_ptr(), y, rows(x), x.size(-1), w, real(a[3]));
+    const int op = c.num(0), w = c.num(2);
+    const float scale = c.real(3);
+    const at::Tensor &x = c.tensor(1, true);
+    if (c.odd || x.dim() < 1) return false;
+    const int dt = c.dtype(x);
+    return along_rows(c, x, out_len(x.size(-1), w, 1, 0), [=](const void *p, void *y, int64_t many, int64_t length, hipStream_t s) {
+        return sws_slide1d_16((sws_op)op, (sws_dtype)dt, p, y, many, length, w, scale, s);
+    });
 } SWS_END
 
 SWS_CALL(slide1d_padded, 7) {
-    const int op = num(a[0]), w = num(a[2]), left = num(a[3]), right = num(a[4]), mode = num(a[5]);
-    const at::Tensor &x = f32(a[1], c.device);
-    same(x.dim() >= 1 && x.size(-1) > 0);
-    const auto shape = with_last(x, out_len(x.size(-1) + left + right, w, 1, 0));
-    float *y = (float *)c.alloc(shape, x);
-    c.go(sws_slide1d_padded, op, (fp)x.data_ptr(), y, rows(x), x.size(-1), w, left, right, mode, real(a[6]));
+    const int op = c.num(0), w = c.num(2), left = c.num(3), right = c.num(4), mode = c.num(5);
+    const float scale = c.real(6);
+    const at::Tensor &x = c.tensor(1);
+    if (c.odd || x.dim() < 1 || x.size(-1) < 1) return false;
+    return along_rows(c, x, out_len(x.size(-1) + left + right, w, 1, 0), [=](const void *p, void *y, int64_t many, int64_t length, hipStream_t s) {
+        return sws_slide1d_padded((sws_op)op, (fp)p, (float *)y, many, length, w, left, right, (sws_pad_mode)mode, scale, s);
+    });
 } SWS_END
 
 SWS_CALL(pool2d, 9) {
-    const int op = num(a[0]), kh = num(a[2]), kw = num(a[3]), sh = num(a[4]), sw = num(a[5]), ph = num(a[6]), pw = num(a[7]);
-    const at::Tensor &x = f32(a[1], c.device);
-    same(x.dim() == 4);
-    float *y = (float *)c.alloc(at::IntArrayRef{x.size(0), x.size(1), out_len(x.size(2), kh, sh, ph), out_len(x.size(3), kw, sw, pw)}, x);
-    c.go(sws_pool2d, op, (fp)x.data_ptr(), y, x.size(0), x.size(1), x.size(2), x.size(3), kh, kw, sh, sw, ph, pw, real(a[8]));
+    const int op = c.num(0), kh = c.num(2), kw = c.num(3), sh = c.num(4), sw = c.num(5), ph = c.num(6), pw = c.num(7);
+    const float scale = c.real(8);
+    const at::Tensor &x = c.tensor(1);
+    if (c.odd || x.dim() != 4) return false;
+    const int64_t N = x.size(0), C = x.size(1), H = x.size(2), W = x.size(3), ho = out_len(H, kh, sh, ph), wo = out_len(W, kw, sw, pw);
+    if (ho < 1 || wo < 1) return false;
+    const fp p = (fp)x.data_ptr();
+    return c.run({N, C, ho, wo}, x, [=](void *y, hipStream_t s) { return sws_pool2d((sws_op)op, p, (float *)y, N, C, H, W, kh, kw, sh, sw, ph, pw, scale, s); });
 } SWS_END
 
 SWS_CALL(pool2d_16, 9) {
-    int dt = 0;
-    const int op = num(a[0]), kh = num(a[2]), kw = num(a[3]), sh = num(a[4]), sw = num(a[5]), ph = num(a[6]), pw = num(a[7]);
-    const at::Tensor &x = half(a[1], c.device, &dt);
-    same(x.dim() == 4);
-    void *y = c.alloc(at::IntArrayRef{x.size(0), x.size(1), out_len(x.size(2), kh, sh, ph), out_len(x.size(3), kw, sw, pw)}, x);
-    c.go(sws_pool2d_16, op, dt, (const void *)x.data_ptr(), y, x.size(0), x.size(1), x.size(2), x.size(3), kh, kw, sh, sw, ph, pw, real(a[8]));
+    const int op = c.num(0), kh = c.num(2), kw = c.num(3), sh = c.num(4), sw = c.num(5), ph = c.num(6), pw = c.num(7);
+    const float scale = c.real(8);
+    const at::Tensor &x = c.tensor(1, true);
+    if (c.odd || x.dim() != 4) return false;
+    const int64_t N = x.size(0), C = x.size(1), H = x.size(2), W = x.size(3), ho = out_len(H, kh, sh, ph), wo = out_len(W, kw, sw, pw);
+    if (ho < 1 || wo < 1) return false;
+    const int dt = c.dtype(x);
+    const void *const p = x.data_ptr();
+    return c.run({N, C, ho, wo}, x, [=](void *y, hipStream_t s) { return sws_pool2d_16((sws_op)op, (sws_dtype)dt, p, y, N, C, H, W, kh, kw, sh, sw, ph, pw, scale, s); });
 } SWS_END
 
 SWS_CALL(maxpool2d_grad, 8) {
-    const int kh = num(a[2]), kw = num(a[3]), sh = num(a[4]), sw = num(a[5]), ph = num(a[6]), pw = num(a[7]);
-    const at::Tensor &x = f32(a[0], c.device), &gy = f32(a[1], c.device);
-    same(x.dim() == 4 && gy.dim() == 4 && gy.size(0) == x.size(0) && gy.size(1) == x.size(1) &&
-         gy.size(2) == out_len(x.size(2), kh, sh, ph) && gy.size(3) == out_len(x.size(3), kw, sw, pw));
-    float *gx = (float *)c.alloc(x.sizes(), x);
-    c.go(sws_maxpool2d_grad, (fp)x.data_ptr(), (fp)gy.data_ptr(), gx, x.size(0), x.size(1), x.size(2), x.size(3), kh, kw, sh, sw, ph, pw);
+    const int kh = c.num(2), kw = c.num(3), sh = c.num(4), sw = c.num(5), ph = c.num(6), pw = c.num(7);
+    const at::Tensor &x = c.tensor(0), &gy = c.tensor(1);
+    if (c.odd || x.dim() != 4 || gy.dim() != 4) return false;
+    const int64_t N = x.size(0), C = x.size(1), H = x.size(2), W = x.size(3), ho = out_len(H, kh, sh, ph), wo = out_len(W, kw, sw, pw);
+    if (ho < 1 || wo < 1 || gy.size(0) != N || gy.size(1) != C || gy.size(2) != ho || gy.size(3) != wo) return false;
+    const fp p = (fp)x.data_ptr(), q = (fp)gy.data_ptr();
+    return c.run({N, C, H, W}, x, [=](void *gx, hipStream_t s) { return sws_maxpool2d_grad(p, q, (float *)gx, N, C, H, W, kh, kw, sh, sw, ph, pw, s); });
 } SWS_END
 
 SWS_CALL(avgpool2d_grad, 11) {
-    const int h = num(a[1]), w = num(a[2]), kh = num(a[3]), kw = num(a[4]), sh = num(a[5]), sw = num(a[6]), ph = num(a[7]), pw = num(a[8]), div = num(a[9]);
-    const at::Tensor &gy = f32(a[0], c.device);
-    same(gy.dim() == 4 && gy.size(2) == out_len(h, kh, sh, ph) && gy.size(3) == out_len(w, kw, sw, pw));
-    float *gx = (float *)c.alloc(at::IntArrayRef{gy.size(0), gy.size(1), h, w}, gy);
-    c.go(sws_avgpool2d_grad, (fp)gy.data_ptr(), gx, gy.size(0), gy.size(1), (int64_t)h, (int64_t)w, kh, kw, sh, sw, ph, pw, div, real(a[10]));
+    const int H = c.num(1), W = c.num(2), kh = c.num(3), kw = c.num(4), sh = c.num(5), sw = c.num(6), ph = c.num(7), pw = c.num(8), div = c.num(9);
+    const float scale = c.real(10);
+    const at::Tensor &gy = c.tensor(0);
+    if (c.odd || gy.dim() != 4) return false;
+    const int64_t N = gy.size(0), C = gy.size(1), ho = out_len(H, kh, sh, ph), wo = out_len(W, kw, sw, pw);
+    if (ho < 1 || wo < 1 || gy.size(2) != ho || gy.size(3) != wo) return false;
+    const fp p = (fp)gy.data_ptr();
+    return c.run({N, C, H, W}, gy, [=](void *gx, hipStream_t s) {
+        return sws_avgpool2d_grad(p, (float *)gx, N, C, H, W, kh, kw, sh, sw, ph, pw, (sws_divisor)div, scale, s);
+    });
 } SWS_END
 
 // layers of several groups: none of their kernels uses a workspace
 SWS_CALL(conv1d, 6) {
-    const int stride = num(a[2]), pad = num(a[3]), dil = num(a[4]), groups = num(a[5]);
-    const at::Tensor &x = f32(a[0], c.device), &w = f32(a[1], c.device);
-    same(x.dim() == 3 && w.dim() == 3 && groups > 1 && w.size(1) * groups == x.size(1));
-    float *y = (float *)c.alloc(at::IntArrayRef{x.size(0), w.size(0), out_len(x.size(2), w.size(2), stride, pad, dil)}, x);
-    c.go(sws_conv1d, (fp)x.data_ptr(), (fp)w.data_ptr(), y, x.size(0), x.size(1), x.size(2), w.size(0), (int32_t)w.size(2), stride, pad, dil, groups);
+    const int stride = c.num(2), pad = c.num(3), dil = c.num(4), groups = c.num(5);
+    const at::Tensor &x = c.tensor(0), &w = c.tensor(1);
+    if (c.odd || x.dim() != 3 || w.dim() != 3 || groups < 2) return false;
+    const int64_t b = x.size(0), cin = x.size(1), len = x.size(2), cout = w.size(0), k = w.size(2), lo = out_len(len, k, stride, pad, dil);
+    if (lo < 1 || w.size(1) * groups != cin) return false;
+    const fp p = (fp)x.data_ptr(), q = (fp)w.data_ptr();
+    return c.run({b, cout, lo}, x, [=](void *y, hipStream_t s) { return sws_conv1d(p, q, (float *)y, b, cin, len, cout, (int32_t)k, stride, pad, dil, groups, s); });
 } SWS_END
 
 SWS_CALL(conv1d_16, 6) {
-    int dt = 0;
-    const int stride = num(a[2]), pad = num(a[3]), dil = num(a[4]), groups = num(a[5]);
-    const at::Tensor &x = half(a[0], c.device, &dt), &w = f32(a[1], c.device);
-    same(x.dim() == 3 && w.dim() == 3 && w.size(1) * groups == x.size(1));
-    void *y = c.alloc(at::IntArrayRef{x.size(0), w.size(0), out_len(x.size(2), w.size(2), stride, pad, dil)}, x);
-    c.go(sws_conv1d_16, dt, (const void *)x.data_ptr(), (fp)w.data_ptr(), y, x.size(0), x.size(1), x.size(2), w.size(0), (int32_t)w.size(2), stride, pad, dil,
-         groups);
+    const int stride = c.num(2), pad = c.num(3), dil = c.num(4), groups = c.num(5);
+    const at::Tensor &x = c.tensor(0, true), &w = c.tensor(1);
+    if (c.odd || x.dim() != 3 || w.dim() != 3) return false;
+    const int64_t b = x.size(0), cin = x.size(1), len = x.size(2), cout = w.size(0), k = w.size(2), lo = out_len(len, k, stride, pad, dil);
+    if (lo < 1 || w.size(1) * groups != cin) return false;
+    const int dt = c.dtype(x);
+    const void *const p = x.data_ptr();
+    const fp q = (fp)w.data_ptr();
+    return c.run({b, cout, lo}, x, [=](void *y, hipStream_t s) {
+        return sws_conv1d_16((sws_dtype)dt, p, q, y, b, cin, len, cout, (int32_t)k, stride, pad, dil, groups, s);
+    });
 } SWS_END
 
 SWS_CALL(conv1d_grad_input, 7) {
-    const int length = num(a[2]), stride = num(a[3]), pad = num(a[4]), dil = num(a[5]), groups = num(a[6]);
-    const at::Tensor &gy = f32(a[0], c.device), &w = f32(a[1], c.device);
-    same(gy.dim() == 3 && w.dim() == 3 && groups > 1 && w.size(0) == gy.size(1) && gy.size(2) == out_len(length, w.size(2), stride, pad, dil));
-    const int64_t cin = w.size(1) * groups;
-    float *gx = (float *)c.alloc(at::IntArrayRef{gy.size(0), cin, length}, gy);
-    c.go(sws_conv1d_grad_input, (fp)gy.data_ptr(), (fp)w.data_ptr(), gx, gy.size(0), cin, (int64_t)length, gy.size(1), (int32_t)w.size(2), stride, pad, dil,
-         groups);
+    const int len = c.num(2), stride = c.num(3), pad = c.num(4), dil = c.num(5), groups = c.num(6);
+    const at::Tensor &gy = c.tensor(0), &w = c.tensor(1);
+    if (c.odd || gy.dim() != 3 || w.dim() != 3 || groups < 2) return false;
+    const int64_t b = gy.size(0), cout = gy.size(1), lo = gy.size(2), cin = w.size(1) * groups, k = w.size(2);
+    if (lo < 1 || w.size(0) != cout || lo != out_len(len, k, stride, pad, dil)) return false;
+    const fp p = (fp)gy.data_ptr(), q = (fp)w.data_ptr();
+    return c.run({b, cin, len}, gy, [=](void *gx, hipStream_t s) {
+        return sws_conv1d_grad_input(p, q, (float *)gx, b, cin, len, cout, (int32_t)k, stride, pad, dil, groups, s);
+    });
 } SWS_END
 
 SWS_CALL(conv1d_grad_weight, 7) {
-    const int k = num(a[2]), stride = num(a[3]), pad = num(a[4]), dil = num(a[5]), groups = num(a[6]);
-    const at::Tensor &x = f32(a[0], c.device), &gy = f32(a[1], c.device);
-    same(x.dim() == 3 && gy.dim() == 3 && groups > 1 && gy.size(0) == x.size(0) && x.size(1) % groups == 0 &&
-         gy.size(2) == out_len(x.size(2), k, stride, pad, dil));
-    float *gw = (float *)c.alloc(at::IntArrayRef{gy.size(1), x.size(1) / groups, k}, x);
-    c.go(sws_conv1d_grad_weight, (fp)x.data_ptr(), (fp)gy.data_ptr(), gw, x.size(0), x.size(1), x.size(2), gy.size(1), k, stride, pad, dil, groups);
+    const int k = c.num(2), stride = c.num(3), pad = c.num(4), dil = c.num(5), groups = c.num(6);
+    const at::Tensor &x = c.tensor(0), &gy = c.tensor(1);
+    if (c.odd || x.dim() != 3 || gy.dim() != 3 || groups < 2) return false;
+    const int64_t b = x.size(0), cin = x.size(1), len = x.size(2), cout = gy.size(1), lo = gy.size(2);
+    if (lo < 1 || gy.size(0) != b || cin % groups != 0 || lo != out_len(len, k, stride, pad, dil)) return false;
+    const fp p = (fp)x.data_ptr(), q = (fp)gy.data_ptr();
+    return c.run({cout, cin / groups, k}, x, [=](void *gw, hipStream_t s) {
+        return sws_conv1d_grad_weight(p, q, (float *)gw, b, cin, len, cout, k, stride, pad, dil, groups, s);
+    });
 } SWS_END
 
 PyObject *set_error(PyObject *, PyObject *cls)

@@ -1,4 +1,6 @@
 """The binding's native calls (csrc/calls.cpp) against its Python code: the same bits, and None for whatever is out of the ordinary."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -26,6 +28,22 @@ def test_calls_out_of_the_ordinary_are_left_to_python(native, name):
     for x in (None, 3, "x", torch.zeros(2, 2, 9), torch.zeros(2, 2, 4, 4), np.zeros((2, 9), np.float32)):
         assert f(*[x if a is None else a for a in args]) is None
     assert f() is None and f(*args, 1) is None
+
+
+@pytest.mark.parametrize("name", ODD)
+def test_refusing_takes_next_to_nothing(native, name):
+    """The Python code's time is all that a call costs that is left to it.  (By a C++ exception a refusal took 35 times as long as a call of len().)"""
+    def least(f):
+        def once():
+            t = time.perf_counter()
+            for _ in range(50):
+                f()
+            return time.perf_counter() - t
+        return min(once() for _ in range(200))
+
+    f, args = getattr(native, name), ODD[name]
+    x = [torch.zeros(2, 2, 9) if a is None else a for a in args]
+    assert least(lambda: f(*x)) < 15 * least(lambda: len(()))
 
 
 def _all(train=True):
@@ -101,3 +119,18 @@ def test_native_calls_refuse_what_python_refuses(native):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, want)
+
+
+@pytest.mark.gpu
+def test_native_calls_take_the_numbers_that_the_python_code_takes(native):
+    """Scales of types derived from float, negative whole ones and truth values; what is refused has not allocated an output."""
+    x = torch.randn(2, 64, device="cuda")
+    for scale in (np.float64(0.25), -2, True):
+        y = native.slide1d(B.OP_ADD, x, 5, scale)
+        assert y is not None and torch.equal(y, B.sws_slide1d(B.OP_ADD, x, 5, float(scale)))
+    assert torch.equal(native.slide1d(True, x, True, 1.0), B.sws_slide1d(B.OP_MAX, x, 1))
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    assert native.slide1d(B.OP_ADD, x, 5, np.float32(0.25)) is None and native.slide1d(B.OP_ADD, x, 5, 1 << 70) is None
+    assert native.slide1d(B.OP_ADD, x, 5, "1") is None and native.slide1d(B.OP_ADD, x, 1 << 31, 1.0) is None
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
