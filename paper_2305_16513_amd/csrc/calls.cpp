@@ -65,15 +65,17 @@ struct Call {
     }
     static int dtype(const at::Tensor &t) { return t.scalar_type() == at::kHalf ? SWS_DTYPE_F16 : SWS_DTYPE_BF16; }
 
-    // The output, of x's type, and the library's call on it: f(address, stream)
+    // The output, of x's type, and the library's call on it: f(address, stream).  Others run meanwhile: the allocator may wait for the device.
     template <class F> bool run(at::IntArrayRef sizes, const at::Tensor &x, F f)
     {
+        const at::TensorOptions like = x.options();
         const hipStream_t stream = c10::hip::getCurrentHIPStream((c10::DeviceIndex)device).stream();
-        out = at::empty(sizes, x.options());
-        void *const y = out.data_ptr();
-        PyThreadState *const save = PyEval_SaveThread();
-        rc = f(y, stream);
-        PyEval_RestoreThread(save);
+        struct Unlocked {
+            PyThreadState *state = PyEval_SaveThread();
+            ~Unlocked() { PyEval_RestoreThread(state); }
+        } unlocked;
+        out = at::empty(sizes, like);
+        rc = f(out.data_ptr(), stream);
         return true;
     }
 };

@@ -134,3 +134,40 @@ def test_native_calls_take_the_numbers_that_the_python_code_takes(native):
     assert native.slide1d(B.OP_ADD, x, 5, np.float32(0.25)) is None and native.slide1d(B.OP_ADD, x, 5, 1 << 70) is None
     assert native.slide1d(B.OP_ADD, x, 5, "1") is None and native.slide1d(B.OP_ADD, x, 1 << 31, 1.0) is None
     assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+
+
+@pytest.mark.gpu
+def test_other_threads_run_while_an_output_is_allocated(native):
+    """16 GB from the device take half a millisecond, in which the allocator may also wait for it.  The longest time that another thread's loop stands still is 4 - 17 % of
+    the call; with the interpreter locked it was 87 %."""
+    import sys
+    import threading
+    x = torch.zeros(8, 1 << 29, device="cuda")
+    native.slide1d(B.OP_ADD, x[:, :64].contiguous(), 5, 1.0)
+    interval, shares = sys.getswitchinterval(), []
+    sys.setswitchinterval(1e-5)
+    try:
+        for _ in range(6):
+            torch.cuda.synchronize()
+            torch.cuda.empty_cache()
+            ticks, done = [], threading.Event()
+
+            def watch():
+                while not done.is_set() and len(ticks) < 1000000:
+                    ticks.append(time.perf_counter())
+
+            other = threading.Thread(target=watch)
+            other.start()
+            time.sleep(0.005)
+            begin = time.perf_counter()
+            y = native.slide1d(B.OP_ADD, x, 5, 1.0)
+            end = time.perf_counter()
+            time.sleep(0.002)
+            done.set()
+            other.join()
+            assert y is not None
+            del y
+            shares.append(max(b - a for a, b in zip(ticks, ticks[1:]) if b > begin and a < end) / (end - begin))
+    finally:
+        sys.setswitchinterval(interval)
+    assert min(shares) < 0.5, shares
