@@ -114,14 +114,17 @@ def lib():
 
 
 def _load_calls():
-    """The native calls, beside the library that they are linked to.  They hold torch's C++ interface of the version that they were
-    built with; where they do not load, the Python code serves every call."""
+    """The native calls, where the library is the one beside them, which they are linked to, and torch the version whose C++ interface they
+    were built with.  Elsewhere, and where they are not built, the Python code serves every call."""
     global _calls
-    if not os.path.samefile(os.path.dirname(LIB_PATH), _HERE):
-        return
+    _calls = None
     try:
+        if not os.path.samefile(LIB_PATH, os.path.join(_HERE, "libsws.so")):
+            return
         from . import _calls as native
-    except ImportError:
+        if native.torch_version != torch.__version__:
+            return
+    except (ImportError, OSError, AttributeError):
         return
     native.set_error(SwsError)
     _calls = native

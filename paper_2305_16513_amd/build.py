@@ -64,7 +64,7 @@ def _build_calls():
     inc = os.path.join(os.path.dirname(torch.__file__), "include")
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", os.path.join(ROOT, "include"),
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DSWS_TORCH_VERSION="%s"' % torch.__version__, "-I", os.path.join(ROOT, "include"),
            "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
            "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "calls.cpp"), "-o", os.path.join(HERE, "_calls.so"),
            "-L", HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN", "-L", lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]

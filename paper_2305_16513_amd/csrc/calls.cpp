@@ -269,4 +269,13 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__calls() { return PyModule_Create(&module_def); }
+// torch_version: the one whose headers this was built with, for binding.py to compare
+PyMODINIT_FUNC PyInit__calls()
+{
+    PyObject *m = PyModule_Create(&module_def);
+    if (m && PyModule_AddStringConstant(m, "torch_version", SWS_TORCH_VERSION) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

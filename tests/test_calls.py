@@ -46,6 +46,35 @@ def test_refusing_takes_next_to_nothing(native, name):
     assert least(lambda: f(*x)) < 15 * least(lambda: len(()))
 
 
+def _loaded(monkeypatch):
+    """What a first use of the library takes the native calls to be."""
+    real = B.lib()
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_calls", None)
+    monkeypatch.setattr(B.ctypes, "CDLL", lambda path: real)
+    assert B.lib() is real
+    return B._calls
+
+
+def test_native_calls_are_not_taken_for_another_torch(native, monkeypatch):
+    assert _loaded(monkeypatch) is native
+    monkeypatch.setattr(torch, "__version__", torch.__version__ + ".other")
+    assert _loaded(monkeypatch) is None
+
+
+def test_native_calls_are_not_taken_for_another_library(native, monkeypatch, tmp_path):
+    """They call the library that they are linked to; options would go to the other one."""
+    (tmp_path / "libother.so").write_bytes(b"")
+    with monkeypatch.context() as m:                  # another file, in the folder that the native calls are looked for beside
+        m.setattr(B, "_HERE", str(tmp_path))
+        m.setattr(B, "LIB_PATH", str(tmp_path / "libother.so"))
+        assert _loaded(m) is None
+    with monkeypatch.context() as m:                  # a path without a folder
+        m.chdir(tmp_path)
+        m.setattr(B, "LIB_PATH", "libother.so")
+        assert _loaded(m) is None
+
+
 def _all(train=True):
     g = torch.Generator(device="cuda").manual_seed(5)
     r = lambda *s: torch.randn(s, generator=g, device="cuda")
