@@ -1,4 +1,7 @@
 """The binding's native calls (csrc/calls.cpp) against its Python code: the same bits, and None for whatever is out of the ordinary."""
+import builtins
+import os
+import shutil
 import time
 
 import numpy as np
@@ -11,8 +14,9 @@ from paper_2305_16513_amd import binding as B
 @pytest.fixture(scope="module")
 def native():
     B.lib()
-    if B._calls is None:
+    if B._calls is None and shutil.which("g++") is None:
         pytest.skip("not built")
+    assert B._calls is not None, "not built, or for another torch"
     return B._calls
 
 
@@ -73,6 +77,38 @@ def test_native_calls_are_not_taken_for_another_library(native, monkeypatch, tmp
         m.chdir(tmp_path)
         m.setattr(B, "LIB_PATH", "libother.so")
         assert _loaded(m) is None
+
+
+@pytest.mark.parametrize("missing", ["torch", "g++", "headers"])
+def test_the_library_is_built_without_what_only_the_native_calls_need(monkeypatch, tmp_path, capsys, missing):
+    """... and old native calls don't stay beside a new library."""
+    from paper_2305_16513_amd import build
+    lib, calls = tmp_path / "libsws.so", tmp_path / "_calls.so"
+    calls.write_bytes(b"old")
+    real_run, real_import = build.subprocess.run, builtins.__import__
+
+    def run(cmd, **k):
+        if cmd[0] == "hipcc":                         # (compiling and linking the library: as if)
+            if "-shared" in cmd:
+                lib.write_bytes(b"new")
+            return build.subprocess.CompletedProcess(cmd, 0, "", "")
+        if missing == "g++":
+            raise FileNotFoundError("g++")
+        return real_run(["false"], **k)
+
+    def imports(name, *a):
+        if missing == "torch" and name == "torch":
+            raise ImportError("no torch")
+        return real_import(name, *a)
+
+    monkeypatch.setattr(build, "LIB", str(lib))
+    monkeypatch.setattr(build, "CALLS", str(calls), raising=False)
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build, "OBJ", str(tmp_path / "obj"))
+    monkeypatch.setattr(build.subprocess, "run", run)
+    monkeypatch.setattr(builtins, "__import__", imports)
+    assert build.build() == str(lib)
+    assert lib.read_bytes() == b"new" and not os.path.exists(calls) and "without native calls" in capsys.readouterr().err
 
 
 def _all(train=True):
