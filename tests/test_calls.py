@@ -111,51 +111,114 @@ def test_the_library_is_built_without_what_only_the_native_calls_need(monkeypatc
     assert lib.read_bytes() == b"new" and not os.path.exists(calls) and "without native calls" in capsys.readouterr().err
 
 
-def _all(train=True):
+def _all():
+    """name of the native function, keyword of the output, the call"""
     g = torch.Generator(device="cuda").manual_seed(5)
     r = lambda *s: torch.randn(s, generator=g, device="cuda")
     x, p, w, gy = r(3, 4, 1001), r(2, 5, 9, 11), r(4, 1, 7), r(3, 4, 1001)
-    h, ph = x.bfloat16(), p.half()
-    yield "slide1d", lambda **k: B.sws_slide1d(B.OP_ADD, x, 5, 0.2, **k)
-    yield "slide1d int scale", lambda **k: B.sws_slide1d(B.OP_MAX, x, 5, 2, **k)
-    yield "slide1d_16", lambda **k: B.sws_slide1d_16(B.OP_ADD, h, 64, 1 / 64, **k)
-    yield "slide1d_padded", lambda **k: B.sws_slide1d_padded(B.OP_MIN, x, 6, 2, 3, B.SWS_PAD_MIRROR, **k)
-    yield "pool2d", lambda **k: B.sws_pool2d(B.OP_ADD, p, 3, 2, 2, 1, 1, 0, 1 / 6, **k)
-    yield "pool2d_16", lambda **k: B.sws_pool2d_16(B.OP_MAX, ph, 3, 3, 2, 2, 1, 1, **k)
-    yield "conv1d", lambda **k: B.sws_conv1d(x, w, 1, 3, 1, 4, **k)
-    yield "conv1d_16", lambda **k: B.sws_conv1d_16(h, w, 1, 3, 1, 4, **k)
-    yield "conv1d strided", lambda **k: B.sws_conv1d(x, w, 2, 3, 2, 4, **k)
-    if train:
-        yield "maxpool2d_grad", lambda **k: B.sws_maxpool2d_grad(p, r(2, 5, 5, 6) * 0 + 1, 3, 3, 2, 2, 1, 1, **k)
-        yield "avgpool2d_grad", lambda **k: B.sws_avgpool2d_grad(p, 9, 11, 3, 3, 1, 1, 1, 1, B.SWS_DIV_REAL_CELLS, 1.0, **k)
-        yield "conv1d_grad_input", lambda **k: B.sws_conv1d_grad_input(gy, w, 1001, 1, 3, 1, 4, **k)
-        yield "conv1d_grad_weight", lambda **k: B.sws_conv1d_grad_weight(x, gy, 7, 1, 3, 1, 4, **k)
+    h, ph, ones = x.bfloat16(), p.half(), torch.ones(2, 5, 5, 6, device="cuda")
+    yield "slide1d", "y", lambda **k: B.sws_slide1d(B.OP_ADD, x, 5, 0.2, **k)
+    yield "slide1d", "y", lambda **k: B.sws_slide1d(B.OP_MAX, x, 5, 2, **k)
+    yield "slide1d_16", "y", lambda **k: B.sws_slide1d_16(B.OP_ADD, h, 64, 1 / 64, **k)
+    yield "slide1d_padded", "y", lambda **k: B.sws_slide1d_padded(B.OP_MIN, x, 6, 2, 3, B.SWS_PAD_MIRROR, **k)
+    yield "pool2d", "y", lambda **k: B.sws_pool2d(B.OP_ADD, p, 3, 2, 2, 1, 1, 0, 1 / 6, **k)
+    yield "pool2d_16", "y", lambda **k: B.sws_pool2d_16(B.OP_MAX, ph, 3, 3, 2, 2, 1, 1, **k)
+    yield "conv1d", "y", lambda **k: B.sws_conv1d(x, w, 1, 3, 1, 4, **k)
+    yield "conv1d_16", "y", lambda **k: B.sws_conv1d_16(h, w, 1, 3, 1, 4, **k)
+    yield "conv1d", "y", lambda **k: B.sws_conv1d(x, w, 2, 3, 2, 4, **k)
+    yield "maxpool2d_grad", "gx", lambda **k: B.sws_maxpool2d_grad(p, ones, 3, 3, 2, 2, 1, 1, **k)
+    yield "avgpool2d_grad", "gx", lambda **k: B.sws_avgpool2d_grad(p, 9, 11, 3, 3, 1, 1, 1, 1, B.SWS_DIV_REAL_CELLS, 1.0, **k)
+    yield "conv1d_grad_input", "gx", lambda **k: B.sws_conv1d_grad_input(gy, w, 1001, 1, 3, 1, 4, **k)
+    yield "conv1d_grad_weight", "gw", lambda **k: B.sws_conv1d_grad_weight(x, gy, 7, 1, 3, 1, 4, **k)
+
+
+class _Noting:
+    """The native calls, and which of them were asked and which of those answered."""
+
+    def __init__(self, native):
+        self.native, self.asked, self.answered = native, [], []
+
+    def __getattr__(self, name):
+        def f(*a):
+            self.asked.append(name)
+            y = getattr(self.native, name)(*a)
+            if y is not None:
+                self.answered.append(name)
+            return y
+        return f
 
 
 @pytest.mark.gpu
 def test_native_calls_give_the_bits_of_the_python_code(native, monkeypatch):
-    side = torch.cuda.Stream()
-    for name, f in _all():
-        got = f()
+    side, seen = torch.cuda.Stream(), set()
+    for name, key, f in _all():
+        noting = _Noting(native)
         monkeypatch.setattr(B, "_calls", None)
         want = f()
-        monkeypatch.setattr(B, "_calls", native)
+        monkeypatch.setattr(B, "_calls", noting)
+        got = f()
         torch.cuda.synchronize()
         with torch.cuda.stream(side):
             other = f()
         side.synchronize()
-        for y in (got, other):
+        assert noting.answered == [name, name], name
+        seen.add(name)
+        out = torch.empty_like(want)                  # an output of the caller's, a stream handed over: the Python code, without asking
+        assert f(**{key: out}) is out
+        torch.cuda.synchronize()
+        handed = f(stream=side)
+        side.synchronize()
+        assert noting.asked == [name, name], name
+        for y in (got, other, out, handed):
             assert type(y) is torch.Tensor and y.shape == want.shape and y.dtype == want.dtype and y.is_contiguous() and not y.requires_grad
-            if name == "conv1d_grad_weight":                                 # (atomic adds: no fixed order)
+            if name == "conv1d_grad_weight":          # (atomic adds: no fixed order)
                 assert torch.allclose(y, want, rtol=1e-5, atol=1e-4)
             else:
                 assert torch.equal(y, want), name
-        for k in ("y", "gx", "gw"):                                          # an output of the caller's, a stream handed over: the Python code
-            try:
-                out = torch.empty_like(want)
-                assert f(**{k: out}) is out
-            except TypeError:
-                continue
+    assert seen == set(ODD)
+
+
+@pytest.mark.gpu
+def test_native_calls_leave_watched_and_wrapped_tensors_to_python(native, monkeypatch):
+    from torch.overrides import TorchFunctionMode
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Functions(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    class Dispatch(TorchDispatchMode):
+        seen = 0
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            Dispatch.seen += 1
+            return func(*args, **(kwargs or {}))
+
+    class Sub(torch.Tensor):
+        pass
+
+    x = torch.randn(3, 200, device="cuda")
+    want = native.slide1d(B.OP_ADD, x, 5, 0.2)
+    assert torch.equal(native.slide1d(B.OP_ADD, torch.nn.Parameter(x), 5, 0.2), want)        # (a plain tensor)
+    noting = _Noting(native)
+    monkeypatch.setattr(B, "_calls", noting)
+    with Functions():
+        y = B.sws_slide1d(B.OP_ADD, x, 5, 0.2)
+    with Dispatch():
+        z = B.sws_slide1d(B.OP_ADD, x, 5, 0.2)
+    assert torch.equal(y, want) and torch.equal(z, want) and Dispatch.seen > 0               # (the output's allocation is seen)
+    assert torch.equal(B.sws_slide1d(B.OP_ADD, x.as_subclass(Sub), 5, 0.2).as_subclass(torch.Tensor), want)
+    assert noting.asked == ["slide1d"] * 3 and not noting.answered
+    inside = []
+    torch.func.vmap(lambda t: inside.append(native.slide1d(B.OP_ADD, t, 5, 0.2)) or t)(x)
+    torch.func.functionalize(lambda t: inside.append(native.slide1d(B.OP_ADD, t, 5, 0.2)) or t)(x)
+    torch.func.jvp(lambda t: inside.append(native.slide1d(B.OP_ADD, t, 5, 0.2)) or t, (x,), (x,))
+    inside.append(native.slide1d(B.OP_ADD, torch.empty(3, 200, device="meta"), 5, 0.2))
+    inside.append(native.slide1d(B.OP_ADD, x.to_sparse(), 5, 0.2))
+    inside.append(native.slide1d(B.OP_ADD, x.t(), 5, 0.2))
+    if torch.cuda.device_count() > 1:
+        inside.append(native.slide1d(B.OP_ADD, x.to("cuda:1"), 5, 0.2))
+    assert inside == [None] * len(inside) and len(inside) >= 6
 
 
 @pytest.mark.gpu
