@@ -42,3 +42,17 @@ def assert_within_tol(y_gpu, y_ref, abs_sum, what="", tol=TOL):
     with np.errstate(divide="ignore", invalid="ignore"):
         ratio = np.where(abs_sum > 0, err / abs_sum, 0.0)
     return float(ratio.max()) if ratio.size else 0.0
+
+
+def kernels(f):
+    """The names of this library's kernels that run in f(), with their template arguments: "conv_split_kernel<1, 2, ...>"."""
+    import re
+
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        f()
+        torch.cuda.synchronize()
+    names = [re.search(r"sws::(?:\(anonymous namespace\)::)?(\w+(?:<[^(]*>)?)\(", e.name) for e in p.events()]
+    return [n[1] for n in names if n]

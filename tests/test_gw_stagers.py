@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 from paper_2305_16513_amd import workloads
-from tests.parity_util import assert_bit_exact, assert_within_tol, to_gpu, to_host
+from tests.parity_util import assert_bit_exact, assert_within_tol, kernels, to_gpu, to_host
 from tests.test_parity_conv_split import SPLIT_TOL, B, _guarded, _taken, automatic, lent  # noqa: F401
 
 # n, cin, cout, h, w, pad: runs of rows as the planner cuts them (of 32 x 32 channels: the blocks of partial sums beside them)
@@ -20,10 +20,24 @@ RUNS = {(3, 320, 128, 18, 60, 1): 12 * 40,            # two strips, runs of half
         (24, 256, 32, 44, 30, 1): 32 * 8}             # the last strip six columns wide, groups of three images
 
 
-def test_the_plans_are_those_of_the_staged_kernel():
+# output channels in blocks of 32: four wavefronts add up
+ONE_BLOCK = {(16, 96, 160, 37, 38, 1)}
+
+
+def test_the_plans_are_those_that_the_runs_are_meant_for():
     from paper_2305_16513_amd import binding
     for (n, cin, cout, h, w, p), blocks in RUNS.items():
         assert binding.lib().sws_conv2d_grad_weight_workspace(n, cin, h, w, cout, 3, 3, 1, 1, p, p) == 4096 * 9 * blocks, (n, cin, cout, h, w, p)
+
+
+def _one_float_on(a):
+    """On the GPU, 4 bytes behind an address that allocations start at."""
+    import torch
+    flat = torch.empty(a.size + 1, device="cuda")
+    t = flat[1:].view(a.shape)
+    t.copy_(torch.from_numpy(a))
+    assert t.data_ptr() % 16 == 4
+    return t
 
 
 @pytest.mark.gpu
@@ -37,7 +51,10 @@ def test_staged_runs(B, case, lent):  # noqa: F811
         gy = workloads.integer_valued(gshape, -3, 3, 63) if integer else rng.standard_normal(gshape).astype(np.float32)
         ref, mag = oracle.conv2d_grad_weight(x, gy, 3, 3, 1, 1, p, p)
         flat, gw = _guarded(ref.shape)
-        B.sws_conv2d_grad_weight(to_gpu(x), to_gpu(gy), 3, 3, 1, 1, p, p, gw=gw)
+        # (the staging loads are of 16 and 8 bytes, which every tensor's alignment has to do for)
+        put = to_gpu if integer else _one_float_on
+        names = kernels(lambda: B.sws_conv2d_grad_weight(put(x), put(gy), 3, 3, 1, 1, p, p, gw=gw))
+        assert "conv_gw_staged_kernel<%d>" % (2 if cout > 32 and case not in ONE_BLOCK else 1) in names, names
         if integer:
             assert_bit_exact(to_host(gw), ref, "gw %s" % (case,))
         else:
