@@ -280,7 +280,10 @@ __global__ __launch_bounds__(WAVES * 64, (2 * WAVES + 3) / 4) void conv2d_mfma_c
                                                                        float *__restrict__ y, ConvGeom g,
                                                                        SegPlan sp)
 {
-    fetch_arguments<24 + sizeof(ConvGeom) + sizeof(SegPlan)>();
+    fetch_arguments<24 + sizeof(ConvGeom) + 4 * SEG>();
+    // (to 128 bytes with the 108 in front: the loops lie on the cache lines that they lay on without them.  20 bytes off, [24,256,45,45] -> 32, 3 x 3 takes 118 us for 114,
+    // [1,480,9,9] -> 64 203 for 199)
+    asm volatile("s_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
     // NB blocks of 8 input channels are staged per barrier pair (NB > 1 for few taps, where one
     // block is too little matrix work between two barriers).
     constexpr int CIB = 8, XP = 12;
