@@ -782,7 +782,8 @@ bool plan(const SplitGeom &g, const Cfg &c, const Shape *shapes, int count, int 
         const bool rounds = (int64_t)tiles * h.cot > cus, half = 2 * g.Cout <= BM;
         const bool staged = c.stagers(h.S) > 0;
         if (staged && c.wm == 4 && rounds && half) continue;
-        if (staged && !(c.wm == 2 && c.wn == 2 && (rounds || half))) {
+        const bool before = c.wm == 2 && c.wn == 2;   // (the tile of 64 x 128)
+        if (staged && !(before && (rounds || half))) {
             // one workgroup per compute unit; a chunk takes its products or its staging (1350 cycles per unit of a staging thread), whichever is longer
             const double prod = 1.157 * mfma / h.nchunk, put = 1350.0 * ((2 * nc * h.PS + 255) / 256);
             const double t = 10000 + __builtin_ceil(n) * (h.nchunk * (prod > put ? prod : put) + 16000 + (c.wk > 1 ? 466 * c.mb * c.nb : 0));
@@ -791,7 +792,7 @@ bool plan(const SplitGeom &g, const Cfg &c, const Shape *shapes, int count, int 
                 h.cost = limit = t;
                 *best = h;
             }
-            continue;
+            if (!before) continue;                    // (that one is never slower than it was: also where its own estimate is the larger one)
         }
         const double full = __builtin_floor(n / res), rem = n - full * res;
         double t = full * (res * shared > alone ? res * shared : alone);
