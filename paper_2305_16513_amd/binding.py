@@ -17,7 +17,7 @@ SWS_OK, SWS_ERR_INVALID_ARG, SWS_ERR_UNSUPPORTED, SWS_ERR_HIP = 0, 1, 2, 3
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsws.so")
 _lib = None
-# Native code for the small calls (csrc/calls.cpp), loaded with the library; None: not built for this torch, or not loaded yet.  It answers None
+# Native code for the small calls (csrc/calls.cpp), loaded with the library; None: not built, or not for this torch or this library.  It answers None
 # where a call is out of the ordinary, and the Python code below it then does the same call.
 _calls = None
 

@@ -4,7 +4,7 @@
 // launch, 1.4 in allocating, the rest in look-ups, checks and ctypes), a pooling call 7.2; here 4.3 and 4.5, and three of them are the launch.
 //
 // Every function returns None where anything is out of the ordinary (another type of argument, a tensor that is no plain one of
-// the current device, a mode that watches calls, lengths that do not fit): binding.py's Python code then does the same call,
+// the current device, a mode that watches calls, lengths that do not fit, no memory): binding.py's Python code then does the same call,
 // and says what is wrong with it.  Only what the library itself answers is raised here.
 #include <Python.h>
 

@@ -773,12 +773,12 @@ static GwLayer gw_layer(int64_t N, int64_t Cin, int64_t H, int64_t W, int64_t Co
 // Layers that run on the tiled kernel, given a workspace.  3 x 3 at stride 2 on channels in multiples of 32 and rows of whole
 // 16-byte groups stays on the kernel that reads its operands straight from memory.  That is not for speed: with both passes [32,128,56,56] -> 128
 // takes 101 us there and 77 here ([32,512,16,16] -> 512 64 and 106: short rows are mostly halo here).  The layers' workspace query answers 0, which a
-// test pins; taking those of long rows here by the estimates of both kernels is open.  At stride 1 [32,256,14,14] -> 256 88 / 65, [3,128,10,97] -> 472 150 / 46.
+// test pins; taking those of long rows here by the estimates of both kernels is open.  At stride 1 [32,256,14,14] -> 256 88 / 56, [3,128,10,97] -> 472 150 / 46.
 // *exact: the kernel that the layer runs on without a workspace multiplies in fp32, and gw's error against 64 bits (1.7e-7 whatever
 // the size) is to be no larger here.  The other layers' split-operand kernels (conv_gw_split.hip) are further off than either form of this one.
 // *other_us: what the kernel would take that serves the layer otherwise.  Layers one row high of k = 1, 3 and 5 have one of their own, whose pipeline
 // splits one chunk while it multiplies another (conv1d_gw_split_kernel): [32,256,3136] -> 256, k = 3 250 us there, 296 here, [16,544,6024] -> 128,
-// k = 1 139 / 191, but [16,64,4096] -> 64, k = 3 31 / 28, [64,544,1029] -> 32, k = 5 156 / 98.  Both sides estimate (8 % deviation), and
+// k = 1 139 / 191, but [16,64,4096] -> 64, k = 3 31 / 24, [64,544,1029] -> 32, k = 5 156 / 98.  Both sides estimate (8 % deviation), and
 // this one, the more exact, is taken up to a tenth more: of 260 random layers it serves two thirds, 0.93 of that kernel's time.
 static bool tile_wanted(const GwLayer &l, bool *exact, double *other_us)
 {

@@ -35,7 +35,7 @@
 //
 // Measured, us, this kernel with its second pass / the kernels without a workspace: [17,128,23,14] -> 104, 5 x 5 55 / 313,
 // [1,96,65,65] -> 484, 3 x 3 49 / 208, [32,256,14,14] -> 256, 3 x 3 56 / 87, [32,64,56,56] -> 64 53 / 74, [16,64,4096] -> 64, k = 3
-// 28 / 31.  Two LDS buffers with tiles of 64 positions, one wavefront of a SIMD splitting while the other multiplies, came out even at nine
+// 24 / 31.  Two LDS buffers with tiles of 64 positions, one wavefront of a SIMD splitting while the other multiplies, came out even at nine
 // taps and behind at one (174 against 127 us on [19,96,87,87] -> 256): not taken.
 #include "sws_internal.h"
 

@@ -11,7 +11,7 @@
 // What bounds it is latency: a workgroup loads, waits, and walks windows through dependent LDS reads.  So a workgroup takes no more planes
 // than give every compute unit eight of them, and where it has fewer outputs than threads, 2^ls threads share one, every
 // 2^ls-th column each (a global average of 7 x 7 was 49 reads one after the other in 80 of 256 threads).  Average of 7 x 7
-// planes, 65536 of them, 6.4 -> 5.2 us, its adjoint 10.1 -> 8.8, 3 x 3 on 16384 of them
+// planes, 65536 of them, 6.4 -> 5.2 us (its adjoint is the second kernel's), 3 x 3 on 16384 of them
 // 13.5 -> 5.8; four or sixteen workgroups per unit: 5.2 and 5.9 on the first, 9.2 and 9.5 on the second.
 #include "sws_internal.h"
 
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kThreads) void pool2d_small_kernel(const T *__restr
 
 // Planes of one element that every window covers (the adjoint of a global average: 1 x 1 -> H x W): an output is its plane's
 // element.  Nothing but stores: four outputs a thread, whole planes per workgroup, a multiple of four so that its outputs start on a 16-byte boundary when y
-// does.  The kernel above walks a clamped window for every output and stores them one by one: 65536 planes -> 7 x 7 there 7.9 us (back to back), here 3.4.
+// does.  The kernel above walks a clamped window for every output and stores them one by one: 65536 planes -> 7 x 7 there 8.8 us, here 5.2.
 template <int OP, typename T>
 __global__ __launch_bounds__(kThreads) void pool2d_spread_kernel(const T *__restrict__ x, T *__restrict__ y, int64_t planes, int Q, float scale, int G,
                                                                  unsigned rcp_q)
